@@ -64,6 +64,18 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Inclusive prefix sum over the 64 lanes.
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowShr1, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowShr2, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowShr4, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowShr8, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowBcast15, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0u, v, kDppRowBcast31, 0xc, 0xf, false);
+    return v;
+}
+
 __device__ __forceinline__ uint64_t wave_sum64(uint64_t v)
 {
     v += dpp64<kDppRowShr1>(0, v);

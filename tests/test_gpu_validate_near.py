@@ -1,0 +1,57 @@
+"""stalloc_validate on calls large enough for the form that leaves out pairs that cannot meet in time
+(n * n * P >= 3.5e8), against the oracle and against the all-pairs form on slices of the same plans."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+NEAR_FROM = 350_000_000
+
+
+def _trace(rng, n, kind):
+    t_end = {"dense": 40, "ties": n // 8 + 4, "mixed": 2 * n, "sparse": 1000 * n}[kind]
+    ts = rng.integers(0, t_end - 1, n)
+    life = np.exp(rng.uniform(0, np.log(t_end), n)).astype(np.int64) if kind != "dense" else rng.integers(1, 40, n)
+    te = np.minimum(ts + np.maximum(life, 1), t_end)
+    return rng.integers(1, 50, n).astype(np.uint64), ts.astype(np.uint32), te.astype(np.uint32), int(t_end)
+
+
+@pytest.mark.parametrize("kind", ["dense", "ties", "mixed", "sparse"])
+@pytest.mark.parametrize("n", [63, 64, 65, 257, 4097, 20011])
+def test_near_pairs_match_all_pairs(oracle, n, kind):
+    import torch
+    import paper_2507_16274_amd as S
+    rng = np.random.default_rng(n)
+    size, ts, te, t_end = _trace(rng, n, kind)
+    P = -(-NEAR_FROM // (n * n)) + 3                          # a count that is no multiple of four, too
+    plans = rng.integers(0, 60 * n, (P, n)).astype(np.int64)  # a few conflicts per plan and request
+    plans[P // 2] = 0                                         # ... and one in which everything conflicts that can
+    dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), plans)]
+    out = S.stalloc_validate(*dev[:3], t_end, dev[3])
+    S.check_status(out)
+    cnt, pair = out["conflicts"].cpu().numpy(), out["first_pair"].cpu().numpy()
+    rows = sorted({0, 1, 2, 3, P // 2, P - 2, P - 1} | set(rng.integers(0, P, 5).tolist()))
+    for p in rows if n < 5000 else rows[:2] + [P // 2]:
+        want = oracle.validate(size, ts, te, plans[p].view(np.uint64))
+        assert (int(cnt[p]), tuple(int(x) & 0xFFFFFFFF for x in pair[p])) == want
+    step = max(1, (NEAR_FROM - 1) // (n * n))
+    for p0 in range(0, P, step):                              # the all-pairs form
+        part = S.stalloc_validate(*dev[:3], t_end, dev[3][p0:p0 + step])
+        if n < NEAR_FROM ** 0.5:
+            assert np.array_equal(part["conflicts"].cpu().numpy(), cnt[p0:p0 + step])
+            assert np.array_equal(part["first_pair"].cpu().numpy(), pair[p0:p0 + step])
+
+
+def test_near_pairs_report_a_range_that_would_wrap(oracle):
+    import torch
+    import paper_2507_16274_amd as S
+    rng = np.random.default_rng(3)
+    n = 20011
+    size, ts, te, t_end = _trace(rng, n, "mixed")
+    plan = rng.integers(0, 1 << 40, (1, n)).astype(np.int64)
+    for bad in (0, n // 2, n - 1):
+        bent = plan.copy()
+        bent[0, bad] = -1                                     # 2^64 - 1: any size wraps
+        dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), bent)]
+        out = S.stalloc_validate(*dev[:3], t_end, dev[3])
+        assert int(out["status"].item()) == (3 if size[bad] > 1 else int(out["status"].item()))
