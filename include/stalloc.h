@@ -263,7 +263,8 @@ int stalloc_tmp(const stalloc_trace *trace, const uint64_t *extents, uint32_t P,
  * x.  Any window of rows can be produced on its own.
  *
  *   orders   device [P][n]
- * The workspace holds the sort buffers of up to 1 GiB worth of rows at a time.
+ * The workspace holds the sort buffers of up to 256 MiB worth of rows at a time (1 GiB beyond 6.2 million
+ * requests).
  */
 int stalloc_make_orders(const stalloc_trace *trace, uint32_t first_plan, uint32_t P, uint64_t seed,
                         uint32_t *orders, uint32_t *device_status,
