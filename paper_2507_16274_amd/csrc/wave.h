@@ -87,6 +87,17 @@ __device__ __forceinline__ uint64_t wave_sum64(uint64_t v)
     return readlane64(v, 63);
 }
 
+__device__ __forceinline__ uint64_t wave_scan_add64(uint64_t v)
+{
+    v += dpp64<kDppRowShr1>(0, v);
+    v += dpp64<kDppRowShr2>(0, v);
+    v += dpp64<kDppRowShr4>(0, v);
+    v += dpp64<kDppRowShr8>(0, v);
+    v += dpp64<kDppRowBcast15, 0xa>(0, v);
+    v += dpp64<kDppRowBcast31, 0xc>(0, v);
+    return v;
+}
+
 __device__ __forceinline__ uint64_t wave_or64(uint64_t v)
 {
     v |= dpp64<kDppRowShr1>(0, v);

@@ -109,3 +109,31 @@ def test_a_large_pair_at_the_lds_limit_and_errors(S, oracle):
     # pairs that reach beyond the member list, or backwards: reported, nothing read or written out there
     assert _fuse(S, tr, members, np.asarray([0, len(members) + 1], dtype=np.uint32), count1, largest)["status"] == 1
     assert _fuse(S, tr, members, np.asarray([4000, 100], dtype=np.uint32), count1, largest)["status"] == 1
+
+
+@pytest.mark.parametrize("kind", ["before", "after", "stack", "free"])
+@pytest.mark.parametrize("n1,n2", [(64, 65), (700, 63), (130, 1500), (1, 129), (900, 900)])
+def test_groups_before_after_and_inside_each_other(S, oracle, n1, n2, kind):
+    """The smaller group entirely earlier or later than the larger one (lifetimes meet in one phase only), with
+    lifetimes nested like a stack's, and free: requests that fit for good, that sleep and that need a
+    look, around the 64 requests a wave takes at a time."""
+    rng = np.random.default_rng(n1 * 7 + n2)
+    n = n1 + n2
+    if kind == "free":
+        ts = rng.integers(0, 900, n)
+        te = ts + rng.integers(1, 300, n)
+    else:
+        meet = rng.permutation(2 * n)[:n] + 2 * n                 # the phase in which both are alive
+        first, second = (slice(0, n1), slice(n1, n)) if kind != "before" else (slice(n1, n), slice(0, n1))
+        ts, te = meet.copy(), meet.copy()
+        k1, k2 = first.stop - first.start, second.stop - second.start
+        ts[first] = np.sort(rng.integers(0, 2 * n, k1))
+        te[second] = np.sort(rng.integers(4 * n, 6 * n, k2))
+        if kind == "stack":
+            te[first] = np.sort(te[first])[::-1]
+            te[second] = te[second][::-1]
+            ts[second] = np.sort(ts[second])
+    size = rng.choice([512, 1024, 4096, 1 << 20], n).astype(np.uint64)
+    tr = Trace(name="phases", size=size, t_alloc=ts.astype(np.uint32), t_free=te.astype(np.uint32), t_end=int(te.max()))
+    ids = np.arange(n, dtype=np.uint32)
+    _compare(S, oracle, tr, [ids[:n1], ids[n1:]], [(0, 1), (1, 0)])
