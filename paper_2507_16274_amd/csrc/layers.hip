@@ -9,9 +9,9 @@
 // a group in the order in which they were opened.
 //
 //   sort     Requests are sorted by (size descending, allocation time, request number): tiles
-//            of 256 keys sorted in LDS (bitonic network), merged in log2(n / 256) passes (an
-//            element's place is its place in its own run plus the number of elements of the
-//            partner run that sort before it, found by binary search).
+//            of 1024 keys sorted in LDS (bitonic network), merged four runs at a time (an
+//            element's place is its place in its own run plus the numbers of elements of the
+//            partner runs that sort before it, found by binary search).
 //   groups   A group starts where the size changes in the sorted sequence; exclusive sums of
 //            the start flags number the groups.
 //   build    One wave per group walks its requests in order -- the construction is
@@ -37,19 +37,21 @@ __global__ void ly_init(uint32_t* v, uint32_t n)
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) v[i] = 0;
 }
 
-// One tile of 256 requests per workgroup, sorted in LDS; slot e past the end holds a key behind
+// One tile of 1024 requests per workgroup, sorted in LDS; slot e past the end holds a key behind
 // every real one, (~0, ~0 << 32 | e) (sizes are > 0, so no real key starts with ~0).
-__global__ void __launch_bounds__(kLyTile)
+__global__ void __launch_bounds__(kSortThreads)
 ly_sort_tiles(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, uint32_t n, ulonglong2* keys,
               const uint32_t* status)
 {
     __shared__ ulonglong2 k[kLyTile];
     if (*status != STALLOC_OK) return;
-    const uint32_t t = threadIdx.x, i = blockIdx.x * kLyTile + t;
-    // (size descending, allocation time, request number) as two ascending 64-bit words
-    k[t] = i < n ? make_ulonglong2(~size[i], ((uint64_t)ta[i] << 32) | i) : filler_key(i);
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kLyTile; t += kSortThreads) {
+        const uint32_t i = blockIdx.x * kLyTile + t;
+        // (size descending, allocation time, request number) as two ascending 64-bit words
+        k[t] = i < n ? make_ulonglong2(~size[i], ((uint64_t)ta[i] << 32) | i) : filler_key(i);
+    }
     sort_tile(k);
-    keys[blockIdx.x * kLyTile + t] = k[t];
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kLyTile; t += kSortThreads) keys[blockIdx.x * kLyTile + t] = k[t];
 }
 
 // sorted[k] = request at sorted position k
@@ -474,7 +476,7 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
 
     uint32_t blocks = (n + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(ly_sort_tiles, dim3(tiles), dim3(kLyTile), 0, stream, tr->size, tr->t_alloc, n, keys, device_status);
+    hipLaunchKernelGGL(ly_sort_tiles, dim3(tiles), dim3(kSortThreads), 0, stream, tr->size, tr->t_alloc, n, keys, device_status);
     const ulonglong2* by_key = launch_merge_tiles(keys, spare, tiles * kLyTile, 1, device_status, stream);
     hipLaunchKernelGGL(ly_ids, dim3(blocks), dim3(256), 0, stream, by_key, n, sorted, device_status);
     hipLaunchKernelGGL(ly_flags, dim3(blocks), dim3(256), 0, stream, tr->size, sorted, n, flag, device_status);

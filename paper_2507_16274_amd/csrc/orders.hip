@@ -15,11 +15,12 @@
 // Every key is packed, with the request number in its lowest 32 bits, into two 64-bit words
 // compared in turn; keys of a row are therefore distinct and no tie rule is needed.
 //
-// Rows 0 .. 2 (and all rows of traces beyond kOrMostBuckets buckets) are sorted as tiles of 256 keys
-// in LDS (bitonic network) followed by passes that merge runs in pairs: an element's place in the
-// merged run is its place in its own run plus the number of elements of the other run that
-// sort before it, found by binary search.  log2(n / 256) passes, all rows of a batch side by side
-// in every launch.
+// Rows 0 .. 2 (and all rows of traces beyond kOrMostBuckets buckets) are sorted as tiles of 1024 keys
+// in LDS (bitonic network) followed by passes that merge four runs at a time: an element's place in
+// the merged run is its place in its own run plus the numbers of elements of the three other runs
+// that sort before it, found by binary search.  log4(n / 1024) passes, all rows of a batch side
+// by side in every launch.  A pass is a chain of dependent loads, whatever the number of searches:
+// 199 748 keys take 4 passes of 13 us where merging in pairs from tiles of 256 took 10 of 13 us.
 //
 // The keys of the other rows are spread in a way that is known in advance -- uniformly, or uniformly
 // inside steps of 2^32 whose counts follow from the sizes -- so that where a key will end up is known to
@@ -80,67 +81,57 @@ __device__ __forceinline__ ulonglong2 order_key(const OrTrace& t, uint64_t p, ui
 }
 
 // grid (tiles, rows): the keys of one tile of one row, sorted in LDS.
-__global__ void __launch_bounds__(kOrTile)
+__global__ void __launch_bounds__(kSortThreads)
 or_sort_tiles(OrTrace t, uint64_t first_plan, uint64_t seed, uint32_t n_pad, ulonglong2* keys, const uint32_t* status)
 {
     __shared__ ulonglong2 k[kOrTile];
     if (*status != STALLOC_OK) return;
-    const uint32_t th = threadIdx.x, e = blockIdx.x * kOrTile + th;
-    const uint64_t p = first_plan + blockIdx.y;
-    k[th] = order_key(t, p, splitmix64_out(seed + p), e, e);
+    const uint64_t p = first_plan + blockIdx.y, stream = splitmix64_out(seed + p);
+    ulonglong2* out = keys + (size_t)blockIdx.y * n_pad + blockIdx.x * kOrTile;
+    for (uint32_t th = threadIdx.x; th < (uint32_t)kOrTile; th += kSortThreads) {
+        const uint32_t e = blockIdx.x * kOrTile + th;
+        k[th] = order_key(t, p, stream, e, e);
+    }
     sort_tile(k);
-    keys[(size_t)blockIdx.y * n_pad + e] = k[th];
+    for (uint32_t th = threadIdx.x; th < (uint32_t)kOrTile; th += kSortThreads) out[th] = k[th];
 }
 
-// Element e of a row whose runs of `run` keys are merged in pairs: where it goes.
+// Element e of a row whose runs of `run` keys (a power of two) are merged four at a time: where it goes.
+// The three searches go side by side; a wave's lanes hold neighbours of a run and take nearly the same steps.
 __device__ __forceinline__ uint32_t merged_place(const ulonglong2* row, uint32_t n_pad, uint32_t run, uint32_t e,
                                                  const ulonglong2& me)
 {
-    const uint32_t mine = e / run;                              // my run; its partner is the other one of the pair
-    const uint32_t other0 = (mine ^ 1u) * run;
-    uint32_t lo = 0, hi = other0 < n_pad ? (n_pad - other0 < run ? n_pad - other0 : run) : 0u;
-    while (lo < hi) {                                           // keys of the partner that sort before mine
-        const uint32_t mid = (lo + hi) >> 1;
-        if (key_before(row[other0 + mid], me)) lo = mid + 1; else hi = mid;
+    const uint32_t mine = e / run, group0 = (mine & ~3u) * run;         // my run; its partners are the others of its four
+    uint32_t from[3], left[3];                                          // first key of a partner; keys of it still in question
+#pragma unroll
+    for (uint32_t v = 0; v < 3; ++v) {
+        const uint64_t at = (uint64_t)(mine & ~3u) * run + (uint64_t)(v + (v >= (mine & 3u) ? 1u : 0u)) * run;
+        from[v] = at < n_pad ? (uint32_t)at : 0u;
+        left[v] = at < n_pad ? (n_pad - from[v] < run ? n_pad - from[v] : run) : 0u;
     }
-    return (mine & ~1u) * run + (e - mine * run) + lo;
+    uint32_t place = group0 + (e - mine * run) - (from[0] + from[1] + from[2]);
+    while (left[0] | left[1] | left[2]) {
+#pragma unroll
+        for (uint32_t v = 0; v < 3; ++v) {
+            if (left[v] == 0) continue;
+            const uint32_t half = left[v] >> 1;
+            const bool before = key_before(row[from[v] + half], me);
+            from[v] = before ? from[v] + half + 1 : from[v];
+            left[v] = before ? left[v] - half - 1 : half;
+        }
+    }
+    return place + from[0] + from[1] + from[2];
 }
 
-// grid (tiles, rows): runs of `run` keys merged in pairs, src -> dst.
-__global__ void __launch_bounds__(kOrTile)
+// grid (256-key pieces, rows): runs of `run` keys merged four at a time, src -> dst.
+__global__ void __launch_bounds__(256)
 or_merge(const ulonglong2* __restrict__ src, ulonglong2* dst, uint32_t n_pad, uint32_t run, const uint32_t* status)
 {
     if (*status != STALLOC_OK) return;
-    const uint32_t e = blockIdx.x * kOrTile + threadIdx.x;
+    const uint32_t e = blockIdx.x * 256 + threadIdx.x;
     const ulonglong2* row = src + (size_t)blockIdx.y * n_pad;
     const ulonglong2 me = row[e];
     dst[(size_t)blockIdx.y * n_pad + merged_place(row, n_pad, run, e, me)] = me;
-}
-
-// A few short rows in one launch (n^2 / 32 steps a row instead of n log n, but no launch per pass), grid (tiles, rows): thread p of workgroup b holds the key at position p
-// of sorted tile b; its place in the row is p plus, for every other tile (staged in LDS), the
-// number of that tile's keys that sort before it.
-constexpr uint32_t kOrShortRow = 8192;
-__global__ void __launch_bounds__(kOrTile)
-or_place_short(const ulonglong2* __restrict__ src, ulonglong2* dst, uint32_t n_pad, const uint32_t* status)
-{
-    __shared__ ulonglong2 k[kOrTile];
-    if (*status != STALLOC_OK) return;
-    const uint32_t p = threadIdx.x, own = blockIdx.x, tiles = n_pad / kOrTile;
-    const ulonglong2* row = src + (size_t)blockIdx.y * n_pad;
-    const ulonglong2 me = row[own * kOrTile + p];
-    uint32_t place = p;
-    for (uint32_t t = 0; t < tiles; ++t) {
-        if (t == own) continue;                                  // (uniform)
-        __syncthreads();
-        k[p] = row[t * kOrTile + p];
-        __syncthreads();
-        uint32_t lo = 0;                                         // first position of the tile not before `me`
-        for (uint32_t half = kOrTile / 2; half > 0; half >>= 1)
-            if (key_before(k[lo + half - 1], me)) lo += half;
-        place += lo + (key_before(k[lo], me) ? 1u : 0u);         // lo <= 255 here
-    }
-    dst[(size_t)blockIdx.y * n_pad + place] = me;
 }
 
 __global__ void __launch_bounds__(256)
@@ -394,15 +385,9 @@ or_buckets(OrTrace t, OrBuckets b, uint64_t first_plan, uint64_t seed, uint32_t*
 ulonglong2* launch_merge_tiles(ulonglong2* keys, ulonglong2* spare, uint32_t n_pad, uint32_t rows, const uint32_t* status,
                                hipStream_t stream)
 {
-    const uint32_t tiles = n_pad / kOrTile;
     ulonglong2 *src = keys, *dst = spare;
-    if (tiles == 1) return keys;
-    if (n_pad <= kOrShortRow && (uint64_t)rows * tiles <= 2048) {       // few short rows: launches are what costs
-        hipLaunchKernelGGL(or_place_short, dim3(tiles, rows), dim3(kOrTile), 0, stream, keys, spare, n_pad, status);
-        return spare;
-    }
-    for (uint64_t run = kOrTile; run < n_pad; run <<= 1) {
-        hipLaunchKernelGGL(or_merge, dim3(tiles, rows), dim3(kOrTile), 0, stream, src, dst, n_pad, (uint32_t)run, status);
+    for (uint64_t run = kOrTile; run < n_pad; run <<= 2) {
+        hipLaunchKernelGGL(or_merge, dim3(n_pad / 256, rows), dim3(256), 0, stream, src, dst, n_pad, (uint32_t)run, status);
         ulonglong2* s = src; src = dst; dst = s;
     }
     return src;
@@ -412,7 +397,7 @@ ulonglong2* launch_merge_tiles(ulonglong2* keys, ulonglong2* spare, uint32_t n_p
 static ulonglong2* sort_rows(const OrTrace& t, uint64_t first_plan, uint32_t rows, uint64_t seed, uint32_t n_pad,
                              ulonglong2* buf_a, ulonglong2* buf_b, const uint32_t* status, hipStream_t stream)
 {
-    hipLaunchKernelGGL(or_sort_tiles, dim3(n_pad / kOrTile, rows), dim3(kOrTile), 0, stream, t, first_plan, seed, n_pad, buf_a,
+    hipLaunchKernelGGL(or_sort_tiles, dim3(n_pad / kOrTile, rows), dim3(kSortThreads), 0, stream, t, first_plan, seed, n_pad, buf_a,
                        status);
     return launch_merge_tiles(buf_a, buf_b, n_pad, rows, status, stream);
 }

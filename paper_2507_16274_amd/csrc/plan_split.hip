@@ -311,15 +311,17 @@ __global__ void sp_ranked_decide(uint64_t* acc, const uint32_t* hist, uint32_t l
 }
 
 // Keys (t_alloc, request) of one tile, sorted in LDS.
-__global__ void __launch_bounds__(kSortTile)
+__global__ void __launch_bounds__(kSortThreads)
 sp_sort_tiles(const uint32_t* __restrict__ ta, uint32_t n, ulonglong2* keys, const uint32_t* gate)
 {
     __shared__ ulonglong2 k[kSortTile];
     if (*gate != 0) return;
-    const uint32_t e = blockIdx.x * kSortTile + threadIdx.x;
-    k[threadIdx.x] = e < n ? make_ulonglong2((uint64_t)ta[e], (uint64_t)e) : filler_key(e);
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kSortTile; t += kSortThreads) {
+        const uint32_t e = blockIdx.x * kSortTile + t;
+        k[t] = e < n ? make_ulonglong2((uint64_t)ta[e], (uint64_t)e) : filler_key(e);
+    }
     sort_tile(k);
-    keys[e] = k[threadIdx.x];
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kSortTile; t += kSortThreads) keys[blockIdx.x * kSortTile + t] = k[t];
 }
 
 // Per rank k of the allocation-time order: (size in granules, t_alloc, t_free, request); the
@@ -1167,7 +1169,7 @@ bool launch_plan_split(const PlanParams& prm, uint32_t t_end, const SplitWorkspa
     hipLaunchKernelGGL(sp_size_histogram, dim3(blocks > 256 ? 256 : blocks), dim3(256), 0, stream, prm.size, prm.ta, prm.tf, n,
                        prm.acc, ws.hist, ws.gate);
     hipLaunchKernelGGL(sp_sigma, dim3(1), dim3(64), 0, stream, ws.hist, ws.gate);
-    hipLaunchKernelGGL(sp_sort_tiles, dim3(ws.n_pad / kSortTile), dim3(kSortTile), 0, stream, prm.ta, n, ws.keys, ws.gate);
+    hipLaunchKernelGGL(sp_sort_tiles, dim3(ws.n_pad / kSortTile), dim3(kSortThreads), 0, stream, prm.ta, n, ws.keys, ws.gate);
     const ulonglong2* sorted = launch_merge_tiles(ws.keys, ws.spare, ws.n_pad, 1, ws.gate, stream);
     hipLaunchKernelGGL(sp_tables, dim3(blocks), dim3(256), 0, stream, sorted, prm.size, prm.ta, prm.tf, n, ws.slots, prm.acc,
                        ws.by_rank, ws.size_by_rank, ws.fit_by_rank, ws.rank_of, ws.is_large, ws.hist, ws.gate);

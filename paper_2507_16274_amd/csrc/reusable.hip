@@ -6,9 +6,9 @@
 // as its maximal intervals in ascending address order.  Windows are half-open like lifespans.
 //
 //   sort     The decisions are sorted by (start address, request number) once per call: tiles of
-//            256 keys are sorted in LDS (bitonic network) and merged in log2(n / 256) passes,
-//            an element's place being its place in its own run plus the number of elements
-//            of the partner run that sort before it (binary search); nothing depends on how
+//            1024 keys are sorted in LDS (bitonic network) and merged four runs at a time,
+//            an element's place being its place in its own run plus the numbers of elements
+//            of the partner runs that sort before it (binary search); nothing depends on how
 //            the addresses are distributed.
 //   gather   (start, end, lifespan) of the decisions in that order; the unit of the pool's
 //            addresses (largest power of two dividing every start and end relative to the
@@ -48,28 +48,35 @@ __global__ void rs_init(RsPool* pool)
     if (threadIdx.x == 0) { pool->lo = ~0ull; pool->hi = 0; pool->bits = 0; pool->shift = 0; pool->narrow = 0; }
 }
 
-// One tile of 256 decisions per workgroup, sorted in LDS; slot e past the end holds a key behind
+// One tile of 1024 decisions per workgroup, sorted in LDS; slot e past the end holds a key behind
 // every real one, (~0, ~0 << 32 | e).  Also the pool's bounds.
-__global__ void __launch_bounds__(kRsTile)
+__global__ void __launch_bounds__(kSortThreads)
 rs_sort_tiles(const uint64_t* __restrict__ size, const uint64_t* __restrict__ offsets, uint32_t n, ulonglong2* keys,
               RsPool* pool, const uint32_t* status)
 {
     __shared__ ulonglong2 k[kRsTile];
     if (*status != STALLOC_OK) return;
-    const uint32_t t = threadIdx.x, i = blockIdx.x * kRsTile + t;
-    const bool ok = i < n;
-    const uint64_t a = ok ? offsets[i] : ~0ull;
-    k[t] = ok ? make_ulonglong2(a, i) : filler_key(i);          // keys (address, request number)
-    {
-        const uint64_t lo = wave_min64(a);                                       // (slots past n hold ~0)
-        const uint64_t hi = wave_max64(ok ? a + size[i] : 0ull);
-        if (lane_id() == 0) {
-            atomicMin((unsigned long long*)&pool->lo, (unsigned long long)lo);
-            atomicMax((unsigned long long*)&pool->hi, (unsigned long long)hi);
-        }
+    __shared__ uint64_t lowest[kSortThreads / kWave], highest[kSortThreads / kWave];
+    uint64_t lo = ~0ull, hi = 0;
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads) {
+        const uint32_t i = blockIdx.x * kRsTile + t;
+        const bool ok = i < n;
+        const uint64_t a = ok ? offsets[i] : ~0ull;
+        k[t] = ok ? make_ulonglong2(a, i) : filler_key(i);      // keys (address, request number)
+        lo = umin64(lo, a);                                     // (slots past n hold ~0)
+        hi = umax64(hi, ok ? a + size[i] : 0ull);
     }
+    lo = wave_min64(lo);
+    hi = wave_max64(hi);
+    if (lane_id() == 0) { lowest[wave_id()] = lo; highest[wave_id()] = hi; }
     sort_tile(k);
-    keys[blockIdx.x * kRsTile + t] = k[t];
+    // one pair of atomics per workgroup: a wave each would queue up on the two words
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kSortThreads / kWave; ++w) { lo = umin64(lo, lowest[w]); hi = umax64(hi, highest[w]); }
+        atomicMin((unsigned long long*)&pool->lo, (unsigned long long)lo);
+        atomicMax((unsigned long long*)&pool->hi, (unsigned long long)hi);
+    }
+    for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads) keys[blockIdx.x * kRsTile + t] = k[t];
 }
 
 // (start, end, lifespan) of the decisions in address order; the bits set in any start or end
@@ -416,7 +423,7 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     uint32_t blocks = (n + 255) / 256;
     if (blocks > 256) blocks = 256;
     hipLaunchKernelGGL(rs_init, dim3(1), dim3(64), 0, stream, pool);
-    hipLaunchKernelGGL(rs_sort_tiles, dim3(tiles), dim3(kRsTile), 0, stream, tr->size, offsets, n, keys, pool, device_status);
+    hipLaunchKernelGGL(rs_sort_tiles, dim3(tiles), dim3(kSortThreads), 0, stream, tr->size, offsets, n, keys, pool, device_status);
     const ulonglong2* sorted = launch_merge_tiles(keys, spare, tiles * kRsTile, 1, device_status, stream);
     hipLaunchKernelGGL(rs_gather, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, offsets, sorted, n,
                        s_lo, s_hi, s_life, pool, device_status);
