@@ -23,12 +23,14 @@
 //            its place in the output; (3) the intervals themselves.  What lies between the last
 //            covered address and the end of the pool is the final interval.
 //            With thousands of windows the roles are exchanged: a wave takes 64 windows, one
-//            per lane, and a contiguous part of the sorted decisions, which
+//            per lane, and a contiguous part of the sorted decisions.  The windows are sorted so
+//            that those of a wave are neighbours of like length (window_key); of 64 decisions
+//            two compares and a ballot leave those that meet the span of all of them, which
 //            are taken one at a time as wave-uniform values -- two compares per decision tell
-//            for all 64 windows whether it counts (most decisions count for none and are done
-//            with), and "covered so far" is a per-lane maximum without any cross-lane step.  The
-//            same three walks (one launch each, a wave per group of windows and part of the
-//            plan), at a fraction of the instructions per decision and window.
+//            for all 64 windows whether it counts, and "covered so far" is a per-lane maximum
+//            without any cross-lane step.  The same three walks (one launch each, a wave per group
+//            of windows and part of the plan; what lies in front of a part is summed up by a small
+//            launch in between), at a fraction of the instructions per decision and window.
 #include "host_util.h"
 #include "sort_keys.h"
 #include "wave.h"
@@ -39,23 +41,53 @@ constexpr int kRsTile = kSortTile;
 constexpr int kRsThreads = 256;
 constexpr int kRsWaves = kRsThreads / kWave;
 
-// A = [lo, hi).  Every start and end address, taken relative to lo, is a multiple of 2^shift
-// (the largest such power); `narrow` says that the pool counted in those units fits 32 bits.
-struct RsPool { uint64_t lo, hi, bits; uint32_t shift, narrow; };
+// A = [lo, hi); bits = all bits set in any start or end address relative to lo.
+struct RsPool { uint64_t lo, hi, bits; };
+
+// Every start and end address, taken relative to the pool's start, is a multiple of 2^shift (the largest
+// such power); `narrow`: the pool counted in those units fits 32 bits.
+struct RsUnits { uint32_t shift; bool narrow; };
+__device__ __forceinline__ RsUnits units_of(const RsPool* pool)
+{
+    const uint64_t span = pool->hi - pool->lo;                  // > 0: sizes are
+    const uint32_t shift = (uint32_t)__builtin_ctzll(pool->bits | span);
+    return {shift, (span >> shift) <= 0xffffffffull};
+}
 
 __global__ void rs_init(RsPool* pool)
 {
-    if (threadIdx.x == 0) { pool->lo = ~0ull; pool->hi = 0; pool->bits = 0; pool->shift = 0; pool->narrow = 0; }
+    if (threadIdx.x == 0) { pool->lo = ~0ull; pool->hi = 0; pool->bits = 0; }
+}
+
+// Windows that are swept together, a lane each, should lie close together and be of like length: the sweep
+// then leaves out what meets none of them 64 decisions at a time.  Order: windows up to the time in which
+// 64 of them begin (`near`), by start; then the longer ones, doubling by doubling, by start.
+__device__ __forceinline__ ulonglong2 window_key(const uint32_t* __restrict__ windows, uint32_t w, uint32_t near)
+{
+    const uint32_t lo = windows[2 * w], hi = windows[2 * w + 1];
+    const uint32_t length = hi > lo ? hi - lo : 0u, times = length / near;
+    const uint32_t cls = times ? 32u - (uint32_t)__builtin_clz(times) : 0u;
+    return make_ulonglong2(((uint64_t)cls << 32) | lo, w);
 }
 
 // One tile of 1024 decisions per workgroup, sorted in LDS; slot e past the end holds a key behind
 // every real one, (~0, ~0 << 32 | e).  Also the pool's bounds.
 __global__ void __launch_bounds__(kSortThreads)
 rs_sort_tiles(const uint64_t* __restrict__ size, const uint64_t* __restrict__ offsets, uint32_t n, ulonglong2* keys,
-              RsPool* pool, const uint32_t* status)
+              RsPool* pool, const uint32_t* __restrict__ windows, uint32_t windows_k, uint32_t near, ulonglong2* window_keys,
+              const uint32_t* status)
 {
     __shared__ ulonglong2 k[kRsTile];
     if (*status != STALLOC_OK) return;
+    const uint32_t tiles = (n + kRsTile - 1) / kRsTile;
+    if (blockIdx.x >= tiles) {                                  // (uniform) the windows' tiles follow the decisions'
+        const uint32_t w0 = (blockIdx.x - tiles) * kRsTile;
+        for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads)
+            k[t] = w0 + t < windows_k ? window_key(windows, w0 + t, near) : filler_key(w0 + t);
+        sort_tile(k);
+        for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads) window_keys[w0 + t] = k[t];
+        return;
+    }
     __shared__ uint64_t lowest[kSortThreads / kWave], highest[kSortThreads / kWave];
     uint64_t lo = ~0ull, hi = 0;
     for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads) {
@@ -108,24 +140,16 @@ rs_gather(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
     }
 }
 
-// The unit of the pool's addresses and whether 32-bit counts of it cover the pool.
-__global__ void rs_units(RsPool* pool, const uint32_t* status)
-{
-    if (*status != STALLOC_OK || threadIdx.x != 0) return;
-    const uint64_t span = pool->hi - pool->lo;                  // > 0: sizes are
-    const uint32_t shift = (uint32_t)__builtin_ctzll(pool->bits | span);
-    pool->shift = shift;
-    pool->narrow = (span >> shift) <= 0xffffffffull ? 1u : 0u;
-}
-
 // Start and end of every sorted decision in units of the pool, relative to its start.
 __global__ void __launch_bounds__(256)
 rs_compress(const uint64_t* __restrict__ s_lo, const uint64_t* __restrict__ s_hi, uint32_t n, const RsPool* pool,
             uint32_t* c_lo, uint32_t* c_hi, const uint32_t* status)
 {
-    if (*status != STALLOC_OK || !pool->narrow) return;
+    if (*status != STALLOC_OK) return;
+    const RsUnits units = units_of(pool);
+    if (!units.narrow) return;
     const uint64_t pool_lo = pool->lo;
-    const uint32_t shift = pool->shift;
+    const uint32_t shift = units.shift;
     for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
         c_lo[r] = (uint32_t)((s_lo[r] - pool_lo) >> shift);
         c_hi[r] = (uint32_t)((s_hi[r] - pool_lo) >> shift);
@@ -140,6 +164,7 @@ struct RsArgs {
     const uint2* s_life;
     const RsPool* pool;
     const uint32_t* windows;     // [k][2]
+    const ulonglong2* window_order;      // [k] window-per-lane sweep: second word = the window at this place (see window_key)
     uint64_t* ranges;            // [k][max_ranges][2] or nullptr
     uint32_t* counts;            // [k]
     uint64_t* idle_bytes;        // [k] or nullptr
@@ -248,128 +273,212 @@ __global__ void __launch_bounds__(kRsThreads) rs_sweep(RsArgs g)
 // prefixes cost more than they save below it), given at least half a wave of windows.
 constexpr uint64_t kRsWideFrom = STALLOC_RS_WIDE_FROM;
 __host__ inline bool rs_window_per_lane(uint32_t n, uint32_t k) { return k >= 32 && (uint64_t)n * k >= kRsWideFrom; }
+// Waves per CU that the window-per-lane sweep is cut into: more than are resident, since the groups of long
+// windows have ten times the work of the others (199 748 decisions, 4096 windows: 0.75 ms a call with 16
+// waves per CU, 0.47 with 32, 0.39 with 64; 1.23 ms when every window looked at every decision).
+constexpr uint32_t kRsWavesPerCu = 64;
 constexpr uint32_t kRsMaxParts = 256;                    // parts the sorted plan is cut into, at most
 
 // Scratch of the window-per-lane sweep, [group of 64 windows][part][lane].
 struct RsParts {
-    uint64_t* reach;        // walk 1: maximum end of the counting decisions of the part
+    uint64_t* reach;        // walk 1: maximum end of the counting decisions of the part; then what is covered in front of it
+    uint64_t* reach_all;    // [group][lane] ... of all parts
     uint64_t* idle;         // walk 2: bytes of the idle intervals closed inside the part
-    uint32_t* found;        //         and their number
+    uint32_t* found;        //         and their number; then the number in front of the part
     uint32_t parts;         // parts per group; one wave each
     uint32_t steps;         // 64-decision steps per part
 };
 
+// The window of this lane in group grp: lanes without a window, and malformed windows, get bounds that no
+// lifespan meets.
+struct RsWindow { uint32_t w, lo, hi; bool live, malformed; };
+__device__ __forceinline__ RsWindow window_of_lane(const RsArgs& g, uint32_t grp)
+{
+    const uint32_t at = grp * kWave + (uint32_t)lane_id();
+    RsWindow r = {0u, 1u, 0u, false, false};
+    if (at < g.k) {
+        r.w = (uint32_t)g.window_order[at].y;
+        const uint32_t lo = g.windows[2 * (size_t)r.w], hi = g.windows[2 * (size_t)r.w + 1];
+        if (lo < hi) { r.lo = lo; r.hi = hi; r.live = true; }
+        else r.malformed = true;
+    }
+    return r;
+}
+
 // One wave = 64 windows (one per lane) x one part of the sorted plan.  kWalk = 1, 2, 3: the
 // three walks, one launch each (a part needs the results of all lower parts of the walk before).
-__device__ __forceinline__ uint32_t read_lane_addr(uint32_t v, int q) { return __builtin_amdgcn_readlane(v, q); }
-__device__ __forceinline__ uint64_t read_lane_addr(uint64_t v, int q) { return readlane64(v, q); }
-
 // Addr = uint32_t: addresses in units of the pool relative to its start (a narrow pool: half the
 // registers, single-instruction compares and maxima); Addr = uint64_t: byte addresses.
+// The decisions that meet the span of the group's windows are put into LDS and taken from there as
+// broadcasts, once 64 have come together: reading them lane by lane (four lane reads and the search
+// for the next lane per decision) made a walk twice as long.  Bound by the integer rate and the longest
+// units: 2.0 million of 12.8 million (group, decision) pairs are left, 63 + 83 + 101 us for the three walks
+// of 199 748 decisions and 4096 windows (273 + 410 + 379 us before).
+template <typename Addr> struct RsKept { uint32_t ts, te; Addr lo, hi; };
+constexpr uint32_t kRsKept = 2 * kWave + 4;                     // (the walk over them takes four at a time)
+
 template <int kWalk, typename Addr>
-__device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& sc)
+__device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& sc, uint32_t shift, RsKept<Addr>* kept)
 {
     constexpr bool kNarrow = sizeof(Addr) == 4;
     const int lane = lane_id();
     const uint64_t pool_lo = g.pool->lo;
-    const uint32_t shift = kNarrow ? g.pool->shift : 0u;
+    if (!kNarrow) shift = 0;
     auto bytes = [&](Addr v) -> uint64_t { return kNarrow ? pool_lo + ((uint64_t)v << shift) : (uint64_t)v; };
     const uint32_t groups = (g.k + kWave - 1) / kWave;
     const uint32_t waves = groups * sc.parts;
     for (uint32_t unit = blockIdx.x * kRsWaves + (uint32_t)wave_id(); unit < waves; unit += gridDim.x * kRsWaves) {
-        const uint32_t grp = unit / sc.parts, part = unit % sc.parts;
-        const uint32_t w = grp * kWave + lane;
-        // lanes without a window, and malformed windows, get bounds that no lifespan meets
-        uint32_t w_lo = 1, w_hi = 0;
-        bool live = false;
-        if (w < g.k) {
-            const uint32_t lo = g.windows[2 * w], hi = g.windows[2 * w + 1];
-            if (lo < hi) { w_lo = lo; w_hi = hi; live = true; }
-            else if (kWalk == 1 && part == 0) atomicMax(g.status, (uint32_t)STALLOC_ERR_BAD_WINDOW);
-        }
-        const size_t row = ((size_t)grp * sc.parts) * kWave + lane;        // [grp][0][lane]; next part: + kWave
+        const uint32_t grp = groups - 1 - unit / sc.parts, part = unit % sc.parts;      // (the longest windows first)
+        const RsWindow win = window_of_lane(g, grp);
+        if (kWalk == 1 && part == 0 && win.malformed) atomicMax(g.status, (uint32_t)STALLOC_ERR_BAD_WINDOW);
+        const size_t cell = ((size_t)grp * sc.parts + part) * kWave + lane;
         const uint32_t first = part * sc.steps * kWave;
-        // body(start, end, counts): called for every decision of this part that counts for at
-        // least one window, in address order, with wave-uniform start and end
-        auto walk = [&](auto&& body) {
-            for (uint32_t s = 0; s < sc.steps; ++s) {
-                const uint32_t k0 = first + s * kWave;
-                if (k0 >= g.n) break;                                     // (uniform)
-                const uint32_t at = k0 + lane;
-                const bool valid = at < g.n;
-                const uint2 life = valid ? g.s_life[at] : make_uint2(0xffffffffu, 0u);   // past the end: meets no window
-                Addr lo = 0, hi = 0;
-                if (valid) {
-                    if constexpr (kNarrow) { lo = g.c_lo[at]; hi = g.c_hi[at]; }
-                    else { lo = g.s_lo[at]; hi = g.s_hi[at]; }
-                }
-#pragma unroll 8
-                for (int q = 0; q < kWave; ++q) {
-                    const uint32_t ts_q = __builtin_amdgcn_readlane(life.x, q), te_q = __builtin_amdgcn_readlane(life.y, q);
-                    const bool counts = ts_q < w_hi && w_lo < te_q;
-                    if (__builtin_amdgcn_ballot_w64(counts) == 0) continue;           // (uniform)
-                    body(read_lane_addr(lo, q), read_lane_addr(hi, q), counts);
-                }
-            }
-        };
-
-        if constexpr (kWalk == 1) {          // how far the decisions of each part reach
-            Addr covered = 0;
-            walk([&](Addr, Addr end, bool counts) { covered = counts ? umax(covered, end) : covered; });
-            sc.reach[row + (size_t)part * kWave] = covered;
-        } else {
-            Addr covered = kNarrow ? (Addr)0 : (Addr)pool_lo;       // covered before this part
-            for (uint32_t v = 0; v < part; ++v) covered = umax(covered, (Addr)sc.reach[row + (size_t)v * kWave]);
-            if constexpr (kWalk == 2) {      // idle intervals closed inside each part
-                uint32_t count = 0;
-                Addr idle = 0;               // (disjoint intervals of the pool: fits the address type)
-                walk([&](Addr start, Addr end, bool counts) {
-                    if (counts && start > covered) { ++count; idle += start - covered; }
-                    covered = counts ? umax(covered, end) : covered;
-                });
-                sc.found[row + (size_t)part * kWave] = count;
-                sc.idle[row + (size_t)part * kWave] = idle;
-            } else {                         // write them; the last part adds the tail of the pool and the totals
-                uint32_t place = 0;
-                for (uint32_t v = 0; v < part; ++v) place += sc.found[row + (size_t)v * kWave];
-                uint64_t* out = (g.ranges && live) ? g.ranges + (size_t)w * g.max_ranges * 2 : nullptr;
-                const Addr covered0 = covered;
-                if (g.ranges) {                                           // (uniform; lanes without a window count nothing)
-                    walk([&](Addr start, Addr end, bool counts) {
-                        if (counts && start > covered) {
-                            if (place < g.max_ranges) { out[2 * place] = bytes(covered); out[2 * place + 1] = bytes(start); }
-                            ++place;
-                        }
-                        covered = counts ? umax(covered, end) : covered;
-                    });
-                }
-                if (part + 1 == sc.parts && live) {
-                    const size_t mine = row + (size_t)part * kWave;
-                    const uint64_t covered_all = bytes(umax(covered0, (Addr)sc.reach[mine]));
-                    uint32_t total = sc.found[mine];
-                    uint64_t idle_total = sc.idle[mine];
-                    for (uint32_t v = 0; v < part; ++v) { total += sc.found[row + (size_t)v * kWave]; idle_total += sc.idle[row + (size_t)v * kWave]; }
-                    idle_total <<= shift;                                 // units of the pool -> bytes
-                    const uint64_t pool_hi = g.pool->hi;
-                    if (covered_all < pool_hi) {                          // from the last covered address to the end of the pool
-                        if (out && total < g.max_ranges) { out[2 * total] = covered_all; out[2 * total + 1] = pool_hi; }
-                        idle_total += pool_hi - covered_all;
-                        ++total;
-                    }
-                    g.counts[w] = total;
-                    if (g.idle_bytes) g.idle_bytes[w] = idle_total;
-                }
-            }
+        // what all windows of the group lie in
+        const uint32_t all_lo = ~read_lane(wave_scan_max(win.live ? ~win.lo : 0u), kWave - 1);
+        const uint32_t all_hi = read_lane(wave_scan_max(win.hi), kWave - 1);
+        Addr covered = 0;
+        uint32_t place = 0;                                               // walk 2: intervals closed; walk 3: where the next one goes
+        Addr idle = 0;                                                    // (disjoint intervals of the pool: fits the address type)
+        uint64_t* out = nullptr;
+        if constexpr (kWalk > 1) covered = (Addr)sc.reach[cell];
+        if constexpr (kWalk == 3) {
+            place = sc.found[cell];
+            out = win.live ? g.ranges + (size_t)win.w * g.max_ranges * 2 : nullptr;
         }
+        // the next decision in address order, the same for all lanes
+        auto take = [&](const RsKept<Addr>& d) {
+            const bool counts = d.ts < win.hi && win.lo < d.te;
+            if constexpr (kWalk == 2) {
+                const bool closes = counts && d.lo > covered;
+                place += closes ? 1u : 0u;
+                idle += closes ? d.lo - covered : (Addr)0;
+            }
+            if constexpr (kWalk == 3) {
+                if (counts && d.lo > covered) {
+                    if (place < g.max_ranges) { out[2 * (size_t)place] = bytes(covered); out[2 * (size_t)place + 1] = bytes(d.lo); }
+                    ++place;
+                }
+            }
+            covered = counts ? umax(covered, d.hi) : covered;
+        };
+        uint32_t many = 0;                                                // decisions in kept[]
+        auto take_kept = [&]() {
+            if (lane < 4) kept[many + lane] = RsKept<Addr>{0xffffffffu, 0u, 0, 0};       // (meets no window) up to a multiple of four
+            __builtin_amdgcn_wave_barrier();                              // (the wave's own LDS: its accesses complete in order)
+            for (uint32_t k = 0; k < many; k += 4) {
+                RsKept<Addr> d[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) d[u] = kept[k + u];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) take(d[u]);
+            }
+            __builtin_amdgcn_wave_barrier();
+            many = 0;
+        };
+        // (the decisions of the next step are on their way while this step's are looked at)
+        auto load = [&](uint32_t s) -> RsKept<Addr> {
+            const uint32_t at = first + s * kWave + lane;
+            RsKept<Addr> d = {0xffffffffu, 0u, 0, 0};                     // past the end: meets no window
+            if (s < sc.steps && at < g.n) {
+                const uint2 life = g.s_life[at];
+                d.ts = life.x; d.te = life.y;
+                if constexpr (kNarrow) { d.lo = g.c_lo[at]; d.hi = g.c_hi[at]; }
+                else { d.lo = g.s_lo[at]; d.hi = g.s_hi[at]; }
+            }
+            return d;
+        };
+        RsKept<Addr> next = load(0);
+        for (uint32_t s = 0; s < sc.steps && first + s * kWave < g.n; ++s) {
+            const RsKept<Addr> d = next;
+            next = load(s + 1);
+            const bool meets = d.ts < all_hi && all_lo < d.te;
+            const uint64_t left = __builtin_amdgcn_ballot_w64(meets);
+            if (meets) kept[many + lanes_below(left)] = d;
+            many += (uint32_t)__builtin_popcountll(left);
+            if (many >= (uint32_t)kWave) take_kept();                     // (uniform)
+        }
+        take_kept();
+        if constexpr (kWalk == 1) sc.reach[cell] = covered;
+        if constexpr (kWalk == 2) { sc.found[cell] = place; sc.idle[cell] = idle; }
     }
 }
 
 template <int kWalk>
 __global__ void __launch_bounds__(kRsThreads) rs_sweep_by_window(RsArgs g, RsParts sc)
 {
+    __shared__ RsKept<uint64_t> kept[kRsWaves][kRsKept];
     if (*g.status != STALLOC_OK) return;
-    if (g.pool->narrow) sweep_by_window<kWalk, uint32_t>(g, sc);       // (uniform)
-    else sweep_by_window<kWalk, uint64_t>(g, sc);
+    const RsUnits units = units_of(g.pool);
+    if (units.narrow) sweep_by_window<kWalk, uint32_t>(g, sc, units.shift, reinterpret_cast<RsKept<uint32_t>*>(kept[wave_id()]));   // (uniform)
+    else sweep_by_window<kWalk, uint64_t>(g, sc, units.shift, kept[wave_id()]);
+}
+
+// What lies in front of every part, one workgroup per group of windows, an equal run of parts per wave.
+// kWalk = 1: highest ends -> what is covered in front of a part (at first the pool's start).  kWalk = 2:
+// numbers of intervals -> the number in front of a part; and with the totals, and the interval from the last
+// covered address to the end of the pool, the answers for the windows.
+constexpr int kRsPrefixWaves = 16;
+template <int kWalk>
+__global__ void __launch_bounds__(kRsPrefixWaves * kWave) rs_prefix(RsArgs g, RsParts sc)
+{
+    constexpr uint32_t kPer = kRsMaxParts / kRsPrefixWaves;
+    __shared__ uint64_t sums[kRsPrefixWaves][kWave], idles[kRsPrefixWaves][kWave];
+    if (*g.status != STALLOC_OK) return;
+    const int lane = lane_id(), wave = wave_id();
+    const RsUnits units = units_of(g.pool);
+    const uint32_t per = (sc.parts + kRsPrefixWaves - 1) / kRsPrefixWaves, p0 = umin((uint32_t)wave * per, sc.parts), p1 = umin(p0 + per, sc.parts);
+    const size_t row = (size_t)blockIdx.x * sc.parts * kWave + lane;
+    uint64_t v[kPer], idle = 0, sum = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+        v[u] = 0;
+        if (p0 + u < p1) {
+            const size_t cell = row + (size_t)(p0 + u) * kWave;
+            v[u] = kWalk == 1 ? sc.reach[cell] : (uint64_t)sc.found[cell];
+            if (kWalk == 2) idle += sc.idle[cell];
+        }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) sum = kWalk == 1 ? umax64(sum, v[u]) : sum + v[u];
+    sums[wave][lane] = sum;
+    idles[wave][lane] = idle;
+    __syncthreads();
+    uint64_t run = kWalk == 1 && !units.narrow ? g.pool->lo : 0ull, all = run;
+    for (int w = 0; w < kRsPrefixWaves; ++w) {
+        const uint64_t other = sums[w][lane];
+        if (w < wave) run = kWalk == 1 ? umax64(run, other) : run + other;
+        all = kWalk == 1 ? umax64(all, other) : all + other;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+        if (p0 + u >= p1) continue;
+        const size_t cell = row + (size_t)(p0 + u) * kWave;
+        if (kWalk == 1) { sc.reach[cell] = run; run = umax64(run, v[u]); }
+        else { sc.found[cell] = (uint32_t)run; run += v[u]; }
+    }
+    if (wave != 0) return;
+    if (kWalk == 1) {
+        sc.reach_all[(size_t)blockIdx.x * kWave + lane] = all;
+        return;
+    }
+    const RsWindow win = window_of_lane(g, blockIdx.x);
+    if (!win.live) return;
+    for (int w = 1; w < kRsPrefixWaves; ++w) idle += idles[w][lane];
+    if (units.narrow) idle <<= units.shift;                               // units of the pool -> bytes
+    const uint64_t reach = sc.reach_all[(size_t)blockIdx.x * kWave + lane], pool_hi = g.pool->hi;
+    const uint64_t covered = units.narrow ? g.pool->lo + (reach << units.shift) : reach;
+    uint32_t total = (uint32_t)all;
+    if (covered < pool_hi) {                                              // from the last covered address to the end of the pool
+        if (g.ranges && total < g.max_ranges) {
+            uint64_t* out = g.ranges + ((size_t)win.w * g.max_ranges + total) * 2;
+            out[0] = covered;
+            out[1] = pool_hi;
+        }
+        idle += pool_hi - covered;
+        ++total;
+    }
+    g.counts[win.w] = total;
+    if (g.idle_bytes) g.idle_bytes[win.w] = idle;
 }
 
 }  // namespace stalloc
@@ -398,18 +507,23 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     uint32_t* c_lo = cv.take<uint32_t>(n);
     uint32_t* c_hi = cv.take<uint32_t>(n);
     // window-per-lane sweep: enough (group of 64 windows) x (part of the plan) waves to fill the chip
-    RsParts sc = {nullptr, nullptr, nullptr, 0, 0};
+    RsParts sc = {nullptr, nullptr, nullptr, nullptr, 0, 0};
+    ulonglong2 *window_keys = nullptr, *window_spare = nullptr;
+    const uint32_t window_tiles = rs_window_per_lane(n, k) ? (k + kRsTile - 1) / kRsTile : 0u;
     const uint32_t groups = (k + kWave - 1) / kWave;
     if (rs_window_per_lane(n, k)) {
         const uint32_t all_steps = (n + kWave - 1) / kWave;
-        uint32_t parts = ((uint32_t)di.cus * 16 + groups - 1) / groups;
+        uint32_t parts = ((uint32_t)di.cus * kRsWavesPerCu + groups - 1) / groups;
         if (parts > kRsMaxParts) parts = kRsMaxParts;
         if (parts > (all_steps + 1) / 2) parts = (all_steps + 1) / 2;     // at least two steps to a part
         sc.steps = (all_steps + parts - 1) / parts;
         sc.parts = (all_steps + sc.steps - 1) / sc.steps;
         const size_t cells = (size_t)groups * sc.parts * kWave;
+        window_keys = cv.take<ulonglong2>((size_t)window_tiles * kRsTile);
+        window_spare = cv.take<ulonglong2>((size_t)window_tiles * kRsTile);
         sc.reach = cv.take<uint64_t>(cells);
         sc.idle = cv.take<uint64_t>(cells);
+        sc.reach_all = cv.take<uint64_t>((size_t)groups * kWave);
         sc.found = cv.take<uint32_t>(cells);
     }
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
@@ -423,7 +537,9 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     uint32_t blocks = (n + 255) / 256;
     if (blocks > 256) blocks = 256;
     hipLaunchKernelGGL(rs_init, dim3(1), dim3(64), 0, stream, pool);
-    hipLaunchKernelGGL(rs_sort_tiles, dim3(tiles), dim3(kSortThreads), 0, stream, tr->size, offsets, n, keys, pool, device_status);
+    const uint64_t near = (uint64_t)tr->t_end * kWave / k + 1;
+    hipLaunchKernelGGL(rs_sort_tiles, dim3(tiles + window_tiles), dim3(kSortThreads), 0, stream, tr->size, offsets, n, keys, pool, windows, k,
+                       near < 0x80000000ull ? (uint32_t)near : 0x80000000u, window_keys, device_status);
     const ulonglong2* sorted = launch_merge_tiles(keys, spare, tiles * kRsTile, 1, device_status, stream);
     hipLaunchKernelGGL(rs_gather, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, offsets, sorted, n,
                        s_lo, s_hi, s_life, pool, device_status);
@@ -431,17 +547,20 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     g.c_lo = c_lo; g.c_hi = c_hi;
     g.s_lo = s_lo; g.s_hi = s_hi; g.s_life = s_life; g.pool = pool; g.windows = windows;
     g.ranges = max_ranges ? ranges : nullptr; g.counts = counts; g.idle_bytes = idle_bytes; g.status = device_status;
-    g.n = n; g.k = k; g.max_ranges = max_ranges;
+    g.n = n; g.k = k; g.max_ranges = max_ranges; g.window_order = nullptr;
     if (rs_window_per_lane(n, k)) {
-        hipLaunchKernelGGL(rs_units, dim3(1), dim3(64), 0, stream, pool, device_status);
+        g.window_order = launch_merge_tiles(window_keys, window_spare, window_tiles * kRsTile, 1, device_status, stream);
         hipLaunchKernelGGL(rs_compress, dim3(blocks), dim3(256), 0, stream, s_lo, s_hi, n, pool, c_lo,
                            c_hi, device_status);
         const uint64_t waves = (uint64_t)groups * sc.parts;
-        uint32_t grid = (uint32_t)di.cus * 8;
+        // (a wave per unit as far as that goes: the hardware hands out the next one when one is done)
+        uint32_t grid = (uint32_t)di.cus * 256;
         if (grid > (waves + kRsWaves - 1) / kRsWaves) grid = (uint32_t)((waves + kRsWaves - 1) / kRsWaves);
         hipLaunchKernelGGL(rs_sweep_by_window<1>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
+        hipLaunchKernelGGL(rs_prefix<1>, dim3(groups), dim3(kRsPrefixWaves * kWave), 0, stream, g, sc);
         hipLaunchKernelGGL(rs_sweep_by_window<2>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
-        hipLaunchKernelGGL(rs_sweep_by_window<3>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
+        hipLaunchKernelGGL(rs_prefix<2>, dim3(groups), dim3(kRsPrefixWaves * kWave), 0, stream, g, sc);
+        if (g.ranges) hipLaunchKernelGGL(rs_sweep_by_window<3>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
     } else {
         uint32_t grid = (uint32_t)di.cus * 8;
         if (grid > k) grid = k;

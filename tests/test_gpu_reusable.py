@@ -175,3 +175,20 @@ def test_reports_malformed_inputs(S):
     # counts and idle bytes only
     status, ranges, counts, idle = _gpu(S, size, ts, te, int(te.max()), a, np.array([[4, 6]], np.uint32), 0)
     assert status == 0 and ranges is None and int(counts[0]) == 4 and int(idle[0]) == 7
+
+
+@pytest.mark.parametrize("shape", ["equal", "whole", "short", "ends", "few"])
+def test_windows_of_unlike_length_and_place(S, oracle, shape):
+    """The sweep by window sorts its windows by length and start: all alike, all spanning everything, all one
+    event long, all at either end, and just enough of them, beside a long pool of decisions."""
+    rng = np.random.default_rng(4400)
+    k = 32 if shape == "few" else 1111
+    n = (1 << 23) // k + 1
+    size, ts, te, t_end = random_trace(rng, n, t_max=3 * n, unique_times=False)
+    te = np.minimum(te, ts + rng.choice([3, 50, 3 * n], n).astype(np.uint32))
+    a = rng.integers(0, 1 << 30, n).astype(np.uint64)
+    lo = {"equal": np.full(k, t_end // 3), "whole": np.zeros(k, np.int64), "short": rng.integers(0, t_end, k),
+          "ends": rng.choice([0, t_end - 2], k), "few": rng.integers(0, t_end, k)}[shape]
+    span = {"equal": 99, "whole": t_end, "short": 1, "ends": 2, "few": rng.integers(1, t_end, k)}[shape]
+    windows = np.stack([lo, lo + span], axis=1).astype(np.uint32)
+    _compare(S, oracle, size, ts, te, int(te.max()), a, windows, cap=8, sample=range(0, k, max(1, k // 12)))
