@@ -80,6 +80,8 @@ constexpr int kAccKernel = 8;                  // which placement kernel took th
 constexpr int kAccWidePlans = 9;               // plans that outgrew 32-bit granule counts and were placed with 64-bit addresses
 constexpr int kAccLargeShort = 10;             // long-list kernel: size (granules) from which a short-lived block counts as large
                                                // (0xffffffff: none does); bits 32..63: how many do
+constexpr int kAccTiles = 11;                  // bitmap kernel with tables per tile of time: 0 = does not place the trace, else its layout (plan_tiled.hip)
+constexpr int kAccTilesMissed = 12;            // plans that outgrew its tables and are left to the other bitmap kernel
 constexpr uint64_t kModeNarrow = 1ull << 8;
 constexpr uint64_t kModeCompact = 1ull << 9;   // sum of sizes in granules below 2^16 as well
 constexpr uint64_t kModeBitmap = 1ull << 10;   // sum <= kBitmapGranules and every size <= kBitmapMaxSize granules

@@ -720,6 +720,8 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     const bool bitmap = bitmap_plan_shapes(n, di, pool_words) && allow_bitmap;
     uint32_t* nbr_begin = bitmap ? cv.take<uint32_t>((size_t)n + 2) : nullptr;
     uint16_t* nbr = bitmap ? cv.take<uint16_t>(bitmap_index_entries(n)) : nullptr;
+    const bool tiled = bitmap && tiled_plan_possible(n, tr->t_end, P, di);
+    int32_t* net = tiled ? cv.take<int32_t>((size_t)tr->t_end + 1) : nullptr;
     // variant for long traces with few long-lived requests: tables in allocation-time order
     const bool split = !lds32;
     SplitWorkspace sw;
@@ -746,6 +748,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     for (int shape = 0; shape < kBitmapShapes; ++shape) prm.bitmap_pool_words[shape] = bitmap ? pool_words[shape] : 0u;
     bool ok = true;
     if (split) ok = ok && launch_plan_split(prm, tr->t_end, sw, di, stream);
+    if (tiled) ok = ok && launch_plan_tiled(prm, tr->t_end, net, di, stream);
     if (bitmap) ok = ok && launch_plan_bitmap(prm, di, stream);
     // exactly one of the launches does the work; the trace decides which (see the mode word)
     if (compact) ok = ok && launch_plan<uint32_t, true, true, kPendLds, kThreadsCompact>(prm, grid_compact, di, stream);

@@ -28,6 +28,7 @@
 //
 // Batches are software-pipelined over two halves of the bitmap pool: batch B is settled while
 // batch B + 1 is built.  Nothing is sorted or merged and no placement needs a second pass.
+#include "bitmap_cells.h"
 #include "host_util.h"
 #include "plan_params.h"
 #include "wave.h"
@@ -43,10 +44,6 @@ namespace stalloc {
 constexpr int kRefillPerWave = STALLOC_BITMAP_REFILL;   // (the pipeline of batches drains at every refill)
 constexpr uint32_t kShares = STALLOC_BITMAP_SHARES; // chunks a building wave takes for every one wave 0 takes
 constexpr int kBmWords = 1056;           // a pool of twice this many words is asked for before workgroups share a CU
-constexpr int kRowPad = 256;             // index rows are padded to this many entries (4 per lane)
-
-constexpr uint32_t kBmMaxRequests = 32768;         // index entries are 16-bit request numbers; the index has n^2 of them at worst
-
 template <int kWaves>
 struct BitmapLds {
     static constexpr int kBmBatch = kRefillPerWave * kWaves;     // 128 requests with eight waves, 256 with sixteen
@@ -72,12 +69,10 @@ struct BitmapLds {
 // dummy that is never placed) -- stored as 4 * j, the byte offset into the plan's table, while
 // 4 * n fits 16 bits (the build phase then needs one instruction less per lookup).  begin[] first
 // holds the degrees, then their exclusive prefix sum in chunks.
-constexpr uint32_t kScaledEntriesBelow = 16384;      // n below this: entries are 4 * j
-__host__ __device__ inline uint32_t entry_shift(uint32_t n) { return n < kScaledEntriesBelow ? 2u : 0u; }
-
 __device__ __forceinline__ bool index_wanted(const PlanParams& prm)
 {
-    return *prm.status == STALLOC_OK && bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0;
+    return *prm.status == STALLOC_OK && bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0 &&
+           (prm.acc[kAccTiles] == 0 || prm.acc[kAccTilesMissed] != 0);      // (nothing left to place, see plan_tiled.hip)
 }
 
 __global__ void __launch_bounds__(256) nbr_count(PlanParams prm)
@@ -122,153 +117,16 @@ __global__ void __launch_bounds__(1024) nbr_scan(PlanParams prm)
     if (threadIdx.x == 1023) prm.nbr_begin[n] = part[1023];
 }
 
-// Fills row i.  The order of a row's entries is free (the bitmap is an OR over the row), so it is
-// chosen for the table lookups of the build phase: one lookup instruction reads the table cells
-// of 64 consecutive entries of this order, and LDS serves them fastest when they lie in different
-// banks (cell j is in bank j mod 32).  Entries are ordered by (rank, bank), rank = how many
-// entries of the same bank come before: any 64 in a row then hold every bank about twice.
-// Within a chunk of 256, entry e belongs to lane e / 4 and lookup e mod 4, hence the transposition.
 __global__ void __launch_bounds__(256) nbr_fill(PlanParams prm)
 {
-    constexpr uint32_t kMaxRank = kBmMaxRequests / 32;
-    __shared__ uint32_t per_thread[256];
-    __shared__ uint32_t in_bank[32];
-    __shared__ uint32_t before_rank[kMaxRank + 1];      // entries with a lower rank
-    __shared__ uint32_t banks_at_rank[kMaxRank + 1];    // banks that have an entry of this rank
+    __shared__ RowLds sh;
     if (!index_wanted(prm)) return;
-    const uint32_t i = blockIdx.x, n = prm.n, t = threadIdx.x;
-    const uint32_t bank = t & 31u;                      // thread t sees j = t, t + 256, ...: all in one bank
-    const uint32_t ta = prm.ta[i], tf = prm.tf[i];
-    uint32_t mine = 0;
-    for (uint32_t j = t; j < n; j += 256) mine += (j != i && prm.ta[j] < tf && ta < prm.tf[j]);
-    per_thread[t] = mine;
-    __syncthreads();
-    uint32_t rank = 0, total = 0;                       // of the 8 threads of a bank, the lower ones come first
-    for (uint32_t m = 0; m < 8; ++m) {
-        const uint32_t c = per_thread[bank + 32 * m];
-        if (m < (t >> 5)) rank += c;
-        total += c;
-    }
-    if (t < 32) in_bank[t] = total;
-    __syncthreads();
-    for (uint32_t r = t; r <= kMaxRank; r += 256) {
-        uint32_t before = 0, banks = 0;
-        for (uint32_t b = 0; b < 32; ++b) {
-            const uint32_t c = in_bank[b];
-            before += c < r ? c : r;
-            banks |= (c > r ? 1u : 0u) << b;
-        }
-        before_rank[r] = before;
-        banks_at_rank[r] = banks;
-    }
-    __syncthreads();
-    uint16_t* row = prm.nbr + (size_t)prm.nbr_begin[i] * kRowPad;
-    const uint32_t room = (prm.nbr_begin[i + 1] - prm.nbr_begin[i]) * kRowPad;
-    auto slot = [](uint32_t pos) {                      // position in the order -> entry of the row
-        const uint32_t p = pos % kRowPad;
-        return pos - p + 4 * (p % kWave) + p / kWave;
-    };
-    for (uint32_t j = t; j < n; j += 256) {
-        if (j != i && prm.ta[j] < tf && ta < prm.tf[j]) {
-            const uint32_t pos = before_rank[rank] + (uint32_t)__builtin_popcount(banks_at_rank[rank] & ((1u << bank) - 1u));
-            if (pos < room) row[slot(pos)] = (uint16_t)(j << entry_shift(n));
-            ++rank;
-        }
-    }
-    const uint32_t filled = before_rank[kMaxRank];      // = number of entries
-    for (uint32_t pos = filled + t; pos < room; pos += 256) row[slot(pos)] = (uint16_t)(n << entry_shift(n));
+    const uint32_t i = blockIdx.x, ta = prm.ta[i], tf = prm.tf[i];
+    fill_row(prm.nbr + (size_t)prm.nbr_begin[i] * kRowPad, (prm.nbr_begin[i + 1] - prm.nbr_begin[i]) * kRowPad, prm.n, sh,
+             [&](uint32_t j) { return j != i && prm.ta[j] < tf && ta < prm.tf[j]; });
 }
 
 // ---------------------------------------------------------------------------------------------
-
-// A placed block as the build phase wants it: bits 0-21 address in granules (bits 0-4 = first bit
-// b in its first word, bits 5-21 = that word), bits 22-26 size in granules (1..31), bits 27-31 the
-// number of granules that spill into the next word.  0 = not placed.
-constexpr uint32_t kCellSizeAt = 22, kCellSpillAt = 27;
-__device__ __forceinline__ uint32_t make_cell(uint32_t x, uint32_t sz)
-{
-    const uint32_t reach = (x & 31) + sz;
-    return x | (sz << kCellSizeAt) | ((reach > 32 ? reach - 32 : 0u) << kCellSpillAt);
-}
-
-// ((1 << width) - 1) << offset with both taken modulo 32.
-__device__ __forceinline__ uint32_t bit_field_mask(uint32_t width, uint32_t offset)
-{
-    uint32_t r;
-    asm("v_bfm_b32 %0, %1, %2" : "=v"(r) : "v"(width), "v"(offset));
-    return r;
-}
-
-typedef __attribute__((address_space(3))) uint32_t lds_word;
-
-// LDS address of the first bitmap word of the block of `cell`: field extract, shift-add.
-__device__ __forceinline__ lds_word* first_word(uint32_t* bm, uint32_t cell)
-{
-    const uint32_t base = (uint32_t)reinterpret_cast<uintptr_t>((lds_word*)bm);
-    uint32_t at;
-    asm("v_bfe_u32 %0, %1, 5, 17\n\tv_lshl_add_u32 %0, %0, 2, %2" : "=&v"(at) : "v"(cell), "s"(base));
-    return reinterpret_cast<lds_word*>((uintptr_t)at);
-}
-
-// ORs the block of `cell` into the bitmap; cell == 0 adds nothing.
-__device__ __forceinline__ void mark_cell(uint32_t* bm, uint32_t cell)
-{
-    lds_word* word = first_word(bm, cell);
-    const uint32_t first = bit_field_mask(cell >> kCellSizeAt, cell);      // ((1 << size) - 1) << b, low 32 bits
-    const uint32_t spill = bit_field_mask(cell >> kCellSpillAt, 0u);       // (1 << spilled) - 1
-    if (cell) __hip_atomic_fetch_or(word, first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (cell >= (1u << kCellSpillAt)) __hip_atomic_fetch_or(word + 1, spill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// The same for four cells per lane, looking before ORing.  Blocks that are alive at different
-// times share addresses (that is the point of the plan), so most blocks of a row only repeat
-// bits that are already set, and many lanes of one instruction aim at the same few words.  LDS
-// serialises atomics on one address lane by lane but broadcasts reads of one address, hence:
-// read the words, and send only the lanes that still add a bit into the atomic.  (A word read
-// just before another wave's OR merely causes a redundant OR.)  Address and masks are worked
-// out for every lane; idle lanes have empty masks and drop out with the rest.
-__device__ __forceinline__ void mark_cells(uint32_t* bm, const uint32_t (&cell)[4])
-{
-    lds_word* word[4];
-    uint32_t first[4], spill[4], seen[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        word[k] = first_word(bm, cell[k]);
-        first[k] = bit_field_mask(cell[k] >> kCellSizeAt, cell[k]);
-        spill[k] = bit_field_mask(cell[k] >> kCellSpillAt, 0u);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) seen[k] = *word[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (first[k] & ~seen[k]) __hip_atomic_fetch_or(word[k], first[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (cell[k] >= (1u << kCellSpillAt)) __hip_atomic_fetch_or(word[k] + 1, spill[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-}
-
-// Lowest bit position x such that bits [x, x + s) of the bitmap are zero; words at and beyond
-// `limit` count as free.  1 <= s <= 32, s and limit uniform.  Whole wave, uniform result.
-__device__ __forceinline__ uint32_t first_fit(const uint32_t* bm, uint32_t limit, uint32_t s)
-{
-    const int lane = lane_id();
-    for (uint32_t t = 0;; t += kWave) {
-        const uint32_t w = t + lane;
-        const uint32_t here = w < limit ? bm[w] : 0u;
-        const uint32_t next = w + 1 < limit ? bm[w + 1] : 0u;
-        uint64_t free_run = ~((uint64_t)here | ((uint64_t)next << 32));     // bit b: granule 32 w + b is free
-        for (uint32_t len = 1; len < s;) {                                  // bit b: free for `len` granules from b
-            const uint32_t step = len < s - len ? len : s - len;
-            free_run &= free_run >> step;
-            len += step;
-        }
-        const uint32_t starts = (uint32_t)free_run;                         // runs that begin inside word w
-        const uint64_t any = __builtin_amdgcn_uicmp(starts, 0u, 33);        // != 0
-        if (any) {
-            const int f = __builtin_ctzll(any);
-            return (t + (uint32_t)f) * 32 + (uint32_t)__builtin_ctz(read_lane(starts, f));
-        }
-    }
-}
 
 // Inclusive prefix sum inside each row of 16 lanes.
 __device__ __forceinline__ uint32_t row_scan_add(uint32_t v)
@@ -295,8 +153,9 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 8 : 4) plan_bitm
     uint32_t* pool = cells + (prm.n + 1);
     const uint32_t n = prm.n;
 
-    if (*prm.status != STALLOC_OK) return;
+    if (!index_wanted(prm)) return;
     if (bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) != kShape) return;
+    const bool some = prm.acc[kAccTiles] != 0;         // only the plans that outgrew the tables of the tiled variant
     const uint32_t shift = (uint32_t)(prm.acc[kAccMode] & 63);
     if (blockIdx.x == 0 && threadIdx.x == 0) const_cast<uint64_t*>(prm.acc)[kAccKernel] = STALLOC_KERNEL_BITMAP | (22u << 8);
     const uint32_t pool_words = prm.bitmap_pool_words[kShape];
@@ -308,6 +167,7 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 8 : 4) plan_bitm
     const uint2* index = reinterpret_cast<const uint2*>(prm.nbr) + lane;   // a chunk: 64 lanes x 4 entries
 
     for (uint32_t p = blockIdx.x; p < prm.P; p += gridDim.x) {
+        if (some && !prm.wide_plans[p]) continue;             // (uniform)
         const uint32_t* order = prm.orders + (size_t)p * n;
         uint64_t* out = prm.offsets ? prm.offsets + (size_t)p * n : nullptr;
         for (uint32_t i = threadIdx.x; i <= n; i += kThreads) cells[i] = 0;     // nothing placed; cell n pads the rows

@@ -16,7 +16,8 @@ struct PlanParams {
     uint32_t* status;
     const uint64_t* acc;     // trace-check accumulators (mode word)
     unsigned char* slabs;    // list in the workspace: gridDim.x slabs of 2 * n entries
-    uint32_t* wide_plans;    // [P] list variant: 1 = the plan outgrew 32-bit granule counts, the 64-bit kernel places it
+    uint32_t* wide_plans;    // [P] 1 = the plan outgrew 32-bit granule counts (list variant) or the tables (tiled bitmap
+                             // variant) of the kernel that tried it; another one places it
     uint32_t* nbr_begin;     // bitmap variant: [n + 2] row starts of the lifetime-conflict index
     uint16_t* nbr;           // bitmap variant: indices of the requests with an overlapping lifetime, row by row
     uint32_t n;
@@ -78,6 +79,8 @@ bool launch_plan_split(const PlanParams& prm, uint32_t t_end, const SplitWorkspa
 // Fills PlanParams::bitmap_pool_words for a trace of n requests; false if no shape fits.
 bool bitmap_plan_shapes(uint32_t n, const DeviceInfo& di, uint32_t (&pool_words)[kBitmapShapes]);
 size_t bitmap_index_entries(uint32_t n);             // uint16_t entries of PlanParams::nbr
+bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInfo& di);   // bitmap variant with tables per tile of time; net: t_end + 1 words
+bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream);
 bool launch_plan_bitmap(const PlanParams& prm, const DeviceInfo& di, hipStream_t stream);
 
 }  // namespace stalloc
