@@ -416,7 +416,7 @@ extern "C" int stalloc_fuse_groups(const stalloc_trace* tr, const uint32_t* memb
     const size_t lds_budget = di.lds_per_block - 1024;
     if ((size_t)largest_pair * per_request > lds_budget) return STALLOC_ERR_TOO_LARGE;
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
     if (!members || !pair_begin || !count1 || !order || !addr || !extents || !accepted || !device_status ||
         *workspace_bytes < cv.used || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)))

@@ -71,6 +71,8 @@ struct Carver {
 // counts can | kModeBitmap when the sizes suit one-bit-per-granule occupancy bitmaps | kModeTry32
 // when only plans that stack nearly everything would overflow 32-bit counts.
 constexpr int kAccWords = 16;
+constexpr int kTraceCheckBlocks = 256;
+constexpr int kAccSpace = kAccWords + 5 * kTraceCheckBlocks;   // what launch_trace_check needs: the words, and five per workgroup behind them
 constexpr int kAccMode = 4;
 constexpr int kAccMaxSize = 5;
 constexpr int kAccGranules = 6;                // sum of sizes in granules

@@ -642,7 +642,7 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
     const uint32_t chunks = (n + kScanChunk - 1) / kScanChunk;
 
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     ulonglong2* keys = cv.take<ulonglong2>((size_t)tiles * kLyTile);
     ulonglong2* spare = cv.take<ulonglong2>((size_t)tiles * kLyTile);
     uint32_t* sorted = cv.take<uint32_t>(n);

@@ -174,6 +174,76 @@ lb_tiles(const int64_t* __restrict__ net, uint32_t t_end, int64_t* tile_sum, LbB
     }
 }
 
+// Short traces: the whole call in one workgroup, net changes in LDS.  Up to this many requests and timestamps it
+// takes less time than the two further launches it saves (6144 requests on 12 288 timestamps: LB_US).
+constexpr uint32_t kLbSmallRequests = 16384, kLbSmallTimes = 16384;
+constexpr int kLbSmallThreads = 1024;
+
+__global__ void __launch_bounds__(kLbSmallThreads)
+lb_small(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end,
+         uint64_t* lower_bound, uint32_t* t_at_max, uint32_t* status)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int kWaves = kLbSmallThreads / kWave;
+    __shared__ uint64_t part[kWaves][3];
+    __shared__ int64_t before[kWaves];
+    __shared__ LbBest best_of[kWaves];
+    unsigned long long* const net = reinterpret_cast<unsigned long long*>(smem);       // [t_end + 1]
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t t = tid; t <= t_end; t += kLbSmallThreads) net[t] = 0;
+    __syncthreads();
+    uint64_t hi = 0, lo = 0;
+    uint32_t bad = 0;
+    for (uint32_t i = tid; i < n; i += kLbSmallThreads) {
+        const uint64_t s = size[i];
+        const uint32_t a = ta[i], f = tf[i];
+        bad |= (s == 0) | (a >= f) | (f > t_end);
+        hi += s >> 32;
+        lo += s & 0xffffffffull;
+        if (a < f && f <= t_end) {   // malformed requests are reported; never index out of range
+            atomicAdd(&net[a], (unsigned long long)s);
+            atomicAdd(&net[f], (unsigned long long)(0 - s));
+        }
+    }
+    hi = wave_sum64(hi);
+    lo = wave_sum64(lo);
+    const uint64_t any_bad = __builtin_amdgcn_ballot_w64(bad != 0);
+    if (lane_id() == 0) { part[wave_id()][0] = hi; part[wave_id()][1] = lo; part[wave_id()][2] = any_bad; }
+    __syncthreads();
+    // a run of timestamps per thread
+    const uint32_t per = (t_end + kLbSmallThreads - 1) / kLbSmallThreads, t0 = umin(tid * per, t_end), t1 = umin(t0 + per, t_end);
+    int64_t sum = 0;
+    for (uint32_t t = t0; t < t1; ++t) sum += (int64_t)net[t];
+    const int64_t incl = (int64_t)wave_scan_add64((uint64_t)sum);
+    if (lane_id() == kWave - 1) before[wave_id()] = incl;
+    __syncthreads();
+    int64_t live = incl - sum;
+    for (int w = 0; w < wave_id(); ++w) live += before[w];
+    int64_t best = INT64_MIN;
+    uint32_t best_t = 0xffffffffu;
+    for (uint32_t t = t0; t < t1; ++t) {
+        live += (int64_t)net[t];
+        if (lb_better(live, t, best, best_t)) { best = live; best_t = t; }
+    }
+    const uint64_t key = (uint64_t)best ^ (1ull << 63);                // order of int64 as unsigned
+    const uint64_t wmax = wave_max64(key), wt = wave_min64(key == wmax ? (uint64_t)best_t : ~0ull);
+    if (lane_id() == 0) best_of[wave_id()] = LbBest{(int64_t)(wmax ^ (1ull << 63)), (uint32_t)wt, 0};
+    __syncthreads();
+    if (tid != 0) return;
+    LbBest all = best_of[0];
+    uint64_t any = part[0][2];
+    hi = part[0][0];
+    lo = part[0][1];
+    for (int w = 1; w < kWaves; ++w) {
+        if (lb_better(best_of[w].live, best_of[w].t, all.live, all.t)) all = best_of[w];
+        hi += part[w][0]; lo += part[w][1]; any |= part[w][2];
+    }
+    if (all.live <= 0) { all.live = 0; all.t = 0; }                   // a maximum of zero live bytes is reported at t = 0
+    *lower_bound = (uint64_t)all.live;
+    if (t_at_max) *t_at_max = all.t;
+    *status = any ? STALLOC_ERR_BAD_TRACE : hi + (lo >> 32) >= (1ull << 31) ? STALLOC_ERR_OVERFLOW : STALLOC_OK;
+}
+
 // Pieces of the scratch memory one call needs, carved from `base` (nullptr: sizes only).
 struct LbScratch {
     uint64_t* acc;
@@ -198,6 +268,20 @@ static int enqueue_lower_bound(const stalloc_trace& tr, uint64_t* lower_bound, u
                                uint32_t* device_status, const LbScratch& sc, hipStream_t stream)
 {
     const uint32_t t_end = tr.t_end;
+    if (tr.n <= kLbSmallRequests && t_end < kLbSmallTimes) {
+        DeviceInfo di;
+        if (!device_info(&di)) return STALLOC_ERR_DEVICE;
+        static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
+        if (!attr_set[di.device]) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&lb_small), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(kLbSmallTimes * sizeof(int64_t))) != hipSuccess)
+                return STALLOC_ERR_DEVICE;
+            attr_set[di.device] = true;
+        }
+        hipLaunchKernelGGL(lb_small, dim3(1), dim3(kLbSmallThreads), ((size_t)t_end + 1) * sizeof(int64_t), stream, tr.size, tr.t_alloc,
+                           tr.t_free, tr.n, t_end, lower_bound, t_at_max, device_status);
+        return hipGetLastError() == hipSuccess ? STALLOC_OK : STALLOC_ERR_DEVICE;
+    }
     uint32_t clear_blocks = (t_end + 1 + kLbThreads - 1) / kLbThreads;
     if (clear_blocks > 4096) clear_blocks = 4096;
     hipLaunchKernelGGL(lb_clear, dim3(clear_blocks), dim3(kLbThreads), 0, stream, sc.net, t_end + 1, sc.acc, device_status);

@@ -432,7 +432,7 @@ extern "C" int stalloc_make_orders(const stalloc_trace* tr, uint32_t first_plan,
     if (spread) merged = first_plan <= 2 ? (uint32_t)(last < 2 ? last + 1 : 3) : (last >= 4 ? 1u : 0u);
 
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     ulonglong2* buf_a = cv.take<ulonglong2>((size_t)merged * n_pad);
     ulonglong2* buf_b = cv.take<ulonglong2>((size_t)merged * n_pad);
     uint32_t* larger = cv.take<uint32_t>(n);

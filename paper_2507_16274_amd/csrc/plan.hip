@@ -563,26 +563,17 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
             __syncthreads();
             if (out && threadIdx.x < staged) out[sh.rq_id[threadIdx.x]] = sh.rq_addr[threadIdx.x];
         }
-        if (outgrown) {
-            if (threadIdx.x == 0) prm.wide_plans[p] = 1;
-            continue;
-        }
+        if (sizeof(Addr) == 4 && threadIdx.x == 0) prm.wide_plans[p] = outgrown ? 1u : 0u;
+        if (outgrown) continue;
         if (threadIdx.x == 0) prm.peaks[p] = (uint64_t)peak << shift;
     }
 }
 
-__global__ void plan_clear_marks(uint32_t* wide_plans, uint32_t P)
-{
-    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) wide_plans[p] = 0;
-}
-
-// best_plan = index of the smallest extent (lowest index among equals); one workgroup.
-__global__ void __launch_bounds__(256) plan_argmin(const uint64_t* __restrict__ peaks, uint32_t P, uint32_t* best_plan,
-                                                   const uint32_t* status)
+// Index of the smallest extent (lowest index among equals), in all threads of a workgroup of 256.
+__device__ __forceinline__ uint32_t index_of_best(const uint64_t* __restrict__ peaks, uint32_t P)
 {
     __shared__ uint64_t w_peak[4];
     __shared__ uint64_t w_idx[4];
-    if (*status != STALLOC_OK) { if (threadIdx.x == 0) *best_plan = 0; return; }
     uint64_t best = ~0ull, idx = ~0ull;
     for (uint32_t p = threadIdx.x; p < P; p += 256) {
         uint64_t v = peaks[p];
@@ -592,12 +583,31 @@ __global__ void __launch_bounds__(256) plan_argmin(const uint64_t* __restrict__ 
     uint64_t widx = wave_min64(best == wbest ? idx : ~0ull);
     if (lane_id() == 0) { w_peak[wave_id()] = wbest; w_idx[wave_id()] = widx; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t b = w_peak[0], i = w_idx[0];
-        for (int k = 1; k < 4; ++k)
-            if (w_peak[k] < b || (w_peak[k] == b && w_idx[k] < i)) { b = w_peak[k]; i = w_idx[k]; }
-        *best_plan = (uint32_t)i;
-    }
+    uint64_t b = w_peak[0], i = w_idx[0];
+    for (int k = 1; k < 4; ++k)
+        if (w_peak[k] < b || (w_peak[k] == b && w_idx[k] < i)) { b = w_peak[k]; i = w_idx[k]; }
+    return (uint32_t)i;
+}
+
+__global__ void __launch_bounds__(256) plan_argmin(const uint64_t* __restrict__ peaks, uint32_t P, uint32_t* best_plan,
+                                                   const uint32_t* status)
+{
+    if (*status != STALLOC_OK) { if (threadIdx.x == 0) *best_plan = 0; return; }
+    const uint32_t best = index_of_best(peaks, P);
+    if (threadIdx.x == 0) *best_plan = best;
+}
+
+// The same and the best plan's addresses in one launch: every workgroup looks for the best plan by itself, which
+// for up to this many plans is less than a launch (4096 extents are 32 KB, read from the L2).
+constexpr uint32_t kBestAlone = 4096;
+__global__ void __launch_bounds__(256) plan_best(const uint64_t* __restrict__ peaks, uint32_t P, const uint64_t* __restrict__ offsets,
+                                                 uint32_t n, uint32_t* best_plan, uint64_t* best_offsets, const uint32_t* status)
+{
+    if (*status != STALLOC_OK) { if (blockIdx.x == 0 && threadIdx.x == 0) *best_plan = 0; return; }
+    const uint32_t best = index_of_best(peaks, P);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *best_plan = best;
+    const uint64_t* src = offsets + (size_t)best * n;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) best_offsets[i] = src[i];
 }
 
 __global__ void __launch_bounds__(256) plan_copy_best(const uint64_t* __restrict__ offsets, const uint32_t* best_plan,
@@ -711,7 +721,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     if (grid_compact > P) grid_compact = P;
 
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* own_offsets = (!offsets && best_offsets) ? cv.take<uint64_t>((size_t)P * n) : nullptr;
     unsigned char* slabs = lds64 ? nullptr : cv.take<unsigned char>((size_t)grid_mem * 2 * n * entry_bytes<uint64_t>());
     uint32_t* wide_plans = cv.take<uint32_t>(P);
@@ -740,11 +750,6 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     prm.peaks = peaks; prm.status = device_status; prm.acc = acc; prm.slabs = slabs; prm.n = n; prm.P = P;
     prm.compact_enqueued = compact ? 1u : 0u;
     prm.nbr_begin = nbr_begin; prm.nbr = nbr; prm.wide_plans = wide_plans;
-    {
-        uint32_t pb = (P + 255) / 256;
-        if (pb > 256) pb = 256;
-        hipLaunchKernelGGL(plan_clear_marks, dim3(pb), dim3(256), 0, stream, wide_plans, P);
-    }
     for (int shape = 0; shape < kBitmapShapes; ++shape) prm.bitmap_pool_words[shape] = bitmap ? pool_words[shape] : 0u;
     bool ok = true;
     if (split) ok = ok && launch_plan_split(prm, tr->t_end, sw, di, stream);
@@ -758,10 +763,15 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     else       ok = ok && launch_plan<uint64_t, false, false, kPendMem, kThreadsMem>(prm, grid_mem, di, stream);
     if (!ok) return STALLOC_ERR_DEVICE;
 
+    uint32_t blocks = (n + 255) / 256;
+    if (blocks > 1024) blocks = 1024;
+    if (best_offsets && P <= kBestAlone) {
+        if (blocks > 256) blocks = 256;
+        hipLaunchKernelGGL(plan_best, dim3(blocks), dim3(256), 0, stream, peaks, P, prm.offsets, n, best_plan, best_offsets, device_status);
+        return hipGetLastError() == hipSuccess ? STALLOC_OK : STALLOC_ERR_DEVICE;
+    }
     hipLaunchKernelGGL(plan_argmin, dim3(1), dim3(256), 0, stream, peaks, P, best_plan, device_status);
     if (best_offsets) {
-        uint32_t blocks = (n + 255) / 256;
-        if (blocks > 1024) blocks = 1024;
         hipLaunchKernelGGL(plan_copy_best, dim3(blocks), dim3(256), 0, stream, prm.offsets, best_plan, n, best_offsets,
                            device_status);
     }

@@ -1102,10 +1102,8 @@ __global__ void __launch_bounds__(kThreads, kRanked ? 6 : 4) plan_split_kernel(P
             if (out && threadIdx.x < staged) out[sh.rq_id[threadIdx.x]] = (uint64_t)sh.rq_addr[threadIdx.x] << shift;
         }
         __syncthreads();
-        if (outgrown) {
-            if (threadIdx.x == 0) prm.wide_plans[p] = 1;
-            continue;
-        }
+        if (threadIdx.x == 0) prm.wide_plans[p] = outgrown ? 1u : 0u;
+        if (outgrown) continue;
         if (threadIdx.x == 0) prm.peaks[p] = (uint64_t)sh.peak << shift;
     }
 }

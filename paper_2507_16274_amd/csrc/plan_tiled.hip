@@ -350,6 +350,7 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
                 atomicAdd((unsigned long long*)&const_cast<uint64_t*>(prm.acc)[kAccTilesMissed], 1ull);
             }
         } else if (threadIdx.x == 0) {
+            prm.wide_plans[p] = 0;
             prm.peaks[p] = (uint64_t)top << shift;
         }
         __syncthreads();                                              // sh read before the next plan clears it

@@ -496,7 +496,7 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     const uint32_t n = tr->n;
 
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     RsPool* pool = cv.take<RsPool>(1);
     const uint32_t tiles = (n + kRsTile - 1) / kRsTile;
     ulonglong2* keys = cv.take<ulonglong2>((size_t)tiles * kRsTile);

@@ -26,46 +26,58 @@ __global__ void tmp_init(TmpAcc* acc)
     if (threadIdx.x == 0) { acc->limb[0] = acc->limb[1] = acc->limb[2] = 0; acc->t_first = 0xffffffffu; acc->t_last = 0; }
 }
 
-__global__ void __launch_bounds__(256)
-tmp_used(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
-         TmpAcc* acc, const uint32_t* status)
+// Sums over the requests that the calling threads take, `step` apart; valid in thread 0 of the workgroup.
+template <int kThreads>
+__device__ __forceinline__ TmpAcc tmp_sum(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta,
+                                          const uint32_t* __restrict__ tf, uint32_t n, uint32_t from, uint32_t step)
 {
-    __shared__ uint64_t part[4][3];
-    __shared__ uint32_t t_lo[4], t_hi[4];
-    if (*status != STALLOC_OK) return;
-    uint64_t l0 = 0, l1 = 0, l2 = 0;
-    uint32_t first = 0xffffffffu, last = 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    __shared__ TmpAcc part[kThreads / kWave];
+    TmpAcc t = {{0, 0, 0}, 0xffffffffu, 0};
+    for (uint32_t i = from; i < n; i += step) {
         const uint64_t s = size[i];
         const uint32_t a = ta[i], f = tf[i];
         const uint64_t life = f - a;
         const uint64_t low = (s & 0xffffffffull) * life;           // < 2^64
         const uint64_t high = (s >> 32) * life + (low >> 32);       // bits 32.. of the product; < 2^64
-        l0 += low & 0xffffffffull;
-        l1 += high & 0xffffffffull;
-        l2 += high >> 32;
-        first = a < first ? a : first;
-        last = f > last ? f : last;
+        t.limb[0] += low & 0xffffffffull;
+        t.limb[1] += high & 0xffffffffull;
+        t.limb[2] += high >> 32;
+        t.t_first = umin(t.t_first, a);
+        t.t_last = umax(t.t_last, f);
     }
-    l0 = wave_sum64(l0); l1 = wave_sum64(l1); l2 = wave_sum64(l2);
-    const uint32_t w_first = 0xffffffffu - (uint32_t)wave_max64(0xffffffffu - first), w_last = (uint32_t)wave_max64(last);
-    if (lane_id() == 0) {
-        part[wave_id()][0] = l0; part[wave_id()][1] = l1; part[wave_id()][2] = l2;
-        t_lo[wave_id()] = w_first; t_hi[wave_id()] = w_last;
-    }
+    for (int k = 0; k < 3; ++k) t.limb[k] = wave_sum64(t.limb[k]);
+    t.t_first = ~read_lane(wave_scan_max(~t.t_first), kWave - 1);
+    t.t_last = read_lane(wave_scan_max(t.t_last), kWave - 1);
+    if (lane_id() == 0) part[wave_id()] = t;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) {
-            l0 += part[w][0]; l1 += part[w][1]; l2 += part[w][2];
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kThreads / kWave; ++w) {
+            for (int k = 0; k < 3; ++k) t.limb[k] += part[w].limb[k];
+            t.t_first = umin(t.t_first, part[w].t_first);
+            t.t_last = umax(t.t_last, part[w].t_last);
         }
-        uint32_t lo = t_lo[0], hi = t_hi[0];
-        for (int w = 1; w < 4; ++w) { lo = t_lo[w] < lo ? t_lo[w] : lo; hi = t_hi[w] > hi ? t_hi[w] : hi; }
-        atomicAdd((unsigned long long*)&acc->limb[0], (unsigned long long)l0);
-        atomicAdd((unsigned long long*)&acc->limb[1], (unsigned long long)l1);
-        atomicAdd((unsigned long long*)&acc->limb[2], (unsigned long long)l2);
-        atomicMin(&acc->t_first, lo);
-        atomicMax(&acc->t_last, hi);
+    return t;
+}
+
+__global__ void __launch_bounds__(256)
+tmp_used(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
+         TmpAcc* acc, const uint32_t* status)
+{
+    if (*status != STALLOC_OK) return;
+    const TmpAcc t = tmp_sum<256>(size, ta, tf, n, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < 3; ++k) atomicAdd((unsigned long long*)&acc->limb[k], (unsigned long long)t.limb[k]);
+        atomicMin(&acc->t_first, t.t_first);
+        atomicMax(&acc->t_last, t.t_last);
     }
+}
+
+__device__ __forceinline__ void tmp_of_plans(const TmpAcc& t, const uint64_t* __restrict__ extents, uint32_t P, double* tmp, uint32_t from,
+                                             uint32_t step)
+{
+    const double used = ((double)t.limb[2] * 4294967296.0 + (double)t.limb[1]) * 4294967296.0 + (double)t.limb[0];
+    const double span = (double)(t.t_last - t.t_first);
+    for (uint32_t p = from; p < P; p += step) tmp[p] = used / ((double)extents[p] * span);
 }
 
 __global__ void __launch_bounds__(256)
@@ -73,10 +85,21 @@ tmp_per_plan(const TmpAcc* __restrict__ acc, const uint64_t* __restrict__ extent
              const uint32_t* status)
 {
     if (*status != STALLOC_OK) return;
-    const double used = ((double)acc->limb[2] * 4294967296.0 + (double)acc->limb[1]) * 4294967296.0 + (double)acc->limb[0];
-    const double span = (double)(acc->t_last - acc->t_first);
-    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x)
-        tmp[p] = used / ((double)extents[p] * span);
+    tmp_of_plans(*acc, extents, P, tmp, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
+// Few requests and plans: sums and ratios in one workgroup instead of three launches.
+constexpr uint32_t kTmpSmallRequests = 8192, kTmpSmallPlans = 8192;
+__global__ void __launch_bounds__(1024)
+tmp_small(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
+          const uint64_t* __restrict__ extents, uint32_t P, double* tmp, const uint32_t* status)
+{
+    __shared__ TmpAcc all;
+    if (*status != STALLOC_OK) return;
+    const TmpAcc t = tmp_sum<1024>(size, ta, tf, n, threadIdx.x, 1024);
+    if (threadIdx.x == 0) all = t;
+    __syncthreads();
+    tmp_of_plans(all, extents, P, tmp, threadIdx.x, 1024);
 }
 
 }  // namespace stalloc
@@ -88,7 +111,7 @@ extern "C" int stalloc_tmp(const stalloc_trace* tr, const uint64_t* extents, uin
 {
     if (!trace_args_ok(tr) || P == 0 || !workspace_bytes) return STALLOC_ERR_INVALID_ARG;
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     TmpAcc* sums = cv.take<TmpAcc>(1);
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
     if (!extents || !tmp || !device_status || *workspace_bytes < cv.used ||
@@ -96,6 +119,11 @@ extern "C" int stalloc_tmp(const stalloc_trace* tr, const uint64_t* extents, uin
         return STALLOC_ERR_INVALID_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     launch_trace_check(*tr, acc, device_status, stream);
+    if (tr->n <= kTmpSmallRequests && P <= kTmpSmallPlans) {
+        hipLaunchKernelGGL(tmp_small, dim3(1), dim3(1024), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, extents, P, tmp,
+                           device_status);
+        return hipGetLastError() == hipSuccess ? STALLOC_OK : STALLOC_ERR_DEVICE;
+    }
     hipLaunchKernelGGL(tmp_init, dim3(1), dim3(64), 0, stream, sums);
     uint32_t blocks = (tr->n + 255) / 256;
     if (blocks > 256) blocks = 256;

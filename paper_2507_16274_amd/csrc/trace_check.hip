@@ -10,85 +10,123 @@
 
 namespace stalloc {
 
-__global__ void trace_check_init(uint64_t* acc, uint32_t* status)
+// Sums of the high and low halves of the sizes, whether a request is malformed, all bits set in any size, the
+// largest size.
+struct TraceSums {
+    uint64_t hi, lo, bad, bits, largest;
+    __device__ __forceinline__ void add(const TraceSums& o)
+    {
+        hi += o.hi; lo += o.lo; bad |= o.bad; bits |= o.bits; largest = umax64(largest, o.largest);
+    }
+};
+static_assert(sizeof(TraceSums) == 5 * sizeof(uint64_t), "kAccSpace holds one per workgroup");
+
+// Of the requests that the calling threads take, `step` apart; valid in thread 0 of the workgroup.
+template <int kThreads>
+__device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta,
+                                                  const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end, uint32_t first, uint32_t step)
 {
-    if (threadIdx.x < kAccWords) acc[threadIdx.x] = 0;
-    if (threadIdx.x == 0) *status = STALLOC_OK;
+    __shared__ TraceSums part[kThreads / kWave];
+    TraceSums t = {0, 0, 0, 0, 0};
+#pragma unroll 4
+    for (uint32_t i = first; i < n; i += step) {
+        const uint64_t s = size[i];
+        const uint32_t a = ta[i], f = tf[i];
+        t.bad |= (s == 0) | (a >= f) | (f > t_end);
+        t.hi += s >> 32;               // n < 2^31 terms below 2^32 each: cannot wrap
+        t.lo += s & 0xffffffffull;
+        t.bits |= s;
+        t.largest = umax64(t.largest, s);
+    }
+    t.hi = wave_sum64(t.hi);
+    t.lo = wave_sum64(t.lo);
+    t.bad = __builtin_amdgcn_ballot_w64(t.bad != 0) ? 1 : 0;
+    t.bits = wave_or64(t.bits);
+    t.largest = wave_max64(t.largest);
+    if (lane_id() == 0) part[wave_id()] = t;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kThreads / kWave; ++w) t.add(part[w]);
+    return t;
+}
+
+// The accumulators (the other words are zero) and the status, from the sums over all requests; one thread.
+__device__ __forceinline__ void write_verdict(const TraceSums& t, uint64_t* acc, uint32_t* status)
+{
+    uint32_t code = STALLOC_OK;
+    uint64_t words[kAccWords] = {t.hi, t.lo, t.bad, t.bits};
+    words[kAccMaxSize] = t.largest;
+    if (t.hi + (t.lo >> 32) < (1ull << 31) && t.bits != 0) {
+        const uint64_t total = (t.hi << 32) + t.lo;                  // below 2^63 here
+        const uint32_t shift = (uint32_t)__builtin_ctzll(t.bits);
+        const uint64_t narrow = (total >> shift) < (1ull << 31) ? kModeNarrow : 0;
+        const uint64_t compact = (total >> shift) < (1ull << 16) ? kModeCompact : 0;
+        const uint64_t bitmap = (total >> shift) <= kBitmapGranules && (t.largest >> shift) <= kBitmapMaxSize ? kModeBitmap : 0;
+        // The sum of sizes bounds every address, but plans worth having end far below it: when the
+        // sum is too large for 32-bit granule counts and no single request is, the 32-bit placement
+        // kernel takes each plan as far as its extent allows and hands the rest to the 64-bit one.
+        const uint64_t try32 = (!narrow && (t.largest >> shift) < (1ull << 30)) ? kModeTry32 : 0;
+        words[kAccMode] = shift | narrow | compact | bitmap | try32;
+        words[kAccGranules] = total >> shift;
+    }
+    // total = hi * 2^32 + lo  >= 2^63  <=>  hi + (lo >> 32) >= 2^31
+    if (t.hi + (t.lo >> 32) >= (1ull << 31)) code = STALLOC_ERR_OVERFLOW;
+    if (t.bad) code = STALLOC_ERR_BAD_TRACE;
+    for (int k = 0; k < kAccWords; ++k) acc[k] = words[k];
+    *status = code;
+}
+
+__global__ void __launch_bounds__(1024)
+trace_check_small(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
+                  uint32_t t_end, uint64_t* acc, uint32_t* status)
+{
+    const TraceSums t = sum_requests<1024>(size, ta, tf, n, t_end, threadIdx.x, 1024);
+    if (threadIdx.x == 0) write_verdict(t, acc, status);
 }
 
 __global__ void __launch_bounds__(256)
 trace_check_scan(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta,
-                 const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end, uint64_t* acc)
+                 const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end, TraceSums* part)
 {
-    __shared__ uint64_t part[4][5];                  // per wave: hi, lo, bad, bits, largest
-    uint64_t hi = 0, lo = 0, bits = 0, largest = 0;
-    uint32_t bad = 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        uint64_t s = size[i];
-        uint32_t a = ta[i], f = tf[i];
-        bad |= (s == 0) | (a >= f) | (f > t_end);
-        hi += s >> 32;               // n < 2^31 terms below 2^32 each: cannot wrap
-        lo += s & 0xffffffffull;
-        bits |= s;
-        largest = umax64(largest, s);
-    }
-    hi = wave_sum64(hi);
-    lo = wave_sum64(lo);
-    bits = wave_or64(bits);
-    largest = wave_max64(largest);
-    uint64_t any_bad = __builtin_amdgcn_ballot_w64(bad != 0);
-    // one set of atomics per workgroup: thousands of waves on five words would queue up
-    if (lane_id() == 0) {
-        uint64_t* mine = part[wave_id()];
-        mine[0] = hi; mine[1] = lo; mine[2] = any_bad ? 1 : 0; mine[3] = bits; mine[4] = largest;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) {
-            hi += part[w][0]; lo += part[w][1]; any_bad |= part[w][2]; bits |= part[w][3];
-            largest = umax64(largest, part[w][4]);
-        }
-        atomicAdd((unsigned long long*)&acc[0], (unsigned long long)hi);
-        atomicAdd((unsigned long long*)&acc[1], (unsigned long long)lo);
-        if (any_bad) atomicOr((unsigned long long*)&acc[2], 1ull);
-        atomicOr((unsigned long long*)&acc[3], (unsigned long long)bits);
-        atomicMax((unsigned long long*)&acc[kAccMaxSize], (unsigned long long)largest);
-    }
+    const TraceSums t = sum_requests<256>(size, ta, tf, n, t_end, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+    if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ void trace_check_finish(uint64_t* acc, uint32_t* status)
+__global__ void __launch_bounds__(kTraceCheckBlocks) trace_check_finish(const TraceSums* part, uint32_t parts, uint64_t* acc, uint32_t* status)
 {
+    __shared__ TraceSums of[kTraceCheckBlocks / kWave];
+    TraceSums t = {0, 0, 0, 0, 0};
+    if (threadIdx.x < parts) t = part[threadIdx.x];
+    t.hi = wave_sum64(t.hi);
+    t.lo = wave_sum64(t.lo);
+    t.bad = wave_or64(t.bad);
+    t.bits = wave_or64(t.bits);
+    t.largest = wave_max64(t.largest);
+    if (lane_id() == 0) of[wave_id()] = t;
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    uint32_t code = STALLOC_OK;
-    acc[kAccMode] = 0;
-    if (acc[0] + (acc[1] >> 32) < (1ull << 31) && acc[3] != 0) {
-        const uint64_t total = (acc[0] << 32) + acc[1];              // below 2^63 here
-        const uint32_t shift = (uint32_t)__builtin_ctzll(acc[3]);
-        const uint64_t narrow = (total >> shift) < (1ull << 31) ? kModeNarrow : 0;
-        const uint64_t compact = (total >> shift) < (1ull << 16) ? kModeCompact : 0;
-        const uint64_t bitmap = (total >> shift) <= kBitmapGranules && (acc[kAccMaxSize] >> shift) <= kBitmapMaxSize
-                                    ? kModeBitmap : 0;
-        // The sum of sizes bounds every address, but plans worth having end far below it: when the
-        // sum is too large for 32-bit granule counts and no single request is, the 32-bit placement
-        // kernel takes each plan as far as its extent allows and hands the rest to the 64-bit one.
-        const uint64_t try32 = (!narrow && (acc[kAccMaxSize] >> shift) < (1ull << 30)) ? kModeTry32 : 0;
-        acc[kAccMode] = shift | narrow | compact | bitmap | try32;
-        acc[kAccGranules] = total >> shift;
-    }
-    // total = acc[0] * 2^32 + acc[1]  >= 2^63  <=>  acc[0] + (acc[1] >> 32) >= 2^31
-    if (acc[0] + (acc[1] >> 32) >= (1ull << 31)) code = STALLOC_ERR_OVERFLOW;
-    if (acc[2] & 1ull) code = STALLOC_ERR_BAD_TRACE;
-    if (code != STALLOC_OK) atomicMax(status, code);
+    for (int w = 1; w < kTraceCheckBlocks / kWave; ++w) t.add(of[w]);
+    write_verdict(t, acc, status);
 }
+
+// One launch for short traces (up to this many requests a single workgroup needs no longer than a launch
+// takes), else two, the workgroups' sums in the workspace in between: 256 workgroups adding to five words
+// with atomics took 14 us on 199 748 requests, and clearing those words was a launch of its own.
+constexpr uint32_t kTraceCheckSmall = 8192;
 
 void launch_trace_check(const stalloc_trace& tr, uint64_t* acc, uint32_t* device_status, hipStream_t stream)
 {
-    hipLaunchKernelGGL(trace_check_init, dim3(1), dim3(64), 0, stream, acc, device_status);
+    if (tr.n <= kTraceCheckSmall) {
+        hipLaunchKernelGGL(trace_check_small, dim3(1), dim3(1024), 0, stream, tr.size, tr.t_alloc, tr.t_free, tr.n, tr.t_end, acc,
+                           device_status);
+        return;
+    }
     uint32_t blocks = (tr.n + 255) / 256;
-    if (blocks > 256) blocks = 256;
+    if (blocks > kTraceCheckBlocks) blocks = kTraceCheckBlocks;
+    TraceSums* part = reinterpret_cast<TraceSums*>(acc + kAccWords);
     hipLaunchKernelGGL(trace_check_scan, dim3(blocks), dim3(256), 0, stream, tr.size, tr.t_alloc, tr.t_free,
-                       tr.n, tr.t_end, acc);
-    hipLaunchKernelGGL(trace_check_finish, dim3(1), dim3(64), 0, stream, acc, device_status);
+                       tr.n, tr.t_end, part);
+    hipLaunchKernelGGL(trace_check_finish, dim3(1), dim3(kTraceCheckBlocks), 0, stream, part, blocks, acc, device_status);
 }
 
 }  // namespace stalloc

@@ -396,7 +396,7 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     const uint64_t tri = tiles * (tiles + 1) / 2;
     if (tri >= 0x7fffffffull) return STALLOC_ERR_INVALID_ARG;   // n beyond ~16.7 million requests
     Carver cv(workspace);
-    uint64_t* acc = cv.take<uint64_t>(kAccWords);
+    uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* first_key = cv.take<uint64_t>(P);
     const bool near = (uint64_t)tr->n * tr->n * P >= kVnFrom;
     VnBuckets buckets = {0, 0, 0};
