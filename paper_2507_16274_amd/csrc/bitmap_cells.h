@@ -86,18 +86,19 @@ __device__ __forceinline__ uint32_t first_fit(const uint32_t* bm, uint32_t limit
     const int lane = lane_id();
     for (uint32_t t = first;; t += kWave) {
         const uint32_t w = t + lane;
-        uint32_t here = ~(w < limit ? bm[w] : 0u);                          // bit b: granule 32 w + b is free
-        uint32_t next = ~(w + 1 < limit ? bm[w + 1] : 0u);
+        const uint32_t here = w < limit ? bm[w] : 0u;
+        const uint32_t next = w + 1 < limit ? bm[w + 1] : 0u;
+        uint64_t free_run = ~((uint64_t)here | ((uint64_t)next << 32));     // bit b: granule 32 w + b is free
         for (uint32_t len = 1; len < s;) {                                  // bit b: free for `len` granules from b
             const uint32_t step = len < s - len ? len : s - len;
-            here &= __builtin_amdgcn_alignbit(next, here, step);
-            next &= next >> step;
+            free_run &= free_run >> step;
             len += step;
         }
-        const uint64_t any = __builtin_amdgcn_uicmp(here, 0u, 33);          // != 0: runs that begin inside word w
+        const uint32_t starts = (uint32_t)free_run;                         // runs that begin inside word w
+        const uint64_t any = __builtin_amdgcn_uicmp(starts, 0u, 33);        // != 0
         if (any) {
             const int f = __builtin_ctzll(any);
-            return (t + (uint32_t)f) * 32 + (uint32_t)__builtin_ctz(read_lane(here, f));
+            return (t + (uint32_t)f) * 32 + (uint32_t)__builtin_ctz(read_lane(starts, f));
         }
     }
 }

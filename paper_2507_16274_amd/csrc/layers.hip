@@ -52,7 +52,7 @@ ly_sort_tiles(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta
         // (size descending, allocation time, request number) as two ascending 64-bit words
         k[t] = i < n ? make_ulonglong2(~size[i], ((uint64_t)ta[i] << 32) | i) : filler_key(i);
     }
-    sort_tile(k);
+    sort_tile(k, keys_of_tile(blockIdx.x * kLyTile, n));
     for (uint32_t t = threadIdx.x; t < (uint32_t)kLyTile; t += kSortThreads) keys[blockIdx.x * kLyTile + t] = k[t];
 }
 
@@ -681,7 +681,9 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
     // Only the device knows how many groups there are: the layer counts of all n slots are summed,
     // the slots past the last group hold none.
     hipLaunchKernelGGL(ly_init, dim3(blocks), dim3(256), 0, stream, group_layers, n);
-    if (n >= kLyMatchFrom) {
+    // (With fewer timestamps than requests the clock is coarse: a large group has tied releases and ly_match would
+    // give up on it, for about 10 us a call.)
+    if (n >= kLyMatchFrom && tr->t_end >= n) {
         const size_t lds_budget = di.lds_per_block - 4096;            // (static LDS takes the rest)
         uint32_t cap = (uint32_t)((lds_budget - 16) / kLyMatchBytes) & ~3u;
         if (cap > n) cap = (n + 3) & ~3u;

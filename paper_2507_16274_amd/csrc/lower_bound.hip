@@ -175,7 +175,7 @@ lb_tiles(const int64_t* __restrict__ net, uint32_t t_end, int64_t* tile_sum, LbB
 }
 
 // Short traces: the whole call in one workgroup, net changes in LDS.  Up to this many requests and timestamps it
-// takes less time than the two further launches it saves (6144 requests on 12 288 timestamps: LB_US).
+// takes less time than the two further launches it saves.
 constexpr uint32_t kLbSmallRequests = 16384, kLbSmallTimes = 16384;
 constexpr int kLbSmallThreads = 1024;
 

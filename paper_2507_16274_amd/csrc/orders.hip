@@ -92,7 +92,7 @@ or_sort_tiles(OrTrace t, uint64_t first_plan, uint64_t seed, uint32_t n_pad, ulo
         const uint32_t e = blockIdx.x * kOrTile + th;
         k[th] = order_key(t, p, stream, e, e);
     }
-    sort_tile(k);
+    sort_tile(k, keys_of_tile(blockIdx.x * kOrTile, t.n));
     for (uint32_t th = threadIdx.x; th < (uint32_t)kOrTile; th += kSortThreads) out[th] = k[th];
 }
 

@@ -320,7 +320,7 @@ sp_sort_tiles(const uint32_t* __restrict__ ta, uint32_t n, ulonglong2* keys, con
         const uint32_t e = blockIdx.x * kSortTile + t;
         k[t] = e < n ? make_ulonglong2((uint64_t)ta[e], (uint64_t)e) : filler_key(e);
     }
-    sort_tile(k);
+    sort_tile(k, keys_of_tile(blockIdx.x * kSortTile, n));
     for (uint32_t t = threadIdx.x; t < (uint32_t)kSortTile; t += kSortThreads) keys[blockIdx.x * kSortTile + t] = k[t];
 }
 

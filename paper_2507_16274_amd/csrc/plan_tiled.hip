@@ -22,7 +22,7 @@
 // What bounds it: on 6144 requests (21 tiles, 173-word rows, two workgroups a CU) the vector issue of the building
 // waves (rows, lists and search in equal parts) and, 40 % of the time, waiting for the wave with the longest
 // request of the batch; on 19 840 (25 tiles, one workgroup of sixteen waves) half the time is such waiting.
-// 1024 plans of 6144 requests: 6.9 -> 4.8 ms; 512 plans of 19 840: 24.0 -> 14.1 ms (91 and 226 listed requests
+// 1024 plans of 6144 requests: 6.9 -> 4.7 ms; 512 plans of 19 840: 24.0 -> 13.8 ms (91 and 226 listed requests
 // instead of 737 and 2211).
 //
 // The tables hold the address range up to an eighth above the largest number of live granules (which no
@@ -397,10 +397,13 @@ bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInf
 bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream)
 {
     const uint32_t wgs = pt_workgroups(prm.n);
-    PtOffer offer = {{pt_words<8>(di.lds_per_block / wgs), pt_words<16>(di.lds_per_block)}};
+    // (up to 3072 requests the eight-wave shape has room for as many tiles as can help; a launch less)
+    const bool large = prm.n > 3072;
+    PtOffer offer = {{pt_words<8>(di.lds_per_block / wgs), large ? pt_words<16>(di.lds_per_block) : 0u}};
     hipLaunchKernelGGL(pt_shape, dim3(1), dim3(1024), 0, stream, prm, t_end, net, offer);
     hipLaunchKernelGGL(pt_lists, dim3(prm.n), dim3(256), 0, stream, prm, t_end);
-    return launch_tiled<8>(prm, t_end, wgs, offer.words[0], di, stream) && launch_tiled<16>(prm, t_end, 1, offer.words[1], di, stream);
+    return launch_tiled<8>(prm, t_end, wgs, offer.words[0], di, stream) &&
+           (!large || launch_tiled<16>(prm, t_end, 1, offer.words[1], di, stream));
 }
 
 }  // namespace stalloc

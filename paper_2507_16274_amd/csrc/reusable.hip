@@ -84,7 +84,7 @@ rs_sort_tiles(const uint64_t* __restrict__ size, const uint64_t* __restrict__ of
         const uint32_t w0 = (blockIdx.x - tiles) * kRsTile;
         for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads)
             k[t] = w0 + t < windows_k ? window_key(windows, w0 + t, near) : filler_key(w0 + t);
-        sort_tile(k);
+        sort_tile(k, keys_of_tile(w0, windows_k));
         for (uint32_t t = threadIdx.x; t < (uint32_t)kRsTile; t += kSortThreads) window_keys[w0 + t] = k[t];
         return;
     }
@@ -101,7 +101,7 @@ rs_sort_tiles(const uint64_t* __restrict__ size, const uint64_t* __restrict__ of
     lo = wave_min64(lo);
     hi = wave_max64(hi);
     if (lane_id() == 0) { lowest[wave_id()] = lo; highest[wave_id()] = hi; }
-    sort_tile(k);
+    sort_tile(k, keys_of_tile(blockIdx.x * kRsTile, n));
     // one pair of atomics per workgroup: a wave each would queue up on the two words
     if (threadIdx.x == 0) {
         for (int w = 1; w < kSortThreads / kWave; ++w) { lo = umin64(lo, lowest[w]); hi = umax64(hi, highest[w]); }
