@@ -292,8 +292,9 @@ int stalloc_make_orders(const stalloc_trace *trace, uint32_t first_plan, uint32_
  *   members       device [m]: the request numbers of all pairs, pair after pair; pair p owns
  *                 members[pair_begin[p] .. pair_begin[p+1]), its first group's requests first.
  *                 The requests of one pair must be distinct (not detected: the result is then
- *                 unspecified, but memory-safe); an entry >= n sets device_status to
- *                 STALLOC_ERR_BAD_ORDER.
+ *                 unspecified, but memory-safe; requests listed so often that the sum of a pair's
+ *                 sizes could wrap set device_status to STALLOC_ERR_OVERFLOW); an entry >= n sets
+ *                 device_status to STALLOC_ERR_BAD_ORDER.
  *   pair_begin    device [k+1], ascending, pair_begin[0] = 0, pair_begin[k] <= m (a pair that reaches
  *                 beyond m, or backwards, sets device_status to STALLOC_ERR_INVALID_ARG).
  *   count1        device [k]: how many of pair p's requests belong to its first group; both

@@ -51,15 +51,18 @@ struct FuseParams {
     uint32_t cap;            // requests of one pair that fit the LDS arrays
 };
 
-__device__ __forceinline__ uint64_t block_sum64(uint64_t v, uint64_t* scratch)
+// Sums over the workgroup, three at once.
+__device__ __forceinline__ void block_sums64(uint64_t (&v)[3], uint64_t (*scratch)[3])
 {
-    const uint64_t w = wave_sum64(v);
+    for (int u = 0; u < 3; ++u) v[u] = wave_sum64(v[u]);
     __syncthreads();
-    if (lane_id() == 0) scratch[wave_id()] = w;
+    if (lane_id() == 0)
+        for (int u = 0; u < 3; ++u) scratch[wave_id()][u] = v[u];
     __syncthreads();
-    uint64_t tot = 0;
-    for (int k = 0; k < kFuThreads / kWave; ++k) tot += scratch[k];
-    return tot;
+    for (int u = 0; u < 3; ++u) {
+        v[u] = 0;
+        for (int k = 0; k < kFuThreads / kWave; ++k) v[u] += scratch[k][u];
+    }
 }
 
 // a * b as a 96-bit number {high 32 bits, low 64 bits}
@@ -102,7 +105,7 @@ __device__ __forceinline__ void sort_keys(uint64_t* keys, uint32_t m)
 __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ uint64_t scratch[kFuThreads / kWave];
+    __shared__ uint64_t scratch[kFuThreads / kWave][3];
     __shared__ uint32_t t_lo[2], t_hi[2];
     __shared__ uint32_t low_of[80];                                   // lowest wake of every 64 requests of the smaller plan
     __shared__ struct { uint64_t addr; uint32_t order, holder, fit; } help;
@@ -123,14 +126,17 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
     if (tid < 2) { t_lo[tid] = 0xffffffffu; t_hi[tid] = 0u; }
     __syncthreads();
     // the two local plans: extent = sum of sizes, span = first allocation .. last release
-    uint64_t sum1 = 0, sum2 = 0;
+    uint64_t sums[3] = {0, 0, 0};                                     // sizes of the first group, of the second, upper halves of all
+    int unknown = 0;
     uint32_t lo_of[2] = {0xffffffffu, 0xffffffffu}, hi_of[2] = {0u, 0u};
     for (uint32_t k = tid; k < m; k += kFuThreads) {
         uint32_t i = prm.members[m0 + k];
-        if (i >= prm.n) { atomicMax(prm.status, (uint32_t)STALLOC_ERR_BAD_ORDER); i = 0; }
+        if (i >= prm.n) { unknown = 1; i = 0; }
         id[k] = i;
         const int g = k < c1 ? 0 : 1;
-        (g ? sum2 : sum1) += prm.size[i];
+        const uint64_t s = prm.size[i];
+        (g ? sums[1] : sums[0]) += s;
+        sums[2] += s >> 32;
         const uint32_t a = prm.ta[i], f = prm.tf[i];
         ts[k] = a; te[k] = f;                                         // (as given, for the sort)
         lo_of[g] = umin(lo_of[g], a);
@@ -140,8 +146,19 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
         const uint32_t lo = ~read_lane(wave_scan_max(~lo_of[g]), kWave - 1), hi = read_lane(wave_scan_max(hi_of[g]), kWave - 1);
         if (lane_id() == 0) { atomicMin(&t_lo[g], lo); atomicMax(&t_hi[g], hi); }
     }
-    const uint64_t ext1 = block_sum64(sum1, scratch), ext2 = block_sum64(sum2, scratch);
-    __syncthreads();
+    block_sums64(sums, scratch);
+    // The chain below counts on starts that ascend with the block, that is on addresses that do not wrap.  Distinct
+    // requests stay below 2^63 together (the trace check); requests listed twice need not, and neither would a
+    // stand-in for an unknown one.  (The lower halves of fewer than 2^13 sizes add up to less than 2^45.)
+    if (__syncthreads_or(unknown)) {
+        if (tid == 0) atomicMax(prm.status, (uint32_t)STALLOC_ERR_BAD_ORDER);
+        return;
+    }
+    if (sums[2] >= (1ull << 32) - (1u << 13)) {                       // (uniform)
+        if (tid == 0) atomicMax(prm.status, (uint32_t)STALLOC_ERR_OVERFLOW);
+        return;
+    }
+    const uint64_t ext1 = sums[0], ext2 = sums[1];
     const bool first_larger = ext1 >= ext2;
     const uint32_t nl = first_larger ? c1 : m - c1, ns = m - nl;
     const uint32_t l0 = first_larger ? 0 : c1, s0 = first_larger ? c1 : 0;     // where the two groups start in id[]
@@ -279,7 +296,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
             uint32_t low0 = (uint32_t)lane < chunks ? low_of[lane] : kPlaced;
             uint32_t low1 = (uint32_t)lane + kWave < chunks ? low_of[lane + kWave] : kPlaced;
             uint32_t order = kDone;
-            while (left) {
+            while (left) {                                            // (every pass raises the holder or places a request)
                 for (;;) {                                            // blocks up to the one that holds addr, 64 at a time
                     const uint32_t q = holder + 1 + lane;
                     const uint64_t start = q < nl ? at[q] : (q == nl ? larger_top : ~0ull);
@@ -333,6 +350,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
                     const uint32_t next = lowest_wake(umin(low0, low1));
                     if (next >= nl) break;
                     addr = at[next];
+                    holder = next;
                 }
             }
             if ((uint32_t)lane < chunks) low_of[lane] = low0;

@@ -137,3 +137,24 @@ def test_groups_before_after_and_inside_each_other(S, oracle, n1, n2, kind):
     tr = Trace(name="phases", size=size, t_alloc=ts.astype(np.uint32), t_free=te.astype(np.uint32), t_end=int(te.max()))
     ids = np.arange(n, dtype=np.uint32)
     _compare(S, oracle, tr, [ids[:n1], ids[n1:]], [(0, 1), (1, 0)])
+
+
+def test_sizes_that_would_wrap_end_with_a_status(S):
+    """Requests near 2^61 bytes listed several times, and beside entries that name no request: starts that would not
+    ascend.  Reported, and the call returns; without the repetition the same requests are placed."""
+    n = 68
+    size = np.full(n, 512, dtype=np.uint64)
+    size[:2] = 1 << 61
+    ts, te = np.zeros(n, np.uint32), np.full(n, 200, np.uint32)
+    te[0], te[1], te[66], te[67], ts[67] = 100, 300, 10, 400, 20
+    tr = Trace(name="wrap", size=size, t_alloc=ts, t_free=te, t_end=400)
+    small = np.asarray([67], dtype=np.uint32)
+    larger = np.concatenate([[1], np.arange(2, 66), [66]]).astype(np.uint32)
+    for extra, status in (([0], 0), ([0] * 7, 3), ([0] + [n] * 6, 6), ([0] + [0xffffffff] * 6, 6), ([0] * 7 + [n], 6)):
+        both = np.concatenate([larger, np.asarray(extra, dtype=np.uint32)])
+        for pair in ((both, small), (small, both)):
+            members, begin, count1, largest = flatten_pairs(list(pair), [(0, 1)])
+            got = _fuse(S, tr, members, begin, count1, largest)
+            assert got["status"] == status
+            if status == 0:
+                assert got["extents"][0, 2] == (1 << 62) + 65 * 512
