@@ -246,6 +246,18 @@ __device__ __forceinline__ uint64_t umax(uint64_t a, uint64_t b) { return a > b 
 // as a scalar: the compiler cannot know, and would otherwise branch on it with lane masks.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// The status word (non-zero: an error) as the whole workgroup is to see it.  A kernel that raises the word itself must
+// not let every wave read it for itself: another workgroup may raise it in between, and waves that stay
+// would wait for ever for what those that left were to do.  `word`: in LDS, not in use yet.  Called by all threads.
+__device__ __forceinline__ uint32_t status_of_workgroup(const uint32_t* status, uint32_t* word)
+{
+    if (threadIdx.x == 0) *word = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint32_t seen = uniform(*word);
+    __syncthreads();                                                  // (the word may be put to its own use)
+    return seen;
+}
+
 // Waits until every vector-memory access this wave has issued is complete.  Placed where that is
 // the case anyway (long after the last one was issued), it tells the compiler so: without it, a load
 // left unread on some path through a loop keeps its register marked as in flight, and the first
