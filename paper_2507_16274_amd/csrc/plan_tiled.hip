@@ -146,12 +146,13 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
     constexpr uint32_t kStage = kPtRefill / kPend * kPend;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint64_t word = prm.acc[kAccTiles];
-    if (*prm.status != STALLOC_OK || word == 0) return;
+    if (word == 0) return;
     const PtShape pt(word);
     if (pt.shape != (kWaves == 8 ? 0u : 1u)) return;
+    Lds& sh = *reinterpret_cast<Lds*>(smem);
+    if (status_of_workgroup(prm.status, sh.top) != STALLOC_OK) return;
     const uint32_t n = prm.n, shift = (uint32_t)(prm.acc[kAccMode] & 63);
     if (blockIdx.x == 0 && threadIdx.x == 0) const_cast<uint64_t*>(prm.acc)[kAccKernel] = STALLOC_KERNEL_BITMAP | (22u << 8);
-    Lds& sh = *reinterpret_cast<Lds*>(smem);
     uint32_t* const cells = reinterpret_cast<uint32_t*>(smem + sizeof(Lds));      // [n + 1] placed blocks, see make_cell
     const uint32_t longest = (uint32_t)(prm.acc[kAccMaxSize] >> shift);
     const uint32_t row = pt.row, stride = row | 1u, bm_words = pt_bitmap_words(row, kPend, longest);

@@ -9,7 +9,7 @@ import re
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_16274_amd", "csrc")
-KERNELS = ["fuse_pairs"]
+KERNELS = ["fuse_pairs", "plan_tiled_kernel"]
 
 
 def _kernels():
