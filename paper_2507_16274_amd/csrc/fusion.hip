@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
     __shared__ uint32_t t_lo[2], t_hi[2];
     __shared__ uint32_t low_of[80];                                   // lowest wake of every 64 requests of the smaller plan
     __shared__ struct { uint64_t addr; uint32_t order, holder, fit; } help;
-    if (status_of_workgroup(prm.status, t_lo) != STALLOC_OK) return;
+    if (status_of_workgroup(read_status(prm.status), t_lo) != STALLOC_OK) return;
     const uint32_t p = blockIdx.x, tid = threadIdx.x;
     const uint32_t m0 = prm.pair_begin[p], m1 = prm.pair_begin[p + 1], m = m1 - m0, c1 = prm.count1[p];
     const bool outside = m1 < m0 || m1 > prm.entries;               // (nothing is read or written beyond the arrays)

@@ -479,7 +479,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
     Lds& sh = *reinterpret_cast<Lds*>(smem);
     const uint32_t n = prm.n;
 
-    if (*prm.status != STALLOC_OK) return;               // malformed trace: nothing to plan
+    const uint32_t status = read_status(prm.status);
     const uint64_t mode = prm.acc[kAccMode];
     if (bitmap_shape(mode, prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0) return;   // the occupancy-bitmap kernel places this trace
     // the kernel that lists only long-lived blocks places it (and leaves the plans that outgrow
@@ -494,6 +494,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
     // of the two 32-bit instantiations the compact one runs when it was enqueued and applies
     const bool compact = prm.compact_enqueued && (mode & kModeCompact) != 0;
     if (sizeof(Addr) == 4 && compact != kCompact) return;
+    if (status_of_workgroup(status, &sh.settled) != STALLOC_OK) return;   // malformed trace: nothing to plan
     const uint32_t shift = sizeof(Addr) == 4 ? (uint32_t)(mode & 63) : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && !(sizeof(Addr) == 8 && try32))
         const_cast<uint64_t*>(prm.acc)[kAccKernel] = (kLds ? STALLOC_KERNEL_LIST_LDS : STALLOC_KERNEL_LIST_MEMORY) |

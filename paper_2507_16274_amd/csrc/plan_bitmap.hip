@@ -69,11 +69,12 @@ struct BitmapLds {
 // dummy that is never placed) -- stored as 4 * j, the byte offset into the plan's table, while
 // 4 * n fits 16 bits (the build phase then needs one instruction less per lookup).  begin[] first
 // holds the degrees, then their exclusive prefix sum in chunks.
-__device__ __forceinline__ bool index_wanted(const PlanParams& prm)
+__device__ __forceinline__ bool plans_wanted(const PlanParams& prm)
 {
-    return *prm.status == STALLOC_OK && bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0 &&
+    return bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0 &&
            (prm.acc[kAccTiles] == 0 || prm.acc[kAccTilesMissed] != 0);      // (nothing left to place, see plan_tiled.hip)
 }
+__device__ __forceinline__ bool index_wanted(const PlanParams& prm) { return *prm.status == STALLOC_OK && plans_wanted(prm); }
 
 __global__ void __launch_bounds__(256) nbr_count(PlanParams prm)
 {
@@ -153,8 +154,10 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 8 : 4) plan_bitm
     uint32_t* pool = cells + (prm.n + 1);
     const uint32_t n = prm.n;
 
-    if (!index_wanted(prm)) return;
+    const uint32_t status = read_status(prm.status);
+    if (!plans_wanted(prm)) return;
     if (bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) != kShape) return;
+    if (status_of_workgroup(status, &sh.top) != STALLOC_OK) return;
     const bool some = prm.acc[kAccTiles] != 0;         // only the plans that outgrew the tables of the tiled variant
     const uint32_t shift = (uint32_t)(prm.acc[kAccMode] & 63);
     if (blockIdx.x == 0 && threadIdx.x == 0) const_cast<uint64_t*>(prm.acc)[kAccKernel] = STALLOC_KERNEL_BITMAP | (22u << 8);

@@ -862,9 +862,9 @@ __global__ void __launch_bounds__(kThreads, kRanked ? 6 : 4) plan_split_kernel(P
     extern __shared__ __align__(16) unsigned char smem[];
     SplitLds& sh = *reinterpret_cast<SplitLds*>(smem);
     const uint32_t n = prm.n;
-    if (*prm.status != STALLOC_OK) return;
     if (!(prm.acc[kAccSplit] & 1)) return;                            // another kernel places this trace
     if (((prm.acc[kAccSplit] & 2) != 0) != kRanked) return;           // the other form of the list does
+    if (status_of_workgroup(read_status(prm.status), &sh.next_plan) != STALLOC_OK) return;
     const uint64_t mode = prm.acc[kAccMode];
     const bool try32 = (mode & kModeTry32) != 0;
     const uint32_t shift = (uint32_t)(mode & 63);

@@ -145,12 +145,13 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
     static_assert(3 * kPend <= kWave, "three batches lie side by side in the lanes of the settling wave");
     constexpr uint32_t kStage = kPtRefill / kPend * kPend;
     extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t status = read_status(prm.status);
     const uint64_t word = prm.acc[kAccTiles];
     if (word == 0) return;
     const PtShape pt(word);
     if (pt.shape != (kWaves == 8 ? 0u : 1u)) return;
     Lds& sh = *reinterpret_cast<Lds*>(smem);
-    if (status_of_workgroup(prm.status, sh.top) != STALLOC_OK) return;
+    if (status_of_workgroup(status, sh.top) != STALLOC_OK) return;
     const uint32_t n = prm.n, shift = (uint32_t)(prm.acc[kAccMode] & 63);
     if (blockIdx.x == 0 && threadIdx.x == 0) const_cast<uint64_t*>(prm.acc)[kAccKernel] = STALLOC_KERNEL_BITMAP | (22u << 8);
     uint32_t* const cells = reinterpret_cast<uint32_t*>(smem + sizeof(Lds));      // [n + 1] placed blocks, see make_cell

@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(kRsThreads) rs_sweep(RsArgs g)
     __shared__ uint64_t wave_reach[kRsWaves];
     __shared__ uint32_t wave_found[kRsWaves];
     __shared__ uint64_t wave_idle[kRsWaves];
-    if (*g.status != STALLOC_OK) return;
+    if (status_of_workgroup(read_status(g.status), wave_found) != STALLOC_OK) return;
     const int lane = lane_id(), wave = wave_id();
     const uint64_t pool_lo = g.pool->lo, pool_hi = g.pool->hi;
     const uint32_t steps = (g.n + kRsThreads - 1) / kRsThreads;           // 64-decision steps per wave

@@ -248,10 +248,15 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgc
 
 // The status word (non-zero: an error) as the whole workgroup is to see it.  A kernel that raises the word itself must
 // not let every wave read it for itself: another workgroup may raise it in between, and waves that stay
-// would wait for ever for what those that left were to do.  `word`: in LDS, not in use yet.  Called by all threads.
-__device__ __forceinline__ uint32_t status_of_workgroup(const uint32_t* status, uint32_t* word)
+// would wait for ever for what those that left were to do.  read_status is for thread 0 only and comes early (a round
+// trip to memory), status_of_workgroup hands what it read to all threads.  `word`: in LDS, not in use yet.
+__device__ __forceinline__ uint32_t read_status(const uint32_t* status)
 {
-    if (threadIdx.x == 0) *word = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return threadIdx.x == 0 ? __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+}
+__device__ __forceinline__ uint32_t status_of_workgroup(uint32_t status, uint32_t* word)
+{
+    if (threadIdx.x == 0) *word = status;
     __syncthreads();
     const uint32_t seen = uniform(*word);
     __syncthreads();                                                  // (the word may be put to its own use)

@@ -9,7 +9,7 @@ import re
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_16274_amd", "csrc")
-KERNELS = ["fuse_pairs", "plan_tiled_kernel"]
+KERNELS = ["fuse_pairs", "plan_tiled_kernel", "plan_kernel", "plan_bitmap_kernel", "plan_split_kernel", "rs_sweep"]
 
 
 def _kernels():
@@ -36,5 +36,5 @@ def test_the_sources_are_read_as_meant():
 def test_one_decision_per_workgroup(name):
     (body,) = [body for kernel, body in _kernels() if kernel == name]
     assert "__syncthreads" in body and re.search(r"atomicMax\((?:prm|g)\.status", body), "it raises the word and its waves meet"
-    assert "status_of_workgroup(" in body
+    assert len(re.findall(r"read_status\(", body)) == 1 and len(re.findall(r"status_of_workgroup\(", body)) == 1
     assert not re.search(r"\*\s*(?:prm|g)\.status\b", body) and "index_wanted" not in body
