@@ -520,7 +520,10 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
         uint32_t count = 0;
         bool outgrown = false;                                // (uniform) 32-bit counts may not hold the next batch
         __syncthreads();                                      // (every wave has taken its decisions about the plan before)
-        if (threadIdx.x == 0) sh.extent_now = 0;
+        if (threadIdx.x == 0) {
+            sh.extent_now = 0;
+            if (sizeof(Addr) == 4) prm.wide_plans[p] = 0;
+        }
 
         for (uint32_t r0 = 0; r0 < n; r0 += kBatch) {
             const uint32_t staged = n - r0 < (uint32_t)kBatch ? n - r0 : (uint32_t)kBatch;
@@ -564,8 +567,10 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
             __syncthreads();
             if (out && threadIdx.x < staged) out[sh.rq_id[threadIdx.x]] = sh.rq_addr[threadIdx.x];
         }
-        if (sizeof(Addr) == 4 && threadIdx.x == 0) prm.wide_plans[p] = outgrown ? 1u : 0u;
-        if (outgrown) continue;
+        if (outgrown) {
+            if (threadIdx.x == 0) prm.wide_plans[p] = 1;
+            continue;
+        }
         if (threadIdx.x == 0) prm.peaks[p] = (uint64_t)peak << shift;
     }
 }

@@ -902,7 +902,7 @@ __global__ void __launch_bounds__(kThreads, kRanked ? 6 : 4) plan_split_kernel(P
         for (uint32_t k = threadIdx.x; k < tb.large_slots; k += kThreads) pt.large_addr[k] = kSpUnplaced;
         for (uint32_t g = threadIdx.x; g < tb.groups; g += kThreads) pt.group_span[g] = make_uint2(0xffffffffu, 0u);
         if (threadIdx.x < kWave) { sh.region_min[threadIdx.x] = 0xffffffffu; sh.region_max[threadIdx.x] = 0u; }
-        if (threadIdx.x == 0) { sh.extent_now = 0; sh.peak = 0; sh.pool_used = 0; sh.reach[0] = 0; sh.large_min = 0xffffffffu; sh.large_max = 0u; }
+        if (threadIdx.x == 0) { sh.extent_now = 0; sh.peak = 0; sh.pool_used = 0; sh.reach[0] = 0; sh.large_min = 0xffffffffu; sh.large_max = 0u; prm.wide_plans[p] = 0; }
         uint32_t turn = 0;                                            // calls of window_reach: slot 0 is clear
         uint32_t wide_turn = 0;                                       // requests settled by the whole workgroup
         uint32_t round = 0;                                           // rounds so far: which wave takes the first ready request
@@ -1102,8 +1102,10 @@ __global__ void __launch_bounds__(kThreads, kRanked ? 6 : 4) plan_split_kernel(P
             if (out && threadIdx.x < staged) out[sh.rq_id[threadIdx.x]] = (uint64_t)sh.rq_addr[threadIdx.x] << shift;
         }
         __syncthreads();
-        if (threadIdx.x == 0) prm.wide_plans[p] = outgrown ? 1u : 0u;
-        if (outgrown) continue;
+        if (outgrown) {
+            if (threadIdx.x == 0) prm.wide_plans[p] = 1;
+            continue;
+        }
         if (threadIdx.x == 0) prm.peaks[p] = (uint64_t)sh.peak << shift;
     }
 }
