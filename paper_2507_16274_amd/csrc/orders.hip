@@ -431,10 +431,12 @@ extern "C" int stalloc_make_orders(const stalloc_trace* tr, uint32_t first_plan,
     uint32_t merged = (uint32_t)batch;
     if (spread) merged = first_plan <= 2 ? (uint32_t)(last < 2 ? last + 1 : 3) : (last >= 4 ? 1u : 0u);
 
+    // (the size depends on n and P only: a workspace serves one window of rows after another)
+    const uint32_t merged_room = spread ? 3u : merged;
     Carver cv(workspace);
     uint64_t* acc = cv.take<uint64_t>(kAccSpace);
-    ulonglong2* buf_a = cv.take<ulonglong2>((size_t)merged * n_pad);
-    ulonglong2* buf_b = cv.take<ulonglong2>((size_t)merged * n_pad);
+    ulonglong2* buf_a = cv.take<ulonglong2>((size_t)merged_room * n_pad);
+    ulonglong2* buf_b = cv.take<ulonglong2>((size_t)merged_room * n_pad);
     uint32_t* larger = cv.take<uint32_t>(n);
     uint32_t* flag = cv.take<uint32_t>(n);
     uint32_t* flags_before = cv.take<uint32_t>(n);
@@ -443,7 +445,7 @@ extern "C" int stalloc_make_orders(const stalloc_trace* tr, uint32_t first_plan,
     uint32_t* class_start = cv.take<uint32_t>(n);
     uint32_t* step = cv.take<uint32_t>((size_t)n + 3);
     OrBuckets ob = {step, nullptr, nullptr, buckets};
-    if (spread && buckets > 1 && last >= 3) {
+    if (spread && buckets > 1) {
         ob.filled = cv.take<uint32_t>((size_t)batch * buckets);
         ob.number = cv.take<uint32_t>((size_t)batch * buckets * kOrCells);
     }
