@@ -737,7 +737,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     uint32_t* nbr_begin = bitmap ? cv.take<uint32_t>((size_t)n + 2) : nullptr;
     uint16_t* nbr = bitmap ? cv.take<uint16_t>(bitmap_index_entries(n)) : nullptr;
     const bool tiled = bitmap && tiled_plan_possible(n, tr->t_end, P, di);
-    int32_t* net = tiled ? cv.take<int32_t>((size_t)tr->t_end + 1) : nullptr;
+    int32_t* net = bitmap ? cv.take<int32_t>(tiled_plan_words(n)) : nullptr;
     // variant for long traces with few long-lived requests: tables in allocation-time order
     const bool split = !lds32;
     SplitWorkspace sw;

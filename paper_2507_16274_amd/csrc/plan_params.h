@@ -79,7 +79,8 @@ bool launch_plan_split(const PlanParams& prm, uint32_t t_end, const SplitWorkspa
 // Fills PlanParams::bitmap_pool_words for a trace of n requests; false if no shape fits.
 bool bitmap_plan_shapes(uint32_t n, const DeviceInfo& di, uint32_t (&pool_words)[kBitmapShapes]);
 size_t bitmap_index_entries(uint32_t n);             // uint16_t entries of PlanParams::nbr
-bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInfo& di);   // bitmap variant with tables per tile of time; net: t_end + 1 words
+bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInfo& di);   // bitmap variant with tables per tile of time
+size_t tiled_plan_words(uint32_t n);                 // its `net`: t_end + 1 words, for every t_end and P that it can be part of a call with
 bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream);
 bool launch_plan_bitmap(const PlanParams& prm, const DeviceInfo& di, hipStream_t stream);
 

@@ -391,10 +391,15 @@ static bool launch_tiled(const PlanParams& prm, uint32_t t_end, uint32_t wgs_per
 // (this one / the other: 1152 requests, 64 plans 0.57 / 0.61 ms, 2048 plans 1.38 / 1.33; 2304 requests, 64 plans
 // 1.11 / 1.29, 1024 plans 1.70 / 1.61; 4608 requests, 512 plans 2.20 / 3.11).  The timestamps must not be far
 // apart (the preparation counts per timestamp).
+constexpr uint32_t kPtFrom = 1024;
+static uint32_t pt_most_times(uint32_t n) { return 4 * n + 4096; }
+
 bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInfo& di)
 {
-    return n >= 1024 && n <= kBmMaxRequests && (uint64_t)t_end <= 4ull * n + 4096 && (n >= 3072 || P <= 2 * (uint32_t)di.cus);
+    return n >= kPtFrom && n <= kBmMaxRequests && t_end <= pt_most_times(n) && (n >= 3072 || P <= 2 * (uint32_t)di.cus);
 }
+
+size_t tiled_plan_words(uint32_t n) { return n >= kPtFrom && n <= kBmMaxRequests ? (size_t)pt_most_times(n) + 1 : 0; }
 
 bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream)
 {

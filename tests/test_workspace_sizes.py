@@ -28,3 +28,32 @@ def test_windows_of_orders_share_a_workspace(n):
         assert len(sizes) == 1, (P, sizes)
         assert sizes.pop() >= last
         last = _orders_need(S, n, 0, P)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [96, 1023, 1024, 2048, 3071, 3072, 6144, 19840, 32768])
+def test_plans_of_one_length_share_a_workspace(n):
+    """(the query asks for the device's LDS) Fewer rows never need more; whatever t_end, as long as a list of all placed
+    blocks fits LDS (beyond, tables by allocation time are part of the workspace)."""
+    import torch
+    import paper_2507_16274_amd as S
+    torch.cuda.init()
+
+    def need(t_end, P, offsets, sized):
+        size = ctypes.c_size_t(0)
+        tr = _trace(S, n, t_end)
+        args = (ctypes.byref(tr), 256, P, 256 if offsets else None, 256, 256, 256, 256)
+        if sized:
+            assert S.lib.stalloc_plan_sized(*args, 1 << 20, 1 << 16, None, ctypes.byref(size), None) == 0
+        else:
+            assert S.lib.stalloc_plan(*args, None, ctypes.byref(size), None) == 0
+        return size.value
+
+    times = (1, n // 2 + 1, 2 * n, 4 * n + 4096, 4 * n + 4097, 1 << 20)
+    for offsets in (True, False):
+        for sized in (True, False):
+            by_rows = [[need(t_end, P, offsets, sized) for t_end in times] for P in (1, 64, 512, 513, 4096)]
+            for fewer, more in zip(by_rows, by_rows[1:]):
+                assert all(a <= b for a, b in zip(fewer, more)), by_rows
+            if n <= S.lib.stalloc_plan_lds_capacity():
+                assert all(len(set(sizes)) == 1 for sizes in by_rows), by_rows
