@@ -72,7 +72,7 @@ struct Carver {
 // when only plans that stack nearly everything would overflow 32-bit counts.
 constexpr int kAccWords = 16;
 constexpr int kTraceCheckBlocks = 256;
-constexpr int kAccSpace = kAccWords + 5 * kTraceCheckBlocks;   // what launch_trace_check needs: the words, and five per workgroup behind them
+constexpr int kAccSpace = kAccWords + 7 * kTraceCheckBlocks;   // what launch_trace_check needs: the words, and seven per workgroup behind them
 constexpr int kAccMode = 4;
 constexpr int kAccMaxSize = 5;
 constexpr int kAccGranules = 6;                // sum of sizes in granules
@@ -83,6 +83,8 @@ constexpr int kAccWidePlans = 9;               // plans that outgrew 32-bit gran
 constexpr int kAccLargeShort = 10;             // long-list kernel: size (granules) from which a short-lived block counts as large
                                                // (0xffffffff: none does); bits 32..63: how many do
 constexpr int kAccTiles = 11;                  // bitmap kernel with tables per tile of time: 0 = does not place the trace, else its layout (plan_tiled.hip)
+constexpr int kAccCrowded = 13;                // 1: the mean lifetime is more than a fifth of the time from first allocation to last release,
+                                               // or that time is less than a sixteenth of t_end
 constexpr int kAccTilesMissed = 12;            // plans that outgrew its tables and are left to the other bitmap kernel
 constexpr uint64_t kModeNarrow = 1ull << 8;
 constexpr uint64_t kModeCompact = 1ull << 9;   // sum of sizes in granules below 2^16 as well

@@ -11,15 +11,24 @@
 namespace stalloc {
 
 // Sums of the high and low halves of the sizes, whether a request is malformed, all bits set in any size, the
-// largest size.
+// largest size, the sum of the lifetimes, first allocation and last release.
 struct TraceSums {
-    uint64_t hi, lo, bad, bits, largest;
+    uint64_t hi, lo, bad, bits, largest, lives;
+    uint32_t t_first, t_last;
     __device__ __forceinline__ void add(const TraceSums& o)
     {
         hi += o.hi; lo += o.lo; bad |= o.bad; bits |= o.bits; largest = umax64(largest, o.largest);
+        lives += o.lives; t_first = umin(t_first, o.t_first); t_last = umax(t_last, o.t_last);
+    }
+    __device__ __forceinline__ void over_wave()                       // in all lanes
+    {
+        hi = wave_sum64(hi); lo = wave_sum64(lo); bad = wave_or64(bad); bits = wave_or64(bits); largest = wave_max64(largest);
+        lives = wave_sum64(lives);
+        t_first = ~read_lane(wave_scan_max(~t_first), kWave - 1); t_last = read_lane(wave_scan_max(t_last), kWave - 1);
     }
 };
-static_assert(sizeof(TraceSums) == 5 * sizeof(uint64_t), "kAccSpace holds one per workgroup");
+static_assert(sizeof(TraceSums) == 7 * sizeof(uint64_t), "kAccSpace holds one per workgroup");
+constexpr uint32_t kNever = 0xffffffffu;
 
 // Of the requests that the calling threads take, `step` apart; valid in thread 0 of the workgroup.
 template <int kThreads>
@@ -27,7 +36,7 @@ __device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ s
                                                   const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end, uint32_t first, uint32_t step)
 {
     __shared__ TraceSums part[kThreads / kWave];
-    TraceSums t = {0, 0, 0, 0, 0};
+    TraceSums t = {0, 0, 0, 0, 0, 0, kNever, 0};
 #pragma unroll 4
     for (uint32_t i = first; i < n; i += step) {
         const uint64_t s = size[i];
@@ -37,12 +46,11 @@ __device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ s
         t.lo += s & 0xffffffffull;
         t.bits |= s;
         t.largest = umax64(t.largest, s);
+        t.lives += f - a;              // n terms below 2^32 each
+        t.t_first = umin(t.t_first, a);
+        t.t_last = umax(t.t_last, f);
     }
-    t.hi = wave_sum64(t.hi);
-    t.lo = wave_sum64(t.lo);
-    t.bad = __builtin_amdgcn_ballot_w64(t.bad != 0) ? 1 : 0;
-    t.bits = wave_or64(t.bits);
-    t.largest = wave_max64(t.largest);
+    t.over_wave();
     if (lane_id() == 0) part[wave_id()] = t;
     __syncthreads();
     if (threadIdx.x == 0)
@@ -51,11 +59,13 @@ __device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ s
 }
 
 // The accumulators (the other words are zero) and the status, from the sums over all requests; one thread.
-__device__ __forceinline__ void write_verdict(const TraceSums& t, uint64_t* acc, uint32_t* status)
+__device__ __forceinline__ void write_verdict(const TraceSums& t, uint32_t n, uint32_t t_end, uint64_t* acc, uint32_t* status)
 {
     uint32_t code = STALLOC_OK;
     uint64_t words[kAccWords] = {t.hi, t.lo, t.bad, t.bits};
     words[kAccMaxSize] = t.largest;
+    const float span = (float)(t.t_last - t.t_first);                // (a choice between two ways to the same answer: rounding does not matter)
+    words[kAccCrowded] = (float)t.lives * 5.0f > (float)n * span || span * 16.0f < (float)t_end ? 1 : 0;
     if (t.hi + (t.lo >> 32) < (1ull << 31) && t.bits != 0) {
         const uint64_t total = (t.hi << 32) + t.lo;                  // below 2^63 here
         const uint32_t shift = (uint32_t)__builtin_ctzll(t.bits);
@@ -81,7 +91,7 @@ trace_check_small(const uint64_t* __restrict__ size, const uint32_t* __restrict_
                   uint32_t t_end, uint64_t* acc, uint32_t* status)
 {
     const TraceSums t = sum_requests<1024>(size, ta, tf, n, t_end, threadIdx.x, 1024);
-    if (threadIdx.x == 0) write_verdict(t, acc, status);
+    if (threadIdx.x == 0) write_verdict(t, n, t_end, acc, status);
 }
 
 __global__ void __launch_bounds__(256)
@@ -92,21 +102,18 @@ trace_check_scan(const uint64_t* __restrict__ size, const uint32_t* __restrict__
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ void __launch_bounds__(kTraceCheckBlocks) trace_check_finish(const TraceSums* part, uint32_t parts, uint64_t* acc, uint32_t* status)
+__global__ void __launch_bounds__(kTraceCheckBlocks) trace_check_finish(const TraceSums* part, uint32_t parts, uint32_t n, uint32_t t_end, uint64_t* acc,
+                                                                        uint32_t* status)
 {
     __shared__ TraceSums of[kTraceCheckBlocks / kWave];
-    TraceSums t = {0, 0, 0, 0, 0};
+    TraceSums t = {0, 0, 0, 0, 0, 0, kNever, 0};
     if (threadIdx.x < parts) t = part[threadIdx.x];
-    t.hi = wave_sum64(t.hi);
-    t.lo = wave_sum64(t.lo);
-    t.bad = wave_or64(t.bad);
-    t.bits = wave_or64(t.bits);
-    t.largest = wave_max64(t.largest);
+    t.over_wave();
     if (lane_id() == 0) of[wave_id()] = t;
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (int w = 1; w < kTraceCheckBlocks / kWave; ++w) t.add(of[w]);
-    write_verdict(t, acc, status);
+    write_verdict(t, n, t_end, acc, status);
 }
 
 // One launch for short traces (up to this many requests a single workgroup needs no longer than a launch
@@ -126,7 +133,7 @@ void launch_trace_check(const stalloc_trace& tr, uint64_t* acc, uint32_t* device
     TraceSums* part = reinterpret_cast<TraceSums*>(acc + kAccWords);
     hipLaunchKernelGGL(trace_check_scan, dim3(blocks), dim3(256), 0, stream, tr.size, tr.t_alloc, tr.t_free,
                        tr.n, tr.t_end, part);
-    hipLaunchKernelGGL(trace_check_finish, dim3(1), dim3(kTraceCheckBlocks), 0, stream, part, blocks, acc, device_status);
+    hipLaunchKernelGGL(trace_check_finish, dim3(1), dim3(kTraceCheckBlocks), 0, stream, part, blocks, tr.n, tr.t_end, acc, device_status);
 }
 
 }  // namespace stalloc

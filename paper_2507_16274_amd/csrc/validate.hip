@@ -1,11 +1,13 @@
 // stalloc_validate: pairwise check of the planning constraint of Sec. 5.1 -- no two
 // allocation decisions may conflict in lifespan and in address range at once.
 //
-// Two forms of the same count.  val_pairs tests all n(n-1)/2 unordered pairs of every plan: the
+// Two forms of the same count.  val_tile tests all n(n-1)/2 unordered pairs of every plan: the
 // pair space is cut into 256 x 256 tiles (upper triangle only); one workgroup owns one tile of
 // one plan: each thread keeps its own request i in registers and walks the 256 requests j of the
 // tile, which sit in LDS and are read as broadcasts.  val_near puts the requests into buckets of
-// like lifetime and allocation time first and leaves out what cannot meet in time (see there).
+// like lifetime and allocation time first and leaves out what cannot meet in time (see there); in
+// traces whose requests live for a fifth of the time on average there is little to leave out, and
+// the launch for one plan takes the first form (the trace check has found out, see kAccCrowded).
 // Per plan both accumulate the number of conflicting pairs and the smallest key (i << 32 | j),
 // i < j, which is the lexicographically first conflicting pair.
 #include "host_util.h"
@@ -15,13 +17,19 @@ namespace stalloc {
 
 constexpr int kValTile = 256;
 
-// val_near takes calls of at least this many requests^2 x plans: its five preparing launches cost about 30 us,
-// which is what val_pairs needs for this many pairs (all pairs / near pairs: 6144 requests, 4 plans 41 / 62
-// us, 8 plans 63 / 66 us, 16 plans 102 / 75 us; 19 840 requests, one plan 79 / 52 us).
+// val_near is part of calls of at least this many requests^2 x plans: its five preparing launches cost 20 to 30 us
+// (10 in a crowded trace, where they return at once), against 210 us and more that all pairs take from here on.
+// Lifetimes of all lengths, all pairs / val_near: 40 000 requests, one plan 219 / 97 us; 6144 requests, 40 plans
+// 213 / 110; 100 000 requests, 16 plans 18.9 / 2.2 ms.  Lifetimes a third of the time long: 220 / 217, 328 / 300,
+// 18.9 / 10.1.  From 3.5e8 on, where they would pay in sparse traces, crowded ones took up to twice as long.
 #ifndef STALLOC_VAL_NEAR_FROM
-#define STALLOC_VAL_NEAR_FROM (350ull * 1000 * 1000)
+#define STALLOC_VAL_NEAR_FROM (1500ull * 1000 * 1000)
 #endif
 constexpr uint64_t kVnFrom = STALLOC_VAL_NEAR_FROM;
+// Below these a wave takes one plan and looks whether the trace is crowded (four plans share a look at the lifetimes
+// otherwise, and are as fast as all pairs in a crowded trace, but need enough waves: 20 000 requests, 4
+// plans, crowded: 260 us all pairs, 295 four together; 40 000 requests, 4 plans 790 / 640).
+constexpr uint64_t kVnTogether = 3000ull * 1000 * 1000, kVnThree = 10000ull * 1000 * 1000;
 
 __global__ void val_init(uint64_t* conflicts, uint64_t* first_key, uint32_t P)
 {
@@ -31,18 +39,13 @@ __global__ void val_init(uint64_t* conflicts, uint64_t* first_key, uint32_t P)
     }
 }
 
-__global__ void __launch_bounds__(kValTile)
-val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf,
-          const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0,
-          uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
+// One tile of one plan; called by a workgroup of 256 threads.
+__device__ __forceinline__ void val_tile(uint64_t (&j_lo)[kValTile], uint64_t (&j_hi)[kValTile], uint32_t (&j_ta)[kValTile],
+                                         uint32_t (&j_tf)[kValTile], const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta,
+                                         const uint32_t* __restrict__ tf, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles,
+                                         uint32_t lin, uint32_t p, uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
 {
-    __shared__ uint64_t j_lo[kValTile];
-    __shared__ uint64_t j_hi[kValTile];
-    __shared__ uint32_t j_ta[kValTile];
-    __shared__ uint32_t j_tf[kValTile];
-
     // linear tile index -> (ti, tj) with ti <= tj, row-major over the upper triangle
-    const uint32_t lin = blockIdx.x;
     const double nt = (double)tiles;
     uint32_t ti = (uint32_t)((2.0 * nt + 1.0 - sqrt((2.0 * nt + 1.0) * (2.0 * nt + 1.0) - 8.0 * (double)lin)) * 0.5);
     if (ti >= tiles) ti = tiles - 1;
@@ -52,7 +55,6 @@ val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
     while (ti + 1 < tiles && row_start(ti + 1) <= lin) ++ti;
     const uint32_t tj = ti + (uint32_t)(lin - row_start(ti));
 
-    const uint32_t p = plan0 + blockIdx.y;
     const uint64_t* off = offsets + (size_t)p * n;
 
     const uint32_t j0 = tj * kValTile;
@@ -99,6 +101,18 @@ val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
     }
 }
 
+__global__ void __launch_bounds__(kValTile)
+val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf,
+          const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0,
+          uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
+{
+    __shared__ uint64_t j_lo[kValTile];
+    __shared__ uint64_t j_hi[kValTile];
+    __shared__ uint32_t j_ta[kValTile];
+    __shared__ uint32_t j_tf[kValTile];
+    val_tile(j_lo, j_hi, j_ta, j_tf, size, ta, tf, offsets, n, tiles, blockIdx.x, plan0 + blockIdx.y, conflicts, first_key, status);
+}
+
 // ------------------------------------------------------------------------------------------
 // Pairs that can meet in time.  A training trace holds few pairs with overlapping lifetimes
 // (3.5e8 of 2.0e10 for the 200k requests of an interleaved schedule), and which ones they are does
@@ -120,23 +134,26 @@ constexpr uint32_t kVnRow = kVnTile + 4;         // (the walk over a tile's requ
 // half of the smallest of them.
 struct VnBuckets {
     uint32_t base, t_end, count;
+    uint32_t apart;              // counters lie 2^apart words apart: on a coarse clock there are few, and atomics on one line of memory queue up
     __host__ __device__ uint32_t shift_of(uint32_t k) const { return k == 0 ? base : (base + k > 2 ? base + k - 2 : 0u); }
     __host__ __device__ uint32_t in_class(uint32_t k) const { return (t_end >> shift_of(k)) + 1; }
-    __device__ uint32_t of(uint32_t ta, uint32_t tf) const
+    __device__ uint32_t of(uint32_t ta, uint32_t tf) const            // place of the counter
     {
         const uint32_t bits = 32u - (uint32_t)__builtin_clz((tf - ta) | 1u);
         const uint32_t cls = bits > base ? bits - base : 0u;
         uint32_t first = 0;
         for (uint32_t k = 0; k < cls; ++k) first += in_class(k);
-        return first + ((ta < t_end ? ta : t_end) >> shift_of(cls));
+        return (first + ((ta < t_end ? ta : t_end) >> shift_of(cls))) << apart;
     }
+    __host__ __device__ uint32_t words() const { return count << apart; }
 };
 
 static VnBuckets vn_buckets(uint32_t n, uint32_t t_end)
 {
-    VnBuckets b = {0, t_end, 0};
+    VnBuckets b = {0, t_end, 0, 0};
     while (b.base < 31 && ((uint64_t)n << b.base) < (uint64_t)t_end * kVnTile) ++b.base;
     for (uint32_t k = 0; k <= 32 - b.base; ++k) b.count += b.in_class(k);
+    while (b.apart < 5 && b.count << b.apart < 16384) ++b.apart;
     return b;
 }
 
@@ -153,6 +170,9 @@ struct VnSorted {
     uint32_t* id;            //     and number of the request
     uint2* span;             // [tiles] first allocation, last release
 };
+
+// acc: nullptr when the all-pairs form is not part of the launch that follows.
+__device__ __forceinline__ bool left_to_all_pairs(const uint64_t* acc) { return acc && acc[kAccCrowded]; }
 
 __global__ void __launch_bounds__(256) vn_clear(uint32_t* bucket, uint32_t buckets, uint64_t* conflicts, uint64_t* first_key, uint32_t P)
 {
@@ -183,8 +203,9 @@ __device__ __forceinline__ uint32_t vn_take(uint32_t* bucket, uint32_t mine, boo
 }
 
 __global__ void __launch_bounds__(256)
-vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, uint32_t* bucket)
+vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, uint32_t* bucket, const uint64_t* acc)
 {
+    if (left_to_all_pairs(acc)) return;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         vn_take(bucket, i < n ? b.of(ta[i], tf[i]) : 0u, i < n);
@@ -192,28 +213,30 @@ vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint3
 }
 
 // Exclusive sums of the bucket sizes, in place; one workgroup, four buckets a thread and step.
-__global__ void __launch_bounds__(1024) vn_starts(uint32_t* bucket, uint32_t buckets)
+__global__ void __launch_bounds__(1024) vn_starts(uint32_t* bucket, uint32_t buckets, uint32_t apart, const uint64_t* acc)
 {
     __shared__ uint32_t part[16];
+    if (left_to_all_pairs(acc)) return;
     uint32_t carry = 0;
     for (uint32_t k0 = 0; k0 < buckets; k0 += 4096) {
         const uint32_t k = k0 + 4 * threadIdx.x;
         uint32_t v[4], mine = 0;
-        for (int u = 0; u < 4; ++u) { v[u] = k + u < buckets ? bucket[k + u] : 0u; mine += v[u]; }
+        for (int u = 0; u < 4; ++u) { v[u] = k + u < buckets ? bucket[(k + u) << apart] : 0u; mine += v[u]; }
         const uint32_t incl = wave_scan_add(mine);
         __syncthreads();                                              // (the step before has read part[])
         if (lane_id() == kWave - 1) part[wave_id()] = incl;
         __syncthreads();
         uint32_t before = carry + incl - mine;
         for (int w = 0; w < 16; ++w) { if (w < wave_id()) before += part[w]; carry += part[w]; }
-        for (int u = 0; u < 4; ++u) { if (k + u < buckets) bucket[k + u] = before; before += v[u]; }
+        for (int u = 0; u < 4; ++u) { if (k + u < buckets) bucket[(k + u) << apart] = before; before += v[u]; }
     }
 }
 
 __global__ void __launch_bounds__(256)
 vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
-           VnBuckets b, VnSorted s)
+           VnBuckets b, VnSorted s, const uint64_t* acc)
 {
+    if (left_to_all_pairs(acc)) return;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         const bool valid = i < n;
@@ -226,13 +249,20 @@ vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, c
     }
 }
 
-__global__ void __launch_bounds__(256) vn_spans(const uint2* __restrict__ life, uint32_t n, uint32_t tiles, uint2* span)
+// One wave: the span of tile t.
+__device__ __forceinline__ void vn_span(const VnSorted& s, uint32_t n, uint32_t t)
 {
-    const uint32_t t = blockIdx.x * kVnWaves + (uint32_t)wave_id(), k = t * kVnTile + lane_id();
-    if (t >= tiles) return;                                           // (uniform)
-    const uint2 l = k < n ? life[k] : make_uint2(0xffffffffu, 0u);
+    const uint32_t k = t * kVnTile + lane_id();
+    const uint2 l = k < n ? s.life[k] : make_uint2(0xffffffffu, 0u);
     const uint32_t first = ~read_lane(wave_scan_max(~l.x), kWave - 1), last = read_lane(wave_scan_max(l.y), kWave - 1);
-    if (lane_id() == 0) span[t] = make_uint2(first, last);
+    if (lane_id() == 0) s.span[t] = make_uint2(first, last);
+}
+
+__global__ void __launch_bounds__(256) vn_spans(VnSorted s, uint32_t n, uint32_t tiles, const uint64_t* acc)
+{
+    const uint32_t t = blockIdx.x * kVnWaves + (uint32_t)wave_id();
+    if (t >= tiles || left_to_all_pairs(acc)) return;                       // (uniform)
+    vn_span(s, n, t);
 }
 
 // One wave = one tile of first requests (a lane each) x up to `chunk` tiles of second requests at or
@@ -240,14 +270,21 @@ __global__ void __launch_bounds__(256) vn_spans(const uint2* __restrict__ life, 
 // others that do not meet the first tile's span 64 at a time; what is left is put into LDS and
 // taken one by one as broadcasts: two lifetime compares for all plans, two address compares a plan.
 // The records of the next tile but one and the addresses of the next are on their way meanwhile.
+// A group of plans beyond the last plan repeats that one, and leaves out its results.
+struct Range { uint64_t lo, hi; };
 template <int kPlans>
-__global__ void __launch_bounds__(kVnWaves * kWave)
-val_near(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t chunk, uint32_t plan0,
-         uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
+struct ValNearLds {
+    uint4 who[kVnWaves][kVnRow];                                      // t_alloc, t_free, number, place in the tile
+    Range range[kVnWaves][kPlans][kVnRow];
+};
+
+template <int kPlans>
+__device__ __forceinline__ void val_near(ValNearLds<kPlans>& sh, const VnSorted& s, const uint64_t* __restrict__ offsets, uint32_t n,
+                                         uint32_t tiles, uint32_t chunk, uint32_t p0, uint32_t plan_end, uint64_t* conflicts,
+                                         uint64_t* first_key, uint32_t* status)
 {
-    struct Range { uint64_t lo, hi; };
-    __shared__ uint4 sh_who[kVnWaves][kVnRow];                        // t_alloc, t_free, number, place in the tile
-    __shared__ Range sh_range[kVnWaves][kPlans][kVnRow];
+    auto& sh_who = sh.who;
+    auto& sh_range = sh.range;
     const int lane = lane_id(), wave = wave_id();
     // workgroup -> (chunk c of second requests, four tiles g of first requests): with r = chunk / 4 chunk c has
     // r (c + 1) groups of four tiles at or in front of it, numbered from r c (c + 1) / 2 on
@@ -257,7 +294,6 @@ val_near(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t 
     while (r * (c + 1) * (c + 2) / 2 <= blockIdx.x) ++c;
     const uint32_t it = uniform((uint32_t)(blockIdx.x - r * c * (c + 1) / 2) * kVnWaves + (uint32_t)wave);
     if (it >= tiles) return;                                          // (uniform; the waves do not meet)
-    const uint32_t p0 = plan0 + blockIdx.y * kPlans;
     const uint2 span = s.span[it];
     const uint32_t first_jt = uniform(c * chunk);
     uint64_t near = 0;
@@ -286,7 +322,7 @@ val_near(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t 
     };
     auto addresses_of = [&](const Record& q, uint64_t (&lo)[kPlans]) {
 #pragma unroll
-        for (int p = 0; p < kPlans; ++p) lo[p] = offsets[(size_t)(p0 + p) * n + q.id];
+        for (int p = 0; p < kPlans; ++p) lo[p] = offsets[(size_t)umin(p0 + p, plan_end - 1) * n + q.id];
     };
     uint64_t ahead = near & (near - 1);
     Record now = record_of(near), next = record_of(ahead);
@@ -297,7 +333,7 @@ val_near(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t 
         const uint64_t size_i = i_ok ? s.size[at_i] : 0u;
 #pragma unroll
         for (int p = 0; p < kPlans; ++p) {
-            const uint64_t lo = i_ok ? offsets[(size_t)(p0 + p) * n + id_i] : 0u;
+            const uint64_t lo = i_ok ? offsets[(size_t)umin(p0 + p, plan_end - 1) * n + id_i] : 0u;
             // an address range that would run past 2^64 is reported, and kept from wrapping so that what
             // it covers still counts
             const bool wraps = lo + size_i < lo;
@@ -365,13 +401,47 @@ val_near(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t 
     }
 #pragma unroll
     for (int p = 0; p < kPlans; ++p) {
-        if (count[p] == 0) continue;                                  // (uniform)
+        if (count[p] == 0 || p0 + p >= plan_end) continue;            // (uniform)
         const uint64_t wave_key = wave_min64(key[p]);
         if (lane == 0) {
             atomicAdd((unsigned long long*)&conflicts[p0 + p], (unsigned long long)count[p]);
             atomicMin((unsigned long long*)&first_key[p0 + p], (unsigned long long)wave_key);
         }
     }
+}
+
+// Four plans a wave.
+__global__ void __launch_bounds__(kVnWaves * kWave)
+val_near_plans(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t chunk, uint32_t plan0,
+               uint32_t plan_end, uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
+{
+    __shared__ ValNearLds<4> sh;
+    val_near<4>(sh, s, offsets, n, tiles, chunk, plan0 + blockIdx.y * 4, plan_end, conflicts, first_key, status);
+}
+
+// One plan a wave; or, in a crowded trace, all of its pairs, the 256 x 256 tiles dealt out grid by grid.  (At most 64
+// registers: with 70, seven waves a SIMD, all pairs of one plan took 4 % longer than in val_pairs.)
+__global__ void __launch_bounds__(kVnWaves * kWave, 8)
+val_one_plan(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, VnSorted s,
+             const uint64_t* __restrict__ offsets, uint32_t n, uint32_t near_tiles, uint32_t chunk, uint32_t tiles, uint64_t* conflicts,
+             uint64_t* first_key, const uint64_t* acc, uint32_t* status)
+{
+    static_assert(kVnWaves * kWave == kValTile, "both forms run in workgroups of one size");
+    __shared__ uint64_t j_lo[kValTile];
+    __shared__ uint64_t j_hi[kValTile];
+    __shared__ uint32_t j_ta[kValTile];
+    __shared__ uint32_t j_tf[kValTile];
+    __shared__ ValNearLds<1> near;
+    const uint32_t p = blockIdx.y;
+    if (left_to_all_pairs(acc)) {                                     // (uniform)
+        const uint32_t tri = (uint32_t)((uint64_t)tiles * (tiles + 1) / 2);
+        for (uint32_t lin = blockIdx.x; lin < tri; lin += gridDim.x) {
+            __syncthreads();                                          // (the tile before has been read)
+            val_tile(j_lo, j_hi, j_ta, j_tf, size, ta, tf, offsets, n, tiles, lin, p, conflicts, first_key, status);
+        }
+        return;
+    }
+    val_near<1>(near, s, offsets, n, near_tiles, chunk, p, p + 1, conflicts, first_key, status);
 }
 
 __global__ void val_finish(const uint64_t* first_key, uint32_t* first_pair, uint32_t P)
@@ -398,20 +468,23 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     Carver cv(workspace);
     uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* first_key = cv.take<uint64_t>(P);
-    const bool near = (uint64_t)tr->n * tr->n * P >= kVnFrom;
-    VnBuckets buckets = {0, 0, 0};
+    bool near = (uint64_t)tr->n * tr->n * P >= kVnFrom;
+    VnBuckets buckets = {0, 0, 0, 0};
     VnSorted sorted = {};
     const uint32_t near_tiles = (tr->n + kVnTile - 1) / kVnTile;
+    const size_t all_pairs = cv.used;
     if (near) {
         buckets = vn_buckets(tr->n, tr->t_end);
-        sorted.bucket = cv.take<uint32_t>(buckets.count);
+        sorted.bucket = cv.take<uint32_t>(buckets.words());
         sorted.life = cv.take<uint2>(tr->n);
         sorted.size = cv.take<uint64_t>(tr->n);
         sorted.id = cv.take<uint32_t>(tr->n);
         sorted.span = cv.take<uint2>(near_tiles);
     }
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
-    if (!offsets || !conflicts || !first_pair || !device_status || *workspace_bytes < cv.used ||
+    // (the first two pieces are all that P asks for; a workspace with room for no more gets the all-pairs form)
+    if (near && *workspace_bytes < cv.used) near = false;
+    if (!offsets || !conflicts || !first_pair || !device_status || *workspace_bytes < (near ? cv.used : all_pairs) ||
         (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)))
         return STALLOC_ERR_INVALID_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -420,30 +493,32 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     uint32_t pb = (P + 255) / 256;
     if (pb > 1024) pb = 1024;
     if (near) {
+        const uint64_t work = (uint64_t)tr->n * tr->n * P;
+        const bool by_plan = P < 3 || (P == 3 && work < kVnThree) || (P < 8 && work < kVnTogether);
+        const uint64_t* crowded = by_plan ? acc : nullptr;
         uint32_t blocks = (tr->n + 255) / 256;
         if (blocks > 1024) blocks = 1024;
-        uint32_t cb = ((buckets.count > P ? buckets.count : P) + 255) / 256;
+        uint32_t cb = ((buckets.words() > P ? buckets.words() : P) + 255) / 256;
         if (cb > 1024) cb = 1024;
-        hipLaunchKernelGGL(vn_clear, dim3(cb), dim3(256), 0, stream, sorted.bucket, buckets.count, conflicts, first_key, P);
-        hipLaunchKernelGGL(vn_count, dim3(blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted.bucket);
-        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, sorted.bucket, buckets.count);
-        hipLaunchKernelGGL(vn_scatter, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, buckets, sorted);
-        hipLaunchKernelGGL(vn_spans, dim3((near_tiles + kVnWaves - 1) / kVnWaves), dim3(256), 0, stream, sorted.life, tr->n,
-                           near_tiles, sorted.span);
+        hipLaunchKernelGGL(vn_clear, dim3(cb), dim3(256), 0, stream, sorted.bucket, buckets.words(), conflicts, first_key, P);
+        hipLaunchKernelGGL(vn_count, dim3(blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted.bucket, crowded);
+        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, sorted.bucket, buckets.count, buckets.apart, crowded);
+        hipLaunchKernelGGL(vn_scatter, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, crowded);
+        hipLaunchKernelGGL(vn_spans, dim3((near_tiles + kVnWaves - 1) / kVnWaves), dim3(256), 0, stream, sorted, tr->n, near_tiles, crowded);
         // (chunk, group of first tiles) workgroups: the last chunk only has the groups that exist
         const uint32_t chunk = vn_chunk(near_tiles);
         const uint64_t chunks = (near_tiles + chunk - 1) / chunk;
         const uint32_t grid = (uint32_t)(chunk / kVnWaves * ((chunks - 1) * chunks / 2) + (near_tiles + kVnWaves - 1) / kVnWaves);
-        uint32_t p0 = 0;
-        for (; P - p0 >= 4;) {                                // four plans share a look at the lifetimes; grid.y is limited to 65535
-            const uint32_t py = (P - p0) / 4 < 32768 ? (P - p0) / 4 : 32768;
-            hipLaunchKernelGGL(val_near<4>, dim3(grid, py), dim3(kVnWaves * kWave), 0, stream, sorted, offsets, tr->n, near_tiles, chunk,
-                               p0, conflicts, first_key, device_status);
-            p0 += 4 * py;
-        }
-        if (p0 < P)
-            hipLaunchKernelGGL(val_near<1>, dim3(grid, P - p0), dim3(kVnWaves * kWave), 0, stream, sorted, offsets, tr->n, near_tiles,
-                               chunk, p0, conflicts, first_key, device_status);
+        if (by_plan)
+            hipLaunchKernelGGL(val_one_plan, dim3(grid, P), dim3(kVnWaves * kWave), 0, stream, tr->size, tr->t_alloc, tr->t_free, sorted,
+                               offsets, tr->n, near_tiles, chunk, (uint32_t)tiles, conflicts, first_key, crowded, device_status);
+        else
+            for (uint32_t p0 = 0; p0 < P;) {                  // four plans share a look at the lifetimes; grid.y is limited to 65535
+                const uint32_t plans = P - p0 < 131072 ? P - p0 : 131072;
+                hipLaunchKernelGGL(val_near_plans, dim3(grid, (plans + 3) / 4), dim3(kVnWaves * kWave), 0, stream, sorted, offsets, tr->n,
+                                   near_tiles, chunk, p0, p0 + plans, conflicts, first_key, device_status);
+                p0 += plans;
+            }
     } else {
         hipLaunchKernelGGL(val_init, dim3(pb), dim3(256), 0, stream, conflicts, first_key, P);
         for (uint32_t p0 = 0; p0 < P; p0 += 32768) {          // grid.y is limited to 65535

@@ -1,11 +1,13 @@
 """stalloc_validate on calls large enough for the form that leaves out pairs that cannot meet in time
-(n * n * P >= 3.5e8), against the oracle and against the all-pairs form on slices of the same plans."""
+(n * n * P >= 1.5e9), against the oracle and against the all-pairs form on slices of the same plans."""
+import ctypes
+
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-NEAR_FROM = 350_000_000
+NEAR_FROM = 1_500_000_000
 
 
 def _trace(rng, n, kind):
@@ -55,3 +57,48 @@ def test_near_pairs_report_a_range_that_would_wrap(oracle):
         dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), bent)]
         out = S.stalloc_validate(*dev[:3], t_end, dev[3])
         assert int(out["status"].item()) == (3 if size[bad] > 1 else int(out["status"].item()))
+
+
+def _all_pairs(S, dev, t_end, plans):
+    """The call with no more workspace than the all-pairs form needs, which a call always accepts."""
+    import torch
+    n, P = plans.shape[1], plans.shape[0]
+    out = [torch.empty(P, dtype=torch.int64, device="cuda"), torch.empty((P, 2), dtype=torch.int32, device="cuda"),
+           torch.empty(1, dtype=torch.int32, device="cuda")]
+    need = ctypes.c_size_t(0)
+    few = S._trace(*[t[:2] for t in dev], t_end)
+    assert S.lib.stalloc_validate(ctypes.byref(few), plans.data_ptr(), P, *[o.data_ptr() for o in out], None, ctypes.byref(need), None) == 0
+    ws = torch.empty(need.value, dtype=torch.uint8, device="cuda")
+    tr = S._trace(*dev, t_end)
+    stream = torch.cuda.current_stream().cuda_stream
+    assert S.lib.stalloc_validate(ctypes.byref(tr), plans.data_ptr(), P, *[o.data_ptr() for o in out], ws.data_ptr(),
+                                  ctypes.byref(need), stream) == 0
+    need.value -= 1
+    assert S.lib.stalloc_validate(ctypes.byref(tr), plans.data_ptr(), P, *[o.data_ptr() for o in out], ws.data_ptr(),
+                                  ctypes.byref(need), stream) == 1
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("P", [1, 3, 4, 6])
+@pytest.mark.parametrize("kind", ["dense", "crowded", "ties", "mixed", "sparse", "far end"])
+def test_both_forms_agree_on_few_plans(kind, P):
+    """One to three plans (crowded traces take the all-pairs form by themselves) and four to six."""
+    import torch
+    import paper_2507_16274_amd as S
+    n = 40011
+    rng = np.random.default_rng(n + P)
+    if kind == "crowded":
+        ts, te = np.sort(rng.permutation(2 * n).reshape(n, 2), axis=1).T
+        size, t_end = rng.integers(1, 50, n).astype(np.uint64), 2 * n
+        ts, te = np.ascontiguousarray(ts).astype(np.uint32), np.ascontiguousarray(te).astype(np.uint32)
+    else:
+        size, ts, te, t_end = _trace(rng, n, "mixed" if kind == "far end" else kind)
+        t_end = 1 << 30 if kind == "far end" else t_end
+    dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
+    plans = torch.from_numpy(rng.integers(0, 60 * n, (P, n)).astype(np.int64)).cuda()
+    out = S.stalloc_validate(*dev, t_end, plans)
+    S.check_status(out)
+    conflicts, first, status = _all_pairs(S, dev, t_end, plans)
+    assert int(status.item()) == 0 and (conflicts > 0).all()
+    assert torch.equal(out["conflicts"], conflicts) and torch.equal(out["first_pair"], first)
