@@ -32,7 +32,9 @@
 
 namespace stalloc {
 
-constexpr int kFuThreads = 512;
+// A pair has a workgroup of 512, so that many waves can help at once where a step has many requests to look at; small
+// pairs one of 128, of which a CU holds more (5000 pairs of 16 requests: 119 -> 47 us; a workgroup of 512 is mostly idle).
+constexpr uint32_t kFuSmall = 256;               // requests of a pair
 
 struct FuseParams {
     const uint64_t* size;
@@ -52,6 +54,7 @@ struct FuseParams {
 };
 
 // Sums over the workgroup, three at once.
+template <int kFuThreads>
 __device__ __forceinline__ void block_sums64(uint64_t (&v)[3], uint64_t (*scratch)[3])
 {
     for (int u = 0; u < 3; ++u) v[u] = wave_sum64(v[u]);
@@ -85,6 +88,7 @@ constexpr uint32_t kDone = 0, kHelp = 1;
 // Sorts keys[0..m) in LDS, ascending; called by the whole workgroup.  A bitonic network whose merges
 // begin by comparing mirrored places, so that every exchange goes the same way and places past
 // the end, which would hold the largest keys, need not exist.
+template <int kFuThreads>
 __device__ __forceinline__ void sort_keys(uint64_t* keys, uint32_t m)
 {
     for (uint32_t span = 2; span < 2 * m; span <<= 1) {
@@ -102,6 +106,7 @@ __device__ __forceinline__ void sort_keys(uint64_t* keys, uint32_t m)
     }
 }
 
+template <int kFuThreads>
 __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -146,7 +151,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
         const uint32_t lo = ~read_lane(wave_scan_max(~lo_of[g]), kWave - 1), hi = read_lane(wave_scan_max(hi_of[g]), kWave - 1);
         if (lane_id() == 0) { atomicMin(&t_lo[g], lo); atomicMax(&t_hi[g], hi); }
     }
-    block_sums64(sums, scratch);
+    block_sums64<kFuThreads>(sums, scratch);
     // The chain below counts on starts that ascend with the block, that is on addresses that do not wrap.  Distinct
     // requests stay below 2^63 together (the trace check); requests listed twice need not, and neither would a
     // stand-in for an unknown one.  (The lower halves of fewer than 2^13 sizes add up to less than 2^45.)
@@ -170,8 +175,8 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
         at[in_larger ? k - l0 : nl + (k - s0)] = key;
     }
     __syncthreads();
-    sort_keys(at, nl);
-    sort_keys(at + nl, ns);
+    sort_keys<kFuThreads>(at, nl);
+    sort_keys<kFuThreads>(at + nl, ns);
     for (uint32_t k = tid; k < m; k += kFuThreads) {
         const uint32_t i = (uint32_t)at[k];
         srt[k] = i;
@@ -441,18 +446,22 @@ extern "C" int stalloc_fuse_groups(const stalloc_trace* tr, const uint32_t* memb
         return STALLOC_ERR_INVALID_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     launch_trace_check(*tr, acc, device_status, stream);
-    static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
-    if (!attr_set[di.device]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fuse_pairs), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_budget) != hipSuccess)     // (the kernel's static LDS takes the rest)
-            return STALLOC_ERR_DEVICE;
-        attr_set[di.device] = true;
-    }
     FuseParams prm;
     prm.size = tr->size; prm.ta = tr->t_alloc; prm.tf = tr->t_free; prm.members = members; prm.pair_begin = pair_begin;
     prm.count1 = count1; prm.order = order; prm.addr = addr; prm.extents = extents; prm.accepted = accepted;
     prm.status = device_status; prm.n = tr->n; prm.entries = m;
     prm.cap = (largest_pair + 1) & ~1u;                               // (keeps the 64-bit arrays aligned)
-    hipLaunchKernelGGL(fuse_pairs, dim3(k), dim3(kFuThreads), (size_t)prm.cap * per_request, stream, prm);
+    if (prm.cap <= kFuSmall) {
+        hipLaunchKernelGGL(fuse_pairs<128>, dim3(k), dim3(128), (size_t)prm.cap * per_request, stream, prm);
+        return hipGetLastError() == hipSuccess ? STALLOC_OK : STALLOC_ERR_DEVICE;
+    }
+    static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
+    if (!attr_set[di.device]) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fuse_pairs<512>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds_budget) != hipSuccess)     // (the kernel's static LDS takes the rest)
+            return STALLOC_ERR_DEVICE;
+        attr_set[di.device] = true;
+    }
+    hipLaunchKernelGGL(fuse_pairs<512>, dim3(k), dim3(512), (size_t)prm.cap * per_request, stream, prm);
     return hipGetLastError() == hipSuccess ? STALLOC_OK : STALLOC_ERR_DEVICE;
 }

@@ -112,7 +112,7 @@ def test_a_large_pair_at_the_lds_limit_and_errors(S, oracle):
 
 
 @pytest.mark.parametrize("kind", ["before", "after", "stack", "free"])
-@pytest.mark.parametrize("n1,n2", [(64, 65), (700, 63), (130, 1500), (1, 129), (900, 900)])
+@pytest.mark.parametrize("n1,n2", [(64, 65), (700, 63), (130, 1500), (1, 129), (900, 900), (127, 129), (128, 129)])
 def test_groups_before_after_and_inside_each_other(S, oracle, n1, n2, kind):
     """The smaller group entirely earlier or later than the larger one (lifetimes meet in one phase only), with
     lifetimes nested like a stack's, and free: requests that fit for good, that sleep and that need a
