@@ -26,8 +26,9 @@
 // instead of 737 and 2211).
 //
 // The tables hold the address range up to an eighth above the largest number of live granules (which no
-// plan can stay below and plans worth having stay close to).  A plan that grows beyond that is given up and
-// placed by plan_bitmap.hip, whose kernels follow on the stream and otherwise return at once.
+// plan can stay below and plans worth having stay close to), and up to two and a half times that number where the LDS has
+// room.  A plan that grows beyond that is given up and placed by plan_bitmap.hip, whose kernels follow on the
+// stream and otherwise return at once; when half of the plans so far did, the later ones are left to it untried.
 #include "bitmap_cells.h"
 #include "host_util.h"
 #include "plan_params.h"
@@ -112,7 +113,11 @@ __global__ void __launch_bounds__(1024) pt_shape(PlanParams prm, uint32_t t_end,
         if (tiles < least) continue;
         const uint32_t width = (t_end + tiles - 1) / tiles;
         tiles = (t_end + width - 1) / width;
-        acc[kAccTiles] = 1ull | (shape << 1) | (tiles << 8) | (row << 16) | ((uint64_t)width << 32);
+        // (rows and bitmaps are rounded up to odd lengths)
+        const uint32_t per_word = 2 * (batch + tiles), spare = offer.words[shape] - fixed - 2 * tiles * stride;
+        const uint32_t more = spare / per_word > 2 ? spare / per_word - 2 : 0u;
+        const uint32_t roomy = umin(umin(row + more, (2 * live + live / 2) / 32 + 4), 0xffffu);
+        acc[kAccTiles] = 1ull | (shape << 1) | (tiles << 8) | (umax(row, roomy) << 16) | ((uint64_t)width << 32);
         return;
     }
 }
@@ -165,6 +170,18 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
     const uint2* const index = reinterpret_cast<const uint2*>(prm.nbr) + lane;    // a chunk: 64 lanes x 4 entries
 
     for (uint32_t p = blockIdx.x; p < prm.P; p += gridDim.x) {
+        if (p >= gridDim.x) {                                         // (uniform)
+            // orders that leave many holes: what the first plans lost is not lost for all
+            if (threadIdx.x == 0) {
+                const uint64_t missed = __hip_atomic_load(&prm.acc[kAccTilesMissed], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh.top[0] = missed > 16 && 2 * missed > p - gridDim.x ? 1u : 0u;     // (of the plans that are no longer being placed)
+                if (sh.top[0]) prm.wide_plans[p] = 1;
+            }
+            __syncthreads();
+            const bool untried = uniform(sh.top[0]) != 0;
+            __syncthreads();
+            if (untried) continue;
+        }
         const uint32_t* order = prm.orders + (size_t)p * n;
         uint64_t* out = prm.offsets ? prm.offsets + (size_t)p * n : nullptr;
         // nothing placed; cell n pads the lists
@@ -359,7 +376,10 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
     }
 }
 
-// Workgroups per CU of the eight-wave shape for a trace of n requests.
+// The share of a CU's LDS that a workgroup of the eight-wave shape gets for a trace of n requests.  (Below kPtShort no
+// more than two ever run on a CU; the smaller share is what sets a number of tiles that suits short traces: with
+// half the LDS, and more tiles, 1500 requests took 545 us instead of 505, 2304 took 870 instead of 800.)
+constexpr uint32_t kPtShort = 3072;
 static uint32_t pt_workgroups(uint32_t n) { return n <= 2048 ? 4u : n <= 4096 ? 3u : 2u; }
 
 template <int kWaves>
@@ -396,7 +416,7 @@ static uint32_t pt_most_times(uint32_t n) { return 4 * n + 4096; }
 
 bool tiled_plan_possible(uint32_t n, uint32_t t_end, uint32_t P, const DeviceInfo& di)
 {
-    return n >= kPtFrom && n <= kBmMaxRequests && t_end <= pt_most_times(n) && (n >= 3072 || P <= 2 * (uint32_t)di.cus);
+    return n >= kPtFrom && n <= kBmMaxRequests && t_end <= pt_most_times(n) && (n >= kPtShort || P <= 2 * (uint32_t)di.cus);
 }
 
 size_t tiled_plan_words(uint32_t n) { return n >= kPtFrom && n <= kBmMaxRequests ? (size_t)pt_most_times(n) + 1 : 0; }
@@ -404,8 +424,8 @@ size_t tiled_plan_words(uint32_t n) { return n >= kPtFrom && n <= kBmMaxRequests
 bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream)
 {
     const uint32_t wgs = pt_workgroups(prm.n);
-    // (up to 3072 requests the eight-wave shape has room for as many tiles as can help; a launch less)
-    const bool large = prm.n > 3072;
+    // (shorter traces have few live granules as a rule, and go to plan_bitmap.hip if they do not; a launch less)
+    const bool large = prm.n >= kPtShort;
     PtOffer offer = {{pt_words<8>(di.lds_per_block / wgs), large ? pt_words<16>(di.lds_per_block) : 0u}};
     hipLaunchKernelGGL(pt_shape, dim3(1), dim3(1024), 0, stream, prm, t_end, net, offer);
     hipLaunchKernelGGL(pt_lists, dim3(prm.n), dim3(256), 0, stream, prm, t_end);
