@@ -34,11 +34,6 @@ constexpr int kLyTile = kSortTile;
 constexpr int kLyRegs = 16;                      // 64 layers per register: 1024 layers of a group in registers
 static_assert(kLyRegs == 16, "ly_build dispatches on one to sixteen registers in use");
 
-__global__ void ly_init(uint32_t* v, uint32_t n)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) v[i] = 0;
-}
-
 // One tile of 1024 requests per workgroup, sorted in LDS; slot e past the end holds a key behind
 // every real one, (~0, ~0 << 32 | e) (sizes are > 0, so no real key starts with ~0).
 __global__ void __launch_bounds__(kSortThreads)
@@ -56,29 +51,45 @@ ly_sort_tiles(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta
     for (uint32_t t = threadIdx.x; t < (uint32_t)kLyTile; t += kSortThreads) keys[blockIdx.x * kLyTile + t] = k[t];
 }
 
-// sorted[k] = request at sorted position k
+// sorted[k] = request at sorted position k; flag[k] = 1 where a group starts; no layers in any group yet.
 __global__ void __launch_bounds__(256)
-ly_ids(const ulonglong2* __restrict__ keys, uint32_t n, uint32_t* sorted, const uint32_t* status)
+ly_ids(const ulonglong2* __restrict__ keys, uint32_t n, uint32_t* sorted, uint32_t* flag, uint32_t* group_layers, const uint32_t* status)
 {
     if (*status != STALLOC_OK) return;
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
         const uint32_t i = (uint32_t)keys[k].y;
         sorted[k] = i < n ? i : 0u;                           // (the first n sorted keys are the real ones)
+        flag[k] = (k == 0 || keys[k].x != keys[k - 1].x) ? 1u : 0u;
+        group_layers[k] = 0;
     }
 }
 
-__global__ void __launch_bounds__(256)
-ly_flags(const uint64_t* __restrict__ size, const uint32_t* __restrict__ sorted, uint32_t n, uint32_t* flag,
-         const uint32_t* status)
-{
-    if (*status != STALLOC_OK) return;
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
-        flag[k] = (k == 0 || size[sorted[k]] != size[sorted[k - 1]]) ? 1u : 0u;
-}
-
-// Exclusive sums of m 32-bit values in three launches: sums of 1024-value chunks, their
-// exclusive sums (one workgroup), and the values' own.  total[0] receives the sum of all.
+// Exclusive sums of m 32-bit values; total[0] receives the sum of all.  Up to kScanSmall values in one launch of one
+// workgroup, four values a thread and step; beyond, in three: sums of 1024-value chunks, their exclusive
+// sums (one workgroup), and the values' own.
 constexpr int kScanChunk = 1024;
+constexpr uint32_t kScanSmall = 16384;
+
+__global__ void __launch_bounds__(1024)
+scan_small(const uint32_t* __restrict__ in, uint32_t m, uint32_t* out, uint32_t* total, const uint32_t* status)
+{
+    __shared__ uint32_t part[16];
+    if (*status != STALLOC_OK) return;
+    uint32_t carry = 0;
+    for (uint32_t k0 = 0; k0 < m; k0 += 4096) {
+        const uint32_t k = k0 + 4 * threadIdx.x;
+        uint32_t v[4], mine = 0;
+        for (int u = 0; u < 4; ++u) { v[u] = k + u < m ? in[k + u] : 0u; mine += v[u]; }
+        const uint32_t incl = wave_scan_add(mine);
+        __syncthreads();                                      // (the step before has read part[])
+        if (lane_id() == kWave - 1) part[wave_id()] = incl;
+        __syncthreads();
+        uint32_t before = carry + incl - mine;
+        for (int w = 0; w < 16; ++w) { if (w < wave_id()) before += part[w]; carry += part[w]; }
+        for (int u = 0; u < 4; ++u) { if (k + u < m) out[k + u] = before; before += v[u]; }
+    }
+    if (threadIdx.x == 0) total[0] = carry;
+}
 
 __global__ void __launch_bounds__(256)
 scan_chunk_sums(const uint32_t* __restrict__ in, uint32_t m, uint32_t* chunk_sum, const uint32_t* status)
@@ -620,6 +631,10 @@ void launch_scan(const uint32_t* in, uint32_t m, uint32_t* out, uint32_t* chunk_
                  const uint32_t* status, hipStream_t stream)
 {
     const uint32_t chunks = (m + kScanChunk - 1) / kScanChunk;
+    if (m <= kScanSmall) {
+        hipLaunchKernelGGL(scan_small, dim3(1), dim3(1024), 0, stream, in, m, out, total, status);
+        return;
+    }
     hipLaunchKernelGGL(scan_chunk_sums, dim3(chunks), dim3(256), 0, stream, in, m, chunk_sum, status);
     hipLaunchKernelGGL(scan_of_chunk_sums, dim3(1), dim3(256), 0, stream, chunk_sum, chunks, total, status);
     hipLaunchKernelGGL(scan_apply, dim3(chunks), dim3(256), 0, stream, in, m, chunk_sum, out, status);
@@ -668,8 +683,7 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(ly_sort_tiles, dim3(tiles), dim3(kSortThreads), 0, stream, tr->size, tr->t_alloc, n, keys, device_status);
     const ulonglong2* by_key = launch_merge_tiles(keys, spare, tiles * kLyTile, 1, device_status, stream);
-    hipLaunchKernelGGL(ly_ids, dim3(blocks), dim3(256), 0, stream, by_key, n, sorted, device_status);
-    hipLaunchKernelGGL(ly_flags, dim3(blocks), dim3(256), 0, stream, tr->size, sorted, n, flag, device_status);
+    hipLaunchKernelGGL(ly_ids, dim3(blocks), dim3(256), 0, stream, by_key, n, sorted, flag, group_layers, device_status);
     launch_scan(flag, n, flags_before, chunk_sum, n_groups, device_status, stream);
     hipLaunchKernelGGL(ly_group_starts, dim3(blocks), dim3(256), 0, stream, flag, flags_before, n, group_start,
                        device_status);
@@ -678,9 +692,6 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
     b.ta = tr->t_alloc; b.tf = tr->t_free; b.sorted = sorted; b.group_start = group_start; b.n_groups = n_groups;
     b.local = local; b.first_ts = first_ts; b.ends = ends; b.group_layers = group_layers; b.status = device_status;
     b.n = n;
-    // Only the device knows how many groups there are: the layer counts of all n slots are summed,
-    // the slots past the last group hold none.
-    hipLaunchKernelGGL(ly_init, dim3(blocks), dim3(256), 0, stream, group_layers, n);
     // (With fewer timestamps than requests the clock is coarse: a large group has tied releases and ly_match would
     // give up on it, for about 10 us a call.)
     if (n >= kLyMatchFrom && tr->t_end >= n) {
@@ -700,6 +711,7 @@ extern "C" int stalloc_memory_layers(const stalloc_trace* tr, uint32_t* layer_of
     uint32_t build_blocks = (n + 3) / 4;                  // at most n groups, four waves to a workgroup
     if (build_blocks > (uint32_t)di.cus * 8) build_blocks = (uint32_t)di.cus * 8;
     hipLaunchKernelGGL(ly_build, dim3(build_blocks), dim3(256), 0, stream, b);
+    // (only the device knows how many groups there are: the slots past the last group hold no layers)
     launch_scan(group_layers, n, group_base, chunk_sum, n_layers, device_status, stream);
 
     LyEmit e;
