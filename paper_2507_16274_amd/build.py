@@ -21,11 +21,12 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build(verbose: bool = False) -> str:
+def build(verbose: bool = False, lib: str = LIB, extra=(), only=None) -> str:
+    """Compiles the library, or (tests) one of the sources `only` with the definitions `extra`."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB + f".tmp{os.getpid()}"
-    extra = os.environ.get("STALLOC_DEFINES", "").split()      # e.g. "-DSTALLOC_THREADS_LDS=512"
-    cmd = [hipcc] + HIPCC_FLAGS + extra + sources() + ["-o", tmp]
+    tmp = lib + f".tmp{os.getpid()}"
+    extra = list(extra) + os.environ.get("STALLOC_DEFINES", "").split()      # e.g. "-DSTALLOC_THREADS_LDS=512"
+    cmd = [hipcc] + HIPCC_FLAGS + extra + [s for s in sources() if only is None or os.path.basename(s) in only] + ["-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -35,8 +36,15 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(f"hipcc failed:\n{out}")
     if verbose and out.strip():
         print(out)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, lib)
+    return lib
+
+
+def build_full_buckets(verbose: bool = False) -> str:
+    """For tests: stalloc_make_orders with buckets meant for nearly as many numbers as they have room for, so that
+    the way around a full bucket (13 standard deviations off in the library proper) is taken all the time."""
+    return build(verbose, os.path.join(os.path.dirname(HERE), "tests", "libfullbuckets.so"), ["-DSTALLOC_OR_BUCKET_MEAN=2040"],
+                 ("orders.hip", "layers.hip", "trace_check.hip"))
 
 
 if __name__ == "__main__":

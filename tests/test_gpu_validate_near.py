@@ -51,12 +51,15 @@ def test_near_pairs_report_a_range_that_would_wrap(oracle):
     n = 20011
     size, ts, te, t_end = _trace(rng, n, "mixed")
     plan = rng.integers(0, 1 << 40, (1, n)).astype(np.int64)
-    for bad in (0, n // 2, n - 1):
-        bent = plan.copy()
-        bent[0, bad] = -1                                     # 2^64 - 1: any size wraps
-        dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), bent)]
-        out = S.stalloc_validate(*dev[:3], t_end, dev[3])
-        assert int(out["status"].item()) == (3 if size[bad] > 1 else int(out["status"].item()))
+    size[n // 2] = 1
+    for P in (4, 1):                                          # (n * n * P on either side of NEAR_FROM)
+        for bad, start, status in ((0, -1, 3), (n // 2, -1, 3), (n - 1, -1, 3),       # 2^64 - 1: any size wraps, 1 as well
+                                   (n // 2, -2, 0), (7, -1 - int(size[7]), 0)):       # ... and these end at 2^64 - 1
+            bent = np.repeat(plan, P, axis=0)
+            bent[P - 1, bad] = start
+            dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), bent)]
+            out = S.stalloc_validate(*dev[:3], t_end, dev[3])
+            assert int(out["status"].item()) == status, (P, bad, start)
 
 
 def _all_pairs(S, dev, t_end, plans):
