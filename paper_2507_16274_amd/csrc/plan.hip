@@ -734,7 +734,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     // occupancy-bitmap variant: lifetime-conflict index of the trace
     uint32_t pool_words[kBitmapShapes];
     const bool bitmap = bitmap_plan_shapes(n, di, pool_words) && allow_bitmap;
-    uint32_t* nbr_begin = bitmap ? cv.take<uint32_t>((size_t)n + 2) : nullptr;
+    uint32_t* nbr_chunks = bitmap ? cv.take<uint32_t>(n) : nullptr;
     uint16_t* nbr = bitmap ? cv.take<uint16_t>(bitmap_index_entries(n)) : nullptr;
     const bool tiled = bitmap && tiled_plan_possible(n, tr->t_end, P, di);
     int32_t* net = bitmap ? cv.take<int32_t>(tiled_plan_words(n)) : nullptr;
@@ -755,7 +755,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     prm.offsets = offsets ? offsets : own_offsets;
     prm.peaks = peaks; prm.status = device_status; prm.acc = acc; prm.slabs = slabs; prm.n = n; prm.P = P;
     prm.compact_enqueued = compact ? 1u : 0u;
-    prm.nbr_begin = nbr_begin; prm.nbr = nbr; prm.wide_plans = wide_plans;
+    prm.nbr_chunks = nbr_chunks; prm.nbr = nbr; prm.wide_plans = wide_plans;
     for (int shape = 0; shape < kBitmapShapes; ++shape) prm.bitmap_pool_words[shape] = bitmap ? pool_words[shape] : 0u;
     bool ok = true;
     if (split) ok = ok && launch_plan_split(prm, tr->t_end, sw, di, stream);

@@ -64,11 +64,10 @@ struct BitmapLds {
 // (smaller batches) beyond that; the rule that admits a trace makes sure it always holds one.
 
 // ---------------------------------------------------------------------------------------------
-// Lifetime-conflict index.  begin[i] .. begin[i + 1] are the 256-entry chunks of request i's row;
-// an entry is j for a request j != i with t_alloc_j < t_free_i and t_alloc_i < t_free_j, or n (a
-// dummy that is never placed) -- stored as 4 * j, the byte offset into the plan's table, while
-// 4 * n fits 16 bits (the build phase then needs one instruction less per lookup).  begin[] first
-// holds the degrees, then their exclusive prefix sum in chunks.
+// Lifetime-conflict index.  Row i holds nbr_chunks[i] chunks of 256 entries; an entry is j for a request
+// j != i with t_alloc_j < t_free_i and t_alloc_i < t_free_j, or n (a dummy that is never placed) -- stored as
+// 4 * j, the byte offset into the plan's table, while 4 * n fits 16 bits (the build phase then needs one
+// instruction less per lookup).
 __device__ __forceinline__ bool plans_wanted(const PlanParams& prm)
 {
     return bitmap_shape(prm.acc[kAccMode], prm.acc[kAccGranules], prm.bitmap_pool_words) >= 0 &&
@@ -76,55 +75,17 @@ __device__ __forceinline__ bool plans_wanted(const PlanParams& prm)
 }
 __device__ __forceinline__ bool index_wanted(const PlanParams& prm) { return *prm.status == STALLOC_OK && plans_wanted(prm); }
 
-__global__ void __launch_bounds__(256) nbr_count(PlanParams prm)
-{
-    __shared__ uint32_t total;
-    if (!index_wanted(prm)) return;
-    const uint32_t i = blockIdx.x, n = prm.n;
-    if (threadIdx.x == 0) total = 0;
-    __syncthreads();
-    const uint32_t ta = prm.ta[i], tf = prm.tf[i];
-    uint32_t c = 0;
-    for (uint32_t j = threadIdx.x; j < n; j += 256) c += (j != i && prm.ta[j] < tf && ta < prm.tf[j]);
-    c = wave_sum32(c);
-    if (lane_id() == 0) atomicAdd(&total, c);
-    __syncthreads();
-    if (threadIdx.x == 0) prm.nbr_begin[i] = total;
-}
-
-__global__ void __launch_bounds__(1024) nbr_scan(PlanParams prm)
-{
-    __shared__ uint32_t part[1024];
-    if (!index_wanted(prm)) return;
-    const uint32_t n = prm.n;
-    const uint32_t per = (n + 1023) / 1024;
-    const uint32_t lo = threadIdx.x * per, hi = lo + per < n ? lo + per : n;
-    uint32_t sum = 0;
-    for (uint32_t i = lo; i < hi; ++i) sum += (prm.nbr_begin[i] + kRowPad - 1) / kRowPad;
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (uint32_t d = 1; d < 1024; d <<= 1) {            // inclusive scan of the per-thread sums
-        const uint32_t add = threadIdx.x >= d ? part[threadIdx.x - d] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    uint32_t run = part[threadIdx.x] - sum;
-    for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t chunks = (prm.nbr_begin[i] + kRowPad - 1) / kRowPad;
-        prm.nbr_begin[i] = run;
-        run += chunks;
-    }
-    if (threadIdx.x == 1023) prm.nbr_begin[n] = part[1023];
-}
+// (Rows have the room of the longest one possible, so that nobody has to count them first: two launches less.)
+__host__ __device__ inline uint32_t row_chunks(uint32_t n) { return (n - 1 + kRowPad - 1) / kRowPad; }
 
 __global__ void __launch_bounds__(256) nbr_fill(PlanParams prm)
 {
     __shared__ RowLds sh;
     if (!index_wanted(prm)) return;
-    const uint32_t i = blockIdx.x, ta = prm.ta[i], tf = prm.tf[i];
-    fill_row(prm.nbr + (size_t)prm.nbr_begin[i] * kRowPad, (prm.nbr_begin[i + 1] - prm.nbr_begin[i]) * kRowPad, prm.n, sh,
-             [&](uint32_t j) { return j != i && prm.ta[j] < tf && ta < prm.tf[j]; });
+    const uint32_t i = blockIdx.x, ta = prm.ta[i], tf = prm.tf[i], room = row_chunks(prm.n) * kRowPad;
+    const uint32_t entries = fill_row(prm.nbr + (size_t)i * room, room, prm.n, sh,
+                                      [&](uint32_t j) { return j != i && prm.ta[j] < tf && ta < prm.tf[j]; });
+    if (threadIdx.x == 0) prm.nbr_chunks[i] = (entries + kRowPad - 1) / kRowPad;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -186,9 +147,8 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 8 : 4) plan_bitm
                 sh.rq_s[threadIdx.x] = (uint32_t)(prm.size[i] >> shift);
                 sh.rq_ta[threadIdx.x] = prm.ta[i];
                 sh.rq_tf[threadIdx.x] = prm.tf[i];
-                const uint32_t c0 = prm.nbr_begin[i];
-                sh.rq_row[threadIdx.x] = c0;
-                sh.rq_chunks[threadIdx.x] = prm.nbr_begin[i + 1] - c0;
+                sh.rq_row[threadIdx.x] = i * row_chunks(n);
+                sh.rq_chunks[threadIdx.x] = prm.nbr_chunks[i];
             }
             __syncthreads();
 
@@ -403,7 +363,7 @@ bool bitmap_plan_shapes(uint32_t n, const DeviceInfo& di, uint32_t (&pool_words)
 
 size_t bitmap_index_entries(uint32_t n)
 {
-    return (size_t)n * (((size_t)n - 1 + kRowPad - 1) / kRowPad * kRowPad);
+    return (size_t)n * row_chunks(n) * kRowPad;
 }
 
 template <int kWaves>
@@ -428,8 +388,6 @@ static bool launch_shape(const PlanParams& prm, uint32_t wgs_per_cu, uint32_t po
 // Enqueues the index build and every shape of the placement kernel that prm.bitmap_pool_words names.
 bool launch_plan_bitmap(const PlanParams& prm, const DeviceInfo& di, hipStream_t stream)
 {
-    hipLaunchKernelGGL(nbr_count, dim3(prm.n), dim3(256), 0, stream, prm);
-    hipLaunchKernelGGL(nbr_scan, dim3(1), dim3(1024), 0, stream, prm);
     hipLaunchKernelGGL(nbr_fill, dim3(prm.n), dim3(256), 0, stream, prm);
     bool ok = true;
     if (prm.bitmap_pool_words[0]) {

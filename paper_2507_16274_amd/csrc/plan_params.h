@@ -18,7 +18,7 @@ struct PlanParams {
     unsigned char* slabs;    // list in the workspace: gridDim.x slabs of 2 * n entries
     uint32_t* wide_plans;    // [P] 1 = the plan outgrew 32-bit granule counts (list variant) or the tables (tiled bitmap
                              // variant) of the kernel that tried it; another one places it
-    uint32_t* nbr_begin;     // bitmap variant: [n + 2] row starts of the lifetime-conflict index
+    uint32_t* nbr_chunks;    // bitmap variants: [n] chunks of 256 entries in a row of the index or list of a request
     uint16_t* nbr;           // bitmap variant: indices of the requests with an overlapping lifetime, row by row
     uint32_t n;
     uint32_t P;

@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(256) pt_lists(PlanParams prm, uint32_t t_end)
         const uint32_t aj = prm.ta[j], fj = prm.tf[j];
         return j != i && aj < tf && ta < fj && !(aj <= a0 && fj >= a1) && !(aj <= b0 && fj >= b1) && !(b > a + 1 && aj < b0 && fj > a1);
     });
-    if (threadIdx.x == 0) prm.nbr_begin[i] = (entries + kRowPad - 1) / kRowPad;       // chunks; the row begins at i * room
+    if (threadIdx.x == 0) prm.nbr_chunks[i] = (entries + kRowPad - 1) / kRowPad;       // chunks; the row begins at i * room
 }
 
 template <int kWaves, bool kScaledEntries>
@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
                 sh.rq_s[threadIdx.x] = (uint32_t)(prm.size[i] >> shift);
                 sh.rq_ta[threadIdx.x] = ta;
                 sh.rq_tf[threadIdx.x] = tf;
-                sh.rq_chunks[threadIdx.x] = prm.nbr_begin[i];
+                sh.rq_chunks[threadIdx.x] = prm.nbr_chunks[i];
                 sh.rq_tiles[threadIdx.x] = a | (b << 8) | (from << 16) | (to << 24);
             }
             __syncthreads();
