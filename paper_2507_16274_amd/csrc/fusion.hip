@@ -77,12 +77,13 @@ __device__ __forceinline__ void mul_64_32(uint64_t a, uint32_t b, uint64_t& hi, 
 
 constexpr uint32_t kPlaced = 0xffffffffu;        // in wake[]: the request has an address
 constexpr int kNear = 8;                         // blocks that all requests of a chunk are held against together
-// A chunk's requests are looked at one by one, each against its whole range, or all at once against the first blocks.  One
-// by one they sleep as long as they can, and the first that fits ends the search, which pays where ranges go on (an
-// interleaved schedule); at once is what pays when lifetimes are so mixed that many are awake and few fit.  So
-// the first is a probe: as long as looks put requests to sleep beyond what all at once would have seen, up to kAlone of
-// them follow, and when kProbes in a row did not, only every eighth chunk begins with one.
-constexpr int kAlone = 4, kProbes = 64;
+// The first kAlone of a chunk's requests that need a look get one each, against their whole range, the rest are held
+// against the first blocks together.  One by one they sleep as long as they can, and the first that fits ends the
+// search, which pays where ranges go on (an interleaved schedule: 0.30 ms, 0.49 without); together is what pays
+// when lifetimes are so mixed that many are awake and few fit (200 pairs of 600 + 600, the smaller group earlier: 2.84
+// ms with four looks always, 2.00 now).  So when the last kProbes chunks put nobody to sleep beyond what
+// holding them together shows, only every eighth chunk still has its single looks.
+constexpr int kAlone = 4, kProbes = 16;
 constexpr uint32_t kDone = 0, kHelp = 1;
 
 // Sorts keys[0..m) in LDS, ascending; called by the whole workgroup.  A bitonic network whose merges
@@ -227,7 +228,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
     auto lowest_wake = [&](uint32_t w) -> uint32_t { return ~read_lane(wave_scan_max(~w), kWave - 1); };
     // The 64 requests of a chunk as the lanes of a wave hold them, tried at the pointer in turn: `fit` is the
     // first that fits (-1: none), those that were found not to are put to sleep.
-    struct Chunk { uint64_t size; uint32_t wake; bool open; uint64_t awake, for_good; int fit, near_looks; bool far_look; };
+    struct Chunk { uint64_t size; uint32_t wake; bool open; uint64_t awake, for_good; int fit; };
     auto try_chunk = [&](uint32_t c, uint64_t addr, uint32_t holder, int alone) -> Chunk {
         const uint32_t k = c * kWave + lane;
         Chunk ch;
@@ -238,16 +239,12 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
         ch.awake = lanes_ge(holder, ch.wake);
         ch.for_good = ch.awake & lanes_ge(holder, clear);             // conflict with nothing any more
         ch.fit = -1;
-        ch.near_looks = 0;
-        ch.far_look = false;
         uint64_t fits = ch.for_good;
         int looks = 0;
-        bool together = false;
         for (uint64_t left = ch.awake; left; left &= left - 1) {
             const int f = __builtin_ctzll(left);
             if (((fits >> f) & 1) == 0) {
-                if (!together && looks == alone) {
-                    together = true;
+                if (looks++ == alone) {
                     // many need a look: all of them at once, at the first blocks from the pointer's on that [addr, addr + size)
                     // meets; those below clear are all released after the request's allocation
                     const uint64_t end = addr + ch.size;
@@ -280,13 +277,6 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
                         if (hit) past = q0 + kWave - (uint32_t)__builtin_clzll(hit);
                         if (__builtin_amdgcn_ballot_w64(meets) != ~0ull) break;       // (uniform)
                     }
-                    ++looks;
-                    if (past > holder + kNear) {
-                        ch.far_look = true;
-                        if (alone != 0 && alone < kAlone) ++alone;
-                    } else {
-                        ++ch.near_looks;
-                    }
                     if (past != 0) {
                         if (lane == f) ch.wake = past;
                         continue;
@@ -306,7 +296,7 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
     uint64_t addr = 0;                                                // lowest start address of the larger plan
     uint32_t holder = 0;                                              // block of the larger plan that holds addr (nl: behind its end)
     uint32_t left = ns;
-    int near_looks = 0, chunks_tried = 0;
+    int near_chunks = 0;                                              // tried since one that put a request to sleep for long
     for (;;) {
         if (wave_id() == 0) {
             // lowest wake of chunk `lane` and of chunk 64 + `lane`
@@ -328,8 +318,9 @@ __global__ void __launch_bounds__(kFuThreads) fuse_pairs(FuseParams prm)
                     const uint32_t c = awake0 ? (uint32_t)__builtin_ctzll(awake0) : kWave + (uint32_t)__builtin_ctzll(awake1);
                     if (awake0) awake0 &= awake0 - 1; else awake1 &= awake1 - 1;
                     const uint32_t k = c * kWave + lane;
-                    Chunk ch = try_chunk(c, addr, holder, near_looks < kProbes || (++chunks_tried & 7) == 0 ? 1 : 0);
-                    near_looks = ch.far_look ? 0 : near_looks + ch.near_looks;
+                    Chunk ch = try_chunk(c, addr, holder, near_chunks < kProbes || (near_chunks & 7) == 0 ? kAlone : 0);
+                    const bool far = (ch.awake & lanes_ge(ch.wake, holder + kNear + 1)) != 0;        // (uniform) put to sleep for long
+                    near_chunks = far ? 0 : near_chunks + 1;
                     if (ch.fit >= 0) {
                         uint64_t placed = 1ull << ch.fit;
                         uint64_t to = addr;
