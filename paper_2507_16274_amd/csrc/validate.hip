@@ -153,7 +153,7 @@ static VnBuckets vn_buckets(uint32_t n, uint32_t t_end)
     VnBuckets b = {0, t_end, 0, 0};
     while (b.base < 31 && ((uint64_t)n << b.base) < (uint64_t)t_end * kVnTile) ++b.base;
     for (uint32_t k = 0; k <= 32 - b.base; ++k) b.count += b.in_class(k);
-    while (b.apart < 5 && b.count << b.apart < 16384) ++b.apart;
+    while (b.apart < 5 && b.count << b.apart < 4096) ++b.apart;
     return b;
 }
 
