@@ -43,7 +43,7 @@ OPS_PER_CANDIDATE = 8       # 2 lifetime compares, and, select, running max, add
 LDS_PEAK_GBS = 256 * 128 * 2.4          # 256 CUs x 128 B/clk x 2.4 GHz = 78 643 GB/s
 HBM_PEAK_GBS = 8000.0
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12  # 256 CUs x 64 integer lanes x 2.4 GHz = 39.3 T lane-ops/s
-KERNEL_NAMES = {"bitmap": "plan_bitmap_kernel", "list_lds": "plan_kernel", "list_memory": "plan_kernel",
+KERNEL_NAMES = {"bitmap": "plan_tiled_kernel or plan_bitmap_kernel", "list_lds": "plan_kernel", "list_memory": "plan_kernel",
                 "long_list": "plan_split_kernel"}
 
 # HBM-side bytes per launch of the placement kernel, from two rocprofv3 --pmc runs of this script
@@ -51,12 +51,12 @@ KERNEL_NAMES = {"bitmap": "plan_bitmap_kernel", "list_lds": "plan_kernel", "list
 # known size in the same run; the summaries are under profiles/).  Keyed by (configuration, orders);
 # each entry names the sources of stalloc_plan it was measured with (source_digest() below): with any
 # other sources the figure is not reported.
-MEASURED_TRAFFIC = {(5, 4096): {"bytes": (269_114_935 * 2 + 102_024_208) * 1024, "sources": "dcab51237f78c6bb"}}
+MEASURED_TRAFFIC = {(5, 4096): {"bytes": (269_489_968 * 2 + 102_027_442) * 1024, "sources": "95bdf35dd8b96382"}}
 
 
 # The sources stalloc_plan and its kernels are built from (the other entry points have files of their own).
-PLAN_SOURCES = ("plan.hip", "plan_split.hip", "plan_bitmap.hip", "plan_list.h", "plan_params.h", "host_util.h", "wave.h",
-                "sort_keys.h", "trace_check.hip", "orders.hip", "layers.hip")
+PLAN_SOURCES = ("plan.hip", "plan_split.hip", "plan_bitmap.hip", "plan_tiled.hip", "bitmap_cells.h", "plan_list.h", "plan_params.h",
+                "host_util.h", "wave.h", "sort_keys.h", "trace_check.hip", "orders.hip", "layers.hip")
 
 
 def source_digest() -> str:
