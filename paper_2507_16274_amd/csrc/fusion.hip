@@ -25,7 +25,7 @@
 //              block of the range it was tried at: as long as it has not, a higher start still reaches it.
 // The lowest wake of every 64 requests sits in a register, so a step looks at the first requests that
 // are awake only, and when none is the pointer goes straight to the block that wakes the next one.
-//   330 pairs of up to 3262 requests: 11.3 -> 0.39 ms.  The longest chain sets the time.
+//   330 pairs of up to 3262 requests: 11.3 -> 0.30 ms.  The longest chain sets the time.
 //   A step at which more than four chunks are awake is shared by all waves (two barriers).
 #include "host_util.h"
 #include "wave.h"
@@ -33,7 +33,7 @@
 namespace stalloc {
 
 // A pair has a workgroup of 512, so that many waves can help at once where a step has many requests to look at; small
-// pairs one of 128, of which a CU holds more (5000 pairs of 16 requests: 119 -> 47 us; a workgroup of 512 is mostly idle).
+// pairs one of 128, of which a CU holds more (5000 pairs of 16 requests: 119 -> 49 us; a workgroup of 512 is mostly idle).
 constexpr uint32_t kFuSmall = 256;               // requests of a pair
 
 struct FuseParams {

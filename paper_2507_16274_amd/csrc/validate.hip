@@ -123,8 +123,8 @@ val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
 // the second kind, and nothing else is looked at.  Which request of a bucket comes first does not
 // matter: the results are a sum and a minimum over the request numbers.
 //   Bound by the integer rate on many plans (6144 requests x 1024 plans: 1.16 ms, all pairs 4.76 ms) and by
-// the chain load -> address gather -> LDS of a wave's tiles on one (199 748 requests: 0.25 ms, of which 0.19
-// ms val_near, all pairs 4.73 ms; an integer floor of 0.07 ms for its 3.5e8 pairs).
+// the chain load -> address gather -> LDS of a wave's tiles on one (199 748 requests: 0.23 ms, of which 0.19
+// ms val_one_plan, all pairs 4.73 ms; an integer floor of 0.07 ms for its 3.5e8 pairs).
 constexpr uint32_t kVnTile = 64;
 constexpr uint32_t kVnWaves = 4;
 constexpr uint32_t kVnRow = kVnTile + 4;         // (the walk over a tile's requests takes four at a time)
@@ -164,7 +164,7 @@ static VnBuckets vn_buckets(uint32_t n, uint32_t t_end)
 static uint32_t vn_chunk(uint32_t tiles) { return tiles <= 1024 ? 4u : 16u; }
 
 struct VnSorted {
-    uint32_t* bucket;        // [buckets.count] requests per bucket, then where the next one of the bucket goes
+    uint32_t* bucket;        // [buckets.words()] requests per bucket, then where the next one of the bucket goes
     uint2* life;             // [n] in bucket order: lifetime,
     uint64_t* size;          //     size
     uint32_t* id;            //     and number of the request
