@@ -6,38 +6,35 @@
 // range at once.  Extent of a plan = max(a + s) (Eq. 2).
 //
 // Per plan the workgroup keeps the list of placed blocks SORTED BY ADDRESS, so that no
-// sorting is needed when a request is placed.  Requests are handled in batches of K:
+// sorting is needed when a request is placed.  Requests are handled in batches of 64:
 //
 //   scan     One pass over the sorted list serves the whole batch, because the list only
 //            changes between batches.  Each wave owns a run of consecutive entries (its
-//            chunk); every entry is loaded once and tested against the K requests: two
-//            compares keep the blocks whose lifetime conflicts with request r, the running
-//            maximum of their end addresses is "covered so far", and a conflicting block that
+//            chunk), a lane holds a request, and every block of the chunk is taken by all 64 lanes
+//            at once: two compares tell whose lifetime it conflicts with, the running maximum of
+//            the conflicting blocks' end addresses is "covered so far", and a conflicting block that
 //            starts at least size_r above it closes a hole [covered, start) in which r could
 //            fit.  Per (wave, request) the wave publishes its chunk maximum and its first
-//            few holes (with chunk-local "covered") to LDS.  Two forms: with the list in LDS
-//            (K = 16) a lane holds a listed block and the running maximum is a wave64 DPP
-//            scan per request; with the list in the workspace (K = 64) a lane holds a
-//            request and the blocks are taken one by one as wave-uniform values, which needs
-//            no cross-lane step at all.
-//   survey   After a barrier, wave r gathers what all waves published for request r into its
+//            few holes (with chunk-local "covered") to LDS.
+//   survey   After a barrier, request r's wave gathers what all waves published for it into its
 //            64 lanes in address order; the true "covered" of a hole is the maximum of its
-//            local value and the chunk maxima of the waves below.  It lists the first holes
-//            that are large enough as such.
-//   resolve  After another barrier, wave 0 settles the K requests in order.  The blocks
-//            settled earlier in the batch (the side buffer, sorted, one per lane) are honoured
-//            through f(c) = lowest address >= c that clears the side-buffer blocks conflicting
-//            with r: r takes the first surveyed hole with f(covered) + size_r <= hole end, else
-//            goes on top at f(maximum).  If the surveyed holes run out while more were
-//            published, all published holes are looked at with f evaluated over "zones" --
-//            maximal groups of conflicting side-buffer blocks whose holes are too small for r.
-//            If a wave had more holes than it could publish and none of the earlier ones
-//            fits, wave 0 walks that wave's chunk again for this one request, with
-//            everything below the chunk known, and takes the chunk's first hole that fits.
+//            local value and the chunk maxima of the waves below.  The first hole that is large
+//            enough is where r lies if the rest of the batch leaves it there, else the top.  If a
+//            wave had more holes than it could publish and no lower one fits, that wave's chunk
+//            is walked again for this one request, with everything below the chunk known.
+//   settle   A request clashes when an earlier one of the batch that is alive at the same time lies
+//            where it would.  All waves look for clashes; wave 0 then goes through those requests in
+//            order (all others stay where they are): each takes the first of its holes in which it
+//            still fits when it moves up past the blocks in its way, else goes on top.
 //   merge    The settled blocks are merged into the sorted list in one pass: listed block k
 //            moves up by the number of new blocks at or below its start address and the new
 //            blocks drop into the gaps (in place through registers when the list is in LDS,
 //            ping-pong between two slabs when it is in the workspace).
+//
+// What bounds it: the scan reads every block as an LDS broadcast (16 bytes, eight cycles of the CU's LDS) and spends six
+// vector instructions on it, per 64 requests; then the chain of clashing requests in wave 0.  6144 requests of 5
+// sizes, 512 orders (list in LDS): 17.9 -> 11.3 ms against batches of 16 with a lane per block, a running maximum across lanes
+// per request, and wave 0 settling every request; 49 920 requests, 256 orders (list in the workspace): 228 -> 175 ms.
 //
 // Addresses are multiples of the largest power of two dividing all sizes.  When the sum of
 // sizes, in those granules, stays below 2^31 the list holds 32-bit granule counts (16-byte
@@ -58,190 +55,56 @@
 namespace stalloc {
 
 constexpr int kBatch = 256;          // requests fetched per refill
+constexpr uint32_t kReadAhead = 12;   // blocks behind the list's last one that may be read (and are not used)
 
-template <typename Addr, int kPend, int kThreads>
+template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
 struct PlanLds {
     static constexpr int kWaves = kThreads / kWave;
 #ifdef STALLOC_HOLE_SLOTS
     static constexpr int kSlots = STALLOC_HOLE_SLOTS;      // (test builds shrink this to exercise the second walk of a chunk)
 #else
-    // holes a wave can publish per request; three when 64 requests with 64-bit addresses share
-    // a pass, so that two workgroups still fit the LDS of a CU
-    static constexpr int kSlots = (sizeof(Addr) == 8 && kPend > 32 && kWaves == 16) ? 3 : kWave / kWaves;
+    // holes a wave can publish per request, besides the one in front of its chunk's first conflicting block
+    static constexpr int kSlots = sizeof(Addr) == 8 ? 2 : 3;
 #endif
+    static constexpr int kCols = kSlots + 1;
+    static_assert(kWaves * kCols <= kWave, "all holes of a request lie side by side in the lanes of a wave");
+    // The scan takes blocks as broadcasts from LDS: from the list itself, or from here (listed in the workspace, or packed)
+    static constexpr int kStaged = kLds && !kCompact ? 1 : sizeof(Addr) == 8 || kCompact ? kWave / 2 : kWave;
+    typename BlockList<Addr, false>::Entry staged[kWaves][kStaged];
     uint64_t rq_size[kBatch];
     uint64_t rq_addr[kBatch];
     uint32_t rq_ta[kBatch];
     uint32_t rq_tf[kBatch];
     uint32_t rq_id[kBatch];
+    Addr first[kWaves][kPend];                             // start of the chunk's first conflicting block, if that may close a hole
     Addr top[kWaves][kPend];                               // chunk maximum per (wave, request)
-    uint32_t holes[kWaves][kPend];                         // holes found per (wave, request), may exceed kSlots
+    uint8_t holes[kWaves][kPend];                          // holes found per (wave, request), may exceed kSlots
     Span<Addr> hole[kWaves][kPend][kSlots];                // {hole end, chunk-local covered}
-    Span<Addr> surveyed[kPend][4];                         // survey: first holes large enough as such {end, covered}
-    uint32_t listed[kPend];                                // survey: how many, bit 8 = more to look at behind them
-    Addr top_of[kPend];                                    // survey: maximum over all chunks
+    uint64_t usable[kPend];                                // holes that are large enough as such (lane = wave * kSlots + slot)
+    uint64_t crowded[kPend];                               // lanes of waves that found more holes than they could publish
+    Addr top_of[kPend];                                    // maximum over all chunks
+    Addr at[kPend];                                        // where the requests of the batch are to lie, as far as known
+    uint64_t clashes;                                      // requests that may not stay where they would lie without the rest of the batch
     Span<Addr> pend_span[kPend];                           // blocks settled in this batch, sorted
     uint2 pend_life[kPend];
-    uint32_t settled;
+    uint32_t word;
     Addr extent_now;                                       // extent of the plan after the last settled batch
 };
 
-// Zones of the side buffer for one request: groups of lifetime-conflicting pending blocks.
-// A zone starts at a conflicting block that leaves a hole of at least `s` above everything
-// conflicting before it; it ends at the running maximum of end addresses.
-template <typename Addr>
-struct Zones {
-    uint64_t starts;     // lanes that open a zone
-    Addr lo;             // per lane: start address of the pending block
-    Addr reach_before;   // per lane: max end of conflicting pending blocks in lower lanes
-    Addr reach_all;      // uniform: max end of all conflicting pending blocks
-};
-
-template <typename Addr>
-__device__ __forceinline__ Zones<Addr> make_zones(const Pending<Addr>& pd, uint32_t pending, Addr s,
-                                                  uint32_t ta, uint32_t tf)
+// One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request, and the
+// blocks of the wave's chunk are taken one at a time, in address order, by all lanes at once: two lifetime compares, an
+// add, a compare, a maximum and a selection per block and 64 requests, and nothing that crosses lanes.  The block comes
+// as a broadcast from LDS (taken out of a register of a lane it costs four more vector instructions: 283 instead of 209
+// million cycles a plan for 49 920 requests with the list in the workspace).  Blocks are looked at four
+// together, so that their compares overlap and one branch asks whether any of them closes a hole.  Published per
+// (wave, request): the chunk maximum of conflicting end addresses, the start of the first conflicting block, and
+// the first holes behind it with chunk-local "covered".
+template <typename Addr, int kPend, int kThreads, bool kDirect, typename List, typename Lds>
+__device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
 {
-    const int lane = lane_id();
-    const bool conflict = lane < (int)pending && pd.ta < tf && ta < pd.tf;
-    const Addr incl = wave_scan_max(conflict ? pd.hi : (Addr)0);
-    Zones<Addr> z;
-    z.lo = pd.lo;
-    z.reach_before = wave_shift_up(incl, (Addr)0);
-    z.reach_all = read_lane(incl, kWave - 1);
-    const uint64_t conflicts = __builtin_amdgcn_ballot_w64(conflict);
-    const uint64_t lower = conflicts & ((1ull << lane) - 1);
-    z.starts = __builtin_amdgcn_ballot_w64(conflict && (lower == 0 || pd.lo >= z.reach_before + s));
-    return z;
-}
-
-// f(e): lowest address >= e at which [e, e + s) clears every zone.
-template <typename Addr>
-__device__ __forceinline__ Addr clear_zones(Addr e, Addr s, const Zones<Addr>& z)
-{
-    uint64_t m = z.starts;
-    if (m == 0) return e;
-    const Addr es = e + s;
-    while (m) {
-        const int q = __builtin_ctzll(m);
-        m &= m - 1;
-        const Addr zone_lo = read_lane(z.lo, q);
-        const Addr zone_hi = m ? read_lane(z.reach_before, __builtin_ctzll(m)) : z.reach_all;
-        if (es > zone_lo && e < zone_hi) e = zone_hi;
-    }
-    return e;
-}
-
-// Sorted insertion of the block [x, x + s) into the register-held side buffer.
-template <typename Addr>
-__device__ __forceinline__ void pending_insert(Pending<Addr>& pd, uint32_t pending, Addr x, Addr s, uint32_t ta,
-                                               uint32_t tf)
-{
-    const int lane = lane_id();
-    const uint64_t keep = __builtin_amdgcn_ballot_w64(lane < (int)pending && pd.lo <= x);
-    const int pos = __builtin_popcountll(keep);
-    const Addr up_lo = wave_shift_up(pd.lo, (Addr)0), up_hi = wave_shift_up(pd.hi, (Addr)0);
-    const uint32_t up_ta = wave_shift_up(pd.ta, 0u), up_tf = wave_shift_up(pd.tf, 0u);
-    if (lane > pos) { pd.lo = up_lo; pd.hi = up_hi; pd.ta = up_ta; pd.tf = up_tf; }
-    if (lane == pos) { pd.lo = x; pd.hi = x + s; pd.ta = ta; pd.tf = tf; }
-}
-
-// One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch: publishes,
-// per (wave, request), the chunk maximum of conflicting end addresses and the first holes.
-template <typename Addr, int kPend, int kThreads, typename List, typename Lds>
-__device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb,
-                                           uint32_t shift, Lds& sh)
-{
-    constexpr int kSlots = Lds::kSlots;
-    const int lane = lane_id(), wave = wave_id();
-    // lane r holds request r of the batch; unused lanes get an empty lifetime (conflicts with nothing)
-    Addr rq_s = 0;
-    uint32_t rq_ta = 0, rq_tf = 0;
-    if (lane < (int)nb) {
-        rq_s = (Addr)(sh.rq_size[b0 + lane] >> shift);
-        rq_ta = sh.rq_ta[b0 + lane];
-        rq_tf = sh.rq_tf[b0 + lane];
-    }
-    Addr run[kPend];        // uniform: running maximum for request r inside this wave's chunk
-    uint32_t found[kPend];  // uniform: holes found for request r
-    Addr s_of[kPend];       // uniform copies of the request parameters
-    uint32_t ta_of[kPend], tf_of[kPend];
-#pragma unroll
-    for (int r = 0; r < kPend; ++r) {
-        run[r] = 0; found[r] = 0;
-        s_of[r] = read_lane(rq_s, r); ta_of[r] = read_lane(rq_ta, r); tf_of[r] = read_lane(rq_tf, r);
-    }
-    const uint32_t sub = (count + kThreads - 1) / kThreads;     // 64-entry steps per wave
-    uint32_t k = (uint32_t)wave * kWave * sub + lane;
-    for (uint32_t j = 0; j < sub; ++j, k += kWave) {
-        const bool valid = k < count;
-        const uint32_t kc = valid ? k : count - 1;
-        const typename List::Entry en = list.load(kc);
-        const Span<Addr> sp = {en.lo(), en.hi()};
-        // lanes past the end of the list get a lifetime that conflicts with nothing
-        const uint2 lf = make_uint2(valid ? en.ta() : 0xffffffffu, valid ? en.tf() : 0u);
-        // requests in groups of kGroup: their running-maximum chains are independent, so the
-        // compiler can interleave the DPP steps of one chain into the wait states of the others
-        constexpr int kGroup = 4;
-#pragma unroll
-        for (int g = 0; g < kPend; g += kGroup) {
-            Addr incl[kGroup], covered[kGroup];
-            uint64_t conflict_m[kGroup], closers[kGroup];
-            uint64_t any_closer = 0;
-            Addr ends[kGroup];
-#pragma unroll
-            for (int q = 0; q < kGroup; ++q) {
-                const int r = g + q;
-                conflict_m[q] = lanes_lt(lf.x, tf_of[r]) & lanes_lt(ta_of[r], lf.y);   // lanes past the end: see above
-            }
-            keep_lanes4(conflict_m, sp.hi, ends);
-#pragma unroll
-            for (int q = 0; q < kGroup; ++q) incl[q] = wave_scan_max(ends[q]);
-#pragma unroll
-            for (int q = 0; q < kGroup; ++q) {
-                const int r = g + q;
-                covered[q] = umax(run[r], wave_shift_up(incl[q], (Addr)0));
-                closers[q] = conflict_m[q] & lanes_ge(sp.lo, (Addr)(covered[q] + s_of[r]));
-                any_closer |= closers[q];
-                run[r] = umax(run[r], read_lane(incl[q], kWave - 1));
-            }
-            if (any_closer) {
-#pragma unroll
-                for (int q = 0; q < kGroup; ++q) {
-                    const int r = g + q;
-                    uint64_t m = closers[q];                     // holes [covered, sp.lo) in front of conflicting blocks
-                    while (m && found[r] < (uint32_t)kSlots) {
-                        const int f = __builtin_ctzll(m);
-                        m &= m - 1;
-                        // uniform address and data: every lane stores the same record
-                        sh.hole[wave][r][found[r]] = Span<Addr>{read_lane(sp.lo, f), read_lane(covered[q], f)};
-                        ++found[r];
-                    }
-                    if (m) found[r] = kSlots + 1;                // more holes than slots
-                }
-            }
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < kPend; ++r) {
-            sh.top[wave][r] = run[r];
-            sh.holes[wave][r] = found[r];
-        }
-    }
-}
-
-// The same pass with the roles of lanes and loop exchanged, for lists in the workspace: lane r
-// holds request r of the batch (up to 64 of them) and the listed blocks of the wave's chunk
-// are taken one at a time, in address order, as wave-uniform values.  A block costs two
-// lifetime compares, an add and two address compares for all requests at once -- no
-// cross-lane running maximum, which is what the lane-per-block form spends its time on when
-// one pass serves many requests.  What is published per (wave, request) is identical.
-template <typename Addr, int kPend, int kThreads, typename List, typename Lds>
-__device__ __forceinline__ void scan_batch_by_request(const List& list, uint32_t count, uint32_t b0, uint32_t nb,
-                                                      uint32_t shift, Lds& sh)
-{
-    constexpr int kSlots = Lds::kSlots;
+    constexpr int kSlots = Lds::kSlots, kTogether = 4, kPart = kDirect ? kWave : Lds::kStaged;
     static_assert(kPend <= kWave, "one lane per request of the batch");
+    typedef typename BlockList<Addr, false>::Entry Block;
     const int lane = lane_id(), wave = wave_id();
     // unused lanes get an empty lifetime (conflicts with nothing)
     Addr rq_s = 0;
@@ -252,40 +115,89 @@ __device__ __forceinline__ void scan_batch_by_request(const List& list, uint32_t
         rq_tf = sh.rq_tf[b0 + lane];
     }
     Addr covered = 0;        // per request: maximum end of the conflicting blocks of this chunk so far
-    uint32_t found = 0;      // per request: holes found in this chunk
+    Addr first = 0;
+    uint32_t found = 0;      // per request: holes found in this chunk behind its first conflicting block
+    uint64_t open = ~0ull;   // requests that have not found more holes than there are slots
     const uint32_t sub = (count + kThreads - 1) / kThreads;     // 64-entry steps per wave
     const uint32_t chunk0 = (uint32_t)wave * kWave * sub;
-    for (uint32_t j = 0; j < sub; ++j) {
-        const uint32_t k0 = chunk0 + j * kWave;
-        if (k0 >= count) break;                                  // (uniform)
-        const uint32_t k = k0 + lane;
-        const bool valid = k < count;
-        const typename List::Entry en = list.load(valid ? k : count - 1);
-        const Addr e_lo = en.lo(), e_hi = en.hi();
-        // lanes past the end of the list get a lifetime that conflicts with nothing
-        const uint32_t e_ta = valid ? en.ta() : 0xffffffffu, e_tf = valid ? en.tf() : 0u;
-#pragma unroll
-        for (int q = 0; q < kWave; ++q) {
-            const uint32_t ta_q = read_lane(e_ta, q), tf_q = read_lane(e_tf, q);
-            const bool conflict = ta_q < rq_tf && rq_ta < tf_q;
-            if (__builtin_amdgcn_ballot_w64(conflict) == 0) continue;   // (uniform) the block concerns no request of the batch
-            const Addr lo_q = read_lane(e_lo, q), hi_q = read_lane(e_hi, q);
-            if (conflict && lo_q >= (Addr)(covered + rq_s)) {    // a hole [covered, lo_q) in front of this block
-                if (found < (uint32_t)kSlots) sh.hole[wave][lane][found] = Span<Addr>{lo_q, covered};
-                found = found < (uint32_t)kSlots ? found + 1 : (uint32_t)kSlots + 1;   // kSlots + 1: more holes than slots
+    uint32_t end = chunk0 + sub * kWave;
+    if (end > count) end = count;
+    for (uint32_t k0 = chunk0; k0 < end; k0 += kPart) {         // (uniform)
+        if constexpr (!kDirect) {
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t k = k0 + lane;
+            if (kPart == kWave || lane < kPart) {
+                // behind the chunk: a lifetime that conflicts with nothing
+                Block fill = BlockList<Addr, false>::make(0, 0, 0xffffffffu, 0);
+                if (k < end) {
+                    const typename List::Entry en = list.load(k);
+                    fill = BlockList<Addr, false>::make(en.lo(), en.hi(), en.ta(), en.tf());
+                }
+                sh.staged[wave][lane] = fill;
             }
-            const Addr reach = umax(covered, hi_q);
-            covered = conflict ? reach : covered;
+            __builtin_amdgcn_wave_barrier();
+        }
+        // (reads behind the chunk are of no consequence; the list has room for kReadAhead blocks behind its last one)
+        auto fetch = [&](Block (&block)[kTogether], uint32_t k) {
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i) {
+                if constexpr (kDirect) block[i] = list.load(k + i);
+                else block[i] = sh.staged[wave][(k - k0 + i) & (kPart - 1)];
+            }
+        };
+        auto look = [&](const Block (&block)[kTogether], uint32_t k) {
+            uint64_t conflict[kTogether], holes[kTogether], some = 0, any = 0;
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i) {
+                conflict[i] = lanes_lt((uint32_t)block[i].ta(), rq_tf) & lanes_lt(rq_ta, (uint32_t)block[i].tf());
+                if (kDirect && k + i >= end) conflict[i] = 0;
+                some |= conflict[i];
+            }
+            if (some == 0) return;                               // (uniform) these blocks concern no request of the batch
+            Addr before[kTogether];
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i) {
+                before[i] = covered;
+                holes[i] = conflict[i] & lanes_ge(block[i].lo(), (Addr)(covered + rq_s));
+                any |= holes[i];
+                const Addr reach = umax(covered, block[i].hi());
+                covered = lane_in(conflict[i]) ? reach : covered;
+            }
+            if ((any & open) == 0) return;                       // (uniform)
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i) {                // holes [before, lo) in front of some of them
+                uint64_t here = holes[i] & open;
+                if (here == 0) continue;
+                const uint64_t lowest = here & ~lanes_lt((Addr)0, before[i]);    // no conflicting block of the chunk lies lower
+                first = lane_in(lowest) ? block[i].lo() : first;
+                here &= ~lowest;
+                if (here == 0) continue;
+                if (lane_in(here)) {
+                    if (found < (uint32_t)kSlots) sh.hole[wave][lane][found] = Span<Addr>{block[i].lo(), before[i]};
+                    ++found;
+                }
+                open = lanes_lt(found, (uint32_t)kSlots + 1);    // (kSlots + 1: more holes than slots)
+            }
+        };
+        Block even[kTogether], odd[kTogether];
+        fetch(even, k0);
+        const uint32_t stop = kDirect ? umin(end, k0 + kPart) : k0 + kPart;
+        for (uint32_t k = k0; k < stop; k += 2 * kTogether) {
+            fetch(odd, k + kTogether);
+            look(even, k);
+            fetch(even, k + 2 * kTogether);
+            look(odd, k + kTogether);
         }
     }
     if (lane < kPend) {
+        sh.first[wave][lane] = first;
         sh.top[wave][lane] = covered;
-        sh.holes[wave][lane] = found;
+        sh.holes[wave][lane] = (uint8_t)found;
     }
 }
 
-// What the waves published for request r, gathered into the 64 lanes of one wave in address
-// order (lane = wave * kSlots + slot), with the true "covered" of every hole.
+// What the waves published for request r, gathered into the 64 lanes of one wave in address order (lane = wave * kCols;
+// first the hole that ends at the chunk's first conflicting block, then those behind it).
 template <typename Addr>
 struct HoleView {
     Addr covered;        // per lane: covered in front of this hole (chunk maxima of lower waves included)
@@ -299,23 +211,24 @@ struct HoleView {
 template <typename Addr, typename Lds>
 __device__ __forceinline__ HoleView<Addr> view_holes(const Lds& sh, uint32_t r)
 {
-    constexpr int kSlots = Lds::kSlots;
+    constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
-    const int w = lane / kSlots, c = lane % kSlots;
-    const bool live = w < Lds::kWaves;                  // (always true unless kSlots was shrunk)
+    const int w = lane / kCols, c = lane % kCols;
+    const bool live = w < Lds::kWaves;
     const int wc = live ? w : 0;
     const Addr topv = live ? sh.top[wc][r] : (Addr)0;
     const uint32_t found = live ? sh.holes[wc][r] : 0u;
-    const Span<Addr> hl = sh.hole[wc][r][c];
+    const Addr first = sh.first[wc][r];
+    const Span<Addr> hl = sh.hole[wc][r][c > 0 ? c - 1 : 0];
     const Addr incl = wave_scan_max(topv);
-    const Addr below = lane_gather(wave_shift_up(incl, (Addr)0), wc * kSlots);
+    const Addr below = lane_gather(wave_shift_up(incl, (Addr)0), wc * kCols);
     HoleView<Addr> v;
-    v.covered = umax(below, hl.hi);
+    v.covered = c > 0 ? umax(below, hl.hi) : below;
     v.below = below;
-    v.end = hl.lo;
+    v.end = c > 0 ? hl.lo : first;
     v.top = read_lane(incl, kWave - 1);
-    v.published = lanes_lt((uint32_t)c, found);
-    v.crowded = __builtin_amdgcn_ballot_w64(found > (uint32_t)kSlots);
+    v.published = __builtin_amdgcn_ballot_w64(live && (c == 0 || (uint32_t)c <= found));
+    v.crowded = __builtin_amdgcn_ballot_w64(found > (uint32_t)Lds::kSlots);
     return v;
 }
 
@@ -323,57 +236,38 @@ __device__ __forceinline__ HoleView<Addr> view_holes(const Lds& sh, uint32_t r)
 template <typename Lds>
 __device__ __forceinline__ bool unpublished_below(uint64_t crowded, int h)
 {
-    return crowded && (h < 0 || __builtin_ctzll(crowded) / Lds::kSlots < h / Lds::kSlots);
+    return crowded && (h < 0 || __builtin_ctzll(crowded) / Lds::kCols < h / Lds::kCols);
 }
 
-constexpr int kSurveyed = 4;     // holes the survey lists per request
-
-// Survey (all waves, request r handled by wave r mod #waves): lists, in address order, the
-// first holes that are large enough as such, and says what follows the list: the top of the
-// plan (every usable hole is listed) or a closer look at everything that was published.
-template <typename Addr, int kPend, int kThreads, typename Lds>
-__device__ __forceinline__ void survey_batch(uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
-{
-    for (uint32_t r = (uint32_t)wave_id(); r < nb; r += Lds::kWaves) {
-        const Addr s = (Addr)(sh.rq_size[b0 + r] >> shift);
-        const HoleView<Addr> v = view_holes<Addr>(sh, r);
-        uint64_t raw = v.published & lanes_ge(v.end, (Addr)(v.covered + s));
-        uint32_t listed = 0;
-        while (raw && listed < (uint32_t)kSurveyed) {
-            const int h = __builtin_ctzll(raw);
-            if (unpublished_below<Lds>(v.crowded, h)) break;          // an unpublished hole may lie lower
-            raw &= raw - 1;
-            sh.surveyed[r][listed] = Span<Addr>{read_lane(v.end, h), read_lane(v.covered, h)};   // uniform store
-            ++listed;
-        }
-        if (lane_id() == 0) {
-            sh.listed[r] = listed | ((raw || v.crowded) ? 0x100u : 0u);     // bit 8: more to look at after the list
-            sh.top_of[r] = v.top;
-        }
-    }
-}
-
-// Lowest address >= c at which [c, c + s) clears the pending blocks selected by `rivals`
-// (lanes of the side buffer whose lifetime conflicts with the request).
+// Lowest address >= c at which [c, c + s) clears the blocks of the batch selected by `rivals` (one per lane, [lo, hi)).
 template <typename Addr>
-__device__ __forceinline__ Addr clear_rivals(Addr c, Addr s, uint64_t rivals, const Pending<Addr>& pd)
+__device__ __forceinline__ Addr clear_rivals(Addr c, Addr s, uint64_t rivals, Addr lo, Addr hi)
 {
-    if (rivals == 0) return c;
-    for (;;) {
-        const uint64_t hit = rivals & lanes_lt(pd.lo, (Addr)(c + s)) & lanes_lt(c, pd.hi);
-        if (hit == 0) return c;
-        c = read_lane(wave_scan_max(keep_lanes(hit, pd.hi)), kWave - 1);   // every address in [c, that end) is blocked
+    auto in_the_way = [&](Addr at) -> uint64_t { return rivals & lanes_lt(lo, (Addr)(at + s)) & lanes_lt(at, hi); };
+    uint64_t hit = in_the_way(c);
+    while (hit) {
+        c = read_lane(hi, __builtin_ctzll(hit));                 // every address in [c, that end) is blocked
+        hit = in_the_way(c);
     }
+    return c;
 }
+
+// A request of the batch as one wave sees it.
+template <typename Addr>
+struct Seeker {
+    Addr s;
+    uint32_t ta, tf;
+    uint64_t rivals;     // lanes whose request comes earlier in the batch and is alive at the same time
+};
 
 // One wave walks the chunk of the list that wave `w` scanned, for one request, with everything
 // below the chunk known (`below` = maximum end of the conflicting blocks of all lower chunks):
-// the first hole of the chunk that takes the request once the zones of the side buffer are
-// cleared.  Returns true and the address if there is one.  This is what a wave could not
+// the first hole of the chunk that takes the request once it has moved up past its rivals.
+// Returns true and the address if there is one.  This is what a wave could not
 // publish when its chunk held more holes than it has slots.
 template <typename Addr, int kThreads, typename List>
-__device__ __forceinline__ bool chunk_lowest_fit(const List& list, uint32_t count, int w, Addr below, Addr s,
-                                                 uint32_t ta, uint32_t tf, const Zones<Addr>& zones, Addr& x)
+__device__ __forceinline__ bool chunk_lowest_fit(const List& list, uint32_t count, int w, Addr below, const Seeker<Addr>& rq,
+                                                 Addr rival_lo, Addr rival_hi, Addr& x)
 {
     const int lane = lane_id();
     const uint32_t sub = (count + kThreads - 1) / kThreads;     // 64-entry steps per wave, as in the scan
@@ -388,92 +282,167 @@ __device__ __forceinline__ bool chunk_lowest_fit(const List& list, uint32_t coun
         const bool valid = k0 + lane < count;
         if (j + 1 < sub && k0 + kWave + lane < count) ahead = list.load(k0 + kWave + lane);
         const Addr e_lo = en.lo();
-        const bool conflict = valid && en.ta() < tf && ta < en.tf();
+        const bool conflict = valid && en.ta() < rq.tf && rq.ta < en.tf();
         const Addr incl = wave_scan_max(conflict ? (Addr)en.hi() : (Addr)0);
         const Addr before = umax(run, wave_shift_up(incl, (Addr)0));
-        const bool opens = conflict && e_lo >= (Addr)(before + s);            // a hole [before, e_lo) large enough as such
-        if (__builtin_amdgcn_ballot_w64(opens)) {
-            const Addr cleared = clear_zones(before, s, zones);
-            const uint64_t fits = __builtin_amdgcn_ballot_w64(opens && e_lo >= (Addr)(cleared + s));
-            if (fits) { x = read_lane(cleared, __builtin_ctzll(fits)); return true; }
+        uint64_t opens = __builtin_amdgcn_ballot_w64(conflict && e_lo >= (Addr)(before + rq.s));   // holes [before, e_lo) large enough as such
+        while (opens) {
+            const int h = __builtin_ctzll(opens);
+            opens &= opens - 1;
+            const Addr c = clear_rivals(read_lane(before, h), rq.s, rq.rivals, rival_lo, rival_hi);
+            if (c + rq.s <= read_lane(e_lo, h)) { x = c; return true; }
         }
         run = umax(run, read_lane(incl, kWave - 1));
     }
     return false;
 }
 
-// Wave 0 settles the requests of the batch in order.  Returns how many were settled (all).
-template <typename Addr, int kPend, int kThreads, typename List, typename Lds>
-__device__ __forceinline__ uint32_t resolve_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb,
-                                                  uint32_t shift, Addr& peak, Lds& sh)
+// The holes published for request r, one per lane as in HoleView: {end, covered}, the latter counting lower chunks in.
+template <typename Addr, typename Lds>
+__device__ __forceinline__ Span<Addr> published_hole(const Lds& sh, uint32_t r)
 {
+    constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
-    // lane r holds request r of the batch
-    Addr rq_s = 0, topv = 0;
-    uint32_t rq_ta = 0, rq_tf = 0, listedv = 0;
+    const int w = lane / kCols < Lds::kWaves ? lane / kCols : 0, c = lane % kCols;
+    const Span<Addr> in_front = {sh.first[w][r], sh.top[w][r]};
+    const Span<Addr> behind = sh.hole[w][r][c > 0 ? c - 1 : 0];
+    return Span<Addr>{c > 0 ? behind.lo : in_front.lo, c > 0 ? behind.hi : in_front.hi};
+}
+
+// Lowest fit of request r of the batch against the list and its rivals.  `hole`: what was published; `usable`: the lanes
+// whose hole is large enough as such; `crowded`: the lanes of waves that found more holes than they could publish (those
+// they did publish are the lowest of the chunk); `top`: where the request goes if no hole takes it.
+template <typename Addr, int kThreads, typename List, typename Lds>
+__device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uint32_t r, const Seeker<Addr>& rq, Addr rival_lo,
+                                           Addr rival_hi, const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top,
+                                           const Lds& sh)
+{
+    constexpr int kCols = Lds::kCols;
+    while (usable | crowded) {
+        const int h = usable ? __builtin_ctzll(usable) : -1;
+        Addr x, end;
+        if (unpublished_below<Lds>(crowded, h)) {
+            const int w = __builtin_ctzll(crowded) / kCols;
+            if (chunk_lowest_fit<Addr, kThreads>(list, count, w, uniform(sh.top[w][r]), rq, rival_lo, rival_hi, x)) return x;
+            crowded &= ~(((1ull << kCols) - 1) << (w * kCols));
+        } else {
+            x = clear_rivals(read_lane(hole.hi, h), rq.s, rq.rivals, rival_lo, rival_hi);
+            end = read_lane(hole.lo, h);
+            if (x + rq.s <= end) return x;
+            usable &= usable - 1;
+        }
+    }
+    return clear_rivals(top, rq.s, rq.rivals, rival_lo, rival_hi);                               // on top of everything
+}
+
+// Settles the requests of the batch.  First every request gets the lowest fit against the list alone, request r from wave
+// r mod #waves.  That address is the right one unless an earlier request of the batch that is alive at the same time lies
+// there (15 to 40 in a hundred): those clashes are looked for by all waves, and wave 0 goes through them in order.  When it
+// comes to a request all earlier ones lie where they are to lie; if the request moves, whoever it now meets
+// among the later ones clashes too.
+template <typename Addr, int kPend, int kThreads, typename List, typename Lds>
+__device__ __forceinline__ void settle_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift,
+                                             Addr& peak, Lds& sh)
+{
+    constexpr int kCols = Lds::kCols, kPer = kPend / Lds::kWaves;
+    static_assert(kPend % Lds::kWaves == 0 && kPend <= kWave, "requests are dealt out evenly, a lane each");
+    const int lane = lane_id(), wave = wave_id();
+    // lane q holds request q of the batch
+    Addr rq_s = 0;
+    uint32_t rq_ta = 0, rq_tf = 0;
     if (lane < (int)nb) {
         rq_s = (Addr)(sh.rq_size[b0 + lane] >> shift);
         rq_ta = sh.rq_ta[b0 + lane];
         rq_tf = sh.rq_tf[b0 + lane];
-        listedv = sh.listed[lane];
-        topv = sh.top_of[lane];
     }
-    Pending<Addr> pd = {0, 0, 0, 0};
-    // lane i < kSurveyed holds surveyed hole i of the current request; fetched one request ahead
-    Span<Addr> holes_next = sh.surveyed[0][lane < kSurveyed ? lane : 0];
-    uint32_t r = 0;
-    for (; r < nb; ++r) {
-        const Addr s = read_lane(rq_s, (int)r);
-        const uint32_t ta = read_lane(rq_ta, (int)r), tf = read_lane(rq_tf, (int)r);
-        const uint32_t listed = read_lane(listedv, (int)r);
-        const Span<Addr> holes = holes_next;
-        if (r + 1 < nb) holes_next = sh.surveyed[r + 1][lane < kSurveyed ? lane : 0];
-        // blocks settled earlier in this batch whose lifetime conflicts with the request
-        const uint64_t rivals = __builtin_amdgcn_ballot_w64(lane < (int)r && pd.ta < tf && ta < pd.tf);
-        Addr x = 0;
-        bool placed = false;
-        for (uint32_t i = 0; i < (listed & 0xffu) && !placed; ++i) {
-            const Addr c = clear_rivals(read_lane(holes.hi, (int)i), s, rivals, pd);
-            if (c + s <= read_lane(holes.lo, (int)i)) { x = c; placed = true; }
+    // those alive at the same time as request r
+    auto alive_with = [&](uint32_t ta, uint32_t tf) -> uint64_t { return lanes_lt(rq_ta, tf) & lanes_lt(ta, rq_tf); };
+#pragma unroll 1
+    for (int i = 0; i < kPer; ++i) {
+        const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
+        if (r >= nb) break;
+        const Seeker<Addr> rq = {read_lane(rq_s, (int)r), read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), 0};
+        const HoleView<Addr> v = view_holes<Addr>(sh, r);
+        const uint64_t usable = v.published & lanes_ge(v.end, (Addr)(v.covered + rq.s));
+        if (lane_in(v.published)) {
+            if (lane % kCols > 0) sh.hole[lane / kCols][r][lane % kCols - 1].hi = v.covered;
+            else sh.top[lane / kCols][r] = v.below;
         }
-        if (!placed) {
-            if (!(listed & 0x100u)) {
-                x = clear_rivals(read_lane(topv, (int)r), s, rivals, pd);       // on top of everything
-            } else {
-                const HoleView<Addr> v = view_holes<Addr>(sh, r);
-                const Zones<Addr> zones = make_zones(pd, r, s, ta, tf);
-                const Addr cleared = clear_zones(v.covered, s, zones);
-                const uint64_t fits = v.published & lanes_ge(v.end, (Addr)(cleared + s));
-                const int h = fits ? __builtin_ctzll(fits) : -1;
-                // chunks with more holes than their wave could publish, lowest first, as long as
-                // they lie below the chunk of hole h: the lowest fit may be one of those
-                bool lower = false;
-                for (uint64_t crowded = v.crowded; unpublished_below<Lds>(crowded, h);) {
-                    const int first = __builtin_ctzll(crowded);
-                    const int w = first / Lds::kSlots;
-                    lower = chunk_lowest_fit<Addr, kThreads>(list, count, w, read_lane(v.below, first), s, ta, tf, zones, x);
-                    if (lower) break;
-                    for (int c = 0; c < Lds::kSlots; ++c) crowded &= ~(1ull << (w * Lds::kSlots + c));
-                }
-                if (!lower) x = fits ? read_lane(cleared, h) : read_lane(clear_zones(v.top, s, zones), 0);
+        if (lane == 0) { sh.usable[r] = usable; sh.crowded[r] = v.crowded; sh.top_of[r] = v.top; }
+        const Addr x = lowest_fit<Addr, kThreads>(list, count, r, rq, (Addr)0, (Addr)0, Span<Addr>{v.end, v.covered}, usable, v.crowded,
+                                                  v.top, sh);
+        if (lane == 0) sh.at[r] = x;
+    }
+    if (threadIdx.x == 0) sh.clashes = 0;
+    __syncthreads();
+    {
+        const Addr lo = sh.at[lane < (int)nb ? lane : 0];
+        uint64_t mine = 0;
+#pragma unroll 1
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
+            if (r >= nb) break;
+            const Addr x = read_lane(lo, (int)r), s = read_lane(rq_s, (int)r);
+            const uint64_t meets = alive_with(read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r)) & lanes_lt(lo, (Addr)(x + s)) &
+                                   lanes_lt(x, (Addr)(lo + rq_s)) & ((1ull << r) - 1);
+            if (meets) mine |= 1ull << r;
+        }
+        if (mine != 0 && lane == 0) atomicOr((unsigned long long*)&sh.clashes, (unsigned long long)mine);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int own = lane < (int)nb ? lane : 0;
+        Addr lo = sh.at[own];
+        const uint64_t usable = sh.usable[own], crowded = sh.crowded[own];
+        const Addr top = sh.top_of[own];
+        uint64_t clashes = uniform(sh.clashes);
+        // the holes of the request that clashes next, as far as known, are read while this one is placed
+        int ahead = clashes ? __builtin_ctzll(clashes) : 0;
+        Span<Addr> ahead_hole = published_hole<Addr>(sh, (uint32_t)ahead);
+        while (clashes) {
+            const int r = __builtin_ctzll(clashes);
+            clashes &= clashes - 1;
+            Span<Addr> hole = ahead_hole;
+            if (r != ahead) hole = published_hole<Addr>(sh, (uint32_t)r);
+            if (clashes) {
+                ahead = __builtin_ctzll(clashes);
+                ahead_hole = published_hole<Addr>(sh, (uint32_t)ahead);
             }
+            Seeker<Addr> rq = {read_lane(rq_s, r), read_lane(rq_ta, r), read_lane(rq_tf, r), 0};
+            const uint64_t alive = alive_with(rq.ta, rq.tf), earlier = (1ull << r) - 1;
+            rq.rivals = alive & earlier;
+            const Addr x = lowest_fit<Addr, kThreads>(list, count, (uint32_t)r, rq, lo, (Addr)(lo + rq_s), hole, read_lane(usable, r),
+                                                      read_lane(crowded, r), read_lane(top, r), sh);
+            lo = write_lane(lo, x, r);
+            clashes |= alive & ~earlier & ~(1ull << r) & lanes_lt(lo, (Addr)(x + rq.s)) & lanes_lt(x, (Addr)(lo + rq_s));
         }
-        peak = umax(peak, (Addr)(x + s));
-        if (lane == 0) sh.rq_addr[b0 + r] = (uint64_t)x << shift;
-        pending_insert(pd, r, x, s, ta, tf);
+        if (lane < (int)nb) sh.at[lane] = lo;
+        peak = umax(peak, read_lane(wave_scan_max(lane < (int)nb ? (Addr)(lo + rq_s) : (Addr)0), kWave - 1));
+        if (lane < (int)nb) sh.rq_addr[b0 + lane] = (uint64_t)lo << shift;
+        if (lane == 0) sh.extent_now = peak;
     }
-    if (lane < (int)r) {
-        sh.pend_span[lane] = Span<Addr>{pd.lo, pd.hi};
-        sh.pend_life[lane] = make_uint2(pd.ta, pd.tf);
+    __syncthreads();
+    // sorted by address for the merge
+    const Addr lo = sh.at[lane < (int)nb ? lane : 0];
+#pragma unroll 1
+    for (int i = 0; i < kPer; ++i) {
+        const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
+        if (r >= nb) break;
+        const Addr x = read_lane(lo, (int)r);
+        const uint64_t below = (lanes_lt(lo, x) | (lanes_ge(x, lo) & ((1ull << r) - 1))) & lanes_lt((uint32_t)lane, nb);
+        const int place = __builtin_popcountll(below);
+        if (lane == (int)r) {
+            sh.pend_span[place] = Span<Addr>{x, (Addr)(x + rq_s)};
+            sh.pend_life[place] = make_uint2(rq_ta, rq_tf);
+        }
     }
-    if (lane == 0) sh.settled = r;
-    return r;
+    __syncthreads();
 }
 
 template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
 __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // <= 128 VGPRs: 16 waves per CU
 {
-    using Lds = PlanLds<Addr, kPend, kThreads>;
+    using Lds = PlanLds<Addr, kLds, kCompact, kPend, kThreads>;
     using List = BlockList<Addr, kCompact>;
     extern __shared__ __align__(16) unsigned char smem[];
     Lds& sh = *reinterpret_cast<Lds*>(smem);
@@ -494,7 +463,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
     // of the two 32-bit instantiations the compact one runs when it was enqueued and applies
     const bool compact = prm.compact_enqueued && (mode & kModeCompact) != 0;
     if (sizeof(Addr) == 4 && compact != kCompact) return;
-    if (status_of_workgroup(status, &sh.settled) != STALLOC_OK) return;   // malformed trace: nothing to plan
+    if (status_of_workgroup(status, &sh.word) != STALLOC_OK) return;   // malformed trace: nothing to plan
     const uint32_t shift = sizeof(Addr) == 4 ? (uint32_t)(mode & 63) : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && !(sizeof(Addr) == 8 && try32))
         const_cast<uint64_t*>(prm.acc)[kAccKernel] = (kLds ? STALLOC_KERNEL_LIST_LDS : STALLOC_KERNEL_LIST_MEMORY) |
@@ -546,21 +515,13 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
                     const uint64_t growth = wave_sum64(lane < (int)nb ? sh.rq_size[b0 + lane] >> shift : 0ull);
                     if ((uint64_t)sh.extent_now + growth > 0xffffffffull) { outgrown = true; break; }
                 }
-                if constexpr (kLds) scan_batch<Addr, kPend, kThreads>(list, count, b0, nb, shift, sh);
-                else scan_batch_by_request<Addr, kPend, kThreads>(list, count, b0, nb, shift, sh);
+                scan_batch<Addr, kPend, kThreads, kLds && !kCompact>(list, count, b0, nb, shift, sh);
                 __syncthreads();
-                survey_batch<Addr, kPend, kThreads>(b0, nb, shift, sh);
-                __syncthreads();
-                if (wave_id() == 0) {
-                    resolve_batch<Addr, kPend, kThreads>(list, count, b0, nb, shift, peak, sh);
-                    if (lane_id() == 0) sh.extent_now = peak;
-                }
-                __syncthreads();
-                const uint32_t settled = sh.settled;
-                const bool last_of_plan = r0 + b0 + settled >= n;
-                if (settled && !last_of_plan) merge_pending<Addr, kLds, kThreads>(list, spare, count, settled, sh);
-                count += settled;
-                b0 += settled;
+                settle_batch<Addr, kPend, kThreads>(list, count, b0, nb, shift, peak, sh);
+                const bool last_of_plan = r0 + b0 + nb >= n;
+                if (!last_of_plan) merge_pending<Addr, kLds, kThreads>(list, spare, count, nb, sh);
+                count += nb;
+                b0 += nb;
             }
             if (outgrown) break;
             // addresses of this batch -> offsets[p][request id]
@@ -626,7 +587,7 @@ __global__ void __launch_bounds__(256) plan_copy_best(const uint64_t* __restrict
 
 // Tuning knobs (overridable at build time with -D).
 #ifndef STALLOC_PEND_LDS
-#define STALLOC_PEND_LDS 16
+#define STALLOC_PEND_LDS 64
 #endif
 #ifndef STALLOC_PEND_MEM
 #define STALLOC_PEND_MEM 64
@@ -648,10 +609,10 @@ constexpr int kThreadsMem = STALLOC_THREADS_MEM;
 constexpr int kThreadsCompact = STALLOC_THREADS_COMPACT;   // two such workgroups share one CU
 
 // Entries the LDS-resident list may hold, for a given entry size and LDS budget.
-template <typename Addr, int kThreads>
+template <typename Addr, bool kCompact, int kThreads>
 inline uint32_t lds_capacity_entries(size_t lds_budget, size_t bytes_per_entry)
 {
-    const size_t fixed = sizeof(PlanLds<Addr, kPendLds, kThreads>);
+    const size_t fixed = sizeof(PlanLds<Addr, true, kCompact, kPendLds, kThreads>) + kReadAhead * bytes_per_entry;
     if (lds_budget <= fixed) return 0;
     return (uint32_t)((lds_budget - fixed) / bytes_per_entry);
 }
@@ -660,8 +621,8 @@ template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
 inline bool launch_plan(const PlanParams& prm, uint32_t grid, const DeviceInfo& di, hipStream_t stream)
 {
     auto kernel = &plan_kernel<Addr, kLds, kCompact, kPend, kThreads>;
-    size_t lds = sizeof(PlanLds<Addr, kPend, kThreads>) +
-                 (kLds ? (size_t)prm.n * BlockList<Addr, kCompact>::kEntryBytes : 0);
+    size_t lds = sizeof(PlanLds<Addr, kLds, kCompact, kPend, kThreads>) +
+                 (kLds ? ((size_t)prm.n + kReadAhead) * BlockList<Addr, kCompact>::kEntryBytes : 0);
     static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
     if (!attr_set[di.device]) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -703,7 +664,7 @@ extern "C" uint32_t stalloc_plan_lds_capacity(void)
 {
     DeviceInfo di;
     if (!device_info(&di)) return 0;
-    return lds_capacity_entries<uint32_t, kThreadsLds>(di.lds_per_block, entry_bytes<uint32_t>());
+    return lds_capacity_entries<uint32_t, false, kThreadsLds>(di.lds_per_block, entry_bytes<uint32_t>());
 }
 
 // allow_bitmap: false when the caller has said that its sizes cannot suit the occupancy-bitmap kernel; that
@@ -716,11 +677,11 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     DeviceInfo di;
     if (!device_info(&di)) return STALLOC_ERR_DEVICE;
     const uint32_t n = tr->n;
-    const bool lds32 = n <= lds_capacity_entries<uint32_t, kThreadsLds>(di.lds_per_block, entry_bytes<uint32_t>());
-    const bool lds64 = n <= lds_capacity_entries<uint64_t, kThreadsLds>(di.lds_per_block, entry_bytes<uint64_t>());
+    const bool lds32 = n <= lds_capacity_entries<uint32_t, false, kThreadsLds>(di.lds_per_block, entry_bytes<uint32_t>());
+    const bool lds64 = n <= lds_capacity_entries<uint64_t, false, kThreadsLds>(di.lds_per_block, entry_bytes<uint64_t>());
     // compact list: 8-byte entries, two workgroups per CU (half the LDS each)
     const bool compact = tr->t_end < 0x10000u &&
-                         n <= lds_capacity_entries<uint32_t, kThreadsCompact>(di.lds_per_block / 2, sizeof(uint2));
+                         n <= lds_capacity_entries<uint32_t, true, kThreadsCompact>(di.lds_per_block / 2, sizeof(uint2));
     uint32_t grid_lds = (uint32_t)di.cus, grid_mem = (uint32_t)di.cus * 2, grid_compact = (uint32_t)di.cus * 2;
     if (grid_lds > P) grid_lds = P;
     if (grid_mem > P) grid_mem = P;

@@ -232,6 +232,9 @@ __device__ __forceinline__ uint64_t keep_lanes(uint64_t mask, uint64_t v)
     return ((uint64_t)keep_lanes(mask, (uint32_t)(v >> 32)) << 32) | keep_lanes(mask, (uint32_t)v);
 }
 
+// A lane mask as a per-lane truth value (no shift or compare: the mask selects lanes as it is).
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // Number of set bits of `mask` in lanes below the calling lane.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
@@ -245,6 +248,10 @@ __device__ __forceinline__ uint64_t umax(uint64_t a, uint64_t b) { return a > b 
 // A value that is the same in all lanes of the wave (read by every lane from one LDS word, say),
 // as a scalar: the compiler cannot know, and would otherwise branch on it with lane masks.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v)
+{
+    return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
 
 // The status word (non-zero: an error) as the whole workgroup is to see it.  A kernel that raises the word itself must
 // not let every wave read it for itself: another workgroup may raise it in between, and waves that stay
