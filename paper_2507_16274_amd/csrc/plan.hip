@@ -60,28 +60,32 @@ constexpr uint32_t kReadAhead = 12;   // blocks behind the list's last one that 
 template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
 struct PlanLds {
     static constexpr int kWaves = kThreads / kWave;
+    // A wave scans one chunk of the list with a request per lane, or two chunks at a time, half of the lanes each, with two
+    // requests per lane (64-bit addresses: what is published per chunk would keep a second workgroup off the CU)
+    static constexpr int kHalves = sizeof(Addr) == 8 ? 1 : 2;
+    static constexpr int kChunks = kWaves * kHalves;
 #ifdef STALLOC_HOLE_SLOTS
     static constexpr int kSlots = STALLOC_HOLE_SLOTS;      // (test builds shrink this to exercise the second walk of a chunk)
 #else
-    // holes a wave can publish per request, besides the one in front of its chunk's first conflicting block
-    static constexpr int kSlots = sizeof(Addr) == 8 ? 2 : 3;
+    // holes published per (chunk, request), besides the one in front of the chunk's first conflicting block
+    static constexpr int kSlots = sizeof(Addr) == 8 ? 2 : kWave / kChunks - 1;
 #endif
     static constexpr int kCols = kSlots + 1;
-    static_assert(kWaves * kCols <= kWave, "all holes of a request lie side by side in the lanes of a wave");
+    static_assert(kChunks * kCols <= kWave && kSlots > 0, "all holes of a request lie side by side in the lanes of a wave");
     // The scan takes blocks as broadcasts from LDS: from the list itself, or from here (listed in the workspace, or packed)
-    static constexpr int kStaged = kLds && !kCompact ? 1 : sizeof(Addr) == 8 || kCompact ? kWave / 2 : kWave;
+    static constexpr int kStaged = kLds && !kCompact ? 1 : sizeof(Addr) == 8 ? kWave / 2 : kWave;
     typename BlockList<Addr, false>::Entry staged[kWaves][kStaged];
     uint64_t rq_size[kBatch];
     uint64_t rq_addr[kBatch];
     uint32_t rq_ta[kBatch];
     uint32_t rq_tf[kBatch];
     uint32_t rq_id[kBatch];
-    Addr first[kWaves][kPend];                             // start of the chunk's first conflicting block, if that may close a hole
-    Addr top[kWaves][kPend];                               // chunk maximum per (wave, request)
-    uint8_t holes[kWaves][kPend];                          // holes found per (wave, request), may exceed kSlots
-    Span<Addr> hole[kWaves][kPend][kSlots];                // {hole end, chunk-local covered}
-    uint64_t usable[kPend];                                // holes that are large enough as such (lane = wave * kSlots + slot)
-    uint64_t crowded[kPend];                               // lanes of waves that found more holes than they could publish
+    Addr first[kChunks][kPend];                            // start of the chunk's first conflicting block, if that may close a hole
+    Addr top[kChunks][kPend];                              // chunk maximum per (chunk, request)
+    uint8_t holes[kChunks][kPend];                         // holes found per (chunk, request), may exceed kSlots
+    Span<Addr> hole[kChunks][kPend][kSlots];               // {hole end, chunk-local covered}
+    uint64_t usable[kPend];                                // holes that are large enough as such (lane = chunk * kCols + column)
+    uint64_t crowded[kPend];                               // lanes of chunks with more holes than could be published
     Addr top_of[kPend];                                    // maximum over all chunks
     Addr at[kPend];                                        // where the requests of the batch are to lie, as far as known
     uint64_t clashes;                                      // requests that may not stay where they would lie without the rest of the batch
@@ -91,121 +95,142 @@ struct PlanLds {
     Addr extent_now;                                       // extent of the plan after the last settled batch
 };
 
-// One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request, and the
-// blocks of the wave's chunk are taken one at a time, in address order, by all lanes at once: two lifetime compares, an
+// The part of the list that is chunk `c`: chunks are equally long, a multiple of eight blocks; the last one that is not
+// empty ends with the list and may begin inside the one before it (a block counted by two chunks changes nothing: what a
+// lower chunk covers is known when holes are judged).  The list is empty or holds at least 64 blocks.
+struct Chunk { uint32_t first, blocks; };
+template <int kChunks>
+__device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
+{
+    const uint32_t blocks = ((count + kChunks - 1) / kChunks + 7) & ~7u;
+    const uint32_t start = c * blocks;
+    const uint32_t end = umin(start + blocks, count);
+    return Chunk{start < count ? end - blocks : 0u, start < count ? blocks : 0u};
+}
+
+// One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request (or two), and
+// the blocks of a chunk are taken one at a time, in address order, by all its lanes at once: two lifetime compares, an
 // add, a compare, a maximum and a selection per block and 64 requests, and nothing that crosses lanes.  The block comes
 // as a broadcast from LDS (taken out of a register of a lane it costs four more vector instructions: 283 instead of 209
-// million cycles a plan for 49 920 requests with the list in the workspace).  Blocks are looked at four
-// together, so that their compares overlap and one branch asks whether any of them closes a hole.  Published per
-// (wave, request): the chunk maximum of conflicting end addresses, the start of the first conflicting block, and
-// the first holes behind it with chunk-local "covered".
+// million cycles a plan for 49 920 requests with the list in the workspace); 64 lanes reading 16 bytes keep the LDS busy for
+// eight cycles whether they read one block or two, so the halves of a wave read a block each and hold all 64
+// requests each, two per lane.  Blocks are looked at four together, so that their compares overlap and one branch asks
+// whether any of them closes a hole.  Published per (chunk, request): the maximum of conflicting end addresses, the
+// start of the first conflicting block, and the first holes behind it with chunk-local "covered".
 template <typename Addr, int kPend, int kThreads, bool kDirect, typename List, typename Lds>
 __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
 {
-    constexpr int kSlots = Lds::kSlots, kTogether = 4, kPart = kDirect ? kWave : Lds::kStaged;
-    static_assert(kPend <= kWave, "one lane per request of the batch");
+    constexpr int kSlots = Lds::kSlots, kTogether = 4, kHalves = Lds::kHalves, kLanes = kWave / kHalves;
+    constexpr uint32_t kPart = Lds::kStaged / kHalves;           // staged blocks per chunk
+    static_assert(kPend == kWave, "kHalves requests per lane");
     typedef typename BlockList<Addr, false>::Entry Block;
     const int lane = lane_id(), wave = wave_id();
-    // unused lanes get an empty lifetime (conflicts with nothing)
-    Addr rq_s = 0;
-    uint32_t rq_ta = 0, rq_tf = 0;
-    if (lane < (int)nb) {
-        rq_s = (Addr)(sh.rq_size[b0 + lane] >> shift);
-        rq_ta = sh.rq_ta[b0 + lane];
-        rq_tf = sh.rq_tf[b0 + lane];
+    const int half = lane / kLanes, place = lane % kLanes;
+    const uint32_t c = (uint32_t)(wave * kHalves + half);
+    const Chunk chunk = chunk_of<Lds::kChunks>(count, c);
+    const uint32_t blocks = uniform(chunk.blocks);               // (of the wave's lowest chunk; the other may be empty)
+    // requests beyond the batch, and all where there is no chunk, get an empty lifetime (conflicts with nothing)
+    Addr rq_s[kHalves], covered[kHalves], first[kHalves];        // covered: maximum end of the conflicting blocks so far
+    uint32_t rq_ta[kHalves], rq_tf[kHalves], found[kHalves];     // found: holes behind the chunk's first conflicting block
+    uint64_t open[kHalves];                                      // lanes that have not found more holes than there are slots
+#pragma unroll
+    for (int u = 0; u < kHalves; ++u) {
+        const int r = place + u * kLanes;
+        rq_s[u] = 0; rq_ta[u] = 0; rq_tf[u] = 0;
+        if (r < (int)nb && chunk.blocks > 0) {
+            rq_s[u] = (Addr)(sh.rq_size[b0 + r] >> shift);
+            rq_ta[u] = sh.rq_ta[b0 + r];
+            rq_tf[u] = sh.rq_tf[b0 + r];
+        }
+        covered[u] = 0; first[u] = 0; found[u] = 0; open[u] = ~0ull;
     }
-    Addr covered = 0;        // per request: maximum end of the conflicting blocks of this chunk so far
-    Addr first = 0;
-    uint32_t found = 0;      // per request: holes found in this chunk behind its first conflicting block
-    uint64_t open = ~0ull;   // requests that have not found more holes than there are slots
-    const uint32_t sub = (count + kThreads - 1) / kThreads;     // 64-entry steps per wave
-    const uint32_t chunk0 = (uint32_t)wave * kWave * sub;
-    uint32_t end = chunk0 + sub * kWave;
-    if (end > count) end = count;
-    for (uint32_t k0 = chunk0; k0 < end; k0 += kPart) {         // (uniform)
+    for (uint32_t k0 = 0; k0 < blocks; k0 += kDirect ? blocks : kPart) {
+        const uint32_t stop = kDirect ? blocks : umin(kPart, blocks - k0);
         if constexpr (!kDirect) {
             __builtin_amdgcn_wave_barrier();
-            const uint32_t k = k0 + lane;
-            if (kPart == kWave || lane < kPart) {
-                // behind the chunk: a lifetime that conflicts with nothing
-                Block fill = BlockList<Addr, false>::make(0, 0, 0xffffffffu, 0);
-                if (k < end) {
-                    const typename List::Entry en = list.load(k);
-                    fill = BlockList<Addr, false>::make(en.lo(), en.hi(), en.ta(), en.tf());
-                }
-                sh.staged[wave][lane] = fill;
+            if (place < (int)kPart && k0 + place < chunk.blocks) {
+                const typename List::Entry en = list.load(chunk.first + k0 + place);
+                sh.staged[wave][half * kPart + place] = BlockList<Addr, false>::make(en.lo(), en.hi(), en.ta(), en.tf());
             }
             __builtin_amdgcn_wave_barrier();
         }
-        // (reads behind the chunk are of no consequence; the list has room for kReadAhead blocks behind its last one)
+        // (reads behind the part are not looked at; the list has room for kReadAhead blocks behind its last one)
         auto fetch = [&](Block (&block)[kTogether], uint32_t k) {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
-                if constexpr (kDirect) block[i] = list.load(k + i);
-                else block[i] = sh.staged[wave][(k - k0 + i) & (kPart - 1)];
+                if constexpr (kDirect) block[i] = list.load(chunk.first + k + i);
+                else block[i] = sh.staged[wave][half * kPart + (k & (kPart - 1)) + i];
             }
         };
-        auto look = [&](const Block (&block)[kTogether], uint32_t k) {
-            uint64_t conflict[kTogether], holes[kTogether], some = 0, any = 0;
+        auto look = [&](const Block (&block)[kTogether]) {
+            uint64_t conflict[kHalves][kTogether], holes[kHalves][kTogether], some = 0, any = 0;
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
-                conflict[i] = lanes_lt((uint32_t)block[i].ta(), rq_tf) & lanes_lt(rq_ta, (uint32_t)block[i].tf());
-                if (kDirect && k + i >= end) conflict[i] = 0;
-                some |= conflict[i];
+#pragma unroll
+                for (int u = 0; u < kHalves; ++u) {
+                    conflict[u][i] = lanes_lt((uint32_t)block[i].ta(), rq_tf[u]) & lanes_lt(rq_ta[u], (uint32_t)block[i].tf());
+                    some |= conflict[u][i];
+                }
             }
             if (some == 0) return;                               // (uniform) these blocks concern no request of the batch
-            Addr before[kTogether];
+            Addr before[kHalves][kTogether];
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
-                before[i] = covered;
-                holes[i] = conflict[i] & lanes_ge(block[i].lo(), (Addr)(covered + rq_s));
-                any |= holes[i];
-                const Addr reach = umax(covered, block[i].hi());
-                covered = lane_in(conflict[i]) ? reach : covered;
+#pragma unroll
+                for (int u = 0; u < kHalves; ++u) {
+                    before[u][i] = covered[u];
+                    holes[u][i] = conflict[u][i] & lanes_ge(block[i].lo(), (Addr)(covered[u] + rq_s[u]));
+                    any |= holes[u][i] & open[u];
+                    const Addr reach = umax(covered[u], block[i].hi());
+                    covered[u] = lane_in(conflict[u][i]) ? reach : covered[u];
+                }
             }
-            if ((any & open) == 0) return;                       // (uniform)
+            if (any == 0) return;                                // (uniform)
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {                // holes [before, lo) in front of some of them
-                uint64_t here = holes[i] & open;
-                if (here == 0) continue;
-                const uint64_t lowest = here & ~lanes_lt((Addr)0, before[i]);    // no conflicting block of the chunk lies lower
-                first = lane_in(lowest) ? block[i].lo() : first;
-                here &= ~lowest;
-                if (here == 0) continue;
-                if (lane_in(here)) {
-                    if (found < (uint32_t)kSlots) sh.hole[wave][lane][found] = Span<Addr>{block[i].lo(), before[i]};
-                    ++found;
+#pragma unroll
+                for (int u = 0; u < kHalves; ++u) {
+                    uint64_t here = holes[u][i] & open[u];
+                    if (here == 0) continue;
+                    const uint64_t lowest = here & ~lanes_lt((Addr)0, before[u][i]);    // no conflicting block of the chunk lies lower
+                    first[u] = lane_in(lowest) ? block[i].lo() : first[u];
+                    here &= ~lowest;
+                    if (here == 0) continue;
+                    if (lane_in(here)) {
+                        if (found[u] < (uint32_t)kSlots) sh.hole[c][place + u * kLanes][found[u]] = Span<Addr>{block[i].lo(), before[u][i]};
+                        ++found[u];
+                    }
+                    open[u] = lanes_lt(found[u], (uint32_t)kSlots + 1);                 // (kSlots + 1: more holes than slots)
                 }
-                open = lanes_lt(found, (uint32_t)kSlots + 1);    // (kSlots + 1: more holes than slots)
             }
         };
         Block even[kTogether], odd[kTogether];
-        fetch(even, k0);
-        const uint32_t stop = kDirect ? umin(end, k0 + kPart) : k0 + kPart;
-        for (uint32_t k = k0; k < stop; k += 2 * kTogether) {
+        fetch(even, 0);
+        for (uint32_t k = 0; k < stop; k += 2 * kTogether) {
             fetch(odd, k + kTogether);
-            look(even, k);
+            look(even);
             fetch(even, k + 2 * kTogether);
-            look(odd, k + kTogether);
+            look(odd);
         }
     }
-    if (lane < kPend) {
-        sh.first[wave][lane] = first;
-        sh.top[wave][lane] = covered;
-        sh.holes[wave][lane] = (uint8_t)found;
+#pragma unroll
+    for (int u = 0; u < kHalves; ++u) {
+        sh.first[c][place + u * kLanes] = first[u];
+        sh.top[c][place + u * kLanes] = covered[u];
+        sh.holes[c][place + u * kLanes] = (uint8_t)found[u];
     }
 }
 
-// What the waves published for request r, gathered into the 64 lanes of one wave in address order (lane = wave * kCols;
+// What was published for request r, gathered into the 64 lanes of one wave in address order (kCols lanes a chunk;
 // first the hole that ends at the chunk's first conflicting block, then those behind it).
 template <typename Addr>
 struct HoleView {
-    Addr covered;        // per lane: covered in front of this hole (chunk maxima of lower waves included)
+    Addr covered;        // per lane: covered in front of this hole (lower chunks included)
     Addr end;            // per lane: address at which the hole ends
     Addr top;            // uniform: maximum over all chunks (where the request goes if no hole fits)
-    Addr below;          // per lane: maximum over the chunks of the waves below this lane's wave
+    Addr below;          // per lane: maximum over the chunks below this lane's chunk
     uint64_t published;  // lanes that hold a hole
-    uint64_t crowded;    // lanes of waves that found more holes than they could publish
+    uint64_t crowded;    // lanes of chunks with more holes than could be published
 };
 
 template <typename Addr, typename Lds>
@@ -214,7 +239,7 @@ __device__ __forceinline__ HoleView<Addr> view_holes(const Lds& sh, uint32_t r)
     constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
     const int w = lane / kCols, c = lane % kCols;
-    const bool live = w < Lds::kWaves;
+    const bool live = w < Lds::kChunks;
     const int wc = live ? w : 0;
     const Addr topv = live ? sh.top[wc][r] : (Addr)0;
     const uint32_t found = live ? sh.holes[wc][r] : 0u;
@@ -232,7 +257,7 @@ __device__ __forceinline__ HoleView<Addr> view_holes(const Lds& sh, uint32_t r)
     return v;
 }
 
-// True if a wave with unpublished holes lies below lane h (h < 0: the request would go on top).
+// True if a chunk with unpublished holes lies below lane h (h < 0: the request would go on top).
 template <typename Lds>
 __device__ __forceinline__ bool unpublished_below(uint64_t crowded, int h)
 {
@@ -260,27 +285,22 @@ struct Seeker {
     uint64_t rivals;     // lanes whose request comes earlier in the batch and is alive at the same time
 };
 
-// One wave walks the chunk of the list that wave `w` scanned, for one request, with everything
-// below the chunk known (`below` = maximum end of the conflicting blocks of all lower chunks):
-// the first hole of the chunk that takes the request once it has moved up past its rivals.
-// Returns true and the address if there is one.  This is what a wave could not
-// publish when its chunk held more holes than it has slots.
-template <typename Addr, int kThreads, typename List>
-__device__ __forceinline__ bool chunk_lowest_fit(const List& list, uint32_t count, int w, Addr below, const Seeker<Addr>& rq,
-                                                 Addr rival_lo, Addr rival_hi, Addr& x)
+// One wave walks a chunk of the list for one request, with everything
+// below the chunk known (`below` = maximum end of the conflicting blocks of all lower chunks): the first hole {end, covered}
+// of the chunk that takes the request once it has moved up past its rivals, to `x`.  Returns true if there is one.
+// This is for chunks with more holes than slots to publish them.
+template <typename Addr, typename List>
+__device__ __forceinline__ bool chunk_lowest_fit(const List& list, const Chunk& chunk, Addr below, const Seeker<Addr>& rq,
+                                                 Addr rival_lo, Addr rival_hi, Addr& x, Span<Addr>& hole)
 {
-    const int lane = lane_id();
-    const uint32_t sub = (count + kThreads - 1) / kThreads;     // 64-entry steps per wave, as in the scan
-    const uint32_t chunk0 = (uint32_t)w * kWave * sub;
+    const uint32_t lane = (uint32_t)lane_id();
     Addr run = below;
     typename List::Entry ahead = List::none();
-    if (chunk0 + lane < count) ahead = list.load(chunk0 + lane);
-    for (uint32_t j = 0; j < sub; ++j) {
-        const uint32_t k0 = chunk0 + j * kWave;
-        if (k0 >= count) break;                                  // (uniform)
+    if (lane < chunk.blocks) ahead = list.load(chunk.first + lane);
+    for (uint32_t k0 = 0; k0 < chunk.blocks; k0 += kWave) {
         const typename List::Entry en = ahead;
-        const bool valid = k0 + lane < count;
-        if (j + 1 < sub && k0 + kWave + lane < count) ahead = list.load(k0 + kWave + lane);
+        const bool valid = k0 + lane < chunk.blocks;
+        if (k0 + kWave + lane < chunk.blocks) ahead = list.load(chunk.first + k0 + kWave + lane);
         const Addr e_lo = en.lo();
         const bool conflict = valid && en.ta() < rq.tf && rq.ta < en.tf();
         const Addr incl = wave_scan_max(conflict ? (Addr)en.hi() : (Addr)0);
@@ -289,8 +309,9 @@ __device__ __forceinline__ bool chunk_lowest_fit(const List& list, uint32_t coun
         while (opens) {
             const int h = __builtin_ctzll(opens);
             opens &= opens - 1;
-            const Addr c = clear_rivals(read_lane(before, h), rq.s, rq.rivals, rival_lo, rival_hi);
-            if (c + rq.s <= read_lane(e_lo, h)) { x = c; return true; }
+            hole = Span<Addr>{read_lane(e_lo, h), read_lane(before, h)};
+            x = clear_rivals(hole.hi, rq.s, rq.rivals, rival_lo, rival_hi);
+            if (x + rq.s <= hole.lo) return true;
         }
         run = umax(run, read_lane(incl, kWave - 1));
     }
@@ -303,16 +324,16 @@ __device__ __forceinline__ Span<Addr> published_hole(const Lds& sh, uint32_t r)
 {
     constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
-    const int w = lane / kCols < Lds::kWaves ? lane / kCols : 0, c = lane % kCols;
+    const int w = lane / kCols < Lds::kChunks ? lane / kCols : 0, c = lane % kCols;
     const Span<Addr> in_front = {sh.first[w][r], sh.top[w][r]};
     const Span<Addr> behind = sh.hole[w][r][c > 0 ? c - 1 : 0];
     return Span<Addr>{c > 0 ? behind.lo : in_front.lo, c > 0 ? behind.hi : in_front.hi};
 }
 
 // Lowest fit of request r of the batch against the list and its rivals.  `hole`: what was published; `usable`: the lanes
-// whose hole is large enough as such; `crowded`: the lanes of waves that found more holes than they could publish (those
-// they did publish are the lowest of the chunk); `top`: where the request goes if no hole takes it.
-template <typename Addr, int kThreads, typename List, typename Lds>
+// whose hole is large enough as such; `crowded`: the lanes of chunks with more holes than could be published (those
+// that were are the lowest of the chunk); `top`: where the request goes if no hole takes it.
+template <typename Addr, typename List, typename Lds>
 __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uint32_t r, const Seeker<Addr>& rq, Addr rival_lo,
                                            Addr rival_hi, const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top,
                                            const Lds& sh)
@@ -320,15 +341,15 @@ __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uin
     constexpr int kCols = Lds::kCols;
     while (usable | crowded) {
         const int h = usable ? __builtin_ctzll(usable) : -1;
-        Addr x, end;
+        Addr x;
         if (unpublished_below<Lds>(crowded, h)) {
             const int w = __builtin_ctzll(crowded) / kCols;
-            if (chunk_lowest_fit<Addr, kThreads>(list, count, w, uniform(sh.top[w][r]), rq, rival_lo, rival_hi, x)) return x;
+            Span<Addr> walked;
+            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), uniform(sh.top[w][r]), rq, rival_lo, rival_hi, x, walked)) return x;
             crowded &= ~(((1ull << kCols) - 1) << (w * kCols));
         } else {
             x = clear_rivals(read_lane(hole.hi, h), rq.s, rq.rivals, rival_lo, rival_hi);
-            end = read_lane(hole.lo, h);
-            if (x + rq.s <= end) return x;
+            if (x + rq.s <= read_lane(hole.lo, h)) return x;
             usable &= usable - 1;
         }
     }
@@ -362,15 +383,29 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
         const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
         if (r >= nb) break;
         const Seeker<Addr> rq = {read_lane(rq_s, (int)r), read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), 0};
-        const HoleView<Addr> v = view_holes<Addr>(sh, r);
-        const uint64_t usable = v.published & lanes_ge(v.end, (Addr)(v.covered + rq.s));
+        HoleView<Addr> v = view_holes<Addr>(sh, r);
+        uint64_t usable = v.published & lanes_ge(v.end, (Addr)(v.covered + rq.s));
+        // A chunk with unpublished holes below the first usable one is walked here, and the first hole that takes the request
+        // goes where the chunk's last published one was (none of those is usable), so that it is not walked again.
+        while (unpublished_below<Lds>(v.crowded, usable ? __builtin_ctzll(usable) : -1)) {
+            const int w = __builtin_ctzll(v.crowded) / kCols, last = w * kCols + kCols - 1;
+            Addr x;
+            Span<Addr> hole;
+            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), read_lane(v.below, last), rq, (Addr)0, (Addr)0, x, hole)) {
+                v.end = write_lane(v.end, hole.lo, last);
+                v.covered = write_lane(v.covered, hole.hi, last);
+                usable |= 1ull << last;
+                if (lane == last) sh.hole[w][r][Lds::kSlots - 1].lo = hole.lo;
+            } else {
+                v.crowded &= ~(((1ull << kCols) - 1) << (w * kCols));
+            }
+        }
         if (lane_in(v.published)) {
             if (lane % kCols > 0) sh.hole[lane / kCols][r][lane % kCols - 1].hi = v.covered;
             else sh.top[lane / kCols][r] = v.below;
         }
         if (lane == 0) { sh.usable[r] = usable; sh.crowded[r] = v.crowded; sh.top_of[r] = v.top; }
-        const Addr x = lowest_fit<Addr, kThreads>(list, count, r, rq, (Addr)0, (Addr)0, Span<Addr>{v.end, v.covered}, usable, v.crowded,
-                                                  v.top, sh);
+        const Addr x = usable ? read_lane(v.covered, __builtin_ctzll(usable)) : v.top;
         if (lane == 0) sh.at[r] = x;
     }
     if (threadIdx.x == 0) sh.clashes = 0;
@@ -396,23 +431,17 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
         const uint64_t usable = sh.usable[own], crowded = sh.crowded[own];
         const Addr top = sh.top_of[own];
         uint64_t clashes = uniform(sh.clashes);
-        // the holes of the request that clashes next, as far as known, are read while this one is placed
-        int ahead = clashes ? __builtin_ctzll(clashes) : 0;
-        Span<Addr> ahead_hole = published_hole<Addr>(sh, (uint32_t)ahead);
         while (clashes) {
             const int r = __builtin_ctzll(clashes);
             clashes &= clashes - 1;
-            Span<Addr> hole = ahead_hole;
-            if (r != ahead) hole = published_hole<Addr>(sh, (uint32_t)r);
-            if (clashes) {
-                ahead = __builtin_ctzll(clashes);
-                ahead_hole = published_hole<Addr>(sh, (uint32_t)ahead);
-            }
             Seeker<Addr> rq = {read_lane(rq_s, r), read_lane(rq_ta, r), read_lane(rq_tf, r), 0};
             const uint64_t alive = alive_with(rq.ta, rq.tf), earlier = (1ull << r) - 1;
             rq.rivals = alive & earlier;
-            const Addr x = lowest_fit<Addr, kThreads>(list, count, (uint32_t)r, rq, lo, (Addr)(lo + rq_s), hole, read_lane(usable, r),
-                                                      read_lane(crowded, r), read_lane(top, r), sh);
+            const uint64_t usable_r = read_lane(usable, r), crowded_r = read_lane(crowded, r);
+            Addr x = read_lane(top, r);
+            if ((usable_r | crowded_r) == 0) x = clear_rivals(x, rq.s, rq.rivals, lo, (Addr)(lo + rq_s));
+            else x = lowest_fit<Addr>(list, count, (uint32_t)r, rq, lo, (Addr)(lo + rq_s), published_hole<Addr>(sh, (uint32_t)r),
+                                      usable_r, crowded_r, x, sh);
             lo = write_lane(lo, x, r);
             clashes |= alive & ~earlier & ~(1ull << r) & lanes_lt(lo, (Addr)(x + rq.s)) & lanes_lt(x, (Addr)(lo + rq_s));
         }
