@@ -86,6 +86,7 @@ constexpr int kAccTiles = 11;                  // bitmap kernel with tables per 
 constexpr int kAccCrowded = 13;                // 1: the mean lifetime is more than a fifth of the time from first allocation to last release,
                                                // or that time is less than a sixteenth of t_end
 constexpr int kAccTilesMissed = 12;            // plans that outgrew its tables and are left to the other bitmap kernel
+constexpr int kAccNextPlan = 14;               // sorted-list kernel: plans handed out so far beyond one per workgroup
 constexpr uint64_t kModeNarrow = 1ull << 8;
 constexpr uint64_t kModeCompact = 1ull << 9;   // sum of sizes in granules below 2^16 as well
 constexpr uint64_t kModeBitmap = 1ull << 10;   // sum <= kBitmapGranules and every size <= kBitmapMaxSize granules

@@ -33,8 +33,8 @@
 //
 // What bounds it: the scan reads every block as an LDS broadcast (16 bytes, eight cycles of the CU's LDS) and spends six
 // vector instructions on it, per 64 requests; then the chain of clashing requests in wave 0.  6144 requests of 5
-// sizes, 512 orders (list in LDS): 17.9 -> 11.3 ms against batches of 16 with a lane per block, a running maximum across lanes
-// per request, and wave 0 settling every request; 49 920 requests, 256 orders (list in the workspace): 228 -> 175 ms.
+// sizes, 512 orders (list in LDS): 17.9 -> 8.9 ms against batches of 16 with a lane per block, a running maximum across lanes
+// per request, and wave 0 settling every request; 49 920 requests, 256 orders (list in the workspace): 228 -> 154 ms.
 //
 // Addresses are multiples of the largest power of two dividing all sizes.  When the sum of
 // sizes, in those granules, stays below 2^31 the list holds 32-bit granule counts (16-byte
@@ -91,6 +91,7 @@ struct PlanLds {
     uint64_t clashes;                                      // requests that may not stay where they would lie without the rest of the batch
     Span<Addr> pend_span[kPend];                           // blocks settled in this batch, sorted
     uint2 pend_life[kPend];
+    uint32_t pend_who[kPend];                              // and the request each belongs to
     uint32_t word;
     Addr extent_now;                                       // extent of the plan after the last settled batch
 };
@@ -233,18 +234,29 @@ struct HoleView {
     uint64_t crowded;    // lanes of chunks with more holes than could be published
 };
 
+template <typename Addr>
+struct HolesRead { Addr top, first; Span<Addr> hole; uint32_t found; };
+
 template <typename Addr, typename Lds>
-__device__ __forceinline__ HoleView<Addr> view_holes(const Lds& sh, uint32_t r)
+__device__ __forceinline__ HolesRead<Addr> read_holes(const Lds& sh, uint32_t r)
+{
+    constexpr int kCols = Lds::kCols;
+    const int w = lane_id() / kCols, c = lane_id() % kCols, wc = w < Lds::kChunks ? w : 0;
+    return HolesRead<Addr>{sh.top[wc][r], sh.first[wc][r], sh.hole[wc][r][c > 0 ? c - 1 : 0], sh.holes[wc][r]};
+}
+
+template <typename Addr, typename Lds>
+__device__ __forceinline__ HoleView<Addr> view_holes(const HolesRead<Addr>& read, const Lds&)
 {
     constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
     const int w = lane / kCols, c = lane % kCols;
     const bool live = w < Lds::kChunks;
     const int wc = live ? w : 0;
-    const Addr topv = live ? sh.top[wc][r] : (Addr)0;
-    const uint32_t found = live ? sh.holes[wc][r] : 0u;
-    const Addr first = sh.first[wc][r];
-    const Span<Addr> hl = sh.hole[wc][r][c > 0 ? c - 1 : 0];
+    const Addr topv = live ? read.top : (Addr)0;
+    const uint32_t found = live ? read.found : 0u;
+    const Addr first = read.first;
+    const Span<Addr> hl = read.hole;
     const Addr incl = wave_scan_max(topv);
     const Addr below = lane_gather(wave_shift_up(incl, (Addr)0), wc * kCols);
     HoleView<Addr> v;
@@ -264,26 +276,34 @@ __device__ __forceinline__ bool unpublished_below(uint64_t crowded, int h)
     return crowded && (h < 0 || __builtin_ctzll(crowded) / Lds::kCols < h / Lds::kCols);
 }
 
-// Lowest address >= c at which [c, c + s) clears the blocks of the batch selected by `rivals` (one per lane, [lo, hi)).
-template <typename Addr>
-__device__ __forceinline__ Addr clear_rivals(Addr c, Addr s, uint64_t rivals, Addr lo, Addr hi)
-{
-    auto in_the_way = [&](Addr at) -> uint64_t { return rivals & lanes_lt(lo, (Addr)(at + s)) & lanes_lt(at, hi); };
-    uint64_t hit = in_the_way(c);
-    while (hit) {
-        c = read_lane(hi, __builtin_ctzll(hit));                 // every address in [c, that end) is blocked
-        hit = in_the_way(c);
-    }
-    return c;
-}
-
-// A request of the batch as one wave sees it.
+// A request of the batch and what the rest of the batch means to it.  Rivals are the blocks of the batch settled so far
+// that are alive at the same time, one per lane in the order of their start addresses.
 template <typename Addr>
 struct Seeker {
     Addr s;
     uint32_t ta, tf;
-    uint64_t rivals;     // lanes whose request comes earlier in the batch and is alive at the same time
+    uint64_t rivals;
+    Addr rival_lo;       // per lane: start address
+    Addr reach_before;   // per lane: highest end of the rivals in lower lanes
+    Addr reach;          // uniform: of all rivals
+
+    // Lowest address >= c at which [c, c + s) clears the rivals: in front of the first of them that leaves room above
+    // c and everything below, else above them all.  (One running maximum per request serves every c; moving up past one
+    // rival after the other took 5 steps of some 100 cycles for a request on top of the list.)
+    __device__ __forceinline__ Addr clear(Addr c) const
+    {
+        const Addr before = umax(c, reach_before);
+        const uint64_t gaps = rivals & lanes_ge(rival_lo, (Addr)(before + s));
+        return gaps ? read_lane(before, __builtin_ctzll(gaps)) : umax(c, reach);
+    }
 };
+
+template <typename Addr>
+__device__ __forceinline__ Seeker<Addr> seeker(Addr s, uint32_t ta, uint32_t tf, uint64_t rivals, Addr rival_lo, Addr rival_hi)
+{
+    const Addr incl = wave_scan_max(keep_lanes(rivals, rival_hi));
+    return Seeker<Addr>{s, ta, tf, rivals, rival_lo, wave_shift_up(incl, (Addr)0), read_lane(incl, kWave - 1)};
+}
 
 // One wave walks a chunk of the list for one request, with everything
 // below the chunk known (`below` = maximum end of the conflicting blocks of all lower chunks): the first hole {end, covered}
@@ -291,29 +311,35 @@ struct Seeker {
 // This is for chunks with more holes than slots to publish them.
 template <typename Addr, typename List>
 __device__ __forceinline__ bool chunk_lowest_fit(const List& list, const Chunk& chunk, Addr below, const Seeker<Addr>& rq,
-                                                 Addr rival_lo, Addr rival_hi, Addr& x, Span<Addr>& hole)
+                                                 Addr& x, Span<Addr>& hole)
 {
+    constexpr int kSteps = sizeof(Addr) == 8 ? 2 : 4;            // 64 blocks each, read together (the list may lie in memory)
     const uint32_t lane = (uint32_t)lane_id();
     Addr run = below;
-    typename List::Entry ahead = List::none();
-    if (lane < chunk.blocks) ahead = list.load(chunk.first + lane);
-    for (uint32_t k0 = 0; k0 < chunk.blocks; k0 += kWave) {
-        const typename List::Entry en = ahead;
-        const bool valid = k0 + lane < chunk.blocks;
-        if (k0 + kWave + lane < chunk.blocks) ahead = list.load(chunk.first + k0 + kWave + lane);
-        const Addr e_lo = en.lo();
-        const bool conflict = valid && en.ta() < rq.tf && rq.ta < en.tf();
-        const Addr incl = wave_scan_max(conflict ? (Addr)en.hi() : (Addr)0);
-        const Addr before = umax(run, wave_shift_up(incl, (Addr)0));
-        uint64_t opens = __builtin_amdgcn_ballot_w64(conflict && e_lo >= (Addr)(before + rq.s));   // holes [before, e_lo) large enough as such
-        while (opens) {
-            const int h = __builtin_ctzll(opens);
-            opens &= opens - 1;
-            hole = Span<Addr>{read_lane(e_lo, h), read_lane(before, h)};
-            x = clear_rivals(hole.hi, rq.s, rq.rivals, rival_lo, rival_hi);
-            if (x + rq.s <= hole.lo) return true;
+    for (uint32_t k0 = 0; k0 < chunk.blocks; k0 += kSteps * kWave) {
+        typename List::Entry en[kSteps];
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const uint32_t k = k0 + j * kWave + lane;
+            en[j] = list.load(chunk.first + (k < chunk.blocks ? k : 0));
         }
-        run = umax(run, read_lane(incl, kWave - 1));
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            if (k0 + j * kWave >= chunk.blocks) break;           // (uniform)
+            const Addr e_lo = en[j].lo();
+            const bool conflict = k0 + j * kWave + lane < chunk.blocks && en[j].ta() < rq.tf && rq.ta < en[j].tf();
+            const Addr incl = wave_scan_max(conflict ? (Addr)en[j].hi() : (Addr)0);
+            const Addr before = umax(run, wave_shift_up(incl, (Addr)0));
+            uint64_t opens = __builtin_amdgcn_ballot_w64(conflict && e_lo >= (Addr)(before + rq.s));   // holes [before, e_lo) large enough as such
+            while (opens) {
+                const int h = __builtin_ctzll(opens);
+                opens &= opens - 1;
+                hole = Span<Addr>{read_lane(e_lo, h), read_lane(before, h)};
+                x = rq.clear(hole.hi);
+                if (x + rq.s <= hole.lo) return true;
+            }
+            run = umax(run, read_lane(incl, kWave - 1));
+        }
     }
     return false;
 }
@@ -334,9 +360,8 @@ __device__ __forceinline__ Span<Addr> published_hole(const Lds& sh, uint32_t r)
 // whose hole is large enough as such; `crowded`: the lanes of chunks with more holes than could be published (those
 // that were are the lowest of the chunk); `top`: where the request goes if no hole takes it.
 template <typename Addr, typename List, typename Lds>
-__device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uint32_t r, const Seeker<Addr>& rq, Addr rival_lo,
-                                           Addr rival_hi, const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top,
-                                           const Lds& sh)
+__device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uint32_t r, const Seeker<Addr>& rq,
+                                           const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top, const Lds& sh)
 {
     constexpr int kCols = Lds::kCols;
     while (usable | crowded) {
@@ -345,15 +370,15 @@ __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uin
         if (unpublished_below<Lds>(crowded, h)) {
             const int w = __builtin_ctzll(crowded) / kCols;
             Span<Addr> walked;
-            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), uniform(sh.top[w][r]), rq, rival_lo, rival_hi, x, walked)) return x;
+            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), uniform(sh.top[w][r]), rq, x, walked)) return x;
             crowded &= ~(((1ull << kCols) - 1) << (w * kCols));
         } else {
-            x = clear_rivals(read_lane(hole.hi, h), rq.s, rq.rivals, rival_lo, rival_hi);
+            x = rq.clear(read_lane(hole.hi, h));
             if (x + rq.s <= read_lane(hole.lo, h)) return x;
             usable &= usable - 1;
         }
     }
-    return clear_rivals(top, rq.s, rq.rivals, rival_lo, rival_hi);                               // on top of everything
+    return rq.clear(top);                                        // on top of everything
 }
 
 // Settles the requests of the batch.  First every request gets the lowest fit against the list alone, request r from wave
@@ -378,12 +403,15 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
     }
     // those alive at the same time as request r
     auto alive_with = [&](uint32_t ta, uint32_t tf) -> uint64_t { return lanes_lt(rq_ta, tf) & lanes_lt(ta, rq_tf); };
-#pragma unroll 1
+    HolesRead<Addr> read[kPer];                                  // (all reads go out before the first is used)
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) read[i] = read_holes<Addr>(sh, (uint32_t)(wave + i * Lds::kWaves));
+#pragma unroll
     for (int i = 0; i < kPer; ++i) {
         const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
         if (r >= nb) break;
-        const Seeker<Addr> rq = {read_lane(rq_s, (int)r), read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), 0};
-        HoleView<Addr> v = view_holes<Addr>(sh, r);
+        const Seeker<Addr> rq = {read_lane(rq_s, (int)r), read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), 0, 0, 0, 0};
+        HoleView<Addr> v = view_holes<Addr>(read[i], sh);
         uint64_t usable = v.published & lanes_ge(v.end, (Addr)(v.covered + rq.s));
         // A chunk with unpublished holes below the first usable one is walked here, and the first hole that takes the request
         // goes where the chunk's last published one was (none of those is usable), so that it is not walked again.
@@ -391,7 +419,7 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
             const int w = __builtin_ctzll(v.crowded) / kCols, last = w * kCols + kCols - 1;
             Addr x;
             Span<Addr> hole;
-            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), read_lane(v.below, last), rq, (Addr)0, (Addr)0, x, hole)) {
+            if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), read_lane(v.below, last), rq, x, hole)) {
                 v.end = write_lane(v.end, hole.lo, last);
                 v.covered = write_lane(v.covered, hole.hi, last);
                 usable |= 1ull << last;
@@ -418,9 +446,18 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
             const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
             if (r >= nb) break;
             const Addr x = read_lane(lo, (int)r), s = read_lane(rq_s, (int)r);
+            const uint64_t lower = (1ull << r) - 1;
             const uint64_t meets = alive_with(read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r)) & lanes_lt(lo, (Addr)(x + s)) &
-                                   lanes_lt(x, (Addr)(lo + rq_s)) & ((1ull << r) - 1);
+                                   lanes_lt(x, (Addr)(lo + rq_s)) & lower;
             if (meets) mine |= 1ull << r;
+            // sorted by address, for wave 0 below and for the merge
+            const uint64_t below = (lanes_lt(lo, x) | (lanes_ge(x, lo) & lower)) & lanes_lt((uint32_t)lane, nb);
+            if (lane == (int)r) {
+                const int place = __builtin_popcountll(below);
+                sh.pend_span[place] = Span<Addr>{x, (Addr)(x + rq_s)};
+                sh.pend_life[place] = make_uint2(rq_ta, rq_tf);
+                sh.pend_who[place] = r;
+            }
         }
         if (mine != 0 && lane == 0) atomicOr((unsigned long long*)&sh.clashes, (unsigned long long)mine);
     }
@@ -431,39 +468,43 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
         const uint64_t usable = sh.usable[own], crowded = sh.crowded[own];
         const Addr top = sh.top_of[own];
         uint64_t clashes = uniform(sh.clashes);
+        // lanes without a block: nobody's, behind all others
+        Pending<Addr> pd = load_pending<Addr>(sh, nb);
+        uint32_t who = sh.pend_who[own];
+        if (lane >= (int)nb) { pd.lo = Top<Addr>::value; who = 0xffffffffu; }
         while (clashes) {
             const int r = __builtin_ctzll(clashes);
             clashes &= clashes - 1;
-            Seeker<Addr> rq = {read_lane(rq_s, r), read_lane(rq_ta, r), read_lane(rq_tf, r), 0};
-            const uint64_t alive = alive_with(rq.ta, rq.tf), earlier = (1ull << r) - 1;
-            rq.rivals = alive & earlier;
+            const Addr s = read_lane(rq_s, r);
+            const uint32_t ta = read_lane(rq_ta, r), tf = read_lane(rq_tf, r);
+            const uint64_t rivals = lanes_lt(pd.ta, tf) & lanes_lt(ta, pd.tf) & lanes_lt(who, (uint32_t)r);
+            const Seeker<Addr> rq = seeker(s, ta, tf, rivals, pd.lo, pd.hi);
             const uint64_t usable_r = read_lane(usable, r), crowded_r = read_lane(crowded, r);
             Addr x = read_lane(top, r);
-            if ((usable_r | crowded_r) == 0) x = clear_rivals(x, rq.s, rq.rivals, lo, (Addr)(lo + rq_s));
-            else x = lowest_fit<Addr>(list, count, (uint32_t)r, rq, lo, (Addr)(lo + rq_s), published_hole<Addr>(sh, (uint32_t)r),
-                                      usable_r, crowded_r, x, sh);
+            if ((usable_r | crowded_r) == 0) x = rq.clear(x);
+            else x = lowest_fit<Addr>(list, count, (uint32_t)r, rq, published_hole<Addr>(sh, (uint32_t)r), usable_r, crowded_r, x, sh);
+            // the block moves up to its place in address order
+            const uint32_t from = (uint32_t)__builtin_ctzll(lanes_eq(who, (uint32_t)r));
+            const uint32_t to = (uint32_t)__builtin_popcountll(lanes_ge(x, pd.lo)) - 1;
+            const Pending<Addr> up = {wave_shift_down(pd.lo, (Addr)0), wave_shift_down(pd.hi, (Addr)0), wave_shift_down(pd.ta, 0u),
+                                      wave_shift_down(pd.tf, 0u)};
+            const uint32_t up_who = wave_shift_down(who, 0u);
+            const bool down = lane_in(lanes_ge((uint32_t)lane, from) & lanes_lt((uint32_t)lane, to)), here = lane == (int)to;
+            pd.lo = here ? x : down ? up.lo : pd.lo;
+            pd.hi = here ? (Addr)(x + s) : down ? up.hi : pd.hi;
+            pd.ta = here ? ta : down ? up.ta : pd.ta;
+            pd.tf = here ? tf : down ? up.tf : pd.tf;
+            who = here ? (uint32_t)r : down ? up_who : who;
             lo = write_lane(lo, x, r);
-            clashes |= alive & ~earlier & ~(1ull << r) & lanes_lt(lo, (Addr)(x + rq.s)) & lanes_lt(x, (Addr)(lo + rq_s));
+            clashes |= alive_with(ta, tf) & ~((2ull << r) - 1) & lanes_lt(lo, (Addr)(x + s)) & lanes_lt(x, (Addr)(lo + rq_s));
         }
-        if (lane < (int)nb) sh.at[lane] = lo;
+        if (lane < (int)nb) {
+            sh.pend_span[lane] = Span<Addr>{pd.lo, pd.hi};
+            sh.pend_life[lane] = make_uint2(pd.ta, pd.tf);
+        }
         peak = umax(peak, read_lane(wave_scan_max(lane < (int)nb ? (Addr)(lo + rq_s) : (Addr)0), kWave - 1));
         if (lane < (int)nb) sh.rq_addr[b0 + lane] = (uint64_t)lo << shift;
         if (lane == 0) sh.extent_now = peak;
-    }
-    __syncthreads();
-    // sorted by address for the merge
-    const Addr lo = sh.at[lane < (int)nb ? lane : 0];
-#pragma unroll 1
-    for (int i = 0; i < kPer; ++i) {
-        const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
-        if (r >= nb) break;
-        const Addr x = read_lane(lo, (int)r);
-        const uint64_t below = (lanes_lt(lo, x) | (lanes_ge(x, lo) & ((1ull << r) - 1))) & lanes_lt((uint32_t)lane, nb);
-        const int place = __builtin_popcountll(below);
-        if (lane == (int)r) {
-            sh.pend_span[place] = Span<Addr>{x, (Addr)(x + rq_s)};
-            sh.pend_life[place] = make_uint2(rq_ta, rq_tf);
-        }
     }
     __syncthreads();
 }
@@ -508,7 +549,19 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
         spare.bind(slab + (size_t)n * entry_bytes<uint64_t>(), n);
     }
 
-    for (uint32_t p = blockIdx.x; p < prm.P; p += gridDim.x) {
+    // Beyond one per workgroup plans are handed out as workgroups get done: an order by time takes twice as long as a random
+    // one, and the workgroup that places it should not have another waiting for it.
+    // Plans to place again are few and stay where they are.
+    auto next_plan = [&](uint32_t p) -> uint32_t {
+        if (sizeof(Addr) == 8 && try32) return p + gridDim.x;
+        if (gridDim.x >= prm.P) return prm.P;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            sh.word = gridDim.x + (uint32_t)atomicAdd((unsigned long long*)&const_cast<uint64_t*>(prm.acc)[kAccNextPlan], 1ull);
+        __syncthreads();
+        return uniform(sh.word);
+    };
+    for (uint32_t p = blockIdx.x; p < prm.P; p = next_plan(p)) {
         if (sizeof(Addr) == 8 && try32 && !prm.wide_plans[p]) continue;   // (uniform) placed with 32-bit counts already
         if (sizeof(Addr) == 8 && try32 && threadIdx.x == 0)
             atomicAdd((unsigned long long*)&const_cast<uint64_t*>(prm.acc)[kAccWidePlans], 1ull);

@@ -13,7 +13,7 @@ __device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < 
 
 // DPP controls (GFX9 encoding)
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
-constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138;
+constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138, kDppWaveShl1 = 0x130;
 constexpr int kDppRowRor1 = 0x121, kDppRowRor2 = 0x122, kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
 
 // Lanes whose DPP source does not exist, or whose row is masked out, receive `fill`.
@@ -172,6 +172,13 @@ __device__ __forceinline__ uint32_t wave_shift_up(uint32_t v, uint32_t fill)
 }
 __device__ __forceinline__ uint64_t wave_shift_up(uint64_t v, uint64_t fill) { return wave_shift_up64(v, fill); }
 
+// Value of the next lane; lane 63 receives `fill`.
+__device__ __forceinline__ uint32_t wave_shift_down(uint32_t v, uint32_t fill)
+{
+    return __builtin_amdgcn_update_dpp(fill, v, kDppWaveShl1, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint64_t wave_shift_down(uint64_t v, uint64_t fill) { return dpp64<kDppWaveShl1>(fill, v); }
+
 __device__ __forceinline__ uint32_t read_lane(uint32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ __forceinline__ uint64_t read_lane(uint64_t v, int lane) { return readlane64(v, lane); }
 
@@ -201,6 +208,8 @@ __device__ __forceinline__ uint64_t lanes_lt(uint32_t a, uint32_t b) { return __
 __device__ __forceinline__ uint64_t lanes_lt(uint64_t a, uint64_t b) { return __builtin_amdgcn_uicmpl(a, b, 36); }
 __device__ __forceinline__ uint64_t lanes_ge(uint32_t a, uint32_t b) { return __builtin_amdgcn_uicmp(a, b, 35); }
 __device__ __forceinline__ uint64_t lanes_ge(uint64_t a, uint64_t b) { return __builtin_amdgcn_uicmpl(a, b, 35); }
+
+__device__ __forceinline__ uint64_t lanes_eq(uint32_t a, uint32_t b) { return __builtin_amdgcn_uicmp(a, b, 32); }
 
 // Per lane: mask bit set ? v : 0.  The trailing wait states keep the result safe for a DPP
 // consumer scheduled right behind the statement (the compiler does not track hazards of
