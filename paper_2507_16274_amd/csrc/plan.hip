@@ -55,9 +55,10 @@
 namespace stalloc {
 
 constexpr int kBatch = 256;          // requests fetched per refill
+constexpr int kPend = kWave;         // requests per batch
 constexpr uint32_t kReadAhead = 12;   // blocks behind the list's last one that may be read (and are not used)
 
-template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
+template <typename Addr, bool kLds, bool kCompact, int kThreads>
 struct PlanLds {
     static constexpr int kWaves = kThreads / kWave;
     // A wave scans one chunk of the list with a request per lane, or two chunks at a time, half of the lanes each, with two
@@ -82,6 +83,7 @@ struct PlanLds {
     uint32_t rq_id[kBatch];
     Addr first[kChunks][kPend];                            // start of the chunk's first conflicting block, if that may close a hole
     Addr top[kChunks][kPend];                              // chunk maximum per (chunk, request)
+    Addr last[kChunks];                                    // start of the chunk's last block
     uint8_t holes[kChunks][kPend];                         // holes found per (chunk, request), may exceed kSlots
     Span<Addr> hole[kChunks][kPend][kSlots];               // {hole end, chunk-local covered}
     uint64_t usable[kPend];                                // holes that are large enough as such (lane = chunk * kCols + column)
@@ -118,12 +120,11 @@ __device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
 // requests each, two per lane.  Blocks are looked at four together, so that their compares overlap and one branch asks
 // whether any of them closes a hole.  Published per (chunk, request): the maximum of conflicting end addresses, the
 // start of the first conflicting block, and the first holes behind it with chunk-local "covered".
-template <typename Addr, int kPend, int kThreads, bool kDirect, typename List, typename Lds>
+template <typename Addr, bool kDirect, typename List, typename Lds>
 __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
 {
     constexpr int kSlots = Lds::kSlots, kTogether = 4, kHalves = Lds::kHalves, kLanes = kWave / kHalves;
     constexpr uint32_t kPart = Lds::kStaged / kHalves;           // staged blocks per chunk
-    static_assert(kPend == kWave, "kHalves requests per lane");
     typedef typename BlockList<Addr, false>::Entry Block;
     const int lane = lane_id(), wave = wave_id();
     const int half = lane / kLanes, place = lane % kLanes;
@@ -145,6 +146,8 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
         }
         covered[u] = 0; first[u] = 0; found[u] = 0; open[u] = ~0ull;
     }
+    Addr last = 0;
+    if (place == 0 && chunk.blocks > 0) last = list.load(chunk.first + chunk.blocks - 1).lo();
     for (uint32_t k0 = 0; k0 < blocks; k0 += kDirect ? blocks : kPart) {
         const uint32_t stop = kDirect ? blocks : umin(kPart, blocks - k0);
         if constexpr (!kDirect) {
@@ -220,6 +223,7 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
         sh.top[c][place + u * kLanes] = covered[u];
         sh.holes[c][place + u * kLanes] = (uint8_t)found[u];
     }
+    if (place == 0) sh.last[c] = last;
 }
 
 // What was published for request r, gathered into the 64 lanes of one wave in address order (kCols lanes a chunk;
@@ -235,18 +239,18 @@ struct HoleView {
 };
 
 template <typename Addr>
-struct HolesRead { Addr top, first; Span<Addr> hole; uint32_t found; };
+struct HolesRead { Addr top, first; Span<Addr> hole; uint32_t found; Addr last; };
 
 template <typename Addr, typename Lds>
 __device__ __forceinline__ HolesRead<Addr> read_holes(const Lds& sh, uint32_t r)
 {
     constexpr int kCols = Lds::kCols;
     const int w = lane_id() / kCols, c = lane_id() % kCols, wc = w < Lds::kChunks ? w : 0;
-    return HolesRead<Addr>{sh.top[wc][r], sh.first[wc][r], sh.hole[wc][r][c > 0 ? c - 1 : 0], sh.holes[wc][r]};
+    return HolesRead<Addr>{sh.top[wc][r], sh.first[wc][r], sh.hole[wc][r][c > 0 ? c - 1 : 0], sh.holes[wc][r], sh.last[wc]};
 }
 
 template <typename Addr, typename Lds>
-__device__ __forceinline__ HoleView<Addr> view_holes(const HolesRead<Addr>& read, const Lds&)
+__device__ __forceinline__ HoleView<Addr> view_holes(const HolesRead<Addr>& read, Addr s, const Lds&)
 {
     constexpr int kCols = Lds::kCols;
     const int lane = lane_id();
@@ -265,7 +269,8 @@ __device__ __forceinline__ HoleView<Addr> view_holes(const HolesRead<Addr>& read
     v.end = c > 0 ? hl.lo : first;
     v.top = read_lane(incl, kWave - 1);
     v.published = __builtin_amdgcn_ballot_w64(live && (c == 0 || (uint32_t)c <= found));
-    v.crowded = __builtin_amdgcn_ballot_w64(found > (uint32_t)Lds::kSlots);
+    // (not those that a large block below covers whole: there are no holes left; 49 920 requests, settling 52 -> 45 million cycles a plan)
+    v.crowded = __builtin_amdgcn_ballot_w64(found > (uint32_t)Lds::kSlots && read.last >= (Addr)(below + s));
     return v;
 }
 
@@ -386,12 +391,12 @@ __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uin
 // there (15 to 40 in a hundred): those clashes are looked for by all waves, and wave 0 goes through them in order.  When it
 // comes to a request all earlier ones lie where they are to lie; if the request moves, whoever it now meets
 // among the later ones clashes too.
-template <typename Addr, int kPend, int kThreads, typename List, typename Lds>
+template <typename Addr, typename List, typename Lds>
 __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift,
                                              Addr& peak, Lds& sh)
 {
     constexpr int kCols = Lds::kCols, kPer = kPend / Lds::kWaves;
-    static_assert(kPend % Lds::kWaves == 0 && kPend <= kWave, "requests are dealt out evenly, a lane each");
+    static_assert(kPend % Lds::kWaves == 0, "requests are dealt out evenly");
     const int lane = lane_id(), wave = wave_id();
     // lane q holds request q of the batch
     Addr rq_s = 0;
@@ -411,7 +416,7 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
         const uint32_t r = (uint32_t)(wave + i * Lds::kWaves);
         if (r >= nb) break;
         const Seeker<Addr> rq = {read_lane(rq_s, (int)r), read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), 0, 0, 0, 0};
-        HoleView<Addr> v = view_holes<Addr>(read[i], sh);
+        HoleView<Addr> v = view_holes<Addr>(read[i], rq.s, sh);
         uint64_t usable = v.published & lanes_ge(v.end, (Addr)(v.covered + rq.s));
         // A chunk with unpublished holes below the first usable one is walked here, and the first hole that takes the request
         // goes where the chunk's last published one was (none of those is usable), so that it is not walked again.
@@ -509,10 +514,10 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
     __syncthreads();
 }
 
-template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
+template <typename Addr, bool kLds, bool kCompact, int kThreads>
 __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // <= 128 VGPRs: 16 waves per CU
 {
-    using Lds = PlanLds<Addr, kLds, kCompact, kPend, kThreads>;
+    using Lds = PlanLds<Addr, kLds, kCompact, kThreads>;
     using List = BlockList<Addr, kCompact>;
     extern __shared__ __align__(16) unsigned char smem[];
     Lds& sh = *reinterpret_cast<Lds*>(smem);
@@ -597,9 +602,9 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
                     const uint64_t growth = wave_sum64(lane < (int)nb ? sh.rq_size[b0 + lane] >> shift : 0ull);
                     if ((uint64_t)sh.extent_now + growth > 0xffffffffull) { outgrown = true; break; }
                 }
-                scan_batch<Addr, kPend, kThreads, kLds && !kCompact>(list, count, b0, nb, shift, sh);
+                scan_batch<Addr, kLds && !kCompact>(list, count, b0, nb, shift, sh);
                 __syncthreads();
-                settle_batch<Addr, kPend, kThreads>(list, count, b0, nb, shift, peak, sh);
+                settle_batch<Addr>(list, count, b0, nb, shift, peak, sh);
                 const bool last_of_plan = r0 + b0 + nb >= n;
                 if (!last_of_plan) merge_pending<Addr, kLds, kThreads>(list, spare, count, nb, sh);
                 count += nb;
@@ -668,20 +673,12 @@ __global__ void __launch_bounds__(256) plan_copy_best(const uint64_t* __restrict
 }
 
 // Tuning knobs (overridable at build time with -D).
-#ifndef STALLOC_PEND_LDS
-#define STALLOC_PEND_LDS 64
-#endif
-#ifndef STALLOC_PEND_MEM
-#define STALLOC_PEND_MEM 64
-#endif
 #ifndef STALLOC_THREADS_LDS
 #define STALLOC_THREADS_LDS 1024
 #endif
 #ifndef STALLOC_THREADS_MEM
 #define STALLOC_THREADS_MEM 1024
 #endif
-constexpr int kPendLds = STALLOC_PEND_LDS;        // requests per batch when the list is in LDS
-constexpr int kPendMem = STALLOC_PEND_MEM;        // ... and when it is in the workspace (every batch costs passes over memory)
 constexpr int kThreadsLds = STALLOC_THREADS_LDS;
 constexpr int kThreadsMem = STALLOC_THREADS_MEM;
 
@@ -694,16 +691,16 @@ constexpr int kThreadsCompact = STALLOC_THREADS_COMPACT;   // two such workgroup
 template <typename Addr, bool kCompact, int kThreads>
 inline uint32_t lds_capacity_entries(size_t lds_budget, size_t bytes_per_entry)
 {
-    const size_t fixed = sizeof(PlanLds<Addr, true, kCompact, kPendLds, kThreads>) + kReadAhead * bytes_per_entry;
+    const size_t fixed = sizeof(PlanLds<Addr, true, kCompact, kThreads>) + kReadAhead * bytes_per_entry;
     if (lds_budget <= fixed) return 0;
     return (uint32_t)((lds_budget - fixed) / bytes_per_entry);
 }
 
-template <typename Addr, bool kLds, bool kCompact, int kPend, int kThreads>
+template <typename Addr, bool kLds, bool kCompact, int kThreads>
 inline bool launch_plan(const PlanParams& prm, uint32_t grid, const DeviceInfo& di, hipStream_t stream)
 {
-    auto kernel = &plan_kernel<Addr, kLds, kCompact, kPend, kThreads>;
-    size_t lds = sizeof(PlanLds<Addr, kLds, kCompact, kPend, kThreads>) +
+    auto kernel = &plan_kernel<Addr, kLds, kCompact, kThreads>;
+    size_t lds = sizeof(PlanLds<Addr, kLds, kCompact, kThreads>) +
                  (kLds ? ((size_t)prm.n + kReadAhead) * BlockList<Addr, kCompact>::kEntryBytes : 0);
     static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
     if (!attr_set[di.device]) {
@@ -805,11 +802,11 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     if (tiled) ok = ok && launch_plan_tiled(prm, tr->t_end, net, di, stream);
     if (bitmap) ok = ok && launch_plan_bitmap(prm, di, stream);
     // exactly one of the launches does the work; the trace decides which (see the mode word)
-    if (compact) ok = ok && launch_plan<uint32_t, true, true, kPendLds, kThreadsCompact>(prm, grid_compact, di, stream);
-    if (lds32) ok = ok && launch_plan<uint32_t, true, false, kPendLds, kThreadsLds>(prm, grid_lds, di, stream);
-    else       ok = ok && launch_plan<uint32_t, false, false, kPendMem, kThreadsMem>(prm, grid_mem, di, stream);
-    if (lds64) ok = ok && launch_plan<uint64_t, true, false, kPendLds, kThreadsLds>(prm, grid_lds, di, stream);
-    else       ok = ok && launch_plan<uint64_t, false, false, kPendMem, kThreadsMem>(prm, grid_mem, di, stream);
+    if (compact) ok = ok && launch_plan<uint32_t, true, true, kThreadsCompact>(prm, grid_compact, di, stream);
+    if (lds32) ok = ok && launch_plan<uint32_t, true, false, kThreadsLds>(prm, grid_lds, di, stream);
+    else       ok = ok && launch_plan<uint32_t, false, false, kThreadsMem>(prm, grid_mem, di, stream);
+    if (lds64) ok = ok && launch_plan<uint64_t, true, false, kThreadsLds>(prm, grid_lds, di, stream);
+    else       ok = ok && launch_plan<uint64_t, false, false, kThreadsMem>(prm, grid_mem, di, stream);
     if (!ok) return STALLOC_ERR_DEVICE;
 
     uint32_t blocks = (n + 255) / 256;
