@@ -758,7 +758,11 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     const uint32_t n = tr->n;
     const bool lds32 = n <= lds_capacity_entries<uint32_t, false, kThreadsLds>(di.lds_per_block, entry_bytes<uint32_t>());
     const bool lds64 = n <= lds_capacity_entries<uint64_t, false, kThreadsLds>(di.lds_per_block, entry_bytes<uint64_t>());
-    // compact list: 8-byte entries, two workgroups per CU (half the LDS each)
+    // Where the lists leave the LDS follows from what the hole tables need of it.  512 orders, sizes of up to 33 KB and an
+    // odd byte: 7300 requests 13.4 ms in LDS, 8000 in the workspace 16.4 (24.4 and 27.7 before); with 64-bit addresses 4200
+    // 7.6, 5000 10.1 (20.1, 25.9).
+    // Compact list: 8-byte entries, two workgroups per CU (half the LDS each); 1024 orders, 3600 requests 6.3 ms, 5000 with
+    // 16-byte entries 13.1 (12.6, 20.2)
     const bool compact = tr->t_end < 0x10000u &&
                          n <= lds_capacity_entries<uint32_t, true, kThreadsCompact>(di.lds_per_block / 2, sizeof(uint2));
     uint32_t grid_lds = (uint32_t)di.cus, grid_mem = (uint32_t)di.cus * 2, grid_compact = (uint32_t)di.cus * 2;
