@@ -687,6 +687,13 @@ constexpr int kThreadsMem = STALLOC_THREADS_MEM;
 #endif
 constexpr int kThreadsCompact = STALLOC_THREADS_COMPACT;   // two such workgroups share one CU
 
+// Calls from this many requests on prepare the kernel for long traces with few long-lived requests and carry its tables.
+// Shorter calls do without, also those whose lists do not fit LDS: their workspace does not depend on t_end, and the some
+// twenty launches of the preparation cost a call that a bitmap kernel places 70 to 100 us and 28 to 34 MB (7500 requests,
+// 1 order: 2.55 ms, with the preparation 2.63).  Where few requests are long-lived the kernel would gain little there:
+// 8200 requests, 256 orders 8.0 ms in the sorted list and 11.8 with it, 512 orders 12.4 and 11.8 (9000: 14.0 and 13.1).
+constexpr uint32_t kLongListFrom = 9096;
+
 // Entries the LDS-resident list may hold, for a given entry size and LDS budget.
 template <typename Addr, bool kCompact, int kThreads>
 inline uint32_t lds_capacity_entries(size_t lds_budget, size_t bytes_per_entry)
@@ -783,7 +790,7 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     const bool tiled = bitmap && tiled_plan_possible(n, tr->t_end, P, di);
     int32_t* net = bitmap ? cv.take<int32_t>(tiled_plan_words(n)) : nullptr;
     // variant for long traces with few long-lived requests: tables in allocation-time order
-    const bool split = !lds32;
+    const bool split = n >= kLongListFrom;
     SplitWorkspace sw;
     if (split) split_workspace(n, tr->t_end, di, cv, &sw);
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }

@@ -99,6 +99,13 @@ def test_random_traces_of_two_kinds(S, oracle, seed):
     assert got["info"]["granule_log2"] == (0 if odd else 9)
 
 
+@pytest.mark.parametrize("n, kernel", [(7500, "list_memory"), (9095, "list_memory"), (9096, "long_list")])
+def test_both_sides_of_the_shortest_trace_of_the_kernel(S, oracle, n, kernel):
+    rng = np.random.default_rng(n)
+    tr = two_kinds(rng, n, 200, 15, [1 << 20, 3 << 20, 5 << 19], [512, 1024, 4096, 1 << 16, 3 << 9])
+    _compare(S, oracle, tr, _orders(rng, tr, 1), want_kernel=kernel)
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_large_short_lived_blocks_have_a_table_of_their_own(S, oracle, seed):
     """A twelfth to a tenth of the short-lived requests are as large as the long-lived ones, the others

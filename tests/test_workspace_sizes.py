@@ -57,3 +57,21 @@ def test_plans_of_one_length_share_a_workspace(n):
                 assert all(a <= b for a, b in zip(fewer, more)), by_rows
             if n <= S.lib.stalloc_plan_lds_capacity():
                 assert all(len(set(sizes)) == 1 for sizes in by_rows), by_rows
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [7300, 7404, 8200, 9095])
+def test_no_tables_by_allocation_time_up_to_their_length(n):
+    """Calls of up to 9095 requests carry none of the long-list kernel's tables, also where no list fits LDS: one workspace
+    does for every t_end."""
+    import torch
+    import paper_2507_16274_amd as S
+    torch.cuda.init()
+    for P in (1, 512, 4096):
+        sizes = set()
+        for t_end in (1, 2 * n, 4 * n + 4096, 4 * n + 4097, 1 << 20):
+            need = ctypes.c_size_t(0)
+            assert S.lib.stalloc_plan(ctypes.byref(_trace(S, n, t_end)), 256, P, 256, 256, 256, 256, 256, None,
+                                      ctypes.byref(need), None) == 0
+            sizes.add(need.value)
+        assert len(sizes) == 1, (P, sizes)
