@@ -56,11 +56,15 @@ namespace stalloc {
 
 constexpr int kBatch = 256;          // requests fetched per refill
 constexpr int kPend = kWave;         // requests per batch
-constexpr uint32_t kReadAhead = 12;   // blocks behind the list's last one that may be read (and are not used)
+constexpr int kTogether = 4;         // blocks that a scan looks at together
 
 template <typename Addr, bool kLds, bool kCompact, int kThreads>
 struct PlanLds {
     static constexpr int kWaves = kThreads / kWave;
+    static constexpr bool kDirect = kLds && !kCompact;     // the scan reads the list itself
+    // Blocks behind the list's last one that the scan may read (and does not use): it fetches the next group while it
+    // looks at one, up to a group behind the end of a chunk, and only where it reads the list itself.
+    static constexpr uint32_t kReadAhead = kDirect ? kTogether : 0;
     // A wave scans one chunk of the list with a request per lane, or two chunks at a time, half of the lanes each, with two
     // requests per lane (64-bit addresses: what is published per chunk would keep a second workgroup off the CU)
     static constexpr int kHalves = sizeof(Addr) == 8 ? 1 : 2;
@@ -74,7 +78,7 @@ struct PlanLds {
     static constexpr int kCols = kSlots + 1;
     static_assert(kChunks * kCols <= kWave && kSlots > 0, "all holes of a request lie side by side in the lanes of a wave");
     // The scan takes blocks as broadcasts from LDS: from the list itself, or from here (listed in the workspace, or packed)
-    static constexpr int kStaged = kLds && !kCompact ? 1 : sizeof(Addr) == 8 ? kWave / 2 : kWave;
+    static constexpr int kStaged = kDirect ? 1 : sizeof(Addr) == 8 ? kWave / 2 : kWave;
     typename BlockList<Addr, false>::Entry staged[kWaves][kStaged];
     uint64_t rq_size[kBatch];
     uint64_t rq_addr[kBatch];
@@ -98,14 +102,16 @@ struct PlanLds {
     Addr extent_now;                                       // extent of the plan after the last settled batch
 };
 
-// The part of the list that is chunk `c`: chunks are equally long, a multiple of eight blocks; the last one that is not
+// The part of the list that is chunk `c`: chunks are equally long, a multiple of two groups of blocks; the last one that is not
 // empty ends with the list and may begin inside the one before it (a block counted by two chunks changes nothing: what a
 // lower chunk covers is known when holes are judged).  The list is empty or holds at least 64 blocks.
 struct Chunk { uint32_t first, blocks; };
 template <int kChunks>
 __device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
 {
-    const uint32_t blocks = ((count + kChunks - 1) / kChunks + 7) & ~7u;
+    constexpr uint32_t kUnit = 2 * kTogether;
+    static_assert((kUnit & (kUnit - 1)) == 0 && kUnit <= (uint32_t)kPend, "a list that is not empty holds a chunk");
+    const uint32_t blocks = ((count + kChunks - 1) / kChunks + kUnit - 1) & ~(kUnit - 1);
     const uint32_t start = c * blocks;
     const uint32_t end = umin(start + blocks, count);
     return Chunk{start < count ? end - blocks : 0u, start < count ? blocks : 0u};
@@ -120,11 +126,13 @@ __device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
 // requests each, two per lane.  Blocks are looked at four together, so that their compares overlap and one branch asks
 // whether any of them closes a hole.  Published per (chunk, request): the maximum of conflicting end addresses, the
 // start of the first conflicting block, and the first holes behind it with chunk-local "covered".
-template <typename Addr, bool kDirect, typename List, typename Lds>
+template <typename Addr, typename List, typename Lds>
 __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
 {
-    constexpr int kSlots = Lds::kSlots, kTogether = 4, kHalves = Lds::kHalves, kLanes = kWave / kHalves;
+    constexpr bool kDirect = Lds::kDirect;
+    constexpr int kSlots = Lds::kSlots, kHalves = Lds::kHalves, kLanes = kWave / kHalves;
     constexpr uint32_t kPart = Lds::kStaged / kHalves;           // staged blocks per chunk
+    static_assert(kDirect || kPart % (2 * kTogether) == 0, "a part is a whole number of steps, and a step ahead wraps to its start");
     typedef typename BlockList<Addr, false>::Entry Block;
     const int lane = lane_id(), wave = wave_id();
     const int half = lane / kLanes, place = lane % kLanes;
@@ -158,7 +166,7 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
             }
             __builtin_amdgcn_wave_barrier();
         }
-        // (reads behind the part are not looked at; the list has room for kReadAhead blocks behind its last one)
+        // (reads behind the part are not looked at: one group behind a chunk of the list, or the staged part's first one again)
         auto fetch = [&](Block (&block)[kTogether], uint32_t k) {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
@@ -602,7 +610,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
                     const uint64_t growth = wave_sum64(lane < (int)nb ? sh.rq_size[b0 + lane] >> shift : 0ull);
                     if ((uint64_t)sh.extent_now + growth > 0xffffffffull) { outgrown = true; break; }
                 }
-                scan_batch<Addr, kLds && !kCompact>(list, count, b0, nb, shift, sh);
+                scan_batch<Addr>(list, count, b0, nb, shift, sh);
                 __syncthreads();
                 settle_batch<Addr>(list, count, b0, nb, shift, peak, sh);
                 const bool last_of_plan = r0 + b0 + nb >= n;
@@ -698,7 +706,8 @@ constexpr uint32_t kLongListFrom = 9096;
 template <typename Addr, bool kCompact, int kThreads>
 inline uint32_t lds_capacity_entries(size_t lds_budget, size_t bytes_per_entry)
 {
-    const size_t fixed = sizeof(PlanLds<Addr, true, kCompact, kThreads>) + kReadAhead * bytes_per_entry;
+    using Lds = PlanLds<Addr, true, kCompact, kThreads>;
+    const size_t fixed = sizeof(Lds) + Lds::kReadAhead * bytes_per_entry;
     if (lds_budget <= fixed) return 0;
     return (uint32_t)((lds_budget - fixed) / bytes_per_entry);
 }
@@ -707,8 +716,8 @@ template <typename Addr, bool kLds, bool kCompact, int kThreads>
 inline bool launch_plan(const PlanParams& prm, uint32_t grid, const DeviceInfo& di, hipStream_t stream)
 {
     auto kernel = &plan_kernel<Addr, kLds, kCompact, kThreads>;
-    size_t lds = sizeof(PlanLds<Addr, kLds, kCompact, kThreads>) +
-                 (kLds ? ((size_t)prm.n + kReadAhead) * BlockList<Addr, kCompact>::kEntryBytes : 0);
+    using Lds = PlanLds<Addr, kLds, kCompact, kThreads>;
+    size_t lds = sizeof(Lds) + (kLds ? ((size_t)prm.n + Lds::kReadAhead) * BlockList<Addr, kCompact>::kEntryBytes : 0);
     static std::atomic<bool> attr_set[64] = {};        // (set twice at worst when threads race)
     if (!attr_set[di.device]) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from helpers import random_trace
-from test_gpu_parity import _T, _compare_plans
+from test_gpu_parity import _T, _compare_plans, _gpu_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +65,25 @@ def test_both_sides_of_the_lds_limit(S, oracle, beyond):
     tr = _trace(rng, n, "narrow")
     got, _, _ = _compare_plans(S, oracle, tr, _orders(rng, tr, n)[:2], method="lists")
     assert got["info"]["kernel"] == ("list_memory" if beyond else "list_lds")
+
+
+def _longest_with(S, rng, kind, lo, hi, **want):
+    """Length of the longest trace that is placed with the given figures in its report (those of `lo` are, those of `hi` not)."""
+    def holds(n):
+        tr = _trace(rng, n, kind)
+        info = _gpu_plan(S, tr, np.arange(n, dtype=np.uint32)[None])["info"]
+        return all(info[k] == v for k, v in want.items())
+    assert holds(lo) and not holds(hi)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if holds(mid) else (lo, mid)
+    return lo
+
+
+def test_both_sides_of_the_packed_list_s_limit(S, oracle):
+    rng = np.random.default_rng(73)
+    last = _longest_with(S, rng, "compact", 3000, 4200, kernel="list_lds", address_bits=16)
+    for n, bits in ((last, 16), (last + 1, 32)):
+        tr = _trace(rng, n, "compact")
+        got, _, _ = _compare_plans(S, oracle, tr, _orders(rng, tr, n), method="lists")
+        assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == bits
