@@ -55,7 +55,8 @@ def test_more_plans_than_workgroups(S, oracle, kind):
     n, P = 200, 700
     tr = _trace(rng, n, kind)
     orders = np.stack([_orders(rng, tr, n)[k % 4] for k in range(P)])
-    _compare_plans(S, oracle, tr, orders, method="allpairs")
+    got, _, _ = _compare_plans(S, oracle, tr, orders, method="allpairs")
+    assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == BITS[kind]
 
 
 @pytest.mark.parametrize("beyond", [0, 1])
@@ -87,3 +88,36 @@ def test_both_sides_of_the_packed_list_s_limit(S, oracle):
         tr = _trace(rng, n, "compact")
         got, _, _ = _compare_plans(S, oracle, tr, _orders(rng, tr, n), method="lists")
         assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == bits
+
+
+@pytest.mark.parametrize("n_clique, n_extra, kernel", [(1000, 2000, "list_lds"), (2000, 5500, "list_memory")])
+def test_some_of_more_plans_than_workgroups_outgrow_32_bit_counts(S, oracle, n_clique, n_extra, kernel):
+    """Odd byte sizes that stack up to nearly 2^32: a workgroup that gives up a plan tried with 32-bit counts takes the next one
+    that is handed out, and those given up, some of each workgroup's, are placed again with 64-bit addresses."""
+    rng = np.random.default_rng(75)
+    unit = 2 ** 21
+    size = np.concatenate([rng.integers(unit // 2, unit * 3 // 2, n_clique), rng.integers(unit // 4, unit * 2, n_extra)]).astype(np.uint64)
+    size[:n_clique] = size[:n_clique].astype(np.float64) * (0.97 * 2 ** 32 / float(size[:n_clique].sum()))
+    size |= np.uint64(1)
+    ts = np.concatenate([np.zeros(n_clique, np.int64), rng.integers(0, 20 * n_extra, n_extra)])
+    te = np.concatenate([np.full(n_clique, 21 * n_extra, np.int64), ts[n_clique:] + rng.integers(1, 60, n_extra)])
+    n, P = n_clique + n_extra, 600
+    tr = _T(size, ts.astype(np.uint32), te.astype(np.uint32), int(te.max()))
+    some = [rng.permutation(n) for _ in range(3)]
+    some += [np.argsort(ts, kind="stable"), np.argsort(-size.astype(np.int64), kind="stable"), np.arange(n)[::-1]]
+    some = np.stack(some).astype(np.uint32)
+    rows = np.arange(P) % len(some)
+    a, ext = oracle.plan_many(tr.size, tr.t_alloc, tr.t_free, some, method="lists")
+
+    def outgrows(order, at):
+        """The sizes of a batch of 64 on top of all before it need not fit 32 bits."""
+        end = np.maximum.accumulate((at + size)[order])
+        return any(int(end[b - 1] if b else 0) + int(size[order[b:b + 64]].sum()) >= 2 ** 32 for b in range(0, n, 64))
+
+    wide = np.asarray([outgrows(o, x) for o, x in zip(some, a)])
+    assert 0 < wide.sum() < len(some)
+    got = _gpu_plan(S, tr, some[rows])
+    info = got["info"]
+    assert got["status"] == 0 and info["kernel"] == kernel and info["address_bits"] == 32
+    assert info["plans_64bit"] == int(wide[rows].sum())
+    assert np.array_equal(got["peaks"], ext[rows]) and np.array_equal(got["offsets"], a[rows])

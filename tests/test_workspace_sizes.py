@@ -75,3 +75,21 @@ def test_no_tables_by_allocation_time_up_to_their_length(n):
                                       ctypes.byref(need), None) == 0
             sizes.add(need.value)
         assert len(sizes) == 1, (P, sizes)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [10_500, 49_920])
+def test_lists_in_the_workspace_are_as_many_as_workgroups_run(n):
+    """One workgroup per CU places plans with its list in the workspace, two lists of 24-byte entries each."""
+    import torch
+    import paper_2507_16274_amd as S
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def need(P):
+        size = ctypes.c_size_t(0)
+        assert S.lib.stalloc_plan_sized(ctypes.byref(_trace(S, n, 2 * n)), 256, P, 256, 256, None, 256, 256, 1 << 20, 1, None,
+                                        ctypes.byref(size), None) == 0
+        return size.value
+
+    assert need(cus) - need(1) >= (cus - 1) * 2 * 24 * n
+    assert need(4096) - need(cus) <= 4 * 4096 + 256                   # a mark per plan
