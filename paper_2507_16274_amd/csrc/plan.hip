@@ -794,13 +794,18 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     Carver cv(workspace);
     uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* own_offsets = (!offsets && best_offsets) ? cv.take<uint64_t>((size_t)P * n) : nullptr;
-    unsigned char* slabs = lds64 ? nullptr : cv.take<unsigned char>((size_t)grid_mem * 2 * n * entry_bytes<uint64_t>());
     uint32_t* wide_plans = cv.take<uint32_t>(P);
     // occupancy-bitmap variant: lifetime-conflict index of the trace
     uint32_t pool_words[kBitmapShapes];
     const bool bitmap = bitmap_plan_shapes(n, di, pool_words) && allow_bitmap;
     uint32_t* nbr_chunks = bitmap ? cv.take<uint32_t>(n) : nullptr;
-    uint16_t* nbr = bitmap ? cv.take<uint16_t>(bitmap_index_entries(n)) : nullptr;
+    // The index and the lists in the workspace share their room: everything that writes or reads the index is enqueued before
+    // the sorted-list kernels.  (5000 requests, 512 orders: 51 MB of index, 61 MB of lists for traces of 64-bit addresses)
+    const size_t index_bytes = bitmap ? bitmap_index_entries(n) * sizeof(uint16_t) : 0;
+    const size_t slab_bytes = lds64 ? 0 : (size_t)grid_mem * 2 * n * entry_bytes<uint64_t>();
+    unsigned char* room = cv.take<unsigned char>(index_bytes > slab_bytes ? index_bytes : slab_bytes);
+    uint16_t* nbr = bitmap ? reinterpret_cast<uint16_t*>(room) : nullptr;
+    unsigned char* slabs = lds64 ? nullptr : room;
     const bool tiled = bitmap && tiled_plan_possible(n, tr->t_end, P, di);
     int32_t* net = bitmap ? cv.take<int32_t>(tiled_plan_words(n)) : nullptr;
     // variant for long traces with few long-lived requests: tables in allocation-time order
@@ -826,7 +831,8 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     if (split) ok = ok && launch_plan_split(prm, tr->t_end, sw, di, stream);
     if (tiled) ok = ok && launch_plan_tiled(prm, tr->t_end, net, di, stream);
     if (bitmap) ok = ok && launch_plan_bitmap(prm, di, stream);
-    // exactly one of the launches does the work; the trace decides which (see the mode word)
+    // exactly one of the launches does the work; the trace decides which (see the mode word).  (From here on the index of the
+    // bitmap variants may be overwritten.)
     if (compact) ok = ok && launch_plan<uint32_t, true, true, kThreadsCompact>(prm, grid_compact, di, stream);
     if (lds32) ok = ok && launch_plan<uint32_t, true, false, kThreadsLds>(prm, grid_lds, di, stream);
     else       ok = ok && launch_plan<uint32_t, false, false, kThreadsMem>(prm, grid_mem, di, stream);

@@ -93,3 +93,21 @@ def test_lists_in_the_workspace_are_as_many_as_workgroups_run(n):
 
     assert need(cus) - need(1) >= (cus - 1) * 2 * 24 * n
     assert need(4096) - need(cus) <= 4 * 4096 + 256                   # a mark per plan
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [4300, 5000, 5600, 8200, 9095])
+def test_lists_in_the_workspace_lie_where_the_index_of_the_bitmap_kernels_may(n):
+    """A trace is placed by the one or the other, so a call needs room for the larger of the two."""
+    import torch
+    import paper_2507_16274_amd as S
+    torch.cuda.init()
+
+    def need(P, largest_size):
+        size = ctypes.c_size_t(0)
+        assert S.lib.stalloc_plan_sized(ctypes.byref(_trace(S, n, 2 * n)), 256, P, 256, 256, None, 256, 256, largest_size, 1, None,
+                                        ctypes.byref(size), None) == 0
+        return size.value
+
+    index, lists = need(1, 8), need(4096, 1 << 20)                  # with sizes for the bitmap kernels, and without
+    assert need(4096, 8) <= max(index, lists) + 4 * 4096 + 24 * n + (1 << 15)        # (marks, and words per request and timestamp)
