@@ -86,8 +86,10 @@ typedef struct stalloc_trace {
  *   workspace     sized for whatever the trace may turn out to need, which only the device
  *                 learns: for n <= 32768 this includes an index of the request pairs with
  *                 overlapping lifetimes at its upper bound of about 2 n^2 bytes (76 MB for
- *                 n = 6144, 0.8 GB for n = 19840); plus (P x n) x 8 bytes when best_offsets
- *                 is wanted without offsets.
+ *                 n = 6144, 0.8 GB for n = 19840) or, where they need more, lists of placed
+ *                 blocks that do not fit LDS (n > 4266: 48 n bytes for each of at most one plan
+ *                 per CU); plus tables by allocation time that depend on t_end as well (n > 9095);
+ *                 plus (P x n) x 8 bytes when best_offsets is wanted without offsets.
  */
 int stalloc_plan(const stalloc_trace *trace, const uint32_t *orders, uint32_t P,
                  uint64_t *offsets, uint64_t *peaks, uint64_t *best_offsets,

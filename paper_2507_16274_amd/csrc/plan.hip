@@ -9,19 +9,20 @@
 // sorting is needed when a request is placed.  Requests are handled in batches of 64:
 //
 //   scan     One pass over the sorted list serves the whole batch, because the list only
-//            changes between batches.  Each wave owns a run of consecutive entries (its
-//            chunk), a lane holds a request, and every block of the chunk is taken by all 64 lanes
-//            at once: two compares tell whose lifetime it conflicts with, the running maximum of
+//            changes between batches.  The list is cut into chunks of consecutive entries, two for
+//            each wave: half of its lanes take a chunk each, a lane holds two requests, and every block
+//            of the chunk is taken by all its lanes at once (64-bit addresses: a chunk a wave, a request
+//            a lane).  Two compares tell whose lifetime it conflicts with, the running maximum of
 //            the conflicting blocks' end addresses is "covered so far", and a conflicting block that
 //            starts at least size_r above it closes a hole [covered, start) in which r could
-//            fit.  Per (wave, request) the wave publishes its chunk maximum and its first
-//            few holes (with chunk-local "covered") to LDS.
-//   survey   After a barrier, request r's wave gathers what all waves published for it into its
+//            fit.  Per (chunk, request) the chunk's maximum and its first few holes (with
+//            chunk-local "covered") are published to LDS.
+//   survey   After a barrier, request r's wave gathers what was published for it into its
 //            64 lanes in address order; the true "covered" of a hole is the maximum of its
-//            local value and the chunk maxima of the waves below.  The first hole that is large
+//            local value and the maxima of the chunks below.  The first hole that is large
 //            enough is where r lies if the rest of the batch leaves it there, else the top.  If a
-//            wave had more holes than it could publish and no lower one fits, that wave's chunk
-//            is walked again for this one request, with everything below the chunk known.
+//            chunk had more holes than could be published and no lower one fits, it
+//            is walked again for this one request, with everything below it known.
 //   settle   A request clashes when an earlier one of the batch that is alive at the same time lies
 //            where it would.  All waves look for clashes; wave 0 then goes through those requests in
 //            order (all others stay where they are): each takes the first of its holes in which it
@@ -32,7 +33,8 @@
 //            ping-pong between two slabs when it is in the workspace).
 //
 // What bounds it: the scan reads every block as an LDS broadcast (16 bytes, eight cycles of the CU's LDS) and spends six
-// vector instructions on it, per 64 requests; then the chain of clashing requests in wave 0.  6144 requests of 5
+// vector instructions on it, per 64 requests (62 % of the scan's cycles for 49 920 requests, where the list is in the workspace and
+// every part of it is waited for); then the chain of clashing requests in wave 0.  6144 requests of 5
 // sizes, 512 orders (list in LDS): 17.9 -> 8.9 ms against batches of 16 with a lane per block, a running maximum across lanes
 // per request, and wave 0 settling every request; 49 920 requests, 256 orders (list in the workspace): 228 -> 154 ms.
 //
@@ -66,15 +68,11 @@ struct PlanLds {
     // looks at one, up to a group behind the end of a chunk, and only where it reads the list itself.
     static constexpr uint32_t kReadAhead = kDirect ? kTogether : 0;
     // A wave scans one chunk of the list with a request per lane, or two chunks at a time, half of the lanes each, with two
-    // requests per lane (64-bit addresses: what is published per chunk would keep a second workgroup off the CU)
+    // requests per lane (64-bit addresses: what is published for twice the chunks would take 17 KB more from the list)
     static constexpr int kHalves = sizeof(Addr) == 8 ? 1 : 2;
     static constexpr int kChunks = kWaves * kHalves;
-#ifdef STALLOC_HOLE_SLOTS
-    static constexpr int kSlots = STALLOC_HOLE_SLOTS;      // (test builds shrink this to exercise the second walk of a chunk)
-#else
     // holes published per (chunk, request), besides the one in front of the chunk's first conflicting block
     static constexpr int kSlots = sizeof(Addr) == 8 ? 2 : kWave / kChunks - 1;
-#endif
     static constexpr int kCols = kSlots + 1;
     static_assert(kChunks * kCols <= kWave && kSlots > 0, "all holes of a request lie side by side in the lanes of a wave");
     // The scan takes blocks as broadcasts from LDS: from the list itself, or from here (listed in the workspace, or packed)
@@ -120,8 +118,7 @@ __device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
 // One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request (or two), and
 // the blocks of a chunk are taken one at a time, in address order, by all its lanes at once: two lifetime compares, an
 // add, a compare, a maximum and a selection per block and 64 requests, and nothing that crosses lanes.  The block comes
-// as a broadcast from LDS (taken out of a register of a lane it costs four more vector instructions: 283 instead of 209
-// million cycles a plan for 49 920 requests with the list in the workspace); 64 lanes reading 16 bytes keep the LDS busy for
+// as a broadcast from LDS (taken out of a register of a lane it costs four more vector instructions); 64 lanes reading 16 bytes keep the LDS busy for
 // eight cycles whether they read one block or two, so the halves of a wave read a block each and hold all 64
 // requests each, two per lane.  Blocks are looked at four together, so that their compares overlap and one branch asks
 // whether any of them closes a hole.  Published per (chunk, request): the maximum of conflicting end addresses, the
