@@ -51,7 +51,7 @@ KERNEL_NAMES = {"bitmap": "plan_tiled_kernel or plan_bitmap_kernel", "list_lds":
 # known size in the same run; the summaries are under profiles/).  Keyed by (configuration, orders);
 # each entry names the sources of stalloc_plan it was measured with (source_digest() below): with any
 # other sources the figure is not reported.
-MEASURED_TRAFFIC = {(5, 4096): {"bytes": (269_417_611 * 2 + 102_028_224) * 1024, "sources": "d6b1e4d668fe31db"}}
+MEASURED_TRAFFIC = {(5, 4096): {"bytes": (269_386_766 * 2 + 102_027_148) * 1024, "sources": "9ce64989dbeb2067"}}
 
 
 # The sources stalloc_plan and its kernels are built from (the other entry points have files of their own).

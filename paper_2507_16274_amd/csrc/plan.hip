@@ -698,8 +698,9 @@ constexpr int kThreadsCompact = STALLOC_THREADS_COMPACT;   // two such workgroup
 // Calls from this many requests on prepare the kernel for long traces with few long-lived requests and carry its tables.
 // Shorter calls do without, also those whose lists do not fit LDS: their workspace does not depend on t_end, and the some
 // twenty launches of the preparation cost a call that a bitmap kernel places 70 to 100 us and 28 to 34 MB (7500 requests,
-// 1 order: 2.55 ms, with the preparation 2.63).  Where few requests are long-lived the kernel would gain little there:
-// 8200 requests, 256 orders 8.0 ms in the sorted list and 11.8 with it, 512 orders 12.4 and 11.8 (9000: 14.0 and 13.1).
+// 1 order: 2.55 ms, with the preparation 2.63).  Where few requests are long-lived the sorted list is the faster there for
+// few orders (8200 requests, 256 orders: 8.0 ms, the long-list kernel 11.8), as fast for two a CU (512: 12.4 and 11.8) and the
+// slower beyond (768: 16.9 and 11.9; 2048: 39 and 25), which the calls of other traces would pay for.
 constexpr uint32_t kLongListFrom = 9096;
 
 // Entries the LDS-resident list may hold, for a given entry size and LDS budget.

@@ -1,6 +1,7 @@
 """Parity of the sorted-list kernel with the CPU oracle where its batches of 64 requests and its equally long chunks of the
 list can go wrong: lengths around whole batches and chunks, orders whose batches are one chain of clashes, requests that
-see many holes beside blocks that cover most of the list, more plans than workgroups, and both sides of the LDS limit."""
+see many holes beside blocks that cover most of the list, more plans than workgroups, plans handed on to 64-bit addresses, and both
+sides of each layout's LDS limit."""
 
 import numpy as np
 import pytest
@@ -88,6 +89,15 @@ def test_both_sides_of_the_packed_list_s_limit(S, oracle):
         tr = _trace(rng, n, "compact")
         got, _, _ = _compare_plans(S, oracle, tr, _orders(rng, tr, n), method="lists")
         assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == bits
+
+
+def test_both_sides_of_the_limit_of_lists_with_64_bit_addresses(S, oracle):
+    rng = np.random.default_rng(74)
+    last = _longest_with(S, rng, "wide", 3000, 6000, kernel="list_lds")
+    for n, kernel in ((last, "list_lds"), (last + 1, "list_memory")):
+        tr = _trace(rng, n, "wide")
+        got, _, _ = _compare_plans(S, oracle, tr, _orders(rng, tr, n), method="lists")
+        assert got["info"]["kernel"] == kernel and got["info"]["address_bits"] == 64
 
 
 @pytest.mark.parametrize("n_clique, n_extra, kernel", [(1000, 2000, "list_lds"), (2000, 5500, "list_memory")])

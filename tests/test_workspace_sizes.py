@@ -34,7 +34,7 @@ def test_windows_of_orders_share_a_workspace(n):
 @pytest.mark.parametrize("n", [96, 1023, 1024, 2048, 3071, 3072, 6144, 19840, 32768])
 def test_plans_of_one_length_share_a_workspace(n):
     """(the query asks for the device's LDS) Fewer rows never need more; whatever t_end, as long as a list of all placed
-    blocks fits LDS (beyond, tables by allocation time are part of the workspace)."""
+    blocks fits LDS (from 9096 requests on tables by allocation time are part of the workspace)."""
     import torch
     import paper_2507_16274_amd as S
     torch.cuda.init()
