@@ -319,10 +319,12 @@ int stalloc_fuse_groups(const stalloc_trace *trace, const uint32_t *members, con
 /*
  * Informational: what the stalloc_plan call that last used `workspace` did with its trace.
  * Synchronises `hip_stream` (the stream of that call) and reads a few words back; `info` is HOST
- * memory.  Which kernel places a trace is decided on the device, from the trace alone:
+ * memory.  Which kernel places a trace is decided on the device, from the trace alone (short traces: on the
+ * host, from n and P):
  *   STALLOC_KERNEL_BITMAP       per-plan table of placed blocks plus per-request occupancy bitmaps
  *                               in LDS (every size at most 31 granules, n <= 32768, few granules)
- *   STALLOC_KERNEL_LIST_LDS     list of all placed blocks sorted by address, in LDS
+ *   STALLOC_KERNEL_LIST_LDS     list of all placed blocks sorted by address, in LDS, or in registers (up to
+ *                               4096 plans of up to 512 requests)
  *   STALLOC_KERNEL_LIST_MEMORY  the same list in the workspace (traces too long for LDS)
  *   STALLOC_KERNEL_LONG_LIST    sorted list of the long-lived blocks in LDS, short-lived blocks in
  *                               a per-plan table ordered by allocation time (long traces in which

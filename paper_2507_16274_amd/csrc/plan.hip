@@ -793,9 +793,10 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* own_offsets = (!offsets && best_offsets) ? cv.take<uint64_t>((size_t)P * n) : nullptr;
     uint32_t* wide_plans = cv.take<uint32_t>(P);
+    const bool brief = short_plan_possible(n, P);
     // occupancy-bitmap variant: lifetime-conflict index of the trace
     uint32_t pool_words[kBitmapShapes];
-    const bool bitmap = bitmap_plan_shapes(n, di, pool_words) && allow_bitmap;
+    const bool bitmap = bitmap_plan_shapes(n, di, pool_words) && allow_bitmap && !brief;
     uint32_t* nbr_chunks = bitmap ? cv.take<uint32_t>(n) : nullptr;
     // The index and the lists in the workspace share their room: everything that writes or reads the index is enqueued before
     // the sorted-list kernels.  (5000 requests, 512 orders: 51 MB of index, 61 MB of lists for traces of 64-bit addresses)
@@ -816,8 +817,6 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
         return STALLOC_ERR_INVALID_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
-    launch_trace_check(*tr, acc, device_status, stream);
-
     PlanParams prm;
     prm.size = tr->size; prm.ta = tr->t_alloc; prm.tf = tr->t_free; prm.orders = orders;
     prm.offsets = offsets ? offsets : own_offsets;
@@ -825,6 +824,9 @@ static int plan_call(const stalloc_trace* tr, const uint32_t* orders, uint32_t P
     prm.compact_enqueued = compact ? 1u : 0u;
     prm.nbr_chunks = nbr_chunks; prm.nbr = nbr; prm.wide_plans = wide_plans;
     for (int shape = 0; shape < kBitmapShapes; ++shape) prm.bitmap_pool_words[shape] = bitmap ? pool_words[shape] : 0u;
+    if (brief) return launch_plan_short(prm, tr->t_end, best_offsets, best_plan, stream) ? STALLOC_OK : STALLOC_ERR_DEVICE;
+
+    launch_trace_check(*tr, acc, device_status, stream);
     bool ok = true;
     if (split) ok = ok && launch_plan_split(prm, tr->t_end, sw, di, stream);
     if (tiled) ok = ok && launch_plan_tiled(prm, tr->t_end, net, di, stream);

@@ -84,4 +84,13 @@ size_t tiled_plan_words(uint32_t n);                 // its `net`: t_end + 1 wor
 bool launch_plan_tiled(const PlanParams& prm, uint32_t t_end, int32_t* net, const DeviceInfo& di, hipStream_t stream);
 bool launch_plan_bitmap(const PlanParams& prm, const DeviceInfo& di, hipStream_t stream);
 
+// The variant for short traces (plan_short.hip): a wave per plan.  A request costs it more the more register sets the list
+// takes; at 512 requests the occupancy-bitmap kernel, eight waves a plan, comes close where few plans share the chip (64 orders:
+// 480 requests 249 us there, 211 here, the last hundred of them 60 and 60).
+constexpr uint32_t kShortMost = 512;                 // requests
+// One workgroup goes through all plans' extents and flags for the best plan (4096 orders: 3 us beside 70 us and more of placing).
+constexpr uint32_t kShortPlans = 4096;
+bool short_plan_possible(uint32_t n, uint32_t P);
+bool launch_plan_short(const PlanParams& prm, uint32_t t_end, uint64_t* best_offsets, uint32_t* best_plan, hipStream_t stream);
+
 }  // namespace stalloc

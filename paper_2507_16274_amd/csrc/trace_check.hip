@@ -6,29 +6,10 @@
 // sum of sizes counted in granules stays below 2^31 the placement kernel may keep
 // addresses as 32-bit granule counts without any loss.
 #include "host_util.h"
+#include "trace_sums.h"
 #include "wave.h"
 
 namespace stalloc {
-
-// Sums of the high and low halves of the sizes, whether a request is malformed, all bits set in any size, the
-// largest size, the sum of the lifetimes, first allocation and last release.
-struct TraceSums {
-    uint64_t hi, lo, bad, bits, largest, lives;
-    uint32_t t_first, t_last;
-    __device__ __forceinline__ void add(const TraceSums& o)
-    {
-        hi += o.hi; lo += o.lo; bad |= o.bad; bits |= o.bits; largest = umax64(largest, o.largest);
-        lives += o.lives; t_first = umin(t_first, o.t_first); t_last = umax(t_last, o.t_last);
-    }
-    __device__ __forceinline__ void over_wave()                       // in all lanes
-    {
-        hi = wave_sum64(hi); lo = wave_sum64(lo); bad = wave_or64(bad); bits = wave_or64(bits); largest = wave_max64(largest);
-        lives = wave_sum64(lives);
-        t_first = ~read_lane(wave_scan_max(~t_first), kWave - 1); t_last = read_lane(wave_scan_max(t_last), kWave - 1);
-    }
-};
-static_assert(sizeof(TraceSums) == 7 * sizeof(uint64_t), "kAccSpace holds one per workgroup");
-constexpr uint32_t kNever = 0xffffffffu;
 
 // Of the requests that the calling threads take, `step` apart; valid in thread 0 of the workgroup.
 template <int kThreads>
@@ -36,20 +17,9 @@ __device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ s
                                                   const uint32_t* __restrict__ tf, uint32_t n, uint32_t t_end, uint32_t first, uint32_t step)
 {
     __shared__ TraceSums part[kThreads / kWave];
-    TraceSums t = {0, 0, 0, 0, 0, 0, kNever, 0};
+    TraceSums t = TraceSums::none();
 #pragma unroll 4
-    for (uint32_t i = first; i < n; i += step) {
-        const uint64_t s = size[i];
-        const uint32_t a = ta[i], f = tf[i];
-        t.bad |= (s == 0) | (a >= f) | (f > t_end);
-        t.hi += s >> 32;               // n < 2^31 terms below 2^32 each: cannot wrap
-        t.lo += s & 0xffffffffull;
-        t.bits |= s;
-        t.largest = umax64(t.largest, s);
-        t.lives += f - a;              // n terms below 2^32 each
-        t.t_first = umin(t.t_first, a);
-        t.t_last = umax(t.t_last, f);
-    }
+    for (uint32_t i = first; i < n; i += step) t.add(size[i], ta[i], tf[i], t_end);
     t.over_wave();
     if (lane_id() == 0) part[wave_id()] = t;
     __syncthreads();
@@ -61,29 +31,9 @@ __device__ __forceinline__ TraceSums sum_requests(const uint64_t* __restrict__ s
 // The accumulators (the other words are zero) and the status, from the sums over all requests; one thread.
 __device__ __forceinline__ void write_verdict(const TraceSums& t, uint32_t n, uint32_t t_end, uint64_t* acc, uint32_t* status)
 {
-    uint32_t code = STALLOC_OK;
-    uint64_t words[kAccWords] = {t.hi, t.lo, t.bad, t.bits};
-    words[kAccMaxSize] = t.largest;
-    const float span = (float)(t.t_last - t.t_first);                // (a choice between two ways to the same answer: rounding does not matter)
-    words[kAccCrowded] = (float)t.lives * 5.0f > (float)n * span || span * 16.0f < (float)t_end ? 1 : 0;
-    if (t.hi + (t.lo >> 32) < (1ull << 31) && t.bits != 0) {
-        const uint64_t total = (t.hi << 32) + t.lo;                  // below 2^63 here
-        const uint32_t shift = (uint32_t)__builtin_ctzll(t.bits);
-        const uint64_t narrow = (total >> shift) < (1ull << 31) ? kModeNarrow : 0;
-        const uint64_t compact = (total >> shift) < (1ull << 16) ? kModeCompact : 0;
-        const uint64_t bitmap = (total >> shift) <= kBitmapGranules && (t.largest >> shift) <= kBitmapMaxSize ? kModeBitmap : 0;
-        // The sum of sizes bounds every address, but plans worth having end far below it: when the
-        // sum is too large for 32-bit granule counts and no single request is, the 32-bit placement
-        // kernel takes each plan as far as its extent allows and hands the rest to the 64-bit one.
-        const uint64_t try32 = (!narrow && (t.largest >> shift) < (1ull << 30)) ? kModeTry32 : 0;
-        words[kAccMode] = shift | narrow | compact | bitmap | try32;
-        words[kAccGranules] = total >> shift;
-    }
-    // total = hi * 2^32 + lo  >= 2^63  <=>  hi + (lo >> 32) >= 2^31
-    if (t.hi + (t.lo >> 32) >= (1ull << 31)) code = STALLOC_ERR_OVERFLOW;
-    if (t.bad) code = STALLOC_ERR_BAD_TRACE;
+    uint64_t words[kAccWords];
+    *status = verdict(t, n, t_end, words);
     for (int k = 0; k < kAccWords; ++k) acc[k] = words[k];
-    *status = code;
 }
 
 __global__ void __launch_bounds__(1024)
@@ -106,7 +56,7 @@ __global__ void __launch_bounds__(kTraceCheckBlocks) trace_check_finish(const Tr
                                                                         uint32_t* status)
 {
     __shared__ TraceSums of[kTraceCheckBlocks / kWave];
-    TraceSums t = {0, 0, 0, 0, 0, 0, kNever, 0};
+    TraceSums t = TraceSums::none();
     if (threadIdx.x < parts) t = part[threadIdx.x];
     t.over_wave();
     if (lane_id() == 0) of[wave_id()] = t;

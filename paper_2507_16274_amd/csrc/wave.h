@@ -192,6 +192,15 @@ __device__ __forceinline__ uint64_t write_lane(uint64_t v, uint64_t value, int l
     return (int)(threadIdx.x & (kWave - 1)) == lane ? value : v;
 }
 
+// The same by one instruction; value and lane are uniform.  (This compiler has the instruction as an intrinsic without a builtin;
+// in an asm statement it would not keep the wait states between a scalar's last vector write and this read of it.)
+extern "C" __device__ __attribute__((const)) uint32_t stalloc_writelane(uint32_t value, uint32_t lane, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t set_lane(uint32_t v, uint32_t value, int lane) { return stalloc_writelane(value, (uint32_t)lane, v); }
+__device__ __forceinline__ uint64_t set_lane(uint64_t v, uint64_t value, int lane)
+{
+    return ((uint64_t)set_lane((uint32_t)(v >> 32), (uint32_t)(value >> 32), lane) << 32) | set_lane((uint32_t)v, (uint32_t)value, lane);
+}
+
 // Value held by lane `src` (any lane index per lane; goes through the LDS crossbar).
 __device__ __forceinline__ uint32_t lane_gather(uint32_t v, int src)
 {
