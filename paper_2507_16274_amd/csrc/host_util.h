@@ -88,6 +88,7 @@ constexpr int kAccCrowded = 13;                // 1: the mean lifetime is more t
 constexpr int kAccTilesMissed = 12;            // plans that outgrew its tables and are left to the other bitmap kernel
 constexpr int kAccNextPlan = 14;               // sorted-list kernel: plans handed out so far beyond one per workgroup
 constexpr int kAccNextWide = 15;               // and by its instantiation with 64-bit addresses (two of them may run in one call)
+constexpr int kAccUnsorted = 14;               // (stalloc_validate) 1: requests are not numbered by allocation time
 constexpr uint64_t kModeNarrow = 1ull << 8;
 constexpr uint64_t kModeCompact = 1ull << 9;   // sum of sizes in granules below 2^16 as well
 constexpr uint64_t kModeBitmap = 1ull << 10;   // sum <= kBitmapGranules and every size <= kBitmapMaxSize granules

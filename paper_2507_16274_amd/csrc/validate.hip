@@ -1,13 +1,11 @@
 // stalloc_validate: pairwise check of the planning constraint of Sec. 5.1 -- no two
 // allocation decisions may conflict in lifespan and in address range at once.
 //
-// Two forms of the same count.  val_tile tests all n(n-1)/2 unordered pairs of every plan: the
+// Two forms of the same count.  val_pairs tests all n(n-1)/2 unordered pairs of every plan: the
 // pair space is cut into 256 x 256 tiles (upper triangle only); one workgroup owns one tile of
 // one plan: each thread keeps its own request i in registers and walks the 256 requests j of the
-// tile, which sit in LDS and are read as broadcasts.  val_near puts the requests into buckets of
-// like lifetime and allocation time first and leaves out what cannot meet in time (see there); in
-// traces whose requests live for a fifth of the time on average there is little to leave out, and
-// the launch for one plan takes the first form (the trace check has found out, see kAccCrowded).
+// tile, which sit in LDS and are read as broadcasts.  val_near puts the short-lived requests in order of
+// time and the long-lived ones in order of address first and leaves out what cannot meet (see there).
 // Per plan both accumulate the number of conflicting pairs and the smallest key (i << 32 | j),
 // i < j, which is the lexicographically first conflicting pair.
 #include "host_util.h"
@@ -17,19 +15,21 @@ namespace stalloc {
 
 constexpr int kValTile = 256;
 
-// val_near is part of calls of at least this many requests^2 x plans: its five preparing launches cost 20 to 30 us
-// (10 in a crowded trace, where they return at once), against 210 us and more that all pairs take from here on.
-// Lifetimes of all lengths, all pairs / val_near: 40 000 requests, one plan 219 / 97 us; 6144 requests, 40 plans
-// 213 / 110; 100 000 requests, 16 plans 18.9 / 2.2 ms.  Lifetimes a third of the time long: 220 / 217, 328 / 300,
-// 18.9 / 10.1.  From 3.5e8 on, where they would pay in sparse traces, crowded ones took up to twice as long.
+// val_near is part of calls of at least this many requests^2 x plans: its seven further launches cost some 35 us, all pairs
+// take 50 us and more from here on (all pairs / val_near: 6144 requests, 10 plans 64 / 49 us; 19 612 requests, one plan 64 / 44;
+// 960 requests, 440 plans 87 / 59).
 #ifndef STALLOC_VAL_NEAR_FROM
-#define STALLOC_VAL_NEAR_FROM (1500ull * 1000 * 1000)
+#define STALLOC_VAL_NEAR_FROM (300ull * 1000 * 1000)
 #endif
 constexpr uint64_t kVnFrom = STALLOC_VAL_NEAR_FROM;
-// Below these a wave takes one plan and looks whether the trace is crowded (four plans share a look at the lifetimes
-// otherwise, and are as fast as all pairs in a crowded trace, but need enough waves: 20 000 requests, 4
-// plans, crowded: 260 us all pairs, 295 four together; 40 000 requests, 4 plans 790 / 640).
-constexpr uint64_t kVnTogether = 3000ull * 1000 * 1000, kVnThree = 10000ull * 1000 * 1000;
+constexpr size_t kVnRoom = (size_t)128 << 20;    // what the plans that are gone through together take of the workspace
+constexpr uint32_t kVnGroup = 65535;             // (largest grid.y)
+// Waves that are resident.  They take the units of work of a few plans (199 748 requests, one plan 64 us, 76 with twice as many
+// waves); with many plans a wave has few units, and twice as many even out (6144 requests, 512 plans 217 -> 206 us).
+constexpr uint64_t kVnResident = 256 * 24;
+// With fewer units than this a unit takes 64 boxes instead of 256, so that there are enough of them (49 920 requests, one plan,
+// val_near alone 65 -> 35 us).
+constexpr uint64_t kVnFewUnits = 4 * kVnResident;
 
 __global__ void val_init(uint64_t* conflicts, uint64_t* first_key, uint32_t P)
 {
@@ -39,12 +39,17 @@ __global__ void val_init(uint64_t* conflicts, uint64_t* first_key, uint32_t P)
     }
 }
 
-// One tile of one plan; called by a workgroup of 256 threads.
-__device__ __forceinline__ void val_tile(uint64_t (&j_lo)[kValTile], uint64_t (&j_hi)[kValTile], uint32_t (&j_ta)[kValTile],
-                                         uint32_t (&j_tf)[kValTile], const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta,
-                                         const uint32_t* __restrict__ tf, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles,
-                                         uint32_t lin, uint32_t p, uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
+// One tile of one plan.
+__global__ void __launch_bounds__(kValTile)
+val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf,
+          const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0,
+          uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
 {
+    __shared__ uint64_t j_lo[kValTile];
+    __shared__ uint64_t j_hi[kValTile];
+    __shared__ uint32_t j_ta[kValTile];
+    __shared__ uint32_t j_tf[kValTile];
+    const uint32_t p = plan0 + blockIdx.y, lin = blockIdx.x;
     // linear tile index -> (ti, tj) with ti <= tj, row-major over the upper triangle
     const double nt = (double)tiles;
     uint32_t ti = (uint32_t)((2.0 * nt + 1.0 - sqrt((2.0 * nt + 1.0) * (2.0 * nt + 1.0) - 8.0 * (double)lin)) * 0.5);
@@ -101,30 +106,20 @@ __device__ __forceinline__ void val_tile(uint64_t (&j_lo)[kValTile], uint64_t (&
     }
 }
 
-__global__ void __launch_bounds__(kValTile)
-val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf,
-          const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0,
-          uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
-{
-    __shared__ uint64_t j_lo[kValTile];
-    __shared__ uint64_t j_hi[kValTile];
-    __shared__ uint32_t j_ta[kValTile];
-    __shared__ uint32_t j_tf[kValTile];
-    val_tile(j_lo, j_hi, j_ta, j_tf, size, ta, tf, offsets, n, tiles, blockIdx.x, plan0 + blockIdx.y, conflicts, first_key, status);
-}
-
 // ------------------------------------------------------------------------------------------
-// Pairs that can meet in time.  A training trace holds few pairs with overlapping lifetimes
-// (3.5e8 of 2.0e10 for the 200k requests of an interleaved schedule), and which ones they are does
-// not depend on the plan.  The requests are put, once per call, into buckets of (lifetime class,
-// allocation time); 64 neighbours of that sequence make a tile with a span [first allocation, last
-// release).  Short-lived requests fill tiles of short spans, long-lived ones tiles of their own at
-// the end of the sequence, so that a tile of the first kind meets its neighbours and the tiles of
-// the second kind, and nothing else is looked at.  Which request of a bucket comes first does not
-// matter: the results are a sum and a minimum over the request numbers.
-//   Bound by the integer rate on many plans (6144 requests x 1024 plans: 1.16 ms, all pairs 4.76 ms) and by
-// the chain load -> address gather -> LDS of a wave's tiles on one (199 748 requests: 0.23 ms, of which 0.19
-// ms val_one_plan, all pairs 4.73 ms; an integer floor of 0.07 ms for its 3.5e8 pairs).
+// Pairs that can meet.  In a plan worth checking few pairs meet in time and in address range, and which of the two says
+// so sooner depends on the pair.  Requests that live shortly meet few others in time, whatever their addresses are (thousands
+// of them share the lowest addresses); requests that live long meet a large part of all others in time, but few in
+// address range (that is what keeps the plan free of conflicts).  So the requests are put, once per call, into buckets of (lifetime
+// class, allocation time), and the long-lived ones, which come last, into buckets by address for each plan.  64 neighbours are a
+// tile with a box, a span of time and of addresses: short spans of time for the short-lived, of addresses for the long-lived.
+// A wave takes a tile, a request a lane, and holds it against the boxes of the tiles at and behind it: few of its requests meet a
+// box, most of them none.  Only then is the other tile looked at, request by request.
+// Which request of a bucket comes first does not matter: the results are a sum and a minimum over the request numbers.
+//   Bound by chains of loads (a tile, its boxes, the tiles that it meets) with few waves, by vector issue with many.  All
+// tiles of requests that meet in time, by request / this: 199 748 requests, one plan 227 / 68 us, of which val_near 29 (before 185);
+// 6144 requests, 512 plans 598 / 215; 49 920 requests, 8 plans 478 / 161.  With the long-lived tile in the lanes and the short ones
+// loaded one after the other, each a round trip to memory, val_near took 216 us on the first of these.
 constexpr uint32_t kVnTile = 64;
 constexpr uint32_t kVnWaves = 4;
 constexpr uint32_t kVnRow = kVnTile + 4;         // (the walk over a tile's requests takes four at a time)
@@ -135,6 +130,7 @@ constexpr uint32_t kVnRow = kVnTile + 4;         // (the walk over a tile's requ
 struct VnBuckets {
     uint32_t base, t_end, count;
     uint32_t apart;              // counters lie 2^apart words apart: on a coarse clock there are few, and atomics on one line of memory queue up
+    uint32_t lasting;            // classes from here on are long-lived
     __host__ __device__ uint32_t shift_of(uint32_t k) const { return k == 0 ? base : (base + k > 2 ? base + k - 2 : 0u); }
     __host__ __device__ uint32_t in_class(uint32_t k) const { return (t_end >> shift_of(k)) + 1; }
     __device__ uint32_t of(uint32_t ta, uint32_t tf) const            // place of the counter
@@ -146,39 +142,69 @@ struct VnBuckets {
         return (first + ((ta < t_end ? ta : t_end) >> shift_of(cls))) << apart;
     }
     __host__ __device__ uint32_t words() const { return count << apart; }
+    __device__ uint32_t longest_short() const { return base + lasting > 32 ? 0xffffffffu : 1u << (base + lasting - 1); }   // (and what is shorter)
+    __host__ __device__ uint32_t before_lasting() const               // buckets of the short-lived classes
+    {
+        uint32_t first = 0;
+        for (uint32_t k = 0; k < lasting && k <= 32 - base; ++k) first += in_class(k);
+        return first;
+    }
 };
 
 static VnBuckets vn_buckets(uint32_t n, uint32_t t_end)
 {
-    VnBuckets b = {0, t_end, 0, 0};
+    VnBuckets b = {0, t_end, 0, 0, 1};
     while (b.base < 31 && ((uint64_t)n << b.base) < (uint64_t)t_end * kVnTile) ++b.base;
     for (uint32_t k = 0; k <= 32 - b.base; ++k) b.count += b.in_class(k);
     while (b.apart < 5 && b.count << b.apart < 4096) ++b.apart;
+    // With c requests alive at once a request meets about 2 c others in time and, as each of them has a c-th of the
+    // addresses, 2 n / c in address range: long-lived is what lives while more than the square root of n are allocated.
+    while (b.lasting < 31 && ((uint64_t)kVnTile << b.lasting) * (kVnTile << b.lasting) <= n) ++b.lasting;
     return b;
 }
 
-// Tiles of second requests per wave: few, so that a small trace still gives the chip enough waves (6144
-// requests, 4 plans: 62 us with 4 tiles a wave, 136 us with 16, 241 us with 64), but on long traces nearly
-// all (wave, chunk) pairs have nothing to do and cost a workgroup's start each (199 748 requests, one
-// plan: 332 us with 4, 245 us with 16, 294 us with 64; 49 920: 131 us with 4, 166 us with 16).
-static uint32_t vn_chunk(uint32_t tiles) { return tiles <= 1024 ? 4u : 16u; }
-
 struct VnSorted {
     uint32_t* bucket;        // [buckets.words()] requests per bucket, then where the next one of the bucket goes
+    uint32_t* shorts_in;     // [n / 256] short-lived requests among 256 (and then: in front of them)
+    uint32_t* shorts;        // [1] how many requests are short-lived: the first ones in bucket order
     uint2* life;             // [n] in bucket order: lifetime,
     uint64_t* size;          //     size
     uint32_t* id;            //     and number of the request
-    uint2* span;             // [tiles] first allocation, last release
 };
 
-// acc: nullptr when the all-pairs form is not part of the launch that follows.
-__device__ __forceinline__ bool left_to_all_pairs(const uint64_t* acc) { return acc && acc[kAccCrowded]; }
+struct Range { uint64_t lo, hi; };
+struct VnBox { uint64_t lo, hi; uint32_t t_first, t_last; };
+// Of every plan of a group: address ranges in bucket order, those of the long-lived in order of their start; the latter's lifetimes
+// and numbers.
+struct VnPlans {
+    uint64_t* top;           // [plans] highest end of a long-lived request
+    uint64_t* start;         // [plans][n] start addresses of the long-lived in bucket order (from place 0)
+    Range* range;            // [plans][n] short-lived in bucket order, then long-lived by address
+    uint2* life;             // [plans][n] of the long-lived (from place 0)
+    uint32_t* id;            // [plans][n]
+    VnBox* box;              // [plans][tiles] of the short-lived, then of the long-lived
+};
 
-__global__ void __launch_bounds__(256) vn_clear(uint32_t* bucket, uint32_t buckets, uint64_t* conflicts, uint64_t* first_key, uint32_t P)
+// Most traces number their requests by allocation time.  Then the short-lived ones are in the order they are wanted in, and only have
+// to be told from the others: shorts_in[k] of the requests 256 k .. are short-lived.
+__device__ __forceinline__ bool vn_short(const VnBuckets& b, uint32_t ta, uint32_t tf) { return tf - ta < b.longest_short(); }
+
+__global__ void __launch_bounds__(256) vn_clear(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, VnSorted s,
+                                                uint64_t* conflicts, uint64_t* first_key, uint32_t P, uint64_t* top, uint32_t group, uint64_t* acc)
 {
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < buckets || k < P; k += gridDim.x * blockDim.x) {
-        if (k < buckets) bucket[k] = 0;
+    const uint32_t buckets = b.words(), first = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t k = first; k < buckets || k < P; k += gridDim.x * 256) {
+        if (k < buckets) s.bucket[k] = 0;
         if (k < P) { conflicts[k] = 0; first_key[k] = ~0ull; }
+        if (k < group) top[k] = 0;                                    // (group <= P)
+    }
+    const bool crowded = acc[kAccCrowded] != 0;
+    for (uint32_t i0 = blockIdx.x * 256; i0 < n; i0 += gridDim.x * 256) {                      // (uniform trip count)
+        const uint32_t i = i0 + threadIdx.x;
+        const uint32_t a = i < n ? ta[i] : 0u, f = i < n ? tf[i] : 0u;
+        if (__builtin_amdgcn_ballot_w64(i + 1 < n && a > ta[i + 1 < n ? i + 1 : 0]) && lane_id() == 0) acc[kAccUnsorted] = 1;
+        const int many = __syncthreads_count(i < n && !crowded && vn_short(b, a, f));
+        if (threadIdx.x == 0) s.shorts_in[i0 / 256] = (uint32_t)many;
     }
 }
 
@@ -202,46 +228,69 @@ __device__ __forceinline__ uint32_t vn_take(uint32_t* bucket, uint32_t mine, boo
     return place;
 }
 
+// A crowded trace (a fifth of all requests alive at once, or a clock of which it covers little) has no short-lived requests
+// worth the name: all count as long-lived, in the order that they have.
 __global__ void __launch_bounds__(256)
 vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, uint32_t* bucket, const uint64_t* acc)
 {
-    if (left_to_all_pairs(acc)) return;
+    if (acc[kAccCrowded] || !acc[kAccUnsorted]) return;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         vn_take(bucket, i < n ? b.of(ta[i], tf[i]) : 0u, i < n);
     }
 }
 
-// Exclusive sums of the bucket sizes, in place; one workgroup, four buckets a thread and step.
-__global__ void __launch_bounds__(1024) vn_starts(uint32_t* bucket, uint32_t buckets, uint32_t apart, const uint64_t* acc)
+// Exclusive sums of the bucket sizes (of shorts_in, when that is all), in place; one workgroup, four a thread and step.
+__global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint32_t n, const uint64_t* acc)
 {
     __shared__ uint32_t part[16];
-    if (left_to_all_pairs(acc)) return;
+    const bool by_bucket = acc[kAccUnsorted] && !acc[kAccCrowded];
+    uint32_t* counted = by_bucket ? s.bucket : s.shorts_in;
+    const uint32_t many = by_bucket ? b.count : (n + 255) / 256, apart = by_bucket ? b.apart : 0u, lasting = by_bucket ? b.before_lasting() : many;
     uint32_t carry = 0;
-    for (uint32_t k0 = 0; k0 < buckets; k0 += 4096) {
+    for (uint32_t k0 = 0; k0 < many; k0 += 4096) {
         const uint32_t k = k0 + 4 * threadIdx.x;
         uint32_t v[4], mine = 0;
-        for (int u = 0; u < 4; ++u) { v[u] = k + u < buckets ? bucket[(k + u) << apart] : 0u; mine += v[u]; }
+        for (int u = 0; u < 4; ++u) { v[u] = k + u < many ? counted[(k + u) << apart] : 0u; mine += v[u]; }
         const uint32_t incl = wave_scan_add(mine);
         __syncthreads();                                              // (the step before has read part[])
         if (lane_id() == kWave - 1) part[wave_id()] = incl;
         __syncthreads();
         uint32_t before = carry + incl - mine;
         for (int w = 0; w < 16; ++w) { if (w < wave_id()) before += part[w]; carry += part[w]; }
-        for (int u = 0; u < 4; ++u) { if (k + u < buckets) bucket[(k + u) << apart] = before; before += v[u]; }
+        for (int u = 0; u < 4; ++u) {
+            if (k + u < many) counted[(k + u) << apart] = before;
+            if (k + u == lasting && k + u < many) *s.shorts = before;
+            before += v[u];
+        }
     }
+    if (threadIdx.x == 0 && lasting >= many) *s.shorts = carry;
 }
 
 __global__ void __launch_bounds__(256)
 vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n,
            VnBuckets b, VnSorted s, const uint64_t* acc)
 {
-    if (left_to_all_pairs(acc)) return;
+    __shared__ uint32_t part[4];
+    const bool crowded = acc[kAccCrowded] != 0, sorted = crowded || !acc[kAccUnsorted];        // (uniform)
+    const uint32_t shorts = *s.shorts;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         const bool valid = i < n;
         const uint32_t a = valid ? ta[i] : 0u, f = valid ? tf[i] : 0u;
-        const uint32_t at = vn_take(s.bucket, b.of(a, f), valid);      // < n: the buckets hold every request once
+        uint32_t at;                                                   // < n: every place is taken once
+        if (sorted) {
+            const bool brief = valid && !crowded && vn_short(b, a, f);
+            const uint64_t wave_shorts = __builtin_amdgcn_ballot_w64(brief);
+            __syncthreads();                                           // (the step before has read part[])
+            if (lane_id() == 0) part[wave_id()] = (uint32_t)__builtin_popcountll(wave_shorts);
+            __syncthreads();
+            uint32_t before = s.shorts_in[i0 / 256] + lanes_below(wave_shorts);
+            for (int w = 0; w < wave_id(); ++w) before += part[w];
+            at = brief ? before : shorts + (i - before);
+        } else {
+            at = vn_take(s.bucket, b.of(a, f), valid);
+        }
         if (!valid) continue;
         s.life[at] = make_uint2(a, f);
         s.size[at] = size[i];
@@ -249,199 +298,209 @@ vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, c
     }
 }
 
-// One wave: the span of tile t.
-__device__ __forceinline__ void vn_span(const VnSorted& s, uint32_t n, uint32_t t)
+__device__ __forceinline__ VnBox vn_box(bool ok, const Range& r, const uint2& life)     // of the requests in a wave's lanes
 {
-    const uint32_t k = t * kVnTile + lane_id();
-    const uint2 l = k < n ? s.life[k] : make_uint2(0xffffffffu, 0u);
-    const uint32_t first = ~read_lane(wave_scan_max(~l.x), kWave - 1), last = read_lane(wave_scan_max(l.y), kWave - 1);
-    if (lane_id() == 0) s.span[t] = make_uint2(first, last);
+    return VnBox{wave_min64(ok ? r.lo : ~0ull), wave_max64(ok ? r.hi : 0ull),
+                 ~read_lane(wave_scan_max(ok ? ~life.x : 0u), kWave - 1), read_lane(wave_scan_max(ok ? life.y : 0u), kWave - 1)};
 }
 
-__global__ void __launch_bounds__(256) vn_spans(VnSorted s, uint32_t n, uint32_t tiles, const uint64_t* acc)
+// The address ranges of a plan in bucket order, and the boxes of its short-lived tiles.
+__global__ void __launch_bounds__(256)
+vn_ranges(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0, VnPlans v, uint32_t* status)
 {
-    const uint32_t t = blockIdx.x * kVnWaves + (uint32_t)wave_id();
-    if (t >= tiles || left_to_all_pairs(acc)) return;                       // (uniform)
-    vn_span(s, n, t);
+    const uint32_t k = blockIdx.x * 256 + threadIdx.x, p = blockIdx.y, shorts = *s.shorts;
+    const size_t row = (size_t)p * n;
+    uint64_t hi = 0;                                                  // of a long-lived request
+    Range r = {0, 0};
+    if (k < n) {
+        const uint64_t lo = offsets[(size_t)(plan0 + p) * n + s.id[k]], size = s.size[k];
+        // an address range that would run past 2^64 is reported, and kept from wrapping so that what
+        // it covers still counts
+        const bool wraps = lo + size < lo;
+        if (wraps) atomicMax(status, (uint32_t)STALLOC_ERR_OVERFLOW);
+        r = Range{lo, wraps ? ~0ull : lo + size};
+        if (k < shorts) v.range[row + k] = r;
+        else { v.start[row + k - shorts] = lo; hi = r.hi; }
+    }
+    const uint64_t top = wave_max64(hi);
+    if (lane_id() == 0 && top) atomicMax((unsigned long long*)&v.top[p], (unsigned long long)top);
+    if (k - lane_id() >= shorts) return;                              // (uniform in a wave, and the rest is by waves)
+    const VnBox box = vn_box(k < shorts, r, k < shorts ? s.life[k] : make_uint2(0u, 0u));
+    if (lane_id() == 0) v.box[(size_t)p * tiles + k / kVnTile] = box;
 }
 
-// One wave = one tile of first requests (a lane each) x up to `chunk` tiles of second requests at or
-// behind it, for kPlans plans.  Tiles whose spans do not meet drop out together, requests of the
-// others that do not meet the first tile's span 64 at a time; what is left is put into LDS and
-// taken one by one as broadcasts: two lifetime compares for all plans, two address compares a plan.
-// The records of the next tile but one and the addresses of the next are on their way meanwhile.
-// A group of plans beyond the last plan repeats that one, and leaves out its results.
-struct Range { uint64_t lo, hi; };
-template <int kPlans>
+// The long-lived requests of a plan in buckets of their start addresses, and their tiles' boxes; one workgroup a plan.
+__global__ void __launch_bounds__(1024) vn_by_address(VnSorted s, uint32_t n, uint32_t tiles, uint32_t place_bits, VnPlans v)
+{
+    extern __shared__ uint32_t bucket[];                              // 2^place_bits
+    __shared__ uint32_t part[16];
+    const uint32_t p = blockIdx.x, shorts = *s.shorts, longs = n - shorts, step = blockDim.x, waves = step / kWave;
+    if (longs == 0) return;
+    const size_t row = (size_t)p * n;
+    const uint64_t top = v.top[p];
+    const uint32_t top_bits = top ? 64 - (uint32_t)__builtin_clzll(top) : 0u, shift = top_bits > place_bits ? top_bits - place_bits : 0u;
+    const uint32_t buckets = 1u << place_bits, per = (buckets + step - 1) / step;       // (buckets a thread sums up)
+    constexpr int kAhead = 4;                                         // requests a thread, or tiles a wave, has under way together
+    for (uint32_t k = threadIdx.x; k < buckets; k += step) bucket[k] = 0;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < longs; k += kAhead * step) {
+        uint64_t lo[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) lo[u] = v.start[row + umin(k + u * step, longs - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (k + u * step < longs) atomicAdd(&bucket[lo[u] >> shift], 1u);
+    }
+    __syncthreads();
+    const uint32_t k0 = threadIdx.x * per;
+    uint32_t mine = 0;
+    for (uint32_t u = 0; u < per; ++u) mine += k0 + u < buckets ? bucket[k0 + u] : 0u;
+    const uint32_t incl = wave_scan_add(mine);
+    if (lane_id() == kWave - 1) part[wave_id()] = incl;
+    __syncthreads();
+    uint32_t before = incl - mine;
+    for (int w = 0; w < wave_id(); ++w) before += part[w];
+    for (uint32_t u = 0; u < per && k0 + u < buckets; ++u) {
+        const uint32_t many = bucket[k0 + u];
+        bucket[k0 + u] = before;
+        before += many;
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < longs; k += kAhead * step) {
+        uint64_t lo[kAhead], size[kAhead];
+        uint2 life[kAhead];
+        uint32_t id[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t at = umin(k + u * step, longs - 1);
+            lo[u] = v.start[row + at]; size[u] = s.size[shorts + at]; life[u] = s.life[shorts + at]; id[u] = s.id[shorts + at];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (k + u * step >= longs) break;
+            const uint32_t at = atomicAdd(&bucket[lo[u] >> shift], 1u);      // < longs: the buckets hold every one of them once
+            v.range[row + shorts + at] = Range{lo[u], lo[u] + size[u] < lo[u] ? ~0ull : lo[u] + size[u]};
+            v.life[row + at] = life[u];
+            v.id[row + at] = id[u];
+        }
+    }
+    __syncthreads();                                                  // (what this workgroup has written is read by itself)
+    VnBox* box = v.box + (size_t)p * tiles + (shorts + kVnTile - 1) / kVnTile;
+    for (uint32_t t0 = (uint32_t)wave_id(); t0 * kVnTile < longs; t0 += kAhead * waves) {
+        Range r[kAhead];
+        uint2 l[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t k = umin((t0 + u * waves) * kVnTile + lane_id(), longs - 1);
+            r[u] = v.range[row + shorts + k];
+            l[u] = v.life[row + k];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t t = t0 + u * waves;
+            const VnBox of = vn_box(t * kVnTile + lane_id() < longs, r[u], l[u]);
+            if (lane_id() == 0 && t * kVnTile < longs) box[t] = of;
+        }
+    }
+    if (threadIdx.x == 0) v.top[p] = 0;                               // (for the next group of plans)
+}
+
+// All pairs of a plan that can meet.  A unit of work is a first tile and 64 kBoxes second tiles at or behind it, whose boxes the
+// wave takes in turn as scalars; `waves` waves a plan take the units in turn (how many tiles there are is known on the device only).
 struct ValNearLds {
     uint4 who[kVnWaves][kVnRow];                                      // t_alloc, t_free, number, place in the tile
-    Range range[kVnWaves][kPlans][kVnRow];
+    Range range[kVnWaves][kVnRow];
 };
+struct VnRecord { uint2 life; Range range; uint32_t id; };
 
-template <int kPlans>
-__device__ __forceinline__ void val_near(ValNearLds<kPlans>& sh, const VnSorted& s, const uint64_t* __restrict__ offsets, uint32_t n,
-                                         uint32_t tiles, uint32_t chunk, uint32_t p0, uint32_t plan_end, uint64_t* conflicts,
-                                         uint64_t* first_key, uint32_t* status)
+template <uint32_t kBoxes>
+__global__ void __launch_bounds__(kVnWaves * kWave, 6)
+val_near(VnSorted s, VnPlans v, uint32_t n, uint32_t box_row, uint32_t plan0, uint32_t plans, uint32_t waves, uint64_t* conflicts,
+         uint64_t* first_key)
 {
-    auto& sh_who = sh.who;
-    auto& sh_range = sh.range;
+    __shared__ ValNearLds sh;
     const int lane = lane_id(), wave = wave_id();
-    // workgroup -> (chunk c of second requests, four tiles g of first requests): with r = chunk / 4 chunk c has
-    // r (c + 1) groups of four tiles at or in front of it, numbered from r c (c + 1) / 2 on
-    const uint64_t r = chunk / kVnWaves;
-    uint32_t c = (uint32_t)((sqrt(1.0 + 8.0 * (double)blockIdx.x / (double)r) - 1.0) * 0.5);
-    while (r * c * (c + 1) / 2 > blockIdx.x) --c;
-    while (r * (c + 1) * (c + 2) / 2 <= blockIdx.x) ++c;
-    const uint32_t it = uniform((uint32_t)(blockIdx.x - r * c * (c + 1) / 2) * kVnWaves + (uint32_t)wave);
-    if (it >= tiles) return;                                          // (uniform; the waves do not meet)
-    const uint2 span = s.span[it];
-    const uint32_t first_jt = uniform(c * chunk);
-    uint64_t near = 0;
-    {
-        const uint32_t jt = first_jt + lane;
-        const bool is = (uint32_t)lane < chunk && jt < tiles && jt >= it;
-        const uint2 other = s.span[is ? jt : it];
-        near = __builtin_amdgcn_ballot_w64(is && other.x < span.y && span.x < other.y);
-    }
-    // the requests with a malformed lifetime meet nothing, but an address range that would wrap is looked for in all
-    const bool own_chunk = it / chunk == c;
-    if (near == 0 && !own_chunk) return;
-    const uint32_t at_i = it * kVnTile + lane;
-    const bool i_ok = at_i < n;
-    const uint2 life_i = i_ok ? s.life[at_i] : make_uint2(0xffffffffu, 0u);
-    const uint32_t id_i = i_ok ? s.id[at_i] : 0u;
-    // the second request of this lane: record of tile jt, then its addresses
-    struct Record { uint2 life; uint64_t size; uint32_t id; };
-    auto record_of = [&](uint64_t tiles_left) -> Record {
-        const uint32_t at = (first_jt + (tiles_left ? (uint32_t)__builtin_ctzll(tiles_left) : 0u)) * kVnTile + lane;
-        const bool ok = tiles_left != 0 && at < n;
-        const uint32_t k = ok ? at : 0u;
-        Record q = {s.life[k], s.size[k], s.id[k]};
-        if (!ok) q.life = make_uint2(0xffffffffu, 0u);
-        return q;
+    const uint32_t nth = blockIdx.x * kVnWaves + (uint32_t)wave, p = nth / waves, shorts = *s.shorts;
+    if (p >= plans) return;                                           // (uniform; the waves do not meet)
+    const uint32_t st = (shorts + kVnTile - 1) / kVnTile, tiles = st + (n - shorts + kVnTile - 1) / kVnTile;
+    const size_t row = (size_t)p * n;
+    const VnBox* box = v.box + (size_t)p * box_row;
+    auto record_of = [&](uint32_t t) -> VnRecord {                    // (t uniform) this lane's request of tile t
+        const bool brief = t < st;
+        const uint32_t at = (brief ? t : t - st) * kVnTile + lane, many = brief ? shorts : n - shorts, k = at < many ? at : many - 1;
+        VnRecord r = {brief ? s.life[k] : v.life[row + k], v.range[row + (brief ? 0u : shorts) + k], brief ? s.id[k] : v.id[row + k]};
+        if (at >= many) r.life = make_uint2(0xffffffffu, 0u);         // (meets nothing)
+        return r;
     };
-    auto addresses_of = [&](const Record& q, uint64_t (&lo)[kPlans]) {
+    uint32_t count = 0;
+    uint64_t key = ~0ull;
+    const uint32_t blocks = (tiles + kBoxes * kWave - 1) / (kBoxes * kWave);
+    for (uint32_t u = nth % waves; u < tiles * blocks; u += waves) {
+        const uint32_t it = u % tiles, jn = u / tiles * kBoxes * kWave;
+        if (jn + kBoxes * kWave <= it) continue;                    // (uniform)
+        const VnBox own = box[it];
+        const VnRecord mine = record_of(it);
+        VnBox other[kBoxes];
 #pragma unroll
-        for (int p = 0; p < kPlans; ++p) lo[p] = offsets[(size_t)umin(p0 + p, plan_end - 1) * n + q.id];
-    };
-    uint64_t ahead = near & (near - 1);
-    Record now = record_of(near), next = record_of(ahead);
-    uint64_t now_lo[kPlans], next_lo[kPlans];
-    addresses_of(now, now_lo);
-    Range mine[kPlans];
-    {
-        const uint64_t size_i = i_ok ? s.size[at_i] : 0u;
+        for (uint32_t c = 0; c < kBoxes; ++c) other[c] = box[umin(jn + c * kWave + lane, tiles - 1)];
 #pragma unroll
-        for (int p = 0; p < kPlans; ++p) {
-            const uint64_t lo = i_ok ? offsets[(size_t)umin(p0 + p, plan_end - 1) * n + id_i] : 0u;
-            // an address range that would run past 2^64 is reported, and kept from wrapping so that what
-            // it covers still counts
-            const bool wraps = lo + size_i < lo;
-            if (own_chunk && wraps) atomicMax(status, (uint32_t)STALLOC_ERR_OVERFLOW);
-            mine[p] = Range{lo, wraps ? ~0ull : lo + size_i};
-        }
-    }
-    uint32_t count[kPlans];
-    uint64_t key[kPlans];
-#pragma unroll
-    for (int p = 0; p < kPlans; ++p) { count[p] = 0; key[p] = ~0ull; }
-
-    for (; near; near &= near - 1) {
-        const uint32_t jt = first_jt + (uint32_t)__builtin_ctzll(near);
-        ahead &= ahead - 1;
-        const Record after = record_of(ahead);
-        addresses_of(next, next_lo);
-        const bool meets = now.life.x < span.y && span.x < now.life.y;
-        const uint64_t left = __builtin_amdgcn_ballot_w64(meets);
-        const uint32_t many = (uint32_t)__builtin_popcountll(left);
-        __builtin_amdgcn_wave_barrier();                              // (the wave's own LDS: its accesses complete in order)
-        if (meets) {
-            const uint32_t to = lanes_below(left);
-            sh_who[wave][to] = make_uint4(now.life.x, now.life.y, now.id, (uint32_t)lane);
-#pragma unroll
-            for (int p = 0; p < kPlans; ++p)
-                sh_range[wave][p][to] = Range{now_lo[p], now_lo[p] + now.size < now_lo[p] ? ~0ull : now_lo[p] + now.size};
-        }
-        now = next;
-        next = after;
-#pragma unroll
-        for (int p = 0; p < kPlans; ++p) now_lo[p] = next_lo[p];
-        if (lane < 4) sh_who[wave][many + lane] = make_uint4(0xffffffffu, 0u, 0u, 0u);      // up to a multiple of four
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t k = 0; k < many; k += 4) {
-            uint64_t hit[4][kPlans], any = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint4 who = sh_who[wave][k + u];
-                const uint64_t together = lanes_lt(who.x, life_i.y) & lanes_lt(life_i.x, who.y);
-#pragma unroll
-                for (int p = 0; p < kPlans; ++p) {
-                    const Range r = sh_range[wave][p][k + u];
-                    hit[u][p] = together & lanes_lt(r.lo, mine[p].hi) & lanes_lt(mine[p].lo, r.hi);
-                    any |= hit[u][p];
+        for (uint32_t c = 0; c < kBoxes; ++c) {
+            const uint32_t j0 = jn + c * kWave;
+            const VnBox& o = other[c];
+            uint64_t near = __builtin_amdgcn_ballot_w64(j0 + lane < tiles && j0 + lane >= it && o.t_first < own.t_last && own.t_first < o.t_last &&
+                                                        o.lo < own.hi && own.lo < o.hi);
+            auto meets = [&](int f) -> uint64_t {                     // requests of the first tile that meet the box of lane f
+                return lanes_lt(mine.life.x, read_lane(o.t_last, f)) & lanes_lt(read_lane(o.t_first, f), mine.life.y) &
+                       lanes_lt(mine.range.lo, read_lane(o.hi, f)) & lanes_lt(read_lane(o.lo, f), mine.range.hi);
+            };
+            uint64_t hit = 0;
+            for (; near; near &= near - 1)
+                if (meets(__builtin_ctzll(near))) hit |= near & -near;
+            if (hit == 0) continue;                                   // (uniform)
+            VnRecord next = record_of(j0 + (uint32_t)__builtin_ctzll(hit));
+            while (hit) {
+                const int f = __builtin_ctzll(hit);
+                const uint32_t jt = j0 + (uint32_t)f;
+                hit &= hit - 1;
+                const VnRecord now = next;
+                if (hit) next = record_of(j0 + (uint32_t)__builtin_ctzll(hit));
+                const uint64_t left = meets(f);
+                const uint32_t many = (uint32_t)__builtin_popcountll(left);
+                __builtin_amdgcn_wave_barrier();                      // (the wave's own LDS: its accesses complete in order)
+                if (lane_in(left)) {
+                    const uint32_t to = lanes_below(left);
+                    sh.who[wave][to] = make_uint4(mine.life.x, mine.life.y, mine.id, (uint32_t)lane);
+                    sh.range[wave][to] = mine.range;
                 }
-            }
-            if (any == 0) continue;                                   // (uniform) the usual case
+                if (lane < 4) sh.who[wave][many + lane] = make_uint4(0xffffffffu, 0u, 0u, 0u);      // up to a multiple of four
+                __builtin_amdgcn_wave_barrier();
+                for (uint32_t k = 0; k < many; k += 4) {
+                    uint64_t pair[4], any = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint4 who = sh_who[wave][k + u];
-                const uint32_t j = who.z, place = uniform(who.w);
-                const uint64_t once = jt == it ? (1ull << place) - 1 : ~0ull;     // inside one tile: the first one lies in front
+                    for (int w = 0; w < 4; ++w) {
+                        const uint4 who = sh.who[wave][k + w];
+                        const Range r = sh.range[wave][k + w];
+                        pair[w] = lanes_lt(who.x, now.life.y) & lanes_lt(now.life.x, who.y) & lanes_lt(r.lo, now.range.hi) & lanes_lt(now.range.lo, r.hi);
+                        if (jt == it) pair[w] &= ~1ull << uniform(who.w);     // inside one tile: the second one lies behind
+                        any |= pair[w];
+                    }
+                    if (any == 0) continue;                           // (uniform) the usual case
 #pragma unroll
-                for (int p = 0; p < kPlans; ++p) {
-                    const uint64_t h = hit[u][p] & once;
-                    count[p] += (uint32_t)__builtin_popcountll(h);
-                    if ((h >> lane) & 1) {
-                        const uint64_t pair = id_i < j ? ((uint64_t)id_i << 32) | j : ((uint64_t)j << 32) | id_i;
-                        key[p] = umin64(key[p], pair);
+                    for (int w = 0; w < 4; ++w) {
+                        const uint32_t i = sh.who[wave][k + w].z, j = now.id;
+                        count += (uint32_t)__builtin_popcountll(pair[w]);
+                        if (lane_in(pair[w])) key = umin64(key, i < j ? ((uint64_t)i << 32) | j : ((uint64_t)j << 32) | i);
                     }
                 }
             }
         }
     }
-#pragma unroll
-    for (int p = 0; p < kPlans; ++p) {
-        if (count[p] == 0 || p0 + p >= plan_end) continue;            // (uniform)
-        const uint64_t wave_key = wave_min64(key[p]);
-        if (lane == 0) {
-            atomicAdd((unsigned long long*)&conflicts[p0 + p], (unsigned long long)count[p]);
-            atomicMin((unsigned long long*)&first_key[p0 + p], (unsigned long long)wave_key);
-        }
+    if (count == 0) return;                                           // (uniform)
+    const uint64_t wave_key = wave_min64(key);
+    if (lane == 0) {
+        atomicAdd((unsigned long long*)&conflicts[plan0 + p], (unsigned long long)count);
+        atomicMin((unsigned long long*)&first_key[plan0 + p], (unsigned long long)wave_key);
     }
-}
-
-// Four plans a wave.
-__global__ void __launch_bounds__(kVnWaves * kWave)
-val_near_plans(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t chunk, uint32_t plan0,
-               uint32_t plan_end, uint64_t* conflicts, uint64_t* first_key, uint32_t* status)
-{
-    __shared__ ValNearLds<4> sh;
-    val_near<4>(sh, s, offsets, n, tiles, chunk, plan0 + blockIdx.y * 4, plan_end, conflicts, first_key, status);
-}
-
-// One plan a wave; or, in a crowded trace, all of its pairs, the 256 x 256 tiles dealt out grid by grid.  (At most 64
-// registers: with 70, seven waves a SIMD, all pairs of one plan took 4 % longer than in val_pairs.)
-__global__ void __launch_bounds__(kVnWaves * kWave, 8)
-val_one_plan(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, VnSorted s,
-             const uint64_t* __restrict__ offsets, uint32_t n, uint32_t near_tiles, uint32_t chunk, uint32_t tiles, uint64_t* conflicts,
-             uint64_t* first_key, const uint64_t* acc, uint32_t* status)
-{
-    static_assert(kVnWaves * kWave == kValTile, "both forms run in workgroups of one size");
-    __shared__ uint64_t j_lo[kValTile];
-    __shared__ uint64_t j_hi[kValTile];
-    __shared__ uint32_t j_ta[kValTile];
-    __shared__ uint32_t j_tf[kValTile];
-    __shared__ ValNearLds<1> near;
-    const uint32_t p = blockIdx.y;
-    if (left_to_all_pairs(acc)) {                                     // (uniform)
-        const uint32_t tri = (uint32_t)((uint64_t)tiles * (tiles + 1) / 2);
-        for (uint32_t lin = blockIdx.x; lin < tri; lin += gridDim.x) {
-            __syncthreads();                                          // (the tile before has been read)
-            val_tile(j_lo, j_hi, j_ta, j_tf, size, ta, tf, offsets, n, tiles, lin, p, conflicts, first_key, status);
-        }
-        return;
-    }
-    val_near<1>(near, s, offsets, n, near_tiles, chunk, p, p + 1, conflicts, first_key, status);
 }
 
 __global__ void val_finish(const uint64_t* first_key, uint32_t* first_pair, uint32_t P)
@@ -469,17 +528,29 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     uint64_t* acc = cv.take<uint64_t>(kAccSpace);
     uint64_t* first_key = cv.take<uint64_t>(P);
     bool near = (uint64_t)tr->n * tr->n * P >= kVnFrom;
-    VnBuckets buckets = {0, 0, 0, 0};
+    VnBuckets buckets = {};
     VnSorted sorted = {};
+    VnPlans plans = {};
     const uint32_t near_tiles = (tr->n + kVnTile - 1) / kVnTile;
+    // plans that are gone through together
+    const size_t of_plan = (sizeof(Range) + sizeof(uint2) + sizeof(uint64_t) + sizeof(uint32_t)) * (size_t)tr->n;
+    const size_t most = kVnRoom / of_plan;
+    const uint32_t group = P < most ? P : most < 1 ? 1u : most < kVnGroup ? (uint32_t)most : kVnGroup;
     const size_t all_pairs = cv.used;
     if (near) {
         buckets = vn_buckets(tr->n, tr->t_end);
         sorted.bucket = cv.take<uint32_t>(buckets.words());
+        sorted.shorts_in = cv.take<uint32_t>((tr->n + 255) / 256);
+        sorted.shorts = cv.take<uint32_t>(1);
         sorted.life = cv.take<uint2>(tr->n);
         sorted.size = cv.take<uint64_t>(tr->n);
         sorted.id = cv.take<uint32_t>(tr->n);
-        sorted.span = cv.take<uint2>(near_tiles);
+        plans.top = cv.take<uint64_t>(group);
+        plans.start = cv.take<uint64_t>((size_t)group * tr->n);
+        plans.range = cv.take<Range>((size_t)group * tr->n);
+        plans.life = cv.take<uint2>((size_t)group * tr->n);
+        plans.id = cv.take<uint32_t>((size_t)group * tr->n);
+        plans.box = cv.take<VnBox>((size_t)group * (near_tiles + 1));
     }
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
     // (the first two pieces are all that P asks for; a workspace with room for no more gets the all-pairs form)
@@ -493,32 +564,35 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     uint32_t pb = (P + 255) / 256;
     if (pb > 1024) pb = 1024;
     if (near) {
-        const uint64_t work = (uint64_t)tr->n * tr->n * P;
-        const bool by_plan = P < 3 || (P == 3 && work < kVnThree) || (P < 8 && work < kVnTogether);
-        const uint64_t* crowded = by_plan ? acc : nullptr;
         uint32_t blocks = (tr->n + 255) / 256;
         if (blocks > 1024) blocks = 1024;
         uint32_t cb = ((buckets.words() > P ? buckets.words() : P) + 255) / 256;
         if (cb > 1024) cb = 1024;
-        hipLaunchKernelGGL(vn_clear, dim3(cb), dim3(256), 0, stream, sorted.bucket, buckets.words(), conflicts, first_key, P);
-        hipLaunchKernelGGL(vn_count, dim3(blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted.bucket, crowded);
-        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, sorted.bucket, buckets.count, buckets.apart, crowded);
-        hipLaunchKernelGGL(vn_scatter, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, crowded);
-        hipLaunchKernelGGL(vn_spans, dim3((near_tiles + kVnWaves - 1) / kVnWaves), dim3(256), 0, stream, sorted, tr->n, near_tiles, crowded);
-        // (chunk, group of first tiles) workgroups: the last chunk only has the groups that exist
-        const uint32_t chunk = vn_chunk(near_tiles);
-        const uint64_t chunks = (near_tiles + chunk - 1) / chunk;
-        const uint32_t grid = (uint32_t)(chunk / kVnWaves * ((chunks - 1) * chunks / 2) + (near_tiles + kVnWaves - 1) / kVnWaves);
-        if (by_plan)
-            hipLaunchKernelGGL(val_one_plan, dim3(grid, P), dim3(kVnWaves * kWave), 0, stream, tr->size, tr->t_alloc, tr->t_free, sorted,
-                               offsets, tr->n, near_tiles, chunk, (uint32_t)tiles, conflicts, first_key, crowded, device_status);
-        else
-            for (uint32_t p0 = 0; p0 < P;) {                  // four plans share a look at the lifetimes; grid.y is limited to 65535
-                const uint32_t plans = P - p0 < 131072 ? P - p0 : 131072;
-                hipLaunchKernelGGL(val_near_plans, dim3(grid, (plans + 3) / 4), dim3(kVnWaves * kWave), 0, stream, sorted, offsets, tr->n,
-                                   near_tiles, chunk, p0, p0 + plans, conflicts, first_key, device_status);
-                p0 += plans;
-            }
+        hipLaunchKernelGGL(vn_clear, dim3(cb > blocks ? cb : blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, conflicts,
+                           first_key, P, plans.top, group, acc);
+        hipLaunchKernelGGL(vn_count, dim3(blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted.bucket, acc);
+        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, buckets, sorted, tr->n, acc);
+        hipLaunchKernelGGL(vn_scatter, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, acc);
+        const uint32_t box_row = near_tiles + 1;                      // (the short-lived and the long-lived may each end with part of a tile)
+        const uint64_t blocks_of_boxes = (box_row + kWave - 1) / kWave;
+        // (short traces come with many plans: small workgroups, with little LDS, of which many are resident)
+        const uint32_t threads = tr->n <= 512 ? 64 : tr->n <= 1024 ? 256 : 1024;
+        uint32_t place_bits = 6;
+        while (place_bits < 12 && (1u << place_bits) < tr->n) ++place_bits;
+        for (uint32_t p0 = 0; p0 < P; p0 += group) {
+            const uint32_t many = P - p0 < group ? P - p0 : group;
+            const bool few = blocks_of_boxes == 1 || blocks_of_boxes * box_row * many < kVnFewUnits;
+            const uint64_t units = box_row * (few ? blocks_of_boxes : (blocks_of_boxes + 3) / 4);
+            uint64_t waves = (many < 64 ? 1 : 2) * kVnResident / many;
+            if (waves < 1) waves = 1;
+            if (waves > units) waves = units;
+            hipLaunchKernelGGL(vn_ranges, dim3((tr->n + 255) / 256, many), dim3(256), 0, stream, sorted, offsets, tr->n, box_row, p0, plans,
+                               device_status);
+            hipLaunchKernelGGL(vn_by_address, dim3(many), dim3(threads), sizeof(uint32_t) << place_bits, stream, sorted, tr->n, box_row,
+                               place_bits, plans);
+            hipLaunchKernelGGL(few ? val_near<1> : val_near<4>, dim3((uint32_t)((waves * many + kVnWaves - 1) / kVnWaves)), dim3(kVnWaves * kWave), 0,
+                               stream, sorted, plans, tr->n, box_row, p0, many, (uint32_t)waves, conflicts, first_key);
+        }
     } else {
         hipLaunchKernelGGL(val_init, dim3(pb), dim3(256), 0, stream, conflicts, first_key, P);
         for (uint32_t p0 = 0; p0 < P; p0 += 32768) {          // grid.y is limited to 65535

@@ -1,0 +1,46 @@
+"""The form of stalloc_validate that sorts short-lived requests by time and long-lived ones by address, where it can go wrong: requests
+numbered by allocation time or not, lengths and shares of long-lived requests around whole tiles, plans that are gone through
+in several groups; against the all-pairs form."""
+import numpy as np
+import pytest
+
+from test_gpu_validate_near import _all_pairs
+
+pytestmark = pytest.mark.gpu
+
+
+def _trace(rng, n, longs):
+    """`longs` of the requests live for a quarter of the trace, the others for up to a dozen allocations."""
+    ts = np.sort(rng.permutation(4 * n)[:n])
+    life = rng.integers(1, 40, n)
+    life[rng.permutation(n)[:longs]] = rng.integers(n // 2, n, longs) if longs else 0
+    size = np.where(life > 40, 4000, 1) * rng.integers(1, 50, n)
+    return size.astype(np.uint64), ts.astype(np.uint32), (ts + life).astype(np.uint32), 5 * n
+
+
+@pytest.mark.parametrize("numbered", ["by time", "at random"])
+@pytest.mark.parametrize("n, longs, P", [(900, 64, 2100), (1024, 65, 1600), (1025, 0, 1500), (4096, 63, 100), (4097, 1280, 95), (4097, 4097, 95),
+                                         (20011, 700, 6), (20011, 4161, 190), (70001, 300, 1), (150001, 40000, 1)])
+def test_forms_agree(n, longs, P, numbered):
+    import torch
+    import paper_2507_16274_amd as S
+    rng = np.random.default_rng([n, longs])
+    size, ts, te, t_end = _trace(rng, n, longs)
+    if numbered == "at random":
+        mixed = rng.permutation(n)
+        size, ts, te = size[mixed], ts[mixed], te[mixed]
+    # each plan puts the long-lived one after the other, the short-lived at low addresses: conflicts between neighbours in either
+    many = min(P, 8)
+    plans = np.empty((many, n), np.int64)
+    for p in range(many):
+        order = rng.permutation(n)
+        at = np.cumsum(np.where(size[order] > 50, size[order], 0))
+        plans[p, order] = np.where(size[order] > 50, at * 9 // 10, rng.integers(0, 4000, n))
+    dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
+    given = torch.from_numpy(plans).cuda()[torch.arange(P, device="cuda") % many].contiguous()
+    out = S.stalloc_validate(*dev, t_end, given)
+    S.check_status(out)
+    conflicts, first, status = _all_pairs(S, dev, t_end, given[:many].contiguous())
+    assert int(status.item()) == 0 and (longs == 0 or int(conflicts.sum()) > 0)
+    where = torch.arange(P, device="cuda") % many
+    assert torch.equal(out["conflicts"], conflicts[where]) and torch.equal(out["first_pair"], first[where])
