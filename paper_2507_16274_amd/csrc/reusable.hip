@@ -279,12 +279,18 @@ __host__ inline bool rs_window_per_lane(uint32_t n, uint32_t k) { return k >= 32
 constexpr uint32_t kRsWavesPerCu = 64;
 constexpr uint32_t kRsMaxParts = 256;                    // parts the sorted plan is cut into, at most
 
+// Intervals that the second walk keeps of a part and window.  Of a plan worth having little is idle, ten intervals a window
+// in 256 parts, so that the third walk mostly has nothing to do.
+constexpr uint32_t kRsGaps = 4;
+
 // Scratch of the window-per-lane sweep, [group of 64 windows][part][lane].
 struct RsParts {
     uint64_t* reach;        // walk 1: maximum end of the counting decisions of the part; then what is covered in front of it
     uint64_t* reach_all;    // [group][lane] ... of all parts
     uint64_t* idle;         // walk 2: bytes of the idle intervals closed inside the part
     uint32_t* found;        //         and their number; then the number in front of the part
+    uint32_t* found_all;    // [group][lane] ... in all parts
+    uint64_t* gap;          // walk 2: [group][part][kRsGaps][lane] the first of them, as the walk has addresses (room for bytes)
     uint32_t parts;         // parts per group; one wave each
     uint32_t steps;         // 64-decision steps per part
 };
@@ -312,9 +318,10 @@ __device__ __forceinline__ RsWindow window_of_lane(const RsArgs& g, uint32_t grp
 // The decisions that meet the span of the group's windows are put into LDS and taken from there as
 // broadcasts, once 64 have come together: reading them lane by lane (four lane reads and the search
 // for the next lane per decision) made a walk twice as long.  Bound by the integer rate and the longest
-// units: 2.0 million of 12.8 million (group, decision) pairs are left, 63 + 83 + 101 us for the three walks
-// of 199 748 decisions and 4096 windows (273 + 410 + 379 us before).
+// units: 2.0 million of 12.8 million (group, decision) pairs are left, 63 + 74 + 7 us for the three walks
+// of 199 748 decisions and 4096 windows (63 + 89 + 101 us while the third walked every part again for the few intervals there are).
 template <typename Addr> struct RsKept { uint32_t ts, te; Addr lo, hi; };
+template <typename Addr> struct RsGap { Addr lo, hi; };
 constexpr uint32_t kRsKept = 2 * kWave + 4;                     // (the walk over them takes four at a time)
 
 template <int kWalk, typename Addr>
@@ -340,16 +347,40 @@ __device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& 
         uint32_t place = 0;                                               // walk 2: intervals closed; walk 3: where the next one goes
         Addr idle = 0;                                                    // (disjoint intervals of the pool: fits the address type)
         uint64_t* out = nullptr;
+        RsGap<Addr>* const gaps = reinterpret_cast<RsGap<Addr>*>(sc.gap) + (cell - lane) * kRsGaps + lane;
         if constexpr (kWalk > 1) covered = (Addr)sc.reach[cell];
+        if constexpr (kWalk == 2) {
+            // No interval is closed in a part whose last decision starts where all windows are covered already.
+            const uint32_t last = umin(first + sc.steps * kWave, g.n) - 1;
+            const Addr last_lo = kNarrow ? (Addr)g.c_lo[last] : (Addr)g.s_lo[last];
+            if (__builtin_amdgcn_ballot_w64(win.live && last_lo > covered) == 0) {          // (uniform)
+                sc.found[cell] = 0;
+                sc.idle[cell] = 0;
+                continue;
+            }
+        }
         if constexpr (kWalk == 3) {
             place = sc.found[cell];
+            const uint32_t behind = part + 1 < sc.parts ? sc.found[cell + kWave] : sc.found_all[(size_t)grp * kWave + lane], mine = behind - place;
             out = win.live ? g.ranges + (size_t)win.w * g.max_ranges * 2 : nullptr;
+            const bool wanted = win.live && mine != 0 && place < g.max_ranges;
+            if (__builtin_amdgcn_ballot_w64(wanted && mine > kRsGaps) == 0) {          // (uniform) the second walk has kept them all
+                if (wanted) {
+                    for (uint32_t k = 0; k < mine && place + k < g.max_ranges; ++k) {
+                        const RsGap<Addr> gap = gaps[k * kWave];
+                        out[2 * (size_t)(place + k)] = bytes(gap.lo);
+                        out[2 * (size_t)(place + k) + 1] = bytes(gap.hi);
+                    }
+                }
+                continue;
+            }
         }
         // the next decision in address order, the same for all lanes
         auto take = [&](const RsKept<Addr>& d) {
             const bool counts = d.ts < win.hi && win.lo < d.te;
             if constexpr (kWalk == 2) {
                 const bool closes = counts && d.lo > covered;
+                if (closes && place < kRsGaps) gaps[place * kWave] = RsGap<Addr>{covered, d.lo};
                 place += closes ? 1u : 0u;
                 idle += closes ? d.lo - covered : (Addr)0;
             }
@@ -461,6 +492,7 @@ __global__ void __launch_bounds__(kRsPrefixWaves * kWave) rs_prefix(RsArgs g, Rs
         sc.reach_all[(size_t)blockIdx.x * kWave + lane] = all;
         return;
     }
+    sc.found_all[(size_t)blockIdx.x * kWave + lane] = (uint32_t)all;
     const RsWindow win = window_of_lane(g, blockIdx.x);
     if (!win.live) return;
     for (int w = 1; w < kRsPrefixWaves; ++w) idle += idles[w][lane];
@@ -507,7 +539,7 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
     uint32_t* c_lo = cv.take<uint32_t>(n);
     uint32_t* c_hi = cv.take<uint32_t>(n);
     // window-per-lane sweep: enough (group of 64 windows) x (part of the plan) waves to fill the chip
-    RsParts sc = {nullptr, nullptr, nullptr, nullptr, 0, 0};
+    RsParts sc = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
     ulonglong2 *window_keys = nullptr, *window_spare = nullptr;
     const uint32_t window_tiles = rs_window_per_lane(n, k) ? (k + kRsTile - 1) / kRsTile : 0u;
     const uint32_t groups = (k + kWave - 1) / kWave;
@@ -525,6 +557,8 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
         sc.idle = cv.take<uint64_t>(cells);
         sc.reach_all = cv.take<uint64_t>((size_t)groups * kWave);
         sc.found = cv.take<uint32_t>(cells);
+        sc.found_all = cv.take<uint32_t>((size_t)groups * kWave);
+        sc.gap = cv.take<uint64_t>(2 * kRsGaps * cells);
     }
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
     if (!offsets || !windows || !counts || !device_status || (max_ranges != 0 && !ranges) ||

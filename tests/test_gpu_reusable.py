@@ -192,3 +192,27 @@ def test_windows_of_unlike_length_and_place(S, oracle, shape):
     span = {"equal": 99, "whole": t_end, "short": 1, "ends": 2, "few": rng.integers(1, t_end, k)}[shape]
     windows = np.stack([lo, lo + span], axis=1).astype(np.uint32)
     _compare(S, oracle, size, ts, te, int(te.max()), a, windows, cap=8, sample=range(0, k, max(1, k // 12)))
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("cap", [0, 1, 7, 40])
+@pytest.mark.parametrize("busy", [1, 2, 3, 7])
+def test_parts_with_few_and_many_intervals(S, oracle, busy, cap, wide):
+    """Many windows, so that the plan is cut into parts whose first intervals are kept on the way: stretches of 100 blocks that
+    touch one another, stretches in which every `busy`-th block is followed by a hole, stretches that lie under one large block;
+    blocks come and go, so that windows differ."""
+    rng = np.random.default_rng([busy, cap])
+    n, k = 20000, 500
+    unit = (1 << 40) + 1 if wide else 4096
+    kind = np.repeat(rng.integers(0, 3, n // 100), 100)
+    hole = np.where(kind == 1, np.arange(n) % busy == 0, False) * rng.integers(1, 4, n)
+    size = rng.integers(1, 4, n)
+    at = np.cumsum(size + hole) - size - hole
+    for s in np.flatnonzero(kind == 2)[::100]:                       # the first block of the stretch covers all of it
+        size[s] = at[min(s + 99, n - 1)] + 1 - at[s]
+    ts = rng.integers(0, 100, n)
+    te = np.where(rng.random(n) < 0.7, 1000, ts + rng.integers(1, 900, n))
+    lo = rng.integers(0, 990, k)
+    windows = np.stack([lo, lo + np.where(rng.random(k) < 0.5, 1, 500)], axis=1)
+    size, at = (x.astype(np.uint64) * np.uint64(unit) for x in (size, at))
+    _compare(S, oracle, size, ts.astype(np.uint32), te.astype(np.uint32), 1000, at + np.uint64(unit), windows, cap, sample=range(0, k, 9))
