@@ -32,11 +32,12 @@
 //            blocks drop into the gaps (in place through registers when the list is in LDS,
 //            ping-pong between two slabs when it is in the workspace).
 //
-// What bounds it: the scan reads every block as an LDS broadcast (16 bytes, eight cycles of the CU's LDS) and spends six
-// vector instructions on it, per 64 requests (62 % of the scan's cycles for 49 920 requests, where the list is in the workspace and
-// every part of it is waited for); then the chain of clashing requests in wave 0.  6144 requests of 5
-// sizes, 512 orders (list in LDS): 17.9 -> 8.9 ms against batches of 16 with a lane per block, a running maximum across lanes
-// per request, and wave 0 settling every request; 49 920 requests, 256 orders (list in the workspace): 228 -> 154 ms.
+// What bounds it: the scan spends five vector and two scalar instructions on a block and 64 requests, and four waves a SIMD do not
+// issue enough of them to keep the vector units busy; an LDS broadcast per block (16 bytes, eight cycles of the CU's LDS) comes close.
+// Then the chain of clashing requests in wave 0.  6144 requests of 5 sizes, 512 orders (list in LDS): 17.9 ms with batches of 16, a
+// lane per block, a running maximum across lanes per request and wave 0 settling every request, 8.8 with a request per lane and lane
+// masks for what conflicts (six and five instructions), 8.4 with lanes switched off by the compares; 49 920 requests, 256 orders (list
+// in the workspace): 228, 153, 145, and 141 with the next part of a chunk on its way while one is looked at.
 //
 // Addresses are multiples of the largest power of two dividing all sizes.  When the sum of
 // sizes, in those granules, stays below 2^31 the list holds 32-bit granule counts (16-byte
@@ -115,6 +116,37 @@ __device__ __forceinline__ Chunk chunk_of(uint32_t count, uint32_t c)
     return Chunk{start < count ? end - blocks : 0u, start < count ? blocks : 0u};
 }
 
+// The requests of the wave's lanes and one block of the list.  Returns the lanes whose request is alive together with the block and
+// would fit in front of it, above what is covered so far (`room_end`: how far it would reach); and adds the block to what is
+// covered.  A wave issues an instruction every four cycles at best, and there are four waves a SIMD: what counts is how many there are,
+// scalar ones among them.  The lifetime compares switch lanes off, the rest is done by those that are left (all lanes are
+// on again at the end): five vector instructions and one scalar; lane masks, combined and selected by, take six and two.
+__device__ __forceinline__ uint64_t take_block(const BlockList<uint32_t, false>::Entry& block, uint32_t s, uint32_t ta, uint32_t tf,
+                                               uint32_t& covered, uint32_t& room_end)
+{
+    uint64_t fits;
+    asm volatile("v_add_u32_e32 %[end], %[covered], %[s]\n\t"
+        "v_cmpx_lt_u32_e64 %[fits], %[b_ta], %[tf]\n\t"
+        "v_cmpx_lt_u32_e64 %[fits], %[ta], %[b_tf]\n\t"
+        "v_cmp_ge_u32_e64 %[fits], %[lo], %[end]\n\t"
+        "v_max_u32_e32 %[covered], %[covered], %[hi]\n\t"
+        "s_mov_b64 exec, -1"
+        : [end] "=&v"(room_end), [fits] "=&s"(fits), [covered] "+&v"(covered)
+        : [s] "v"(s), [ta] "v"(ta), [tf] "v"(tf), [lo] "v"(block.lo()), [hi] "v"(block.hi()), [b_ta] "v"(block.ta()), [b_tf] "v"(block.tf()));
+    return fits;
+}
+__device__ __forceinline__ uint64_t take_block(const BlockList<uint64_t, false>::Entry& block, uint64_t s, uint32_t ta, uint32_t tf,
+                                               uint64_t& covered, uint64_t& room_end)
+{
+    const uint64_t conflict = lanes_lt((uint32_t)block.ta(), tf) & lanes_lt(ta, (uint32_t)block.tf());
+    room_end = covered + s;
+    const uint64_t fits = conflict & lanes_ge(block.lo(), room_end), reach = umax(covered, block.hi());
+    covered = lane_in(conflict) ? reach : covered;
+    return fits;
+}
+// The size of a request whose further holes are not looked for: never room for it below 2^31 granules (above, they are looked at in vain).
+template <typename Addr> struct Closed { static constexpr Addr value = (Addr)1 << (8 * sizeof(Addr) - 1); };
+
 // One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request (or two), and
 // the blocks of a chunk are taken one at a time, in address order, by all its lanes at once: two lifetime compares, an
 // add, a compare, a maximum and a selection per block and 64 requests, and nothing that crosses lanes.  The block comes
@@ -153,15 +185,21 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
     }
     Addr last = 0;
     if (place == 0 && chunk.blocks > 0) last = list.load(chunk.first + chunk.blocks - 1).lo();
+    // (the list in the workspace: the blocks of the next part are on their way while those of this one are looked at)
+    auto part_of = [&](uint32_t k0) -> typename List::Entry {
+        typename List::Entry en = List::none();
+        if (place < (int)kPart && k0 + place < chunk.blocks) en = list.load(chunk.first + k0 + place);
+        return en;
+    };
+    typename List::Entry next = List::none();
+    if constexpr (!kDirect) next = part_of(0);
     for (uint32_t k0 = 0; k0 < blocks; k0 += kDirect ? blocks : kPart) {
         const uint32_t stop = kDirect ? blocks : umin(kPart, blocks - k0);
         if constexpr (!kDirect) {
             __builtin_amdgcn_wave_barrier();
-            if (place < (int)kPart && k0 + place < chunk.blocks) {
-                const typename List::Entry en = list.load(chunk.first + k0 + place);
-                sh.staged[wave][half * kPart + place] = BlockList<Addr, false>::make(en.lo(), en.hi(), en.ta(), en.tf());
-            }
+            if (place < (int)kPart) sh.staged[wave][half * kPart + place] = BlockList<Addr, false>::make(next.lo(), next.hi(), next.ta(), next.tf());
             __builtin_amdgcn_wave_barrier();
+            next = part_of(k0 + kPart);
         }
         // (reads behind the part are not looked at: one group behind a chunk of the list, or the staged part's first one again)
         auto fetch = [&](Block (&block)[kTogether], uint32_t k) {
@@ -172,26 +210,15 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
             }
         };
         auto look = [&](const Block (&block)[kTogether]) {
-            uint64_t conflict[kHalves][kTogether], holes[kHalves][kTogether], some = 0, any = 0;
+            // room_end: what a request would reach in front of a block; holes: requests for which a block closes one
+            uint64_t holes[kHalves][kTogether], any = 0;
+            Addr room_end[kHalves][kTogether];
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
 #pragma unroll
                 for (int u = 0; u < kHalves; ++u) {
-                    conflict[u][i] = lanes_lt((uint32_t)block[i].ta(), rq_tf[u]) & lanes_lt(rq_ta[u], (uint32_t)block[i].tf());
-                    some |= conflict[u][i];
-                }
-            }
-            if (some == 0) return;                               // (uniform) these blocks concern no request of the batch
-            Addr before[kHalves][kTogether];
-#pragma unroll
-            for (int i = 0; i < kTogether; ++i) {
-#pragma unroll
-                for (int u = 0; u < kHalves; ++u) {
-                    before[u][i] = covered[u];
-                    holes[u][i] = conflict[u][i] & lanes_ge(block[i].lo(), (Addr)(covered[u] + rq_s[u]));
-                    any |= holes[u][i] & open[u];
-                    const Addr reach = umax(covered[u], block[i].hi());
-                    covered[u] = lane_in(conflict[u][i]) ? reach : covered[u];
+                    holes[u][i] = take_block(block[i], rq_s[u], rq_ta[u], rq_tf[u], covered[u], room_end[u][i]);
+                    any |= holes[u][i];
                 }
             }
             if (any == 0) return;                                // (uniform)
@@ -201,17 +228,20 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
                 for (int u = 0; u < kHalves; ++u) {
                     uint64_t here = holes[u][i] & open[u];
                     if (here == 0) continue;
-                    const uint64_t lowest = here & ~lanes_lt((Addr)0, before[u][i]);    // no conflicting block of the chunk lies lower
+                    const Addr before = room_end[u][i] - rq_s[u];
+                    const uint64_t lowest = here & ~lanes_lt((Addr)0, before);          // no conflicting block of the chunk lies lower
                     first[u] = lane_in(lowest) ? block[i].lo() : first[u];
                     here &= ~lowest;
                     if (here == 0) continue;
                     if (lane_in(here)) {
-                        if (found[u] < (uint32_t)kSlots) sh.hole[c][place + u * kLanes][found[u]] = Span<Addr>{block[i].lo(), before[u][i]};
+                        if (found[u] < (uint32_t)kSlots) sh.hole[c][place + u * kLanes][found[u]] = Span<Addr>{block[i].lo(), before};
                         ++found[u];
                     }
                     open[u] = lanes_lt(found[u], (uint32_t)kSlots + 1);                 // (kSlots + 1: more holes than slots)
                 }
             }
+#pragma unroll
+            for (int u = 0; u < kHalves; ++u) rq_s[u] = lane_in(open[u]) ? rq_s[u] : Closed<Addr>::value;
         };
         Block even[kTogether], odd[kTogether];
         fetch(even, 0);
