@@ -2,6 +2,8 @@
 // LDS, and the search for a run of free granules.
 #pragma once
 
+#include <type_traits>
+
 #include "host_util.h"
 #include "wave.h"
 
@@ -101,6 +103,38 @@ __device__ __forceinline__ uint32_t first_fit(const uint32_t* bm, uint32_t limit
             return (t + (uint32_t)f) * 32 + (uint32_t)__builtin_ctz(read_lane(starts, f));
         }
     }
+}
+
+// Lowest fit of a request of s granules among the 64 granules from the word of its candidate x on (`word`: how its bitmap has
+// them), if the blocks of the lanes in `rivals` are there as well, each ((1 << size) - 1 = ones) from granule lo on; kNoFit if there is
+// none.  The blocks become bits in their lanes, those are ORed over the wave, and the search goes on in scalar registers: nothing
+// here waits for LDS, and a lone wave, which issues an instruction every six cycles or so, gets by with some seventy.
+constexpr uint32_t kNoFit = 0xffffffffu;
+__device__ __forceinline__ uint32_t fit_among(uint64_t word, uint32_t s, uint32_t x, uint64_t rivals, uint32_t lo, uint32_t ones)
+{
+    const uint32_t base = x & ~31u;
+    // the 64 bits from the word before on hold what reaches into the first word, the 64 from the first on what reaches into the second
+    const uint32_t up = lo + (32u - base), on = lo - base;
+    const uint32_t in_first = lane_in(rivals & lanes_lt(up, 64u)) ? ones : 0u, in_second = lane_in(rivals & lanes_lt(on, 64u)) ? ones : 0u;
+    uint32_t u = (uint32_t)(((uint64_t)in_first << (up & 63u)) >> 32), v = (uint32_t)(((uint64_t)in_second << (on & 63u)) >> 32);
+    auto both = [&](auto ctrl, auto rows) {
+        u |= __builtin_amdgcn_update_dpp(0u, u, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        v |= __builtin_amdgcn_update_dpp(0u, v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    both(std::integral_constant<int, kDppRowShr1>(), std::integral_constant<int, 0xf>());
+    both(std::integral_constant<int, kDppRowShr2>(), std::integral_constant<int, 0xf>());
+    both(std::integral_constant<int, kDppRowShr4>(), std::integral_constant<int, 0xf>());
+    both(std::integral_constant<int, kDppRowShr8>(), std::integral_constant<int, 0xf>());
+    both(std::integral_constant<int, kDppRowBcast15>(), std::integral_constant<int, 0xa>());
+    both(std::integral_constant<int, kDppRowBcast31>(), std::integral_constant<int, 0xc>());
+    const uint64_t rest = ((uint64_t)read_lane(v, kWave - 1) << 32) | read_lane(u, kWave - 1);
+    uint64_t free_run = ~(word | rest);
+    for (uint32_t len = 1; len < s;) {                                       // bit b: free for `len` granules from b, all of them in the 64
+        const uint32_t step = len < s - len ? len : s - len;
+        free_run &= free_run >> step;
+        len += step;
+    }
+    return free_run ? base + (uint32_t)__builtin_ctzll(free_run) : kNoFit;
 }
 
 // Fills the row of one request with the requests j for which listed(j) holds; called by a workgroup of 256

@@ -19,11 +19,12 @@
 //   mark     A round later, in front of its next build, the wave enters the blocks of its requests into the
 //            tables, a tile per lane.
 //
-// What bounds it: on 6144 requests (21 tiles, 173-word rows, two workgroups a CU) the vector issue of the building
-// waves (rows, lists and search in equal parts) and, 40 % of the time, waiting for the wave with the longest
-// request of the batch; on 19 840 (25 tiles, one workgroup of sixteen waves) half the time is such waiting.
-// 1024 plans of 6144 requests: 6.9 -> 4.7 ms; 512 plans of 19 840: 24.0 -> 13.8 ms (91 and 226 listed requests
-// instead of 737 and 2211).
+// What bounds it: on 6144 requests (two workgroups a CU) the vector issue of the building waves and waiting for the wave with the
+// longest request of the batch; on 19 840 (one workgroup of sixteen waves) half the time is such waiting.  In orders by size and by
+// time, where nearly every request meets the one before it, the chain of those in wave 0 (an order by time of 19 840 requests: 8.4 ms
+// alone, a random one 4.4; it sets the time of a launch with two plans a workgroup).
+// 1024 plans of 6144 requests: 6.9 ms looking up every request, 4.66 with tables read a word at a time, 4.09 four words at a time and
+// with chains in registers (fit_among); 512 plans of 19 840: 24.0, 13.85, 12.15 ms.
 //
 // The tables hold the address range up to an eighth above the largest number of live granules (which no
 // plan can stay below and plans worth having stay close to), and up to two and a half times that number where the LDS has
@@ -52,8 +53,15 @@ struct PtShape {
 // bitmaps of thirty requests would take the tables' room: 14.1 ms for 512 plans of 19 840, 17.0 with two).
 __host__ __device__ constexpr uint32_t pt_per_wave(uint32_t waves) { return waves == 8 ? 2u : 1u; }
 __host__ __device__ constexpr uint32_t pt_batch(uint32_t waves) { return (waves - 1) * pt_per_wave(waves); }
+// With more clashing requests in a batch than this, what follows their candidates is fetched for all of them at once.
+constexpr int kPtFew = 2;
+// Rows and bitmaps begin at multiples of four words, so that a lane reads or writes four at a time (a request that lives through 25
+// tiles of 400 words: 50 reads instead of 175).  An odd multiple, so that the tiles of a block that is marked, a lane each, lie in as many
+// banks as that leaves (16 of 64).
+__host__ __device__ inline uint32_t pt_fours(uint32_t words) { return (words + 3) / 4 * 4; }
+__host__ __device__ inline uint32_t pt_stride(uint32_t row) { return pt_fours(row) | 4u; }
 // A bitmap holds a row of the tables and what three batches of the longest requests can add to the extent.
-__host__ __device__ inline uint32_t pt_bitmap_words(uint32_t row, uint32_t batch, uint32_t longest) { return (row + (3 * batch * longest + 31) / 32 + 2) | 1u; }
+__host__ __device__ inline uint32_t pt_bitmap_words(uint32_t row, uint32_t batch, uint32_t longest) { return pt_fours(row + (3 * batch * longest + 31) / 32 + 2); }
 
 struct PtOffer { uint32_t words[2]; };           // LDS words behind TiledLds per shape; 0: not part of this call
 
@@ -104,18 +112,18 @@ __global__ void __launch_bounds__(1024) pt_shape(PlanParams prm, uint32_t t_end,
     if (tid != 0) return;
     uint32_t live = 0;
     for (int w = 0; w < 16; ++w) live = umax(live, (uint32_t)peak[w]);
-    const uint32_t row = (live + live / 8) / 32 + 4, stride = row | 1u;
+    const uint32_t row = (live + live / 8) / 32 + 4, stride = pt_stride(row);
     for (uint32_t shape = 0; shape < 2; ++shape) {
         const uint32_t batch = pt_batch(shape == 0 ? 8u : 16u), least = shape == 0 ? 12u : 8u;
-        const uint32_t fixed = n + 1 + 2 * batch * pt_bitmap_words(row, batch, (uint32_t)(acc[kAccMaxSize] >> shift));
+        const uint32_t fixed = pt_fours(n + 1) + 2 * batch * pt_bitmap_words(row, batch, (uint32_t)(acc[kAccMaxSize] >> shift));
         if (row > 0xffffu || offer.words[shape] < fixed) continue;
         uint32_t tiles = umin((offer.words[shape] - fixed) / (2 * stride), umin(kPtMostTiles, t_end));
         if (tiles < least) continue;
         const uint32_t width = (t_end + tiles - 1) / tiles;
         tiles = (t_end + width - 1) / width;
-        // (rows and bitmaps are rounded up to odd lengths)
+        // (rows are rounded up by as much as seven words and bitmaps by three)
         const uint32_t per_word = 2 * (batch + tiles), spare = offer.words[shape] - fixed - 2 * tiles * stride;
-        const uint32_t more = spare / per_word > 2 ? spare / per_word - 2 : 0u;
+        const uint32_t more = spare / per_word > 8 ? spare / per_word - 8 : 0u;
         const uint32_t roomy = umin(umin(row + more, (2 * live + live / 2) / 32 + 4), 0xffffu);
         acc[kAccTiles] = 1ull | (shape << 1) | (tiles << 8) | (umax(row, roomy) << 16) | ((uint64_t)width << 32);
         return;
@@ -161,8 +169,8 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
     if (blockIdx.x == 0 && threadIdx.x == 0) const_cast<uint64_t*>(prm.acc)[kAccKernel] = STALLOC_KERNEL_BITMAP | (22u << 8);
     uint32_t* const cells = reinterpret_cast<uint32_t*>(smem + sizeof(Lds));      // [n + 1] placed blocks, see make_cell
     const uint32_t longest = (uint32_t)(prm.acc[kAccMaxSize] >> shift);
-    const uint32_t row = pt.row, stride = row | 1u, bm_words = pt_bitmap_words(row, kPend, longest);
-    uint32_t* const cover = cells + (n + 1);                          // [tiles][stride]
+    const uint32_t row = pt.row, stride = pt_stride(row), bm_words = pt_bitmap_words(row, kPend, longest);
+    uint32_t* const cover = cells + pt_fours(n + 1);                  // [tiles][stride]
     uint32_t* const any = cover + pt.tiles * stride;
     uint32_t* const pool = any + pt.tiles * stride;                   // bitmaps of two batches
     const int lane = lane_id(), wave = wave_id();
@@ -185,9 +193,10 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
         const uint32_t* order = prm.orders + (size_t)p * n;
         uint64_t* out = prm.offsets ? prm.offsets + (size_t)p * n : nullptr;
         // nothing placed; cell n pads the lists
-        for (uint32_t i = threadIdx.x; i < n + 1 + 2 * pt.tiles * stride; i += kThreads) cells[i] = 0;
+        for (uint32_t i = threadIdx.x; i < pt_fours(n + 1) + 2 * pt.tiles * stride; i += kThreads) cells[i] = 0;
         uint32_t top = 0;                                             // extent so far, granules
         bool missed = false;                                          // the plan has outgrown the tables
+        bool chained = false;                                         // (wave 0) nearly all requests of the last batch had to move
 
         for (uint32_t r0 = 0; r0 < n; r0 += kStage) {
             const uint32_t staged = n - r0 < kStage ? n - r0 : kStage;
@@ -243,13 +252,26 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
                     uint32_t* const bitmap = pool + ((batch & 1) * kPend + at - batch * kPend) * bm_words;
                     const uint32_t chunks = uniform(sh.rq_chunks[at]), tiles = uniform(sh.rq_tiles[at]);
                     const uint32_t a = tiles & 0xffu, b = (tiles >> 8) & 0xffu;
-                    for (uint32_t w0 = 0; w0 < limit; w0 += kWave) {
-                        const uint32_t w = w0 + lane, wc = umin(w, row - 1);
-                        uint32_t bits = cover[a * stride + wc] | cover[b * stride + wc];
+                    for (uint32_t w = 4 * lane; w < limit; w += 4 * kWave) {
+                        const uint32_t wc = umin(w, stride - 4);      // (a row's words from `row` on are zero)
+                        auto four = [&](const uint32_t* at) -> uint4 { return *reinterpret_cast<const uint4*>(at); };
+                        const uint4 c0 = four(cover + a * stride + wc), c1 = four(cover + b * stride + wc);
+                        uint4 bits = make_uint4(c0.x | c1.x, c0.y | c1.y, c0.z | c1.z, c0.w | c1.w);
                         const uint32_t* from = any + (a + 1) * stride + wc;
-#pragma unroll 8
-                        for (uint32_t t = a + 1; t < b; ++t, from += stride) bits |= *from;
-                        if (w < limit) bitmap[w] = w < row ? bits : 0u;
+                        uint32_t t = a + 1;
+                        for (; t + 3 < b; t += 4, from += 4 * stride) {
+                            const uint4 r0 = four(from), r1 = four(from + stride), r2 = four(from + 2 * stride), r3 = four(from + 3 * stride);
+                            bits.x |= r0.x | r1.x | r2.x | r3.x;
+                            bits.y |= r0.y | r1.y | r2.y | r3.y;
+                            bits.z |= r0.z | r1.z | r2.z | r3.z;
+                            bits.w |= r0.w | r1.w | r2.w | r3.w;
+                        }
+                        for (; t < b; ++t, from += stride) {
+                            const uint4 r0 = four(from);
+                            bits.x |= r0.x; bits.y |= r0.y; bits.z |= r0.z; bits.w |= r0.w;
+                        }
+                        if (w != wc) bits = make_uint4(0u, 0u, 0u, 0u);
+                        *reinterpret_cast<uint4*>(bitmap + w) = bits;
                     }
                     __builtin_amdgcn_wave_barrier();                  // (the wave's own LDS: its accesses complete in order)
 #pragma unroll
@@ -285,30 +307,49 @@ __global__ void __launch_bounds__(kWaves * kWave, kWaves == 8 ? 6 : 4) plan_tile
                     mine = prev ? sh.rq_x[at] : sh.cand[batch & 1][lane - kBefore];
                 }
                 // Which requests of the batch meet an earlier one in lifetime and address range, as if every candidate
-                // stood: independent of one another, so written out for all K.
-                uint32_t redo = 0;
+                // stood: independent of one another, so written out for all K.  (Where nearly all did in the batch before,
+                // as in an order by time, that is not asked.)
+                uint32_t redo = nb < 32 ? (1u << nb) - 1u : ~0u;
                 const uint32_t my_end = mine + my_s;
+                if (!chained) {
+                    redo = 0;
 #pragma unroll
-                for (int r = 0; r < kPend; ++r) {
-                    const int at = kBefore + r;
-                    const uint32_t s = read_lane(my_s, at), ta = read_lane(my_ta, at), tf = read_lane(my_tf, at), x = read_lane(mine, at);
-                    const uint64_t hit = lanes_lt(my_ta, tf) & lanes_lt(ta, my_tf) & lanes_lt(mine, x + s) & lanes_lt(x, my_end);
-                    if (hit & ((1ull << at) - 1)) redo |= 1u << r;
+                    for (int r = 0; r < kPend; ++r) {
+                        const int at = kBefore + r;
+                        const uint32_t s = read_lane(my_s, at), ta = read_lane(my_ta, at), tf = read_lane(my_tf, at), x = read_lane(mine, at);
+                        const uint64_t hit = lanes_lt(my_ta, tf) & lanes_lt(ta, my_tf) & lanes_lt(mine, x + s) & lanes_lt(x, my_end);
+                        if (hit & ((1ull << at) - 1)) redo |= 1u << r;
+                    }
                 }
                 // Those are searched again, in order, with the earlier ones marked in their bitmaps (blocks only remove
                 // room, so from the old candidate on); whatever meets the new address is searched again after them.
                 // (One that met an old address only is searched for nothing and finds its candidate.)
+                uint32_t moved = 0;
+                uint64_t view = 0;                                    // 64 granules from the candidate's word on, as the bitmap has them
+                const bool many = __builtin_popcount(redo) > kPtFew;
+                if (many && cur) {
+                    const uint32_t* at = bitmaps + (lane - kBefore) * bm_words;
+                    const uint32_t w = mine / 32;
+                    view = (w < limit ? at[w] : 0u) | ((uint64_t)(w + 1 < limit ? at[w + 1] : 0u) << 32);
+                }
+                const uint32_t ones = (1u << my_s) - 1u;              // (sizes are below 32)
                 while (redo) {
                     const uint32_t r = (uint32_t)__builtin_ctz(redo);
                     const int at = kBefore + (int)r;
-                    const uint32_t s = read_lane(my_s, at), ta = read_lane(my_ta, at), tf = read_lane(my_tf, at);
-                    const bool together = my_ta < tf && ta < my_tf;
-                    if (lane < at && together) mark_cell(bitmaps + r * bm_words, make_cell(mine, my_s));
-                    const uint32_t x = first_fit(bitmaps + r * bm_words, limit, s, read_lane(mine, at) / 32);
-                    if (lane == at) mine = x;
-                    const uint64_t hit = __builtin_amdgcn_ballot_w64(lane > at && together && mine < x + s && x < mine + my_s);
-                    redo = (redo & (redo - 1)) | (uint32_t)(hit >> kBefore);
+                    const uint32_t s = read_lane(my_s, at), ta = read_lane(my_ta, at), tf = read_lane(my_tf, at), from = read_lane(mine, at);
+                    const uint64_t together = lanes_lt(my_ta, tf) & lanes_lt(ta, my_tf), behind = ~1ull << at;
+                    const uint64_t earlier = together & ~behind & ~(1ull << at);
+                    uint32_t x = many ? fit_among(read_lane(view, at), s, from, earlier, mine, ones) : kNoFit;
+                    if (x == kNoFit) {
+                        if (lane_in(earlier)) mark_cell(bitmaps + r * bm_words, make_cell(mine, my_s));
+                        x = first_fit(bitmaps + r * bm_words, limit, s, from / 32);
+                    }
+                    mine = set_lane(mine, x, at);
+                    moved += x != from ? 1u : 0u;
+                    redo &= redo - 1;
+                    if (!chained) redo |= (uint32_t)((together & behind & lanes_lt(mine, x + s) & lanes_lt(x, mine + my_s)) >> kBefore);
                 }
+                chained = 4 * moved >= 3 * (uint32_t)kPend;
                 if (cur) {
                     cells[sh.rq_id[first + lane - kBefore]] = make_cell(mine, my_s);
                     sh.rq_x[first + lane - kBefore] = mine;
