@@ -50,6 +50,8 @@
 // check leaves it in the mode word), so every instantiation that could apply is enqueued and
 // those with nothing to do return at once.  The list lives in LDS when it fits and in the
 // workspace otherwise.
+#include <type_traits>
+
 #include "host_util.h"
 #include "plan_list.h"
 #include "plan_params.h"
@@ -156,7 +158,7 @@ template <typename Addr> struct Closed { static constexpr Addr value = (Addr)1 <
 // whether any of them closes a hole.  Published per (chunk, request): the maximum of conflicting end addresses, the
 // start of the first conflicting block, and the first holes behind it with chunk-local "covered".
 template <typename Addr, typename List, typename Lds>
-__device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, Lds& sh)
+__device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uint32_t b0, uint32_t nb, uint32_t shift, uint32_t& calm, Lds& sh)
 {
     constexpr bool kDirect = Lds::kDirect;
     constexpr int kSlots = Lds::kSlots, kHalves = Lds::kHalves, kLanes = kWave / kHalves;
@@ -183,6 +185,10 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
         }
         covered[u] = 0; first[u] = 0; found[u] = 0; open[u] = ~0ull;
     }
+    // Where most groups of blocks concern no request of the batch at all, as in an interleaved schedule once the large requests of
+    // an order by size are placed, that is asked first: four instructions per block and 64 requests if they do not, eleven if they do,
+    // seven without asking.  `calm` tells from the first groups of the wave's last scans.  (8944 requests, nearly all
+    // short-lived, 178 orders: 7.2 ms, 7.5 never asking.)
     Addr last = 0;
     if (place == 0 && chunk.blocks > 0) last = list.load(chunk.first + chunk.blocks - 1).lo();
     // (the list in the workspace: the blocks of the next part are on their way while those of this one are looked at)
@@ -209,10 +215,21 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
                 else block[i] = sh.staged[wave][half * kPart + (k & (kPart - 1)) + i];
             }
         };
-        auto look = [&](const Block (&block)[kTogether]) {
-            // room_end: what a request would reach in front of a block; holes: requests for which a block closes one
+        // do the blocks concern any request of the batch?
+        auto concerned = [&](const Block (&block)[kTogether]) -> bool {
+            uint64_t some = 0;
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i)
+#pragma unroll
+                for (int u = 0; u < kHalves; ++u)
+                    some |= lanes_lt((uint32_t)block[i].ta(), rq_tf[u]) & lanes_lt(rq_ta[u], (uint32_t)block[i].tf());
+            return some != 0;
+        };
+        // room_end: what a request would reach in front of a block; holes: requests for which a block closes one
+        auto look = [&](const Block (&block)[kTogether], auto ask) {
             uint64_t holes[kHalves][kTogether], any = 0;
             Addr room_end[kHalves][kTogether];
+            if (decltype(ask)::value && !concerned(block)) return;       // (uniform)
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
 #pragma unroll
@@ -245,12 +262,17 @@ __device__ __forceinline__ void scan_batch(const List& list, uint32_t count, uin
         };
         Block even[kTogether], odd[kTogether];
         fetch(even, 0);
-        for (uint32_t k = 0; k < stop; k += 2 * kTogether) {
-            fetch(odd, k + kTogether);
-            look(even);
-            fetch(even, k + 2 * kTogether);
-            look(odd);
-        }
+        if (k0 == 0) calm = concerned(even) ? (calm > 2 ? calm - 2 : 0u) : umin(calm + 1, 12u);
+        auto look_at_all = [&](auto ask) {
+            for (uint32_t k = 0; k < stop; k += 2 * kTogether) {
+                fetch(odd, k + kTogether);
+                look(even, ask);
+                fetch(even, k + 2 * kTogether);
+                look(odd, ask);
+            }
+        };
+        if (calm >= 6) look_at_all(std::true_type());                // (uniform)
+        else look_at_all(std::false_type());
     }
 #pragma unroll
     for (int u = 0; u < kHalves; ++u) {
@@ -612,6 +634,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
         uint64_t* out = prm.offsets ? prm.offsets + (size_t)p * n : nullptr;
         Addr peak = 0;                                        // tracked by wave 0
         uint32_t count = 0;
+        uint32_t calm = 0;                                    // (of this wave's scans)
         bool outgrown = false;                                // (uniform) 32-bit counts may not hold the next batch
         __syncthreads();                                      // (every wave has taken its decisions about the plan before)
         if (threadIdx.x == 0) {
@@ -640,7 +663,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
                     const uint64_t growth = wave_sum64(lane < (int)nb ? sh.rq_size[b0 + lane] >> shift : 0ull);
                     if ((uint64_t)sh.extent_now + growth > 0xffffffffull) { outgrown = true; break; }
                 }
-                scan_batch<Addr>(list, count, b0, nb, shift, sh);
+                scan_batch<Addr>(list, count, b0, nb, shift, calm, sh);
                 __syncthreads();
                 settle_batch<Addr>(list, count, b0, nb, shift, peak, sh);
                 const bool last_of_plan = r0 + b0 + nb >= n;
