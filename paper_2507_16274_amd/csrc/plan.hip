@@ -22,7 +22,8 @@
 //            local value and the maxima of the chunks below.  The first hole that is large
 //            enough is where r lies if the rest of the batch leaves it there, else the top.  If a
 //            chunk had more holes than could be published and no lower one fits, it
-//            is walked again for this one request, with everything below it known.
+//            is walked again for this one request, with everything below it known.  Where the chain below
+//            often gets into such chunks (orders by time), more of their holes are noted here for it.
 //   settle   A request clashes when an earlier one of the batch that is alive at the same time lies
 //            where it would.  All waves look for clashes; wave 0 then goes through those requests in
 //            order (all others stay where they are): each takes the first of its holes in which it
@@ -37,7 +38,8 @@
 // Then the chain of clashing requests in wave 0.  6144 requests of 5 sizes, 512 orders (list in LDS): 17.9 ms with batches of 16, a
 // lane per block, a running maximum across lanes per request and wave 0 settling every request, 8.8 with a request per lane and lane
 // masks for what conflicts (six and five instructions), 8.4 with lanes switched off by the compares; 49 920 requests, 256 orders (list
-// in the workspace): 228, 153, 145, and 141 with the next part of a chunk on its way while one is looked at.
+// in the workspace): 228, 153, 145, 141 with the next part of a chunk on its way while one is looked at, and 125 where the survey notes
+// what the chain would look for (the order by time, which sets the launch's time: 131 -> 114 ms).
 //
 // Addresses are multiples of the largest power of two dividing all sizes.  When the sum of
 // sizes, in those granules, stays below 2^31 the list holds 32-bit granule counts (16-byte
@@ -67,6 +69,8 @@ template <typename Addr, bool kLds, bool kCompact, int kThreads>
 struct PlanLds {
     static constexpr int kWaves = kThreads / kWave;
     static constexpr bool kDirect = kLds && !kCompact;     // the scan reads the list itself
+    // Lists in the workspace leave room for the spares below.  32-bit addresses only: the 64-bit kernel's registers are all in use.
+    static constexpr bool kKeeps = !kLds && sizeof(Addr) == 4;
     // Blocks behind the list's last one that the scan may read (and does not use): it fetches the next group while it
     // looks at one, up to a group behind the end of a chunk, and only where it reads the list itself.
     static constexpr uint32_t kReadAhead = kDirect ? kTogether : 0;
@@ -91,6 +95,12 @@ struct PlanLds {
     Addr last[kChunks];                                    // start of the chunk's last block
     uint8_t holes[kChunks][kPend];                         // holes found per (chunk, request), may exceed kSlots
     Span<Addr> hole[kChunks][kPend][kSlots];               // {hole end, chunk-local covered}
+    // Orders by time and the like: for each request the holes of the lowest chunk with more than could be published
+    static constexpr int kSpares = 15;
+    Span<Addr> spare[kKeeps ? kPend : 0][kSpares];           // {hole end, covered}
+    uint8_t spares[kKeeps ? kPend : 0];                      // how many (may exceed kSpares; 0: they were not looked for)
+    uint8_t spare_chunk[kKeeps ? kPend : 0];
+    uint32_t walks[kKeeps ? 1 : 0];                          // looks at such chunks in the last chain
     uint64_t usable[kPend];                                // holes that are large enough as such (lane = chunk * kCols + column)
     uint64_t crowded[kPend];                               // lanes of chunks with more holes than could be published
     Addr top_of[kPend];                                    // maximum over all chunks
@@ -151,7 +161,7 @@ template <typename Addr> struct Closed { static constexpr Addr value = (Addr)1 <
 
 // One pass over the sorted list for the requests b0 .. b0+nb-1 of the staged batch.  A lane holds a request (or two), and
 // the blocks of a chunk are taken one at a time, in address order, by all its lanes at once: two lifetime compares, an
-// add, a compare, a maximum and a selection per block and 64 requests, and nothing that crosses lanes.  The block comes
+// add, a compare and a maximum per block and 64 requests (64 bits: and selections), and nothing that crosses lanes.  The block comes
 // as a broadcast from LDS (taken out of a register of a lane it costs four more vector instructions); 64 lanes reading 16 bytes keep the LDS busy for
 // eight cycles whether they read one block or two, so the halves of a wave read a block each and hold all 64
 // requests each, two per lane.  Blocks are looked at four together, so that their compares overlap and one branch asks
@@ -406,6 +416,39 @@ __device__ __forceinline__ bool chunk_lowest_fit(const List& list, const Chunk& 
     return false;
 }
 
+// One wave: the holes of a chunk that are large enough for a request as such, the first `room` of them to out[]; returns how many it found
+// (it stops once there are more than that).
+template <typename Addr, typename List>
+__device__ __forceinline__ uint32_t holes_of_chunk(const List& list, const Chunk& chunk, Addr below, Addr s, uint32_t ta, uint32_t tf,
+                                                   Span<Addr>* out, uint32_t room)
+{
+    constexpr int kSteps = 2;                                    // 64 blocks each, read together
+    const uint32_t lane = (uint32_t)lane_id();
+    Addr run = below;
+    uint32_t found = 0;
+    for (uint32_t k0 = 0; k0 < chunk.blocks && found <= room; k0 += kSteps * kWave) {
+        typename List::Entry en[kSteps];
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const uint32_t k = k0 + j * kWave + lane;
+            en[j] = list.load(chunk.first + (k < chunk.blocks ? k : 0));
+        }
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const Addr e_lo = en[j].lo();
+            const bool conflict = k0 + j * kWave + lane < chunk.blocks && en[j].ta() < tf && ta < en[j].tf();
+            const Addr incl = wave_scan_max(conflict ? (Addr)en[j].hi() : (Addr)0);
+            const Addr before = umax(run, wave_shift_up(incl, (Addr)0));
+            const uint64_t opens = __builtin_amdgcn_ballot_w64(conflict && e_lo >= (Addr)(before + s));
+            const uint32_t at = found + lanes_below(opens);
+            if (lane_in(opens) && at < room) out[at] = Span<Addr>{e_lo, before};
+            found += (uint32_t)__builtin_popcountll(opens);
+            run = umax(run, read_lane(incl, kWave - 1));
+        }
+    }
+    return found;
+}
+
 // The holes published for request r, one per lane as in HoleView: {end, covered}, the latter counting lower chunks in.
 template <typename Addr, typename Lds>
 __device__ __forceinline__ Span<Addr> published_hole(const Lds& sh, uint32_t r)
@@ -423,7 +466,7 @@ __device__ __forceinline__ Span<Addr> published_hole(const Lds& sh, uint32_t r)
 // that were are the lowest of the chunk); `top`: where the request goes if no hole takes it.
 template <typename Addr, typename List, typename Lds>
 __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uint32_t r, const Seeker<Addr>& rq,
-                                           const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top, const Lds& sh)
+                                           const Span<Addr>& hole, uint64_t usable, uint64_t crowded, Addr top, Lds& sh)
 {
     constexpr int kCols = Lds::kCols;
     while (usable | crowded) {
@@ -432,6 +475,19 @@ __device__ __forceinline__ Addr lowest_fit(const List& list, uint32_t count, uin
         if (unpublished_below<Lds>(crowded, h)) {
             const int w = __builtin_ctzll(crowded) / kCols;
             Span<Addr> walked;
+            if constexpr (Lds::kKeeps) {
+                if (lane_id() == 0) ++sh.walks[0];
+                // (the survey has noted its holes)
+                const uint32_t many = uniform((uint32_t)sh.spares[r]);
+                if (many != 0 && uniform((uint32_t)sh.spare_chunk[r]) == (uint32_t)w) {
+                    const Span<Addr> mine = sh.spare[r][lane_id() < Lds::kSpares ? lane_id() : 0];
+                    for (uint32_t k = 0; k < umin(many, (uint32_t)Lds::kSpares); ++k) {
+                        x = rq.clear(read_lane(mine.hi, (int)k));
+                        if (x + rq.s <= read_lane(mine.lo, (int)k)) return x;
+                    }
+                    if (many <= (uint32_t)Lds::kSpares) { crowded &= ~(((1ull << kCols) - 1) << (w * kCols)); continue; }
+                }
+            }
             if (chunk_lowest_fit(list, chunk_of<Lds::kChunks>(count, (uint32_t)w), uniform(sh.top[w][r]), rq, x, walked)) return x;
             crowded &= ~(((1ull << kCols) - 1) << (w * kCols));
         } else {
@@ -498,6 +554,24 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
         const Addr x = usable ? read_lane(v.covered, __builtin_ctzll(usable)) : v.top;
         if (lane == 0) sh.at[r] = x;
     }
+    if constexpr (Lds::kKeeps) {
+        // Where the chain of the batch before went through crowded chunks, their holes are looked for here, by all waves, and not by
+        // wave 0 in the middle of the chain (49 920 requests in order of time: 23 400 walks of 3600 cycles, 131 -> 114 ms).  Not
+        // for every batch: orders that seldom go through them would wait for holes that nobody asks for.
+        const bool often = uniform(sh.walks[0]) >= kPend / 4;    // (wave 0 counts anew behind the next two barriers)
+#pragma unroll 1
+        for (uint32_t r = (uint32_t)wave; r < nb; r += Lds::kWaves) {
+            const uint64_t crowded = often ? uniform(sh.crowded[r]) : 0;
+            uint32_t many = 0;
+            if (crowded) {
+                const uint32_t w = (uint32_t)__builtin_ctzll(crowded) / kCols;
+                many = holes_of_chunk<Addr>(list, chunk_of<Lds::kChunks>(count, w), uniform(sh.top[w][r]), read_lane(rq_s, (int)r),
+                                            read_lane(rq_ta, (int)r), read_lane(rq_tf, (int)r), sh.spare[r], (uint32_t)Lds::kSpares);
+                if (lane == 0) sh.spare_chunk[r] = (uint8_t)w;
+            }
+            if (lane == 0) sh.spares[r] = (uint8_t)umin(many, 255u);
+        }
+    }
     if (threadIdx.x == 0) sh.clashes = 0;
     __syncthreads();
     {
@@ -526,6 +600,7 @@ __device__ __forceinline__ void settle_batch(const List& list, uint32_t count, u
     __syncthreads();
     if (wave == 0) {
         const int own = lane < (int)nb ? lane : 0;
+        if constexpr (Lds::kKeeps) { if (lane == 0) sh.walks[0] = 0; }
         Addr lo = sh.at[own];
         const uint64_t usable = sh.usable[own], crowded = sh.crowded[own];
         const Addr top = sh.top_of[own];
@@ -639,6 +714,7 @@ __global__ void __launch_bounds__(kThreads, 4) plan_kernel(PlanParams prm)   // 
         __syncthreads();                                      // (every wave has taken its decisions about the plan before)
         if (threadIdx.x == 0) {
             sh.extent_now = 0;
+            if constexpr (Lds::kKeeps) sh.walks[0] = 0;
             if (sizeof(Addr) == 4) prm.wide_plans[p] = 0;
         }
 

@@ -131,3 +131,25 @@ def test_some_of_more_plans_than_workgroups_outgrow_32_bit_counts(S, oracle, n_c
     assert got["status"] == 0 and info["kernel"] == kernel and info["address_bits"] == 32
     assert info["plans_64bit"] == int(wide[rows].sum())
     assert np.array_equal(got["peaks"], ext[rows]) and np.array_equal(got["offsets"], a[rows])
+
+
+@pytest.mark.parametrize("narrow", [8, 40, 400])
+def test_whole_batches_go_through_one_crowded_chunk_of_a_list_in_the_workspace(S, oracle, narrow):
+    """Blocks that stay alternate with blocks that go, one hole each; what comes later wants those holes, all of a batch the same one
+    first.  `narrow` holes in a row suit the few small requests only: with fewer than a request's noted holes the search ends among
+    them or goes on in the next chunk, with more it falls back on the list.  Wholly free holes and half-filled ones are both met."""
+    rng = np.random.default_rng([76, narrow])
+    n_base, n = 4800, S.lib.stalloc_plan_lds_capacity() + 321
+    n_late = n - n_base
+    unit = 2 ** 12
+    size = rng.integers(2, 6, n).astype(np.uint64)
+    size[1:n_base:2] = np.where(np.arange(n_base // 2) // narrow % 2 == 0, 1, size[1:n_base:2])
+    size[n_base:] = np.where(rng.random(n_late) < 0.3, 1, size[n_base:])
+    size = size * np.uint64(unit) + np.uint64(1)
+    ts = np.concatenate([np.zeros(n_base, np.int64), 10 + np.arange(n_late)])
+    te = np.concatenate([np.where(np.arange(n_base) % 2 == 0, 2 * n, 5), ts[n_base:] + rng.integers(500, 1500, n_late)])
+    tr = _T(size, ts.astype(np.uint32), te.astype(np.uint32), int(te.max()))
+    late = n_base + rng.permutation(n_late)
+    orders = np.stack([np.arange(n), np.concatenate([np.arange(n_base), late])]).astype(np.uint32)
+    got, _, _ = _compare_plans(S, oracle, tr, orders, method="lists")
+    assert got["info"]["kernel"] == "list_memory" and got["info"]["address_bits"] == 32
