@@ -29,9 +29,9 @@
 // the keys per expected place (2048 cells) and comparing inside a cell only.  A key is worked out
 // from the request number wherever it is needed; memory only sees the numbers, once out and
 // once in between.
-//   256 rows of 199 748 requests: 8.72 -> 0.69 ms, of which or_scatter 0.22 (bound by its scattered 4-byte
-// stores and the key arithmetic), or_buckets 0.27 (LDS counting and key arithmetic), rows 0 .. 2 and the size
-// classes 0.19; the sorted numbers alone take 0.04 ms to write.  Merging moved 16-byte keys ten times.
+//   256 rows of 199 748 requests: 8.72 (all rows merged) -> 0.65 -> 0.53 ms, of which or_scatter 0.10 (key arithmetic; 0.22 with a
+// scattered 4-byte store per number), or_buckets 0.28 (LDS counting and key arithmetic), rows 0 .. 2 and the size
+// classes 0.17; the sorted numbers alone take 0.04 ms to write.  Merging moved 16-byte keys ten times.
 #include "host_util.h"
 #include "sort_keys.h"
 #include "wave.h"
@@ -39,6 +39,8 @@
 namespace stalloc {
 
 constexpr int kOrTile = kSortTile;
+
+constexpr uint64_t kOrStream = 0xD1342543DE82EF95ull;
 
 __device__ __forceinline__ uint64_t splitmix64_out(uint64_t x)
 {
@@ -73,7 +75,7 @@ __device__ __forceinline__ ulonglong2 order_key(const OrTrace& t, uint64_t p, ui
         k.x = t.ta[i];
         k.y = i;
     } else {
-        const uint64_t r = splitmix64_out((uint64_t)i * 0xD1342543DE82EF95ull + stream);
+        const uint64_t r = splitmix64_out((uint64_t)i * kOrStream + stream);
         k.x = (p & 1) ? r : (((uint64_t)t.larger[i] + 1) << 32) + (r >> 31);
         k.y = i;
     }
@@ -188,10 +190,11 @@ struct OrBuckets {
 
 // Request i of row p (>= 3): its key, and the cell of the row in which it is expected (never
 // descending with the key; bucket = cell / kOrCells).
-__device__ __forceinline__ uint64_t spread_key(const OrTrace& t, const OrBuckets& b, uint64_t p, uint64_t stream, uint32_t i,
-                                               uint32_t& cell)
+// `at`: i * kOrStream + stream.
+__device__ __forceinline__ uint64_t spread_key_at(const OrTrace& t, const OrBuckets& b, uint64_t p, uint64_t at, uint32_t i,
+                                                  uint32_t& cell)
 {
-    const uint64_t r = splitmix64_out((uint64_t)i * 0xD1342543DE82EF95ull + stream);
+    const uint64_t r = splitmix64_out(at);
     if (p & 1) {                                                  // (uniform)
         cell = __umulhi((uint32_t)(r >> 32), b.buckets * kOrCells);
         return r;
@@ -200,6 +203,12 @@ __device__ __forceinline__ uint64_t spread_key(const OrTrace& t, const OrBuckets
     const uint32_t k = (uint32_t)(key >> 32), first = b.step[k];
     cell = first + __umulhi((uint32_t)key, b.step[k + 1] - first);
     return key;
+}
+
+__device__ __forceinline__ uint64_t spread_key(const OrTrace& t, const OrBuckets& b, uint64_t p, uint64_t stream, uint32_t i,
+                                               uint32_t& cell)
+{
+    return spread_key_at(t, b, p, (uint64_t)i * kOrStream + stream, i, cell);
 }
 
 // step[k], k = 0 .. classes + 2: a request of class c is at [c + 1, c + 3) * 2^32, half of them in either
@@ -223,42 +232,79 @@ __global__ void __launch_bounds__(256) or_empty(uint32_t* filled, uint32_t m)
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < m; k += gridDim.x * blockDim.x) filled[k] = 0;
 }
 
-// grid (pieces of 8192 requests, rows): a piece reserves its room in every bucket with one atomic.
+// grid (pieces of 8192 requests, rows): a piece reserves its room in every bucket with one atomic.  Its numbers are put in order of bucket in
+// LDS first, so that the lanes of a store mostly write beside one another: each by itself they were a line per lane, and the L2s,
+// which take some 270 of them a nanosecond, set the time (256 rows of 199 748 requests: 220 us, now 98).  The multiplication by the stream's
+// constant is an addition from one request of a thread to the next.
 __global__ void __launch_bounds__(kOrScatterThreads)
 or_scatter(OrTrace t, OrBuckets b, uint64_t first_plan, uint64_t seed, const uint32_t* status)
 {
-    extern __shared__ uint32_t room[];                            // [buckets] numbers of the piece, then where they go
+    constexpr uint32_t kPiece = kOrScatterThreads * kOrPerThread, kOwn = kOrMostBuckets / kOrScatterThreads;
+    static_assert((uint64_t)kPiece * kOrMostBuckets <= 1ull << 32, "a request of the piece and its bucket share a word");
+    __shared__ uint32_t staged[kPiece];                           // bucket * kPiece + request of the piece, by bucket
+    __shared__ uint32_t part[kOrScatterThreads / kWave];
+    extern __shared__ uint32_t room[];                            // [buckets] numbers of the piece; where they begin in `staged`; from there to the bucket
     if (*status != STALLOC_OK) return;
     const uint64_t p = first_plan + blockIdx.y, stream = splitmix64_out(seed + p);
-    const uint32_t i0 = blockIdx.x * (kOrScatterThreads * kOrPerThread) + threadIdx.x;
+    const uint32_t piece = blockIdx.x * kPiece, i0 = piece + threadIdx.x;
+    const uint32_t many = t.n - piece < kPiece ? t.n - piece : kPiece;
     for (uint32_t k = threadIdx.x; k < b.buckets; k += kOrScatterThreads) room[k] = 0;
     __syncthreads();
     uint32_t bucket[kOrPerThread], place[kOrPerThread];
+    uint64_t at = (uint64_t)i0 * kOrStream + stream;
 #pragma unroll
     for (int u = 0; u < kOrPerThread; ++u) {
         const uint32_t i = i0 + u * kOrScatterThreads;
         bucket[u] = 0;
         if (i < t.n) {
             uint32_t cell;
-            spread_key(t, b, p, stream, i, cell);
+            spread_key_at(t, b, p, at, i, cell);
             bucket[u] = cell / kOrCells;
             place[u] = atomicAdd(&room[bucket[u]], 1u);
         }
+        at += kOrScatterThreads * kOrStream;
     }
     __syncthreads();
+    // a thread sees to `own` buckets in a row
     uint32_t* filled = b.filled + (size_t)blockIdx.y * b.buckets;
-    for (uint32_t k = threadIdx.x; k < b.buckets; k += kOrScatterThreads) {
-        const uint32_t mine = room[k];
-        room[k] = mine ? atomicAdd(&filled[k], mine) : 0u;
+    const uint32_t own = (b.buckets + kOrScatterThreads - 1) / kOrScatterThreads, k0 = threadIdx.x * own;
+    uint32_t count[kOwn], reserved[kOwn], mine = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kOwn; ++q) {
+        const uint32_t k = k0 + q;
+        count[q] = q < own && k < b.buckets ? room[k] : 0u;
+        reserved[q] = count[q] ? atomicAdd(&filled[k], count[q]) : 0u;
+        mine += count[q];
     }
+    const uint32_t incl = wave_scan_add(mine);
+    if (lane_id() == kWave - 1) part[wave_id()] = incl;
+    __syncthreads();
+    uint32_t begin = incl - mine;
+    for (int w = 0; w < wave_id(); ++w) begin += part[w];
+#pragma unroll
+    for (uint32_t q = 0; q < kOwn; ++q) {
+        if (q < own && k0 + q < b.buckets) room[k0 + q] = begin;
+        reserved[q] -= begin;
+        begin += count[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kOrPerThread; ++u) {
+        const uint32_t e = threadIdx.x + u * kOrScatterThreads;
+        if (e < many) staged[room[bucket[u]] + place[u]] = bucket[u] * kPiece + e;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kOwn; ++q)
+        if (q < own && k0 + q < b.buckets) room[k0 + q] = reserved[q];
     __syncthreads();
     uint32_t* number = b.number + (size_t)blockIdx.y * b.buckets * kOrCells;
 #pragma unroll
     for (int u = 0; u < kOrPerThread; ++u) {
-        const uint32_t i = i0 + u * kOrScatterThreads;
-        if (i >= t.n) continue;
-        const uint32_t to = room[bucket[u]] + place[u];
-        if (to < kOrCells) number[(size_t)bucket[u] * kOrCells + to] = i;     // (or_buckets sees from `filled` when it did not fit)
+        const uint32_t e = threadIdx.x + u * kOrScatterThreads;
+        if (e >= many) break;
+        const uint32_t to_bucket = staged[e] / kPiece, to = room[to_bucket] + e;
+        if (to < kOrCells) number[(size_t)to_bucket * kOrCells + to] = piece + staged[e] % kPiece;     // (or_buckets sees from `filled` when it did not fit)
     }
 }
 

@@ -81,3 +81,16 @@ def test_reports_malformed_trace(S):
     size = np.array([8, 0, 8], np.uint64)
     status, _ = _gpu_orders(S, size, np.array([0, 1, 2], np.uint32), np.array([3, 4, 5], np.uint32), 5, 4)
     assert status == 2                                                   # STALLOC_ERR_BAD_TRACE
+
+
+@pytest.mark.parametrize("n", [2049, 8191, 8192, 8193, 16383, 16385, 24577, 786_433, 1_600_001])
+@pytest.mark.parametrize("sizes", [3, 1000])
+def test_pieces_and_buckets_of_the_spread_rows(S, oracle, n, sizes):
+    """Requests are dropped into buckets by pieces of 8192, whose threads look after one bucket each up to 512 (786 432
+    requests) and after two, three beyond: lengths around a piece and those, odd and even rows, few and many sizes."""
+    rng = np.random.default_rng([n, sizes])
+    size, ts, te, t_end = random_trace(rng, n, t_max=n // 2, sizes=list(range(8, 8 * sizes + 8, 8)))
+    P = 6 if n < 100_000 else 2
+    status, got = _gpu_orders(S, size, ts, te, t_end, P, seed=n, first_plan=3)
+    assert status == 0
+    assert np.array_equal(got, oracle.make_orders(size, ts, te, P, seed=n, first_plan=3))
