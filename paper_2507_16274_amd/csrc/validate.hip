@@ -117,7 +117,7 @@ val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
 // box, most of them none.  Only then is the other tile looked at, request by request.
 // Which request of a bucket comes first does not matter: the results are a sum and a minimum over the request numbers.
 //   Bound by chains of loads (a tile, its boxes, the tiles that it meets) with few waves, by vector issue with many.  All
-// tiles of requests that meet in time, by request / this: 199 748 requests, one plan 227 / 68 us, of which val_near 29 (before 185);
+// tiles of requests that meet in time, by request / this: 199 748 requests, one plan 226 / 71 us, of which val_near 29 (before 185);
 // 6144 requests, 512 plans 598 / 215; 49 920 requests, 8 plans 478 / 161.  With the long-lived tile in the lanes and the short ones
 // loaded one after the other, each a round trip to memory, val_near took 216 us on the first of these.
 constexpr uint32_t kVnTile = 64;
