@@ -432,7 +432,7 @@ val_near(VnSorted s, VnPlans v, uint32_t n, uint32_t box_row, uint32_t plan0, ui
         if (at >= many) r.life = make_uint2(0xffffffffu, 0u);         // (meets nothing)
         return r;
     };
-    uint32_t count = 0;
+    uint64_t count = 0;                                               // (a wave's units hold more than 2^32 pairs from 7.3 million requests on)
     uint64_t key = ~0ull;
     const uint32_t blocks = (tiles + kBoxes * kWave - 1) / (kBoxes * kWave);
     for (uint32_t u = nth % waves; u < tiles * blocks; u += waves) {

@@ -44,3 +44,23 @@ def test_forms_agree(n, longs, P, numbered):
     assert int(status.item()) == 0 and (longs == 0 or int(conflicts.sum()) > 0)
     where = torch.arange(P, device="cuda") % many
     assert torch.equal(out["conflicts"], conflicts[where]) and torch.equal(out["first_pair"], first[where])
+
+
+def test_one_wave_finds_more_pairs_than_32_bits_count():
+    """7.5 million requests, all alive at once.  1216 of them cover all addresses from their start on, 64 that share a start in front
+    of every 6143 * 64 others that keep clear of one another: in order of address every 6144th tile is one of theirs, and with a
+    plan's tiles dealt out to 6144 waves in turn the same wave gets them all, 4.8e9 pairs."""
+    import torch
+    import paper_2507_16274_amd as S
+    spans, each, segment = 19, 6143 * 64, 64 << 13          # (64 of 2^11 buckets of addresses a span)
+    n, end = spans * (each + 64), (1 << 24) + 1
+    start = torch.arange(spans, device="cuda")[:, None] * segment
+    offsets = torch.cat([start.expand(spans, 64), start + 8192 + torch.arange(each, device="cuda")], dim=1)
+    size = torch.cat([(end - start).expand(spans, 64), torch.ones((spans, each), dtype=torch.int64, device="cuda")], dim=1)
+    assert int((offsets + size)[:, 64:].max()) <= spans * segment < end and int((offsets[:, -1] - start[:, 0]).max()) < segment
+    once = torch.ones(n, dtype=torch.int32, device="cuda")
+    out = S.stalloc_validate(size.reshape(n).contiguous(), once - 1, once, 1, offsets.reshape(1, n).contiguous())
+    S.check_status(out)
+    meet = sum(64 * ((spans - g) * (each + 64) - 64) + 64 * 63 // 2 for g in range(spans))          # with what begins at or behind their start
+    assert meet > 1 << 32
+    assert int(out["conflicts"].item()) == meet and out["first_pair"].tolist() == [[0, 1]]
