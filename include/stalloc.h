@@ -177,7 +177,9 @@ int stalloc_lower_bound_static(const stalloc_trace *trace, uint64_t *lower_bound
  *   counts      device [k], number of intervals of each window (may exceed max_ranges)
  *   idle_bytes  device [k], total length of all intervals of each window; may be NULL
  *
- * The workspace size depends on n and k: query it with the k of the call.
+ * The workspace size depends on n and k: query it with the k of the call.  (48 n bytes and more for the plan in order of
+ * address; from n * k = 2^23 on 84 bytes per window and part of the plan, about a million of these pairs for up to a million
+ * windows, and 64 bytes per window for more than two million.)
  */
 int stalloc_reusable_space(const stalloc_trace *trace, const uint64_t *offsets,
                            const uint32_t *windows, uint32_t k, uint32_t max_ranges,

@@ -280,8 +280,11 @@ constexpr uint32_t kRsWavesPerCu = 64;
 constexpr uint32_t kRsMaxParts = 256;                    // parts the sorted plan is cut into, at most
 
 // Intervals that the second walk keeps of a part and window.  Of a plan worth having little is idle, ten intervals a window
-// in 256 parts, so that the third walk mostly has nothing to do.
+// in 256 parts, so that the third walk mostly has nothing to do.  Not where nobody asks for intervals (199 748 decisions, 512 windows:
+// 190 us, 199 when they are kept all the same), and not for more (part, window) pairs than this, 128 MiB of intervals: from two million
+// windows on a part is the whole plan and has more of them.
 constexpr uint32_t kRsGaps = 4;
+constexpr size_t kRsGapCells = (size_t)1 << 21;
 
 // Scratch of the window-per-lane sweep, [group of 64 windows][part][lane].
 struct RsParts {
@@ -324,7 +327,7 @@ template <typename Addr> struct RsKept { uint32_t ts, te; Addr lo, hi; };
 template <typename Addr> struct RsGap { Addr lo, hi; };
 constexpr uint32_t kRsKept = 2 * kWave + 4;                     // (the walk over them takes four at a time)
 
-template <int kWalk, typename Addr>
+template <int kWalk, bool kKeeps, typename Addr>
 __device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& sc, uint32_t shift, RsKept<Addr>* kept)
 {
     constexpr bool kNarrow = sizeof(Addr) == 4;
@@ -364,7 +367,7 @@ __device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& 
             const uint32_t behind = part + 1 < sc.parts ? sc.found[cell + kWave] : sc.found_all[(size_t)grp * kWave + lane], mine = behind - place;
             out = win.live ? g.ranges + (size_t)win.w * g.max_ranges * 2 : nullptr;
             const bool wanted = win.live && mine != 0 && place < g.max_ranges;
-            if (__builtin_amdgcn_ballot_w64(wanted && mine > kRsGaps) == 0) {          // (uniform) the second walk has kept them all
+            if (__builtin_amdgcn_ballot_w64(wanted && mine > (kKeeps ? kRsGaps : 0u)) == 0) {          // (uniform) the second walk has kept them all
                 if (wanted) {
                     for (uint32_t k = 0; k < mine && place + k < g.max_ranges; ++k) {
                         const RsGap<Addr> gap = gaps[k * kWave];
@@ -380,7 +383,7 @@ __device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& 
             const bool counts = d.ts < win.hi && win.lo < d.te;
             if constexpr (kWalk == 2) {
                 const bool closes = counts && d.lo > covered;
-                if (closes && place < kRsGaps) gaps[place * kWave] = RsGap<Addr>{covered, d.lo};
+                if (kKeeps && closes && place < kRsGaps) gaps[place * kWave] = RsGap<Addr>{covered, d.lo};
                 place += closes ? 1u : 0u;
                 idle += closes ? d.lo - covered : (Addr)0;
             }
@@ -434,14 +437,14 @@ __device__ __forceinline__ void sweep_by_window(const RsArgs& g, const RsParts& 
     }
 }
 
-template <int kWalk>
+template <int kWalk, bool kKeeps>
 __global__ void __launch_bounds__(kRsThreads) rs_sweep_by_window(RsArgs g, RsParts sc)
 {
     __shared__ RsKept<uint64_t> kept[kRsWaves][kRsKept];
     if (*g.status != STALLOC_OK) return;
     const RsUnits units = units_of(g.pool);
-    if (units.narrow) sweep_by_window<kWalk, uint32_t>(g, sc, units.shift, reinterpret_cast<RsKept<uint32_t>*>(kept[wave_id()]));   // (uniform)
-    else sweep_by_window<kWalk, uint64_t>(g, sc, units.shift, kept[wave_id()]);
+    if (units.narrow) sweep_by_window<kWalk, kKeeps, uint32_t>(g, sc, units.shift, reinterpret_cast<RsKept<uint32_t>*>(kept[wave_id()]));   // (uniform)
+    else sweep_by_window<kWalk, kKeeps, uint64_t>(g, sc, units.shift, kept[wave_id()]);
 }
 
 // What lies in front of every part, one workgroup per group of windows, an equal run of parts per wave.
@@ -558,7 +561,7 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
         sc.reach_all = cv.take<uint64_t>((size_t)groups * kWave);
         sc.found = cv.take<uint32_t>(cells);
         sc.found_all = cv.take<uint32_t>((size_t)groups * kWave);
-        sc.gap = cv.take<uint64_t>(2 * kRsGaps * cells);
+        if (cells <= kRsGapCells) sc.gap = cv.take<uint64_t>(2 * kRsGaps * cells);
     }
     if (!workspace) { *workspace_bytes = cv.used; return STALLOC_OK; }
     if (!offsets || !windows || !counts || !device_status || (max_ranges != 0 && !ranges) ||
@@ -590,11 +593,13 @@ extern "C" int stalloc_reusable_space(const stalloc_trace* tr, const uint64_t* o
         // (a wave per unit as far as that goes: the hardware hands out the next one when one is done)
         uint32_t grid = (uint32_t)di.cus * 256;
         if (grid > (waves + kRsWaves - 1) / kRsWaves) grid = (uint32_t)((waves + kRsWaves - 1) / kRsWaves);
-        hipLaunchKernelGGL(rs_sweep_by_window<1>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
+        const bool keeps = sc.gap && g.ranges;
+        hipLaunchKernelGGL((rs_sweep_by_window<1, false>), dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
         hipLaunchKernelGGL(rs_prefix<1>, dim3(groups), dim3(kRsPrefixWaves * kWave), 0, stream, g, sc);
-        hipLaunchKernelGGL(rs_sweep_by_window<2>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
+        hipLaunchKernelGGL((keeps ? rs_sweep_by_window<2, true> : rs_sweep_by_window<2, false>), dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
         hipLaunchKernelGGL(rs_prefix<2>, dim3(groups), dim3(kRsPrefixWaves * kWave), 0, stream, g, sc);
-        if (g.ranges) hipLaunchKernelGGL(rs_sweep_by_window<3>, dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
+        if (g.ranges)
+            hipLaunchKernelGGL((keeps ? rs_sweep_by_window<3, true> : rs_sweep_by_window<3, false>), dim3(grid), dim3(kRsThreads), 0, stream, g, sc);
     } else {
         uint32_t grid = (uint32_t)di.cus * 8;
         if (grid > k) grid = k;

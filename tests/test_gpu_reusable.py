@@ -216,3 +216,16 @@ def test_parts_with_few_and_many_intervals(S, oracle, busy, cap, wide):
     windows = np.stack([lo, lo + np.where(rng.random(k) < 0.5, 1, 500)], axis=1)
     size, at = (x.astype(np.uint64) * np.uint64(unit) for x in (size, at))
     _compare(S, oracle, size, ts.astype(np.uint32), te.astype(np.uint32), 1000, at + np.uint64(unit), windows, cap, sample=range(0, k, 9))
+
+
+def test_more_windows_than_intervals_are_kept_for(S, oracle):
+    """2.2 million windows: there is no room for the first intervals of a part, the third walk goes through all of them."""
+    rng = np.random.default_rng(4500)
+    n, k = 131, (1 << 21) + 100001
+    size, ts, te, t_end = random_trace(rng, n, t_max=200, unique_times=False)
+    a = rng.integers(0, 4 * n, n).astype(np.uint64)
+    lo = rng.integers(0, t_end, k)
+    hi = np.minimum(lo + rng.integers(1, 60, k), t_end)
+    lo = np.minimum(lo, hi - 1)
+    windows = np.stack([lo, hi], axis=1).astype(np.uint32)
+    _compare(S, oracle, size, ts, te, t_end, a, windows, cap=6, sample=range(0, k, 2111))

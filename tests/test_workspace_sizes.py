@@ -111,3 +111,22 @@ def test_lists_in_the_workspace_lie_where_the_index_of_the_bitmap_kernels_may(n)
 
     index, lists = need(1, 8), need(4096, 1 << 20)                  # with sizes for the bitmap kernels, and without
     assert need(4096, 8) <= max(index, lists) + 4 * 4096 + 24 * n + (1 << 15)        # (marks, and words per request and timestamp)
+
+
+@pytest.mark.gpu
+def test_very_many_windows_need_no_room_for_intervals():
+    """What a window adds to the workspace of the dynamic reusable space is its place in the sorted sequence (twice), and for every part of
+    the plan (one, with this many windows) what is covered and found there."""
+    import torch
+    import paper_2507_16274_amd as S
+    torch.cuda.init()
+
+    def need(k):
+        size = ctypes.c_size_t(0)
+        assert S.lib.stalloc_reusable_space(ctypes.byref(_trace(S, 6144, 12288)), 256, 256, k, 0, None, 256, 256, 256, None,
+                                            ctypes.byref(size), None) == 0
+        return size.value
+
+    windows = 1 << 24
+    assert need(2 * windows) - need(windows) <= windows * (2 * 16 + 8 + 8 + 8 + 4 + 4) + 4096
+    assert need(4096) - need(1) <= (128 << 20) + 4096 * 256 * 20 + (1 << 20)
