@@ -64,3 +64,44 @@ def test_one_wave_finds_more_pairs_than_32_bits_count():
     meet = sum(64 * ((spans - g) * (each + 64) - 64) + 64 * 63 // 2 for g in range(spans))          # with what begins at or behind their start
     assert meet > 1 << 32
     assert int(out["conflicts"].item()) == meet and out["first_pair"].tolist() == [[0, 1]]
+
+
+@pytest.mark.parametrize("n, longs, P", [(4097, 1280, 95), (20011, 20011, 6), (70001, 40000, 1)])
+def test_addresses_far_off(n, longs, P):
+    """Damaged decisions near 2^62 or at 0, and starts far from 0 in all: the same conflicts, and about the same time -- the buckets that
+    the long-lived requests are put into follow the addresses that most of them have."""
+    import torch
+    import paper_2507_16274_amd as S
+    rng = np.random.default_rng([n, longs, 7])
+    size, ts, te, t_end = _trace(rng, n, longs)
+    order = rng.permutation(n)
+    plan = np.empty(n, np.int64)
+    at = np.cumsum(np.where(size[order] > 50, size[order], 0)).astype(np.int64)
+    plan[order] = np.where(size[order] > 50, at * 9 // 10, rng.integers(0, 4000, n))
+    high = plan + (1 << 61)
+    plans = {"as it is": plan, "all far from 0": high}
+    for name, base, far in (("one far above", plan, [1 << 62]), ("three far above", plan, [1 << 62, 1 << 61, (1 << 63) - (1 << 20)]),
+                            ("one far below", high, [0]), ("both", high, [0, (1 << 62) + (1 << 61)])):
+        bent = base.copy()
+        bent[np.flatnonzero(size > 50)[-len(far):] if longs else [0]] = far
+        plans[name] = bent
+    plans["none apart"] = np.full(n, 5, np.int64)
+    dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
+    took = {}
+    for name, one in plans.items():
+        given = torch.from_numpy(one).cuda().expand(P, n).contiguous()
+        kept = {}
+        out = S.stalloc_validate(*dev, t_end, given, workspace_cache=kept)
+        S.check_status(out)
+        conflicts, first, status = _all_pairs(S, dev, t_end, given[:1].contiguous())
+        assert int(status.item()) == 0, name
+        assert (out["conflicts"] == conflicts).all() and (out["first_pair"] == first).all(), name
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for _ in range(10):
+            begin.record()
+            S.stalloc_validate(*dev, t_end, given, workspace_cache=kept)
+            end.record()
+            end.synchronize()
+            took[name] = min(took.get(name, 1e9), begin.elapsed_time(end))
+    del took["none apart"]                                            # (nearly all pairs that are alive together conflict)
+    assert max(took.values()) < 1.7 * took["as it is"] + 0.03, took     # ms; 2.4 and 3.4 times in the larger two while they did not
