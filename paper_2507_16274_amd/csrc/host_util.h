@@ -83,8 +83,10 @@ constexpr int kAccWidePlans = 9;               // plans that outgrew 32-bit gran
 constexpr int kAccLargeShort = 10;             // long-list kernel: size (granules) from which a short-lived block counts as large
                                                // (0xffffffff: none does); bits 32..63: how many do
 constexpr int kAccTiles = 11;                  // bitmap kernel with tables per tile of time: 0 = does not place the trace, else its layout (plan_tiled.hip)
-constexpr int kAccCrowded = 13;                // 1: the mean lifetime is more than a fifth of the time from first allocation to last release,
-                                               // or that time is less than a sixteenth of t_end
+constexpr int kAccCrowded = 13;                // kCrowded: the mean lifetime is more than a fifth of the time from first allocation to last release,
+                                               // or that time is less than a sixteenth of t_end; kFewAlive, kHardlyAnyAlive: fewer than 80, 24 requests are
+                                               // alive at a time
+constexpr uint64_t kCrowded = 1, kFewAlive = 2, kHardlyAnyAlive = 4;
 constexpr int kAccTilesMissed = 12;            // plans that outgrew its tables and are left to the other bitmap kernel
 constexpr int kAccNextPlan = 14;               // sorted-list kernel: plans handed out so far beyond one per workgroup
 constexpr int kAccNextWide = 15;               // and by its instantiation with 64-bit addresses (two of them may run in one call)

@@ -47,7 +47,8 @@ __device__ __forceinline__ uint32_t verdict(const TraceSums& t, uint32_t n, uint
     words[0] = t.hi; words[1] = t.lo; words[2] = t.bad; words[3] = t.bits;
     words[kAccMaxSize] = t.largest;
     const float span = (float)(t.t_last - t.t_first);                // (a choice between two ways to the same answer: rounding does not matter)
-    words[kAccCrowded] = (float)t.lives * 5.0f > (float)n * span || span * 16.0f < (float)t_end ? 1 : 0;
+    words[kAccCrowded] = ((float)t.lives * 5.0f > (float)n * span || span * 16.0f < (float)t_end ? kCrowded : 0) |
+                         ((float)t.lives < 80.0f * span ? kFewAlive : 0) | ((float)t.lives < 24.0f * span ? kHardlyAnyAlive : 0);
     if (t.hi + (t.lo >> 32) < (1ull << 31) && t.bits != 0) {
         const uint64_t total = (t.hi << 32) + t.lo;                  // below 2^63 here
         const uint32_t shift = (uint32_t)__builtin_ctzll(t.bits);

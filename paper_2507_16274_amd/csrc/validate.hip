@@ -22,6 +22,13 @@ constexpr int kValTile = 256;
 #define STALLOC_VAL_NEAR_FROM (300ull * 1000 * 1000)
 #endif
 constexpr uint64_t kVnFrom = STALLOC_VAL_NEAR_FROM;
+// Four plans a wave (val_four) where a look at the lifetimes is most of the work, from four plans on: in short traces; and, up to some length
+// and from some requests x plans on, in traces of which few requests are alive at a time, which only the device knows, so that both forms
+// are enqueued and one of them returns at once (3 us).
+constexpr uint32_t kVfPlans = 4;
+constexpr uint32_t kVfShort = 192, kVfMiddling = 2048, kVfLongest = 8192;
+constexpr uint64_t kVfFrom = 1000 * 1000, kVfLongFrom = 2000 * 1000;
+constexpr uint32_t kVfGroups = 32768;          // workgroups: several times what is resident; they take further plans in turn
 constexpr size_t kVnRoom = (size_t)128 << 20;    // what the plans that are gone through together take of the workspace
 constexpr uint32_t kVnGroup = 65535;             // (largest grid.y)
 // Waves that are resident.  They take the units of work of a few plans (199 748 requests, one plan 64 us, 76 with twice as many
@@ -166,7 +173,7 @@ static VnBuckets vn_buckets(uint32_t n, uint32_t t_end)
 struct VnSorted {
     uint32_t* bucket;        // [buckets.words()] requests per bucket, then where the next one of the bucket goes
     uint32_t* shorts_in;     // [n / 256] short-lived requests among 256 (and then: in front of them)
-    uint32_t* shorts;        // [1] how many requests are short-lived: the first ones in bucket order
+    uint2* shorts;           // [1] x: how many requests are short-lived: the first ones in bucket order; y: whether val_four has the plans
     uint2* life;             // [n] in bucket order: lifetime,
     uint64_t* size;          //     size
     uint32_t* id;            //     and number of the request
@@ -198,7 +205,7 @@ __global__ void __launch_bounds__(256) vn_clear(const uint32_t* __restrict__ ta,
         if (k < P) { conflicts[k] = 0; first_key[k] = ~0ull; }
         if (k < group) top[k] = 0;                                    // (group <= P)
     }
-    const bool crowded = acc[kAccCrowded] != 0;
+    const bool crowded = (acc[kAccCrowded] & kCrowded) != 0;
     for (uint32_t i0 = blockIdx.x * 256; i0 < n; i0 += gridDim.x * 256) {                      // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         const uint32_t a = i < n ? ta[i] : 0u, f = i < n ? tf[i] : 0u;
@@ -233,7 +240,7 @@ __device__ __forceinline__ uint32_t vn_take(uint32_t* bucket, uint32_t mine, boo
 __global__ void __launch_bounds__(256)
 vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, uint32_t* bucket, const uint64_t* acc)
 {
-    if (acc[kAccCrowded] || !acc[kAccUnsorted]) return;
+    if ((acc[kAccCrowded] & kCrowded) || !acc[kAccUnsorted]) return;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         vn_take(bucket, i < n ? b.of(ta[i], tf[i]) : 0u, i < n);
@@ -241,10 +248,11 @@ vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint3
 }
 
 // Exclusive sums of the bucket sizes (of shorts_in, when that is all), in place; one workgroup, four a thread and step.
-__global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint32_t n, const uint64_t* acc)
+// `form`: val_four has the plans (2: if few requests are alive at a time).
+__global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint32_t n, uint32_t form, const uint64_t* acc)
 {
     __shared__ uint32_t part[16];
-    const bool by_bucket = acc[kAccUnsorted] && !acc[kAccCrowded];
+    const bool by_bucket = acc[kAccUnsorted] && !(acc[kAccCrowded] & kCrowded);
     uint32_t* counted = by_bucket ? s.bucket : s.shorts_in;
     const uint32_t many = by_bucket ? b.count : (n + 255) / 256, apart = by_bucket ? b.apart : 0u, lasting = by_bucket ? b.before_lasting() : many;
     uint32_t carry = 0;
@@ -260,11 +268,15 @@ __global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint3
         for (int w = 0; w < 16; ++w) { if (w < wave_id()) before += part[w]; carry += part[w]; }
         for (int u = 0; u < 4; ++u) {
             if (k + u < many) counted[(k + u) << apart] = before;
-            if (k + u == lasting && k + u < many) *s.shorts = before;
+            if (k + u == lasting && k + u < many) s.shorts->x = before;
             before += v[u];
         }
     }
-    if (threadIdx.x == 0 && lasting >= many) *s.shorts = carry;
+    if (threadIdx.x != 0) return;
+    if (lasting >= many) s.shorts->x = carry;
+    // (long traces of which hardly any are alive have so few tiles that meet that val_near is the faster)
+    const uint64_t alive = acc[kAccCrowded];
+    s.shorts->y = form == 1 || (form == 2 && (alive & kFewAlive) && (n <= kVfMiddling || !(alive & kHardlyAnyAlive))) ? 1u : 0u;
 }
 
 __global__ void __launch_bounds__(256)
@@ -272,8 +284,8 @@ vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, c
            VnBuckets b, VnSorted s, const uint64_t* acc)
 {
     __shared__ uint32_t part[4];
-    const bool crowded = acc[kAccCrowded] != 0, sorted = crowded || !acc[kAccUnsorted];        // (uniform)
-    const uint32_t shorts = *s.shorts;
+    const bool crowded = (acc[kAccCrowded] & kCrowded) != 0, sorted = crowded || !acc[kAccUnsorted];        // (uniform)
+    const uint32_t shorts = s.shorts->x;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         const bool valid = i < n;
@@ -308,7 +320,9 @@ __device__ __forceinline__ VnBox vn_box(bool ok, const Range& r, const uint2& li
 __global__ void __launch_bounds__(256)
 vn_ranges(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plan0, VnPlans v, uint32_t* status)
 {
-    const uint32_t k = blockIdx.x * 256 + threadIdx.x, p = blockIdx.y, shorts = *s.shorts;
+    const uint2 parted = *s.shorts;
+    if (parted.y) return;
+    const uint32_t k = blockIdx.x * 256 + threadIdx.x, p = blockIdx.y, shorts = parted.x;
     const size_t row = (size_t)p * n;
     uint64_t hi = 0;                                                  // of a long-lived request
     Range r = {0, 0};
@@ -336,7 +350,12 @@ vn_ranges(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t
 struct VnPlaces {
     uint64_t from, width;
     uint32_t shift;
-    __device__ __forceinline__ uint32_t of(uint64_t start) const { return (uint32_t)(umin64(start > from ? start - from : 0ull, width) >> shift); }
+    bool all;                                                         // nothing lies beyond
+    __device__ __forceinline__ uint32_t of(uint64_t start) const
+    {
+        if (all) return (uint32_t)(start >> shift);                   // (uniform; one workgroup sees to a plan: the limits took 1.2 of 63 us)
+        return (uint32_t)(umin64(start > from ? start - from : 0ull, width) >> shift);
+    }
 };
 __device__ __forceinline__ VnPlaces vn_places(uint64_t sample, uint64_t top, uint32_t place_bits)     // one start per lane
 {
@@ -349,7 +368,7 @@ __device__ __forceinline__ VnPlaces vn_places(uint64_t sample, uint64_t top, uin
     const uint64_t from = middle > far ? middle - far : 0ull, to = top - middle < far ? top : middle + far;
     const uint64_t width = to - from;                                 // (no start is above the highest end)
     const uint32_t width_bits = width ? 64 - (uint32_t)__builtin_clzll(width) : 0u;
-    return VnPlaces{from, width, width_bits > place_bits ? width_bits - place_bits : 0u};
+    return VnPlaces{from, width, width_bits > place_bits ? width_bits - place_bits : 0u, width == top};
 }
 
 // The long-lived requests of a plan in buckets of their start addresses, and their tiles' boxes; one workgroup a plan.
@@ -357,19 +376,24 @@ __global__ void __launch_bounds__(1024) vn_by_address(VnSorted s, uint32_t n, ui
 {
     extern __shared__ uint32_t bucket[];                              // 2^place_bits
     __shared__ uint32_t part[16];
-    const uint32_t p = blockIdx.x, shorts = *s.shorts, longs = n - shorts, step = blockDim.x, waves = step / kWave;
-    if (longs == 0) return;
+    const uint2 parted = *s.shorts;
+    const uint32_t p = blockIdx.x, shorts = parted.x, longs = n - shorts, step = blockDim.x, waves = step / kWave;
+    if (longs == 0 || parted.y) return;
     const size_t row = (size_t)p * n;
     const uint64_t top = v.top[p], sample = v.start[row + (uint32_t)((uint64_t)longs * lane_id() / kWave)];
-    const uint32_t buckets = 1u << place_bits, per = (buckets + step - 1) / step;       // (buckets a thread sums up)
     constexpr int kAhead = 4;                                         // requests a thread, or tiles a wave, has under way together
+    uint64_t lo[kAhead];
+    auto load_starts = [&](uint32_t k) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) lo[u] = v.start[row + umin(k + u * step, longs - 1)];
+    };
+    load_starts(threadIdx.x);
+    const uint32_t buckets = 1u << place_bits, per = (buckets + step - 1) / step;       // (buckets a thread sums up)
     for (uint32_t k = threadIdx.x; k < buckets; k += step) bucket[k] = 0;
     const VnPlaces places = vn_places(sample, top, place_bits);
     __syncthreads();
     for (uint32_t k = threadIdx.x; k < longs; k += kAhead * step) {
-        uint64_t lo[kAhead];
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) lo[u] = v.start[row + umin(k + u * step, longs - 1)];
+        if (k != threadIdx.x) load_starts(k);
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
             if (k + u * step < longs) atomicAdd(&bucket[places.of(lo[u])], 1u);
@@ -390,7 +414,7 @@ __global__ void __launch_bounds__(1024) vn_by_address(VnSorted s, uint32_t n, ui
     }
     __syncthreads();
     for (uint32_t k = threadIdx.x; k < longs; k += kAhead * step) {
-        uint64_t lo[kAhead], size[kAhead];
+        uint64_t size[kAhead];
         uint2 life[kAhead];
         uint32_t id[kAhead];
 #pragma unroll
@@ -443,8 +467,10 @@ val_near(VnSorted s, VnPlans v, uint32_t n, uint32_t box_row, uint32_t plan0, ui
 {
     __shared__ ValNearLds sh;
     const int lane = lane_id(), wave = wave_id();
-    const uint32_t nth = blockIdx.x * kVnWaves + (uint32_t)wave, p = nth / waves, shorts = *s.shorts;
-    if (p >= plans) return;                                           // (uniform; the waves do not meet)
+    const uint32_t nth = blockIdx.x * kVnWaves + (uint32_t)wave, p = nth / waves;
+    const uint2 parted = *s.shorts;
+    const uint32_t shorts = parted.x;
+    if (p >= plans || parted.y) return;                               // (uniform; the waves do not meet)
     const uint32_t st = (shorts + kVnTile - 1) / kVnTile, tiles = st + (n - shorts + kVnTile - 1) / kVnTile;
     const size_t row = (size_t)p * n;
     const VnBox* box = v.box + (size_t)p * box_row;
@@ -526,6 +552,147 @@ val_near(VnSorted s, VnPlans v, uint32_t n, uint32_t box_row, uint32_t plan0, ui
     }
 }
 
+// All pairs of four plans that meet in time, in the order of VnSorted: a wave takes a tile of first requests, a request a lane, and
+// holds it against four tiles of second requests at or behind it, request by request as broadcasts from LDS: two lifetime compares for all
+// plans, two address compares a plan, and neither address ranges nor boxes are written first.  Tiles whose spans of time do not
+// meet drop out together, requests of the others that do not meet the first tile's span 64 at a time.  The records of the next tile
+// but one and the addresses of the next are on their way meanwhile.  A group of plans beyond the last plan repeats that one, and leaves out its results.
+//   Bound by vector issue.  Whole calls with val_near / this: 500 requests of which 29 are alive at a time, 10 000 plans 287 / 215 us; 2000
+// and 48, 2500 plans 395 / 293; 4000 and 67, 5000 plans 1784 / 1229; 8000 and 71, 2500 plans 2136 / 1403; 256 of an interleaved
+// schedule, 24 414 plans 400 / 237.  With more alive it looks at more pairs, and val_near, which leaves out what is apart in address, catches up: 256
+// requests and 92 equal, 384 and 139 val_near 7 to 15 % faster.  With hardly any alive so few tiles meet that val_near is the faster
+// from some length on: 8000 and 11, 2500 plans 820 / 1120, 2000 and 11, 10 000 plans 835 / 772.
+struct ValFourLds {
+    uint4 who[kVnWaves][kVnRow];                                      // t_alloc, t_free, number, place in the tile
+    Range range[kVnWaves][kVfPlans][kVnRow];
+};
+
+// The four tiles of a workgroup's waves and four second ones at or behind them: groups of four tiles in pairs (g, c), g <= c, numbered from c (c + 1) / 2 on.
+__global__ void __launch_bounds__(kVnWaves * kWave, 5)
+val_four(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t tiles, uint32_t plans, uint64_t* conflicts,
+         uint64_t* first_key, uint32_t* status)
+{
+    __shared__ ValFourLds sh;
+    __shared__ uint2 spans[kVnWaves];
+    if (!s.shorts->y) return;                                         // (left to val_near)
+    const int lane = lane_id(), wave = wave_id();
+    // (with one tile or two, the workgroup's waves share them out four times or twice)
+    const uint32_t per = tiles <= 2 ? tiles : kVnWaves, shares = kVnWaves / per, tile = (uint32_t)wave % per, share = (uint32_t)wave / per;
+    uint32_t c = (uint32_t)((sqrt(1.0 + 8.0 * (double)blockIdx.x) - 1.0) * 0.5);
+    while (c * (c + 1) / 2 > blockIdx.x) --c;
+    while ((c + 1) * (c + 2) / 2 <= blockIdx.x) ++c;
+    const uint32_t g = blockIdx.x - c * (c + 1) / 2, it = g * kVnWaves + tile, first_jt = c * kVnWaves;
+    struct Record { uint2 life; uint64_t size; uint32_t id; };
+    auto record_of = [&](uint32_t t) -> Record {                      // (t uniform) this lane's request of tile t
+        const uint32_t at = t * kVnTile + lane;
+        const bool ok = t < tiles && at < n;
+        const uint32_t k = ok ? at : 0u;
+        Record q = {s.life[k], s.size[k], s.id[k]};
+        if (!ok) { q.life = make_uint2(0xffffffffu, 0u); q.size = 0; }        // (meets nothing)
+        return q;
+    };
+    auto span_of = [&](const uint2& life) -> uint2 {
+        return make_uint2(~read_lane(wave_scan_max(~life.x), kWave - 1), read_lane(wave_scan_max(life.y), kWave - 1));
+    };
+    const Record own = record_of(it);
+    const uint2 span = span_of(own.life);
+    {
+        const uint2 second = g == c ? span : span_of(record_of(first_jt + tile).life);
+        if (lane == 0) spans[wave] = second;
+    }
+    __syncthreads();
+    uint64_t meets = 0;
+    {
+        const uint2 other = spans[lane & (kVnWaves - 1)];
+        meets = __builtin_amdgcn_ballot_w64(lane < (int)per && first_jt + lane >= it && other.x < span.y && span.x < other.y);
+    }
+    // the requests with a malformed lifetime meet nothing, but an address range that would wrap is looked for in all
+    if (meets == 0 && g != c) return;                                 // (uniform; the waves do not meet from here on)
+    auto next_record = [&](uint64_t tiles_left) -> Record { return record_of(tiles_left ? first_jt + (uint32_t)__builtin_ctzll(tiles_left) : tiles); };
+    for (uint64_t next_plan = (uint64_t)(blockIdx.y * shares + share) * kVfPlans; next_plan < plans; next_plan += gridDim.y * shares * kVfPlans) {
+        const uint32_t p0 = (uint32_t)next_plan;
+        auto addresses_of = [&](const Record& q, uint64_t (&lo)[kVfPlans]) {
+#pragma unroll
+            for (uint32_t p = 0; p < kVfPlans; ++p) lo[p] = offsets[(size_t)umin(p0 + p, plans - 1) * n + q.id];
+        };
+        uint64_t near = meets, ahead = near & (near - 1);
+        Record now = next_record(near), next = next_record(ahead);
+        uint64_t now_lo[kVfPlans], next_lo[kVfPlans], own_lo[kVfPlans];
+        addresses_of(now, now_lo);
+        addresses_of(own, own_lo);
+        Range mine[kVfPlans];
+        uint32_t count[kVfPlans];
+        uint64_t key[kVfPlans];
+#pragma unroll
+        for (uint32_t p = 0; p < kVfPlans; ++p) {
+            // an address range that would run past 2^64 is reported, and kept from wrapping so that what
+            // it covers still counts
+            const bool wraps = own_lo[p] + own.size < own_lo[p];
+            if (g == c && wraps) atomicMax(status, (uint32_t)STALLOC_ERR_OVERFLOW);
+            mine[p] = Range{own_lo[p], wraps ? ~0ull : own_lo[p] + own.size};
+            count[p] = 0; key[p] = ~0ull;
+        }
+        for (; near; near &= near - 1) {
+            const uint32_t jt = first_jt + (uint32_t)__builtin_ctzll(near);
+            ahead &= ahead - 1;
+            const Record after = next_record(ahead);
+            addresses_of(next, next_lo);
+            const uint64_t left = lanes_lt(now.life.x, span.y) & lanes_lt(span.x, now.life.y);
+            const uint32_t many = (uint32_t)__builtin_popcountll(left);
+            __builtin_amdgcn_wave_barrier();                              // (the wave's own LDS: its accesses complete in order)
+            if (lane_in(left)) {
+                const uint32_t to = lanes_below(left);
+                sh.who[wave][to] = make_uint4(now.life.x, now.life.y, now.id, (uint32_t)lane);
+#pragma unroll
+                for (uint32_t p = 0; p < kVfPlans; ++p)
+                    sh.range[wave][p][to] = Range{now_lo[p], now_lo[p] + now.size < now_lo[p] ? ~0ull : now_lo[p] + now.size};
+            }
+            now = next;
+            next = after;
+#pragma unroll
+            for (uint32_t p = 0; p < kVfPlans; ++p) now_lo[p] = next_lo[p];
+            if (lane < 4) sh.who[wave][many + lane] = make_uint4(0xffffffffu, 0u, 0u, 0u);      // up to a multiple of four
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t k = 0; k < many; k += 2) {
+                uint64_t hit[2][kVfPlans], any = 0;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint4 who = sh.who[wave][k + u];
+                    const uint64_t together = lanes_lt(who.x, own.life.y) & lanes_lt(own.life.x, who.y);
+#pragma unroll
+                    for (uint32_t p = 0; p < kVfPlans; ++p) {
+                        const Range r = sh.range[wave][p][k + u];
+                        hit[u][p] = together & lanes_lt(r.lo, mine[p].hi) & lanes_lt(mine[p].lo, r.hi);
+                        any |= hit[u][p];
+                    }
+                }
+                if (any == 0) continue;                                   // (uniform) the usual case
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint4 who = sh.who[wave][k + u];
+                    const uint32_t j = who.z;
+                    const uint64_t once = jt == it ? (1ull << uniform(who.w)) - 1 : ~0ull;      // inside one tile: the first one lies in front
+#pragma unroll
+                    for (uint32_t p = 0; p < kVfPlans; ++p) {
+                        const uint64_t h = hit[u][p] & once;
+                        count[p] += (uint32_t)__builtin_popcountll(h);     // (at most 64 * 256)
+                        if (lane_in(h)) key[p] = umin64(key[p], own.id < j ? ((uint64_t)own.id << 32) | j : ((uint64_t)j << 32) | own.id);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (uint32_t p = 0; p < kVfPlans; ++p) {
+            if (count[p] == 0 || p0 + p >= plans) continue;            // (uniform)
+            const uint64_t wave_key = wave_min64(key[p]);
+            if (lane == 0) {
+                atomicAdd((unsigned long long*)&conflicts[p0 + p], (unsigned long long)count[p]);
+                atomicMin((unsigned long long*)&first_key[p0 + p], (unsigned long long)wave_key);
+            }
+        }
+    }
+}
+
 __global__ void val_finish(const uint64_t* first_key, uint32_t* first_pair, uint32_t P)
 {
     for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) {
@@ -558,13 +725,16 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
     // plans that are gone through together
     const size_t of_plan = (sizeof(Range) + sizeof(uint2) + sizeof(uint64_t) + sizeof(uint32_t)) * (size_t)tr->n;
     const size_t most = kVnRoom / of_plan;
-    const uint32_t group = P < most ? P : most < 1 ? 1u : most < kVnGroup ? (uint32_t)most : kVnGroup;
+    const uint32_t group_room = P < most ? P : most < 1 ? 1u : most < kVnGroup ? (uint32_t)most : kVnGroup;
     const size_t all_pairs = cv.used;
+    const bool four_only = P >= kVfPlans && tr->n <= kVfShort;
+    const bool four = four_only || (P >= kVfPlans && tr->n <= kVfLongest && (uint64_t)tr->n * P >= (tr->n <= kVfMiddling ? kVfFrom : kVfLongFrom));
+    const uint32_t group = four_only ? 0 : group_room;
     if (near) {
         buckets = vn_buckets(tr->n, tr->t_end);
         sorted.bucket = cv.take<uint32_t>(buckets.words());
         sorted.shorts_in = cv.take<uint32_t>((tr->n + 255) / 256);
-        sorted.shorts = cv.take<uint32_t>(1);
+        sorted.shorts = cv.take<uint2>(1);
         sorted.life = cv.take<uint2>(tr->n);
         sorted.size = cv.take<uint64_t>(tr->n);
         sorted.id = cv.take<uint32_t>(tr->n);
@@ -594,7 +764,7 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
         hipLaunchKernelGGL(vn_clear, dim3(cb > blocks ? cb : blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, conflicts,
                            first_key, P, plans.top, group, acc);
         hipLaunchKernelGGL(vn_count, dim3(blocks), dim3(256), 0, stream, tr->t_alloc, tr->t_free, tr->n, buckets, sorted.bucket, acc);
-        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, buckets, sorted, tr->n, acc);
+        hipLaunchKernelGGL(vn_starts, dim3(1), dim3(1024), 0, stream, buckets, sorted, tr->n, four_only ? 1u : four ? 2u : 0u, acc);
         hipLaunchKernelGGL(vn_scatter, dim3(blocks), dim3(256), 0, stream, tr->size, tr->t_alloc, tr->t_free, tr->n, buckets, sorted, acc);
         const uint32_t box_row = near_tiles + 1;                      // (the short-lived and the long-lived may each end with part of a tile)
         const uint64_t blocks_of_boxes = (box_row + kWave - 1) / kWave;
@@ -602,7 +772,13 @@ extern "C" int stalloc_validate(const stalloc_trace* tr, const uint64_t* offsets
         const uint32_t threads = tr->n <= 512 ? 64 : tr->n <= 1024 ? 256 : 1024;
         uint32_t place_bits = 6;
         while (place_bits < 12 && (1u << place_bits) < tr->n) ++place_bits;
-        for (uint32_t p0 = 0; p0 < P; p0 += group) {
+        const uint32_t fours = (near_tiles + kVnWaves - 1) / kVnWaves;
+        if (four) {
+            const uint32_t pairs = fours * (fours + 1) / 2, rows = (P - 1) / (kVfPlans * (near_tiles <= 2 ? kVnWaves / near_tiles : 1u)) + 1, most_rows = (kVfGroups + pairs - 1) / pairs;
+            hipLaunchKernelGGL(val_four, dim3(pairs, rows < most_rows ? rows : most_rows), dim3(kVnWaves * kWave), 0, stream, sorted, offsets, tr->n,
+                               near_tiles, P, conflicts, first_key, device_status);
+        }
+        for (uint32_t p0 = 0; !four_only && p0 < P; p0 += group) {
             const uint32_t many = P - p0 < group ? P - p0 : group;
             const bool few = blocks_of_boxes == 1 || blocks_of_boxes * box_row * many < kVnFewUnits;
             const uint64_t units = box_row * (few ? blocks_of_boxes : (blocks_of_boxes + 3) / 4);
