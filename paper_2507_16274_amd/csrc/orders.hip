@@ -179,6 +179,11 @@ constexpr uint32_t kOrBucketMean = STALLOC_OR_BUCKET_MEAN;         // numbers a 
 constexpr uint32_t kOrMostBuckets = 4096;
 constexpr int kOrScatterThreads = 512, kOrPerThread = 16;
 constexpr int kOrBucketThreads = 512;
+// Numbers are put in order of bucket in LDS before they are stored (or_scatter) from this many numbers a launch on, in rows of more than two
+// buckets or so: below, there are few waves that stores could hold up, and two barriers and a sum more are 1.5 us a launch (directly /
+// staged: 4096 requests, 1024 rows 82 / 83 us; 16 384, 64 rows 76.6 / 77.7, 256 rows 97.7 / 97.3; 49 920, 64 rows 109.5 / 107.9).
+constexpr uint64_t kOrStagedFrom = 4000 * 1000;
+constexpr uint32_t kOrStagedRow = 4096;
 
 struct OrBuckets {
     const uint32_t* step;        // [classes + 3] first cell of the keys k * 2^32 .. of an even row (OrTrace::larger counts the classes)
@@ -232,16 +237,17 @@ __global__ void __launch_bounds__(256) or_empty(uint32_t* filled, uint32_t m)
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < m; k += gridDim.x * blockDim.x) filled[k] = 0;
 }
 
-// grid (pieces of 8192 requests, rows): a piece reserves its room in every bucket with one atomic.  Its numbers are put in order of bucket in
+// grid (pieces of 8192 requests, rows): a piece reserves its room in every bucket with one atomic.  Staged, its numbers are put in order of bucket in
 // LDS first, so that the lanes of a store mostly write beside one another: each by itself they were a line per lane, and the L2s,
 // which take some 270 of them a nanosecond, set the time (256 rows of 199 748 requests: 220 us, now 98).  The multiplication by the stream's
 // constant is an addition from one request of a thread to the next.
+template <bool kStaged>
 __global__ void __launch_bounds__(kOrScatterThreads)
 or_scatter(OrTrace t, OrBuckets b, uint64_t first_plan, uint64_t seed, const uint32_t* status)
 {
     constexpr uint32_t kPiece = kOrScatterThreads * kOrPerThread, kOwn = kOrMostBuckets / kOrScatterThreads;
     static_assert((uint64_t)kPiece * kOrMostBuckets <= 1ull << 32, "a request of the piece and its bucket share a word");
-    __shared__ uint32_t staged[kPiece];                           // bucket * kPiece + request of the piece, by bucket
+    __shared__ uint32_t staged[kStaged ? kPiece : 1];             // bucket * kPiece + request of the piece, by bucket
     __shared__ uint32_t part[kOrScatterThreads / kWave];
     extern __shared__ uint32_t room[];                            // [buckets] numbers of the piece; where they begin in `staged`; from there to the bucket
     if (*status != STALLOC_OK) return;
@@ -265,8 +271,24 @@ or_scatter(OrTrace t, OrBuckets b, uint64_t first_plan, uint64_t seed, const uin
         at += kOrScatterThreads * kOrStream;
     }
     __syncthreads();
-    // a thread sees to `own` buckets in a row
     uint32_t* filled = b.filled + (size_t)blockIdx.y * b.buckets;
+    uint32_t* number = b.number + (size_t)blockIdx.y * b.buckets * kOrCells;
+    if constexpr (!kStaged) {
+        for (uint32_t k = threadIdx.x; k < b.buckets; k += kOrScatterThreads) {
+            const uint32_t mine = room[k];
+            room[k] = mine ? atomicAdd(&filled[k], mine) : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kOrPerThread; ++u) {
+            const uint32_t i = i0 + u * kOrScatterThreads;
+            if (i >= t.n) break;
+            const uint32_t to = room[bucket[u]] + place[u];
+            if (to < kOrCells) number[(size_t)bucket[u] * kOrCells + to] = i;     // (or_buckets sees from `filled` when it did not fit)
+        }
+        return;
+    }
+    // a thread sees to `own` buckets in a row
     const uint32_t own = (b.buckets + kOrScatterThreads - 1) / kOrScatterThreads, k0 = threadIdx.x * own;
     uint32_t count[kOwn], reserved[kOwn], mine = 0;
 #pragma unroll
@@ -298,7 +320,6 @@ or_scatter(OrTrace t, OrBuckets b, uint64_t first_plan, uint64_t seed, const uin
     for (uint32_t q = 0; q < kOwn; ++q)
         if (q < own && k0 + q < b.buckets) room[k0 + q] = reserved[q];
     __syncthreads();
-    uint32_t* number = b.number + (size_t)blockIdx.y * b.buckets * kOrCells;
 #pragma unroll
     for (int u = 0; u < kOrPerThread; ++u) {
         const uint32_t e = threadIdx.x + u * kOrScatterThreads;
@@ -541,7 +562,8 @@ extern "C" int stalloc_make_orders(const stalloc_trace* tr, uint32_t first_plan,
         if (buckets > 1) {
             const uint32_t m = rows * buckets;
             hipLaunchKernelGGL(or_empty, dim3(m < 262144 ? (m + 255) / 256 : 1024), dim3(256), 0, stream, ob.filled, m);
-            hipLaunchKernelGGL(or_scatter, dim3((n + kPiece - 1) / kPiece, rows), dim3(kOrScatterThreads), buckets * sizeof(uint32_t),
+            const bool staged = n > kOrStagedRow && (uint64_t)n * rows >= kOrStagedFrom;
+            hipLaunchKernelGGL((staged ? or_scatter<true> : or_scatter<false>), dim3((n + kPiece - 1) / kPiece, rows), dim3(kOrScatterThreads), buckets * sizeof(uint32_t),
                                stream, t, ob, (uint64_t)first_plan + p0, seed, device_status);
         }
         hipLaunchKernelGGL(or_buckets, dim3(buckets, rows), dim3(kOrBucketThreads), 0, stream, t, ob, (uint64_t)first_plan + p0, seed,

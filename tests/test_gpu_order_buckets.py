@@ -28,8 +28,9 @@ def test_edges_of_buckets_and_windows(oracle, n, sizes):
         assert np.array_equal(out["orders"].cpu().numpy().view(np.uint32), want), (first, P)
 
 
-@pytest.mark.parametrize("n", [4080, 6120, 20400])
-def test_full_buckets_are_sorted_all_the_same(oracle, n):
+@pytest.mark.parametrize("n, P", [(4080, 8), (6120, 8), (20400, 8), (20400, 200)])
+def test_full_buckets_are_sorted_all_the_same(oracle, n, P):
+    """(20400, 200): enough numbers for those that are stored in runs."""
     import torch
     import paper_2507_16274_amd as S
     from paper_2507_16274_amd import build
@@ -41,7 +42,7 @@ def test_full_buckets_are_sorted_all_the_same(oracle, n):
     size, ts, te, t_end = random_trace(rng, n, t_max=n)
     size = rng.choice([512, 1024, 8192, 1 << 33], n).astype(np.uint64)
     dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
-    tr, P, first = S._trace(*dev, t_end), 8, 3
+    tr, first = S._trace(*dev, t_end), 3
     orders = torch.empty((P, n), dtype=torch.int32, device="cuda")
     status = torch.empty(1, dtype=torch.int32, device="cuda")
     need = ctypes.c_size_t(0)

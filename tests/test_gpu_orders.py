@@ -94,3 +94,20 @@ def test_pieces_and_buckets_of_the_spread_rows(S, oracle, n, sizes):
     status, got = _gpu_orders(S, size, ts, te, t_end, P, seed=n, first_plan=3)
     assert status == 0
     assert np.array_equal(got, oracle.make_orders(size, ts, te, P, seed=n, first_plan=3))
+
+
+@pytest.mark.parametrize("n, P", [(4096, 980), (4097, 980), (8192, 490), (8193, 490), (16385, 246), (49920, 81), (786_433, 6), (1_600_001, 3)])
+def test_numbers_stored_one_by_one_and_in_runs(S, oracle, n, P):
+    """From four million numbers a launch on, and beyond 4096 requests, the numbers of a piece are put in order of bucket before they
+    are stored (more buckets than 512: a thread looks after two, three): the same rows as in calls of half as many."""
+    import torch
+    rng = np.random.default_rng([n, P])
+    size, ts, te, t_end = random_trace(rng, n, t_max=n // 2, sizes=list(range(8, 4008, 8)))
+    dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
+    whole = S.stalloc_make_orders(*dev, t_end, P, seed=n, first_plan=3)
+    half = [S.stalloc_make_orders(*dev, t_end, many, seed=n, first_plan=first) for first, many in ((3, P // 2), (3 + P // 2, P - P // 2))]
+    for out in (whole, *half):
+        S.check_status(out)
+    assert torch.equal(whole["orders"], torch.cat([h["orders"] for h in half]))
+    for row in (0, P - 1):
+        assert np.array_equal(whole["orders"][row].cpu().numpy().view(np.uint32), oracle.make_orders(size, ts, te, 1, seed=n, first_plan=3 + row)[0])
