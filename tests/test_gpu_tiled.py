@@ -150,3 +150,30 @@ def test_plans_that_outgrow_the_tables_are_placed_all_the_same(oracle):
     plan = S.stalloc_plan(*args, dev(bad, np.int32))
     assert int(plan["status"].item()) == 6
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("least, most", [(1, 2), (1, 31), (24, 31), (31, 31)])
+@pytest.mark.parametrize("n, alive", [(1100, 12), (1500, 60), (3001, 80), (4100, 60)])
+def test_chains_of_clashing_requests(oracle, n, alive, least, most):
+    """Orders in which nearly every request meets the one before it (by time, by release, by size), so that a chain of them is settled one
+    after the other: places within the 64 granules from a candidate's word on, and, with large sizes in tall stacks, mostly beyond, where they
+    are looked for in the bitmap, and random orders, which leave such chains again."""
+    import torch
+    import paper_2507_16274_amd as S
+    rng = np.random.default_rng([n, alive, least, most])
+    ts = np.sort(rng.integers(0, 2 * n, n))
+    te = ts + rng.integers(1, 4 * alive, n)
+    size = (rng.integers(least, most + 1, n) * 512).astype(np.uint64)
+    size[0] = 512                                                 # (the granule)
+    mixed = rng.permutation(n)
+    mixed[: n // 2].sort()                                        # first by time, then at random
+    by_size = np.lexsort((ts, -size.astype(np.int64)))
+    orders = np.stack([np.arange(n), np.arange(n)[::-1], np.argsort(te, kind="stable"), by_size, mixed, rng.permutation(n)]).astype(np.uint32)
+    ts, te = ts.astype(np.uint32), te.astype(np.uint32)
+    dev = lambda x, t: torch.from_numpy(np.ascontiguousarray(x).view(t)).cuda()
+    plan = S.stalloc_plan(dev(size, np.int64), dev(ts, np.int32), dev(te, np.int32), int(te.max()), dev(orders, np.int32))
+    S.check_status(plan)
+    assert S.stalloc_plan_report(plan)["kernel"] == "bitmap" and _path(plan)[0] == 0
+    a, ext = oracle.plan_many(size, ts, te, orders, threads=6, method="lists")
+    assert np.array_equal(plan["peaks"].cpu().numpy().view(np.uint64), ext)
+    assert np.array_equal(plan["offsets"].cpu().numpy().view(np.uint64), a)
