@@ -4,15 +4,17 @@
 //
 // A plan is a chain: each request needs the address of the one before it.  What a short trace costs is the length
 // of one link of that chain, and launches.  A workgroup that shares a request out among its waves pays barriers and LDS round
-// trips for every link; here a link is some fifty instructions of one wave that never leave its registers: the list
+// trips for every link; here a link is some sixty instructions of one wave that never leave its registers: the list
 // lies in the lanes in address order, J blocks a lane.  Two compares keep the blocks alive together with
 // the request, a running maximum of their ends over the lanes (DPP) is "covered so far", the first of them that starts at
 // least `size` above it closes the hole that the request takes (else it goes on top), and the blocks above move up by one.
 // The first 64 requests of an order see one block per lane, the next 64 two, and so on.
 // A wave also checks the trace by itself (512 requests are eight loads per lane): a call is two launches.
-//   Bound by the instructions of a lone wave, one after another (about seven cycles each): 75 per request with one block per
-// lane, some 25 more for each further one.  The workgroup kernels before / this one: 96 requests, 64 orders 64 / 28 us, 384
-// requests, 64 orders 182 / 152, 480 requests in 32-bit counts, 64 orders 306 / 229, 4096 orders 3112 / 397.
+//   Bound by the instructions of a lone wave, one after another: about 60 per request with one block per lane, some 16 more for each
+// further one (75 and 25 while the place in the list was counted out and written to by a branch per block of a lane).  The
+// workgroup kernels / this one with such branches / now: 96 requests, 64 orders 64 / 28 / 24 us, 384 requests, 64 orders 190 / 152 / 108,
+// 480 requests in 32-bit counts, 64 orders 340 / 229 / 163, 4096 orders 3502 / 397 / 323; one order by size of 512 requests of an
+// interleaved schedule 178 / 251 / 177.
 #include <utility>
 
 #include "host_util.h"
@@ -118,7 +120,7 @@ __device__ __forceinline__ bool place_set(uint32_t (&block)[kSets][Cells::kField
     for (uint32_t q = 0; q < many; ++q) {
         const Addr s = read_lane(granules, (int)q);
         const uint32_t ta = read_lane(rq_ta, (int)q), tf = read_lane(rq_tf, (int)q);
-        if (sizeof(Addr) == 4 && try32 && (uint64_t)peak + (uint64_t)s > 0xffffffffull) return false;      // (uniform)
+        if (sizeof(Addr) == 4 && try32 && s > (Addr)~peak) return false;       // (uniform) peak + s may not fit
         // covered so far in front of each block, and the first hole that is large enough
         uint64_t alive[J], some = 0;
         Key before[J], run = 0;
@@ -126,7 +128,7 @@ __device__ __forceinline__ bool place_set(uint32_t (&block)[kSets][Cells::kField
         for (int u = 0; u < J; ++u) {
             alive[u] = Cells::alive(block[u], ta, tf);
             before[u] = run;
-            run = umax(run, keep_lanes(alive[u], Cells::end(block[u])));
+            run = umax(run, lane_in(alive[u]) ? Cells::end(block[u]) : (Key)0);
         }
         const Key incl = wave_scan_max(run), below = wave_shift_up(incl, (Key)0);
         Addr covered = 0;                                             // in front of the lane's first such hole
@@ -140,24 +142,26 @@ __device__ __forceinline__ bool place_set(uint32_t (&block)[kSets][Cells::kField
         const Addr x = some ? read_lane(covered, __builtin_ctzll(some)) : Cells::covered(read_lane(incl, kWave - 1));
         peak = umax(peak, (Addr)(x + s));
         mine = set_lane(mine, x, (int)q);
-        // the blocks that start above it move up by one
-        uint32_t at = 0;
-#pragma unroll
-        for (int u = 0; u < J; ++u) at += (uint32_t)__builtin_popcountll(lanes_ge(x, Cells::lo(block[u])));
-        const uint32_t lane_at = at / J, slot = at % J;               // (at < 64 J: the list has room for the request)
-        const uint64_t above = lane_at < (uint32_t)kWave ? ~0ull << lane_at : 0ull, beyond = above & (above - 1);
+        // The blocks that start above it move up by one, and it takes the place of the first of them: block k is one of them if it starts
+        // above, and gets the one before if that does, too.  (Counting them for the place and writing the block there, a branch per block
+        // of a lane, took twice as many instructions.)
+        uint32_t field[kFields], last[kFields];
 #pragma unroll
         for (int f = 0; f < kFields; ++f) {
-            const uint32_t first = wave_shift_up(block[J - 1][f], 0u);
-#pragma unroll
-            for (int u = J - 1; u >= 0; --u)
-                block[u][f] = lane_in((uint32_t)u > slot ? above : beyond) ? (u > 0 ? block[u - 1][f] : first) : block[u][f];
+            field[f] = Cells::field(f, x, (Addr)(x + s), ta, tf);
+            last[f] = wave_shift_up(block[J - 1][f], 0u);
         }
+        uint64_t above[J];
 #pragma unroll
-        for (int u = 0; u < J; ++u) {
-            if (slot != (uint32_t)u) continue;                        // (uniform)
+        for (int u = 0; u < J; ++u) above[u] = lanes_lt(x, Cells::lo(block[u]));
 #pragma unroll
-            for (int f = 0; f < kFields; ++f) block[u][f] = set_lane(block[u][f], Cells::field(f, x, (Addr)(x + s), ta, tf), (int)lane_at);
+        for (int u = J - 1; u >= 0; --u) {
+            const uint64_t further = u > 0 ? above[u > 0 ? u - 1 : 0] : above[J - 1] << 1;
+#pragma unroll
+            for (int f = 0; f < kFields; ++f) {
+                const uint32_t here = lane_in(above[u]) ? field[f] : block[u][f];
+                block[u][f] = lane_in(further) ? (u > 0 ? block[u > 0 ? u - 1 : 0][f] : last[f]) : here;
+            }
         }
     }
     return true;
