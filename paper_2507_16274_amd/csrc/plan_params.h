@@ -86,7 +86,7 @@ bool launch_plan_bitmap(const PlanParams& prm, const DeviceInfo& di, hipStream_t
 
 // The variant for short traces (plan_short.hip): a wave per plan.  A request costs it more the more register sets the list
 // takes: 512 requests 159 to 179 us, where one order by size, which leaves the workgroup kernels little to settle, takes those
-// 178 to 278; orders by time, and more orders than CUs, up to 20 times as long.
+// 178 to 278; orders by time, and more orders than CUs, up to ten times as long.
 constexpr uint32_t kShortMost = 512;                 // requests
 // One workgroup goes through all plans' extents and flags for the best plan (4096 orders: 3 us beside 70 us and more of placing).
 constexpr uint32_t kShortPlans = 4096;

@@ -1,4 +1,4 @@
-"""Parity of the sorted-list kernel with the CPU oracle where its batches of 64 requests and its equally long chunks of the
+"""Parity of the sorted-list kernel (and, up to 512 requests in up to 4096 plans, of the kernel for short traces) with the CPU oracle where its batches of 64 requests and its equally long chunks of the
 list can go wrong: lengths around whole batches and chunks, orders whose batches are one chain of clashes, requests that
 see many holes beside blocks that cover most of the list, more plans than workgroups, plans handed on to 64-bit addresses, and both
 sides of each layout's LDS limit."""
@@ -50,14 +50,70 @@ def test_lengths_around_batches_and_chunks(S, oracle, kind, n):
         assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == BITS[kind]
 
 
+MANY = 4097                                                       # plans; up to 4096 of up to 512 requests go to the kernel for short traces
+NEXT_PLAN = {16: 14, 32: 14, 64: 15}                              # words of the workspace that plans are handed out by (kAccNextPlan, kAccNextWide)
+
+
+def _compare_many(S, oracle, tr, orders, P=MANY, kernel=None):
+    """`orders` over and over, P plans in all.  The sorted-list kernel hands out plans beyond one per workgroup, which no other does."""
+    import torch
+    rows = np.arange(P) % len(orders)
+    dev = torch.from_numpy(np.ascontiguousarray(orders[rows]).view(np.int32)).cuda()
+    plan = S.stalloc_plan(*S.trace_to_device(tr), tr.t_end, dev)
+    S.check_status(plan)
+    info = S.stalloc_plan_report(plan)
+    a, ext = oracle.plan_many(tr.size, tr.t_alloc, tr.t_free, orders, method="allpairs")
+    assert np.array_equal(plan["peaks"].cpu().numpy().view(np.uint64), ext[rows])
+    offsets = torch.from_numpy(a.view(np.int64)).cuda()
+    assert torch.equal(plan["offsets"], offsets[torch.from_numpy(rows).cuda()])
+    assert int(plan["best_plan"].item()) == int(np.argmin(ext))
+    if kernel:
+        assert info["kernel"] == kernel
+    if kernel == "list_lds":
+        words = plan["workspace"][:16 * 8].view(torch.int64).cpu()
+        assert int(words[NEXT_PLAN[info["address_bits"]]]) > 0, "plans were handed out"
+    return info
+
+
+@pytest.mark.parametrize("kind", ["compact", "narrow", "wide"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257, 321, 511, 512])
+def test_short_lengths_in_many_plans(S, oracle, kind, n):
+    """The lengths around batches and chunks that only a call of more than 4096 plans takes to this kernel."""
+    rng = np.random.default_rng([n, BITS[kind]])
+    tr = _trace(rng, n, kind)
+    info = _compare_many(S, oracle, tr, _orders(rng, tr, n), kernel="list_lds" if n >= 64 else None)
+    assert n < 64 or info["address_bits"] == BITS[kind]
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 300, 512])
+def test_short_lengths_in_many_plans_of_the_bitmap_kernel(S, oracle, n):
+    rng = np.random.default_rng([n, 4])
+    size, ts, te, t_end = random_trace(rng, n, t_max=max(4, n // 3), sizes=[1, 2, 3, 8])
+    tr = _T(size * np.uint64(4096), ts, te, t_end)
+    _compare_many(S, oracle, tr, _orders(rng, tr, n), kernel="bitmap")
+
+
 @pytest.mark.parametrize("kind", ["narrow", "wide"])
 def test_more_plans_than_workgroups(S, oracle, kind):
     rng = np.random.default_rng(71)
-    n, P = 200, 700
+    n = 577
     tr = _trace(rng, n, kind)
-    orders = np.stack([_orders(rng, tr, n)[k % 4] for k in range(P)])
-    got, _, _ = _compare_plans(S, oracle, tr, orders, method="allpairs")
-    assert got["info"]["kernel"] == "list_lds" and got["info"]["address_bits"] == BITS[kind]
+    info = _compare_many(S, oracle, tr, _orders(rng, tr, n), P=2500, kernel="list_lds")
+    assert info["address_bits"] == BITS[kind]
+
+
+@pytest.mark.parametrize("n", [3000, 8900])
+def test_blocks_that_concern_no_request_of_a_batch(S, oracle, n):
+    """Requests that live for a dozen allocations, one in a hundred for long: in an order by size whole groups of blocks lie at other times than
+    the batch, in orders by time and at random few do; lists in LDS and in the workspace."""
+    rng = np.random.default_rng([77, n])
+    ts = np.arange(n) * 2
+    te = ts + 2 * rng.integers(1, 12, n) + np.where(rng.random(n) < 0.01, n // 4, 0)
+    size = (rng.choice([1, 2, 5, 1000, 70000], n) * 512 + 1).astype(np.uint64)
+    tr = _T(size, ts.astype(np.uint32), te.astype(np.uint32), int(te.max()))
+    orders = np.concatenate([_orders(rng, tr, n), np.lexsort((ts, -size.astype(np.int64)))[None].astype(np.uint32)])
+    got, _, _ = _compare_plans(S, oracle, tr, orders, method="lists")
+    assert got["info"]["kernel"] == ("list_lds" if n == 3000 else "list_memory") and got["info"]["address_bits"] == 32
 
 
 @pytest.mark.parametrize("beyond", [0, 1])
@@ -100,6 +156,12 @@ def test_both_sides_of_the_limit_of_lists_with_64_bit_addresses(S, oracle):
         assert got["info"]["kernel"] == kernel and got["info"]["address_bits"] == 64
 
 
+def _outgrows(size, order, at):
+    """The sizes of a batch of 64 on top of all before it need not fit 32 bits."""
+    end = np.maximum.accumulate((at + size)[order])
+    return any(int(end[b - 1] if b else 0) + int(size[order[b:b + 64]].sum()) >= 2 ** 32 for b in range(0, len(size), 64))
+
+
 @pytest.mark.parametrize("n_clique, n_extra, kernel", [(1000, 2000, "list_lds"), (2000, 5500, "list_memory")])
 def test_some_of_more_plans_than_workgroups_outgrow_32_bit_counts(S, oracle, n_clique, n_extra, kernel):
     """Odd byte sizes that stack up to nearly 2^32: a workgroup that gives up a plan tried with 32-bit counts takes the next one
@@ -118,19 +180,31 @@ def test_some_of_more_plans_than_workgroups_outgrow_32_bit_counts(S, oracle, n_c
     some = np.stack(some).astype(np.uint32)
     rows = np.arange(P) % len(some)
     a, ext = oracle.plan_many(tr.size, tr.t_alloc, tr.t_free, some, method="lists")
-
-    def outgrows(order, at):
-        """The sizes of a batch of 64 on top of all before it need not fit 32 bits."""
-        end = np.maximum.accumulate((at + size)[order])
-        return any(int(end[b - 1] if b else 0) + int(size[order[b:b + 64]].sum()) >= 2 ** 32 for b in range(0, n, 64))
-
-    wide = np.asarray([outgrows(o, x) for o, x in zip(some, a)])
+    wide = np.asarray([_outgrows(size, o, x) for o, x in zip(some, a)])
     assert 0 < wide.sum() < len(some)
     got = _gpu_plan(S, tr, some[rows])
     info = got["info"]
     assert got["status"] == 0 and info["kernel"] == kernel and info["address_bits"] == 32
     assert info["plans_64bit"] == int(wide[rows].sum())
     assert np.array_equal(got["peaks"], ext[rows]) and np.array_equal(got["offsets"], a[rows])
+
+
+@pytest.mark.parametrize("fill", [0.80, 0.95])
+def test_short_plans_that_outgrow_32_bit_counts_among_many(S, oracle, fill):
+    """A clique of odd sizes with a sum of `fill` x 2^32 bytes and half as many requests in between, tried with 32-bit counts by the sorted-list
+    kernel: plans go on to 64-bit addresses where the sizes of a batch on top of all before it need not fit."""
+    rng = np.random.default_rng(78)
+    n = 300
+    size = rng.integers(1, 1 << 20, n).astype(np.float64)
+    size = (size * (fill * 2 ** 32 / size[:200].sum())).astype(np.uint64) | np.uint64(1)
+    ts = np.r_[np.zeros(200, np.int64), rng.integers(0, 90, 100)]
+    te = np.r_[np.full(200, 100), ts[200:] + rng.integers(1, 9, 100)]
+    tr = _T(size, ts.astype(np.uint32), te.astype(np.uint32), 100)
+    orders = np.stack([rng.permutation(n) for _ in range(20)]).astype(np.uint32)
+    info = _compare_many(S, oracle, tr, orders, kernel="list_lds")
+    a, _ = oracle.plan_many(tr.size, tr.t_alloc, tr.t_free, orders, method="allpairs")
+    wide = np.asarray([_outgrows(tr.size, o, x) for o, x in zip(orders, a)])
+    assert info["address_bits"] == 32 and info["plans_64bit"] == int(wide[np.arange(MANY) % 20].sum()) and wide.any() == (fill > 0.9)
 
 
 @pytest.mark.parametrize("narrow", [8, 40, 400])

@@ -1,5 +1,5 @@
-"""stalloc_validate on calls large enough for the form that leaves out pairs that cannot meet in time
-(n * n * P >= 1.5e9), against the oracle and against the all-pairs form on slices of the same plans."""
+"""stalloc_validate on calls large enough for the forms that leave out pairs that cannot meet (n * n * P >= 3e8), against the
+oracle and against the all-pairs form, which a call with a smaller call's workspace gets."""
 import ctypes
 
 import numpy as np
@@ -7,7 +7,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-NEAR_FROM = 1_500_000_000
+WORK = 1_500_000_000                                          # n * n * P
 
 
 def _trace(rng, n, kind):
@@ -25,7 +25,7 @@ def test_near_pairs_match_all_pairs(oracle, n, kind):
     import paper_2507_16274_amd as S
     rng = np.random.default_rng(n)
     size, ts, te, t_end = _trace(rng, n, kind)
-    P = -(-NEAR_FROM // (n * n)) + 3                          # a count that is no multiple of four, too
+    P = -(-WORK // (n * n)) + 3                               # a count that is no multiple of four, too
     plans = rng.integers(0, 60 * n, (P, n)).astype(np.int64)  # a few conflicts per plan and request
     plans[P // 2] = 0                                         # ... and one in which everything conflicts that can
     dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), plans)]
@@ -36,12 +36,9 @@ def test_near_pairs_match_all_pairs(oracle, n, kind):
     for p in rows if n < 5000 else rows[:2] + [P // 2]:
         want = oracle.validate(size, ts, te, plans[p].view(np.uint64))
         assert (int(cnt[p]), tuple(int(x) & 0xFFFFFFFF for x in pair[p])) == want
-    step = max(1, (NEAR_FROM - 1) // (n * n))
-    for p0 in range(0, P, step):                              # the all-pairs form
-        part = S.stalloc_validate(*dev[:3], t_end, dev[3][p0:p0 + step])
-        if n < NEAR_FROM ** 0.5:
-            assert np.array_equal(part["conflicts"].cpu().numpy(), cnt[p0:p0 + step])
-            assert np.array_equal(part["first_pair"].cpu().numpy(), pair[p0:p0 + step])
+    conflicts, first, status = _all_pairs(S, dev[:3], t_end, dev[3])
+    assert int(status.item()) == 0
+    assert torch.equal(out["conflicts"], conflicts) and torch.equal(out["first_pair"], first)
 
 
 def test_near_pairs_report_a_range_that_would_wrap(oracle):
@@ -52,7 +49,7 @@ def test_near_pairs_report_a_range_that_would_wrap(oracle):
     size, ts, te, t_end = _trace(rng, n, "mixed")
     plan = rng.integers(0, 1 << 40, (1, n)).astype(np.int64)
     size[n // 2] = 1
-    for P in (4, 1):                                          # (n * n * P on either side of NEAR_FROM)
+    for P in (4, 1):                                          # (four plans: one form or the other, by how many are alive together)
         for bad, start, status in ((0, -1, 3), (n // 2, -1, 3), (n - 1, -1, 3),       # 2^64 - 1: any size wraps, 1 as well
                                    (n // 2, -2, 0), (7, -1 - int(size[7]), 0)):       # ... and these end at 2^64 - 1
             bent = np.repeat(plan, P, axis=0)
@@ -60,6 +57,7 @@ def test_near_pairs_report_a_range_that_would_wrap(oracle):
             dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32), bent)]
             out = S.stalloc_validate(*dev[:3], t_end, dev[3])
             assert int(out["status"].item()) == status, (P, bad, start)
+            assert int(_all_pairs(S, dev[:3], t_end, dev[3])[2].item()) == status, (P, bad, start)
 
 
 def _all_pairs(S, dev, t_end, plans):
@@ -86,7 +84,7 @@ def _all_pairs(S, dev, t_end, plans):
 @pytest.mark.parametrize("P", [1, 3, 4, 6])
 @pytest.mark.parametrize("kind", ["dense", "crowded", "ties", "mixed", "sparse", "far end"])
 def test_both_forms_agree_on_few_plans(kind, P):
-    """One to three plans (crowded traces take the all-pairs form by themselves) and four to six."""
+    """Beyond the lengths at which plans are gone through four at a time; in crowded traces all requests count as long-lived."""
     import torch
     import paper_2507_16274_amd as S
     n = 40011

@@ -130,3 +130,22 @@ def test_very_many_windows_need_no_room_for_intervals():
     windows = 1 << 24
     assert need(2 * windows) - need(windows) <= windows * (2 * 16 + 8 + 8 + 8 + 4 + 4) + 4096
     assert need(4096) - need(1) <= (128 << 20) + 4096 * 256 * 20 + (1 << 20)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [96, 512, 513])
+def test_short_calls_carry_no_index(n):
+    """Up to 4096 plans of up to 512 requests are placed in registers: no index of requests with overlapping lifetimes is part of those
+    calls; it is from 4097 plans on, so that the size jumps there and never falls."""
+    import torch
+    import paper_2507_16274_amd as S
+    torch.cuda.init()
+
+    def need(P):
+        size = ctypes.c_size_t(0)
+        assert S.lib.stalloc_plan(ctypes.byref(_trace(S, n, 2 * n)), 256, P, 256, 256, 256, 256, 256, None, ctypes.byref(size), None) == 0
+        return size.value
+
+    index = n * n                                                 # (256 entries of two bytes for each request at least)
+    assert need(1) <= need(64) <= need(4096) <= need(4097)
+    assert (need(4097) - need(4096) >= index) == (n <= 512)
