@@ -123,7 +123,7 @@ int stalloc_plan_sized(const stalloc_trace *trace, const uint32_t *orders, uint3
  *               overlap and whose address ranges overlap
  *   first_pair  device [P][2], the lexicographically first such pair with i < j,
  *               {0xFFFFFFFF, 0xFFFFFFFF} when the plan is valid
- *   workspace   from n * n * P = 3e8 on and beyond 192 requests up to 128 MiB for the address ranges of plans that are gone
+ *   workspace   from n * n * P = 3e8 on and beyond 224 requests up to 128 MiB for the address ranges of plans that are gone
  *               through together (36 bytes per request and plan, one plan at least); a workspace with room for what a smaller
  *               call asks for (16 KiB and 8 bytes per plan) is accepted as well, and all pairs are looked at then.
  */

@@ -23,8 +23,8 @@
 // longest request of the batch; on 19 840 (one workgroup of sixteen waves) half the time is such waiting.  In orders by size and by
 // time, where nearly every request meets the one before it, the chain of those in wave 0 (an order by time of 19 840 requests: 8.4 ms
 // alone, a random one 4.4; it sets the time of a launch with two plans a workgroup).
-// 1024 plans of 6144 requests: 6.9 ms looking up every request, 4.66 with tables read a word at a time, 4.09 four words at a time and
-// with chains in registers (fit_among); 512 plans of 19 840: 24.0, 13.85, 12.15 ms.
+// 1024 plans of 6144 requests: 6.9 ms looking up every request, 4.66 with tables read a word at a time, 4.05 four words at a time and
+// with chains in registers (fit_among), 3.96 where those pay; 512 plans of 19 840: 24.0, 13.85, 12.2, 12.0 ms.
 //
 // The tables hold the address range up to an eighth above the largest number of live granules (which no
 // plan can stay below and plans worth having stay close to), and up to two and a half times that number where the LDS has

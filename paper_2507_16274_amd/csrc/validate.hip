@@ -1,12 +1,12 @@
 // stalloc_validate: pairwise check of the planning constraint of Sec. 5.1 -- no two
 // allocation decisions may conflict in lifespan and in address range at once.
 //
-// Two forms of the same count.  val_pairs tests all n(n-1)/2 unordered pairs of every plan: the
+// Three forms of the same count.  val_pairs tests all n(n-1)/2 unordered pairs of every plan: the
 // pair space is cut into 256 x 256 tiles (upper triangle only); one workgroup owns one tile of
 // one plan: each thread keeps its own request i in registers and walks the 256 requests j of the
 // tile, which sit in LDS and are read as broadcasts.  val_near puts the short-lived requests in order of
-// time and the long-lived ones in order of address first and leaves out what cannot meet (see there).
-// Per plan both accumulate the number of conflicting pairs and the smallest key (i << 32 | j),
+// time and the long-lived ones in order of address first and leaves out what cannot meet (see there); val_four goes through four
+// plans together in order of time.  Per plan all accumulate the number of conflicting pairs and the smallest key (i << 32 | j),
 // i < j, which is the lexicographically first conflicting pair.
 #include "host_util.h"
 #include "wave.h"
@@ -16,8 +16,9 @@ namespace stalloc {
 constexpr int kValTile = 256;
 
 // val_near is part of calls of at least this many requests^2 x plans: its seven further launches cost some 35 us, all pairs
-// take 50 us and more from here on (all pairs / val_near: 6144 requests, 10 plans 64 / 49 us; 19 612 requests, one plan 64 / 44;
-// 960 requests, 440 plans 87 / 59).
+// take 50 us and more from here on (all pairs / val_near: 6144 requests, 10 plans 65 / 50 us; 19 612 requests, one plan 65 / 43;
+// 960 requests, 440 plans 87 / 59; of an expert-parallel trace, where all requests go into buckets by address, 6144 and 8 plans 58 / 63,
+// 10 plans 66 / 63).
 #ifndef STALLOC_VAL_NEAR_FROM
 #define STALLOC_VAL_NEAR_FROM (300ull * 1000 * 1000)
 #endif
@@ -26,13 +27,13 @@ constexpr uint64_t kVnFrom = STALLOC_VAL_NEAR_FROM;
 // and from some requests x plans on, in traces of which few requests are alive at a time, which only the device knows, so that both forms
 // are enqueued and one of them returns at once (3 us).
 constexpr uint32_t kVfPlans = 4;
-constexpr uint32_t kVfShort = 192, kVfMiddling = 2048, kVfLongest = 8192;
-constexpr uint64_t kVfFrom = 1000 * 1000, kVfLongFrom = 2000 * 1000;
+constexpr uint32_t kVfShort = 224, kVfMiddling = 2048, kVfLongest = 8192;
+constexpr uint64_t kVfFrom = 1000 * 1000, kVfLongFrom = 4000 * 1000;
 constexpr uint32_t kVfGroups = 32768;          // workgroups: several times what is resident; they take further plans in turn
 constexpr size_t kVnRoom = (size_t)128 << 20;    // what the plans that are gone through together take of the workspace
 constexpr uint32_t kVnGroup = 65535;             // (largest grid.y)
-// Waves that are resident.  They take the units of work of a few plans (199 748 requests, one plan 64 us, 76 with twice as many
-// waves); with many plans a wave has few units, and twice as many even out (6144 requests, 512 plans 217 -> 206 us).
+// Waves that are resident.  They take the units of work of a few plans (199 748 requests, one plan 12 us more with twice as many);
+// with many plans a wave has few units, and twice as many even out (6144 requests, 512 plans 217 -> 206 us).
 constexpr uint64_t kVnResident = 256 * 24;
 // With fewer units than this a unit takes 64 boxes instead of 256, so that there are enough of them (49 920 requests, one plan,
 // val_near alone 65 -> 35 us).
@@ -124,8 +125,8 @@ val_pairs(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, co
 // box, most of them none.  Only then is the other tile looked at, request by request.
 // Which request of a bucket comes first does not matter: the results are a sum and a minimum over the request numbers.
 //   Bound by chains of loads (a tile, its boxes, the tiles that it meets) with few waves, by vector issue with many.  All
-// tiles of requests that meet in time, by request / this: 199 748 requests, one plan 226 / 71 us, of which val_near 29 (before 185);
-// 6144 requests, 512 plans 598 / 215; 49 920 requests, 8 plans 478 / 161.  With the long-lived tile in the lanes and the short ones
+// tiles of requests that meet in time, by request / this: 199 748 requests, one plan 228 / 68 us, of which val_near 29 (before 185);
+// 6144 requests, 512 plans 599 / 200; 49 920 requests, 8 plans 474 / 165.  With the long-lived tile in the lanes and the short ones
 // loaded one after the other, each a round trip to memory, val_near took 216 us on the first of these.
 constexpr uint32_t kVnTile = 64;
 constexpr uint32_t kVnWaves = 4;
@@ -252,7 +253,8 @@ vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint3
 __global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint32_t n, uint32_t form, const uint64_t* acc)
 {
     __shared__ uint32_t part[16];
-    const bool by_bucket = acc[kAccUnsorted] && !(acc[kAccCrowded] & kCrowded);
+    const uint64_t alive = acc[kAccCrowded];
+    const bool by_bucket = acc[kAccUnsorted] && !(alive & kCrowded);
     uint32_t* counted = by_bucket ? s.bucket : s.shorts_in;
     const uint32_t many = by_bucket ? b.count : (n + 255) / 256, apart = by_bucket ? b.apart : 0u, lasting = by_bucket ? b.before_lasting() : many;
     uint32_t carry = 0;
@@ -275,7 +277,6 @@ __global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint3
     if (threadIdx.x != 0) return;
     if (lasting >= many) s.shorts->x = carry;
     // (long traces of which hardly any are alive have so few tiles that meet that val_near is the faster)
-    const uint64_t alive = acc[kAccCrowded];
     s.shorts->y = form == 1 || (form == 2 && (alive & kFewAlive) && (n <= kVfMiddling || !(alive & kHardlyAnyAlive))) ? 1u : 0u;
 }
 
@@ -350,12 +351,7 @@ vn_ranges(VnSorted s, const uint64_t* __restrict__ offsets, uint32_t n, uint32_t
 struct VnPlaces {
     uint64_t from, width;
     uint32_t shift;
-    bool all;                                                         // nothing lies beyond
-    __device__ __forceinline__ uint32_t of(uint64_t start) const
-    {
-        if (all) return (uint32_t)(start >> shift);                   // (uniform; one workgroup sees to a plan: the limits took 1.2 of 63 us)
-        return (uint32_t)(umin64(start > from ? start - from : 0ull, width) >> shift);
-    }
+    __device__ __forceinline__ uint32_t of(uint64_t start) const { return (uint32_t)(umin64(start > from ? start - from : 0ull, width) >> shift); }
 };
 __device__ __forceinline__ VnPlaces vn_places(uint64_t sample, uint64_t top, uint32_t place_bits)     // one start per lane
 {
@@ -368,7 +364,7 @@ __device__ __forceinline__ VnPlaces vn_places(uint64_t sample, uint64_t top, uin
     const uint64_t from = middle > far ? middle - far : 0ull, to = top - middle < far ? top : middle + far;
     const uint64_t width = to - from;                                 // (no start is above the highest end)
     const uint32_t width_bits = width ? 64 - (uint32_t)__builtin_clzll(width) : 0u;
-    return VnPlaces{from, width, width_bits > place_bits ? width_bits - place_bits : 0u, width == top};
+    return VnPlaces{from, width, width_bits > place_bits ? width_bits - place_bits : 0u};
 }
 
 // The long-lived requests of a plan in buckets of their start addresses, and their tiles' boxes; one workgroup a plan.

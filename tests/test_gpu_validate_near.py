@@ -113,7 +113,7 @@ def _alive(rng, n, alive):
 
 
 @pytest.mark.parametrize("alive", [4, 50, 150])
-@pytest.mark.parametrize("n", [5, 63, 64, 65, 128, 129, 191, 192, 193, 256, 257, 2048, 2049, 8192, 8193])
+@pytest.mark.parametrize("n", [5, 63, 64, 65, 128, 129, 223, 224, 225, 257, 2048, 2049, 8192, 8193])
 def test_four_plans_a_wave(n, alive):
     """Lengths around one, two and four tiles and around those at which plans are gone through four at a time, always or if few requests
     are alive together; a number of plans that is no multiple of four; requests numbered by time and not."""
@@ -124,7 +124,7 @@ def test_four_plans_a_wave(n, alive):
     if n % 2:
         mixed = rng.permutation(n)
         size, ts, te = size[mixed], ts[mixed], te[mixed]
-    P = max(300_000_000 // (n * n), 2_000_000 // n) + 3
+    P = max(300_000_000 // (n * n), 4_000_000 // n) + 3
     dev = [torch.from_numpy(x).cuda() for x in (size.view(np.int64), ts.view(np.int32), te.view(np.int32))]
     gen = torch.Generator(device="cuda").manual_seed(n)
     plans = torch.randint(0, 25 * min(n, 2 * alive) * 4 + 1, (P, n), device="cuda", generator=gen)
