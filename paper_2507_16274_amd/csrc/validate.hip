@@ -241,7 +241,8 @@ __device__ __forceinline__ uint32_t vn_take(uint32_t* bucket, uint32_t mine, boo
 __global__ void __launch_bounds__(256)
 vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint32_t n, VnBuckets b, uint32_t* bucket, const uint64_t* acc)
 {
-    if ((acc[kAccCrowded] & kCrowded) || !acc[kAccUnsorted]) return;
+    const uint64_t alive = acc[kAccCrowded], unsorted = acc[kAccUnsorted];        // (loaded together: mostly that is all the kernel does)
+    if ((alive & kCrowded) | (unsorted == 0)) return;
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         vn_take(bucket, i < n ? b.of(ta[i], tf[i]) : 0u, i < n);
@@ -253,8 +254,8 @@ vn_count(const uint32_t* __restrict__ ta, const uint32_t* __restrict__ tf, uint3
 __global__ void __launch_bounds__(1024) vn_starts(VnBuckets b, VnSorted s, uint32_t n, uint32_t form, const uint64_t* acc)
 {
     __shared__ uint32_t part[16];
-    const uint64_t alive = acc[kAccCrowded];
-    const bool by_bucket = acc[kAccUnsorted] && !(alive & kCrowded);
+    const uint64_t alive = acc[kAccCrowded], unsorted = acc[kAccUnsorted];
+    const bool by_bucket = (unsorted != 0) & !(alive & kCrowded);
     uint32_t* counted = by_bucket ? s.bucket : s.shorts_in;
     const uint32_t many = by_bucket ? b.count : (n + 255) / 256, apart = by_bucket ? b.apart : 0u, lasting = by_bucket ? b.before_lasting() : many;
     uint32_t carry = 0;
@@ -285,8 +286,9 @@ vn_scatter(const uint64_t* __restrict__ size, const uint32_t* __restrict__ ta, c
            VnBuckets b, VnSorted s, const uint64_t* acc)
 {
     __shared__ uint32_t part[4];
-    const bool crowded = (acc[kAccCrowded] & kCrowded) != 0, sorted = crowded || !acc[kAccUnsorted];        // (uniform)
+    const uint64_t alive = acc[kAccCrowded], unsorted = acc[kAccUnsorted];
     const uint32_t shorts = s.shorts->x;
+    const bool crowded = (alive & kCrowded) != 0, sorted = crowded | (unsorted == 0);         // (uniform)
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {        // (uniform trip count)
         const uint32_t i = i0 + threadIdx.x;
         const bool valid = i < n;
