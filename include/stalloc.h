@@ -84,7 +84,7 @@ typedef struct stalloc_trace {
  *   best_plan     device [1], index of the smallest extent, lowest index among equals.
  *   device_status device [1], see above; must not be NULL.
  *   workspace     sized for whatever the trace may turn out to need, which only the device
- *                 learns: for n <= 32768 this includes an index of the request pairs with
+ *                 learns: for n <= 32768 (but not for n <= 512 and P <= 4096) this includes an index of the request pairs with
  *                 overlapping lifetimes at its upper bound of about 2 n^2 bytes (76 MB for
  *                 n = 6144, 0.8 GB for n = 19840) or, where they need more, lists of placed
  *                 blocks that do not fit LDS (n > 4266: 48 n bytes for each of at most one plan
